@@ -3,14 +3,16 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfb_amd.so")
-SOURCES = ["fb_kernels.hip", "fb_graph.cpp", "fb_sell.cpp", "fb_stream.cpp", "fb_pstream.cpp", "fb_api.cpp", "fb_leaky.hip"]
+SOURCES = ["fb_kernels.hip", "fb_graph.cpp", "fb_sell.cpp", "fb_stream.cpp", "fb_pstream.cpp", "fb_small.cpp", "fb_api.cpp", "fb_leaky.hip",
+           "fb_small.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
+    "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # never emit packed FP32 arithmetic
     "-Wall", "-Wno-unused-function", "-x", "hip",
 ]
@@ -24,15 +26,29 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "fb_internal.h"), os.path.join(HERE, "..", "include", "fb.h")]
+    deps = sources() + [os.path.join(CSRC, "fb_internal.h"), os.path.join(CSRC, "fb_device.h"), os.path.join(HERE, "..", "include", "fb.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
 def build_library(verbose: bool = False) -> str:
-    cmd = [HIPCC] + FLAGS + sources() + ["-o", LIB]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.check_call(cmd)
+    # one compiler per source, side by side, then the link
+    objs, running = [], []
+    for src in sources():
+        obj = os.path.join(tempfile.gettempdir(), f"fb_amd_{os.getpid()}_{os.path.basename(src)}.o")
+        cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
+        if verbose:
+            print(" ".join(cmd))
+        objs.append(obj)
+        running.append(subprocess.Popen(cmd))
+    codes = [p.wait() for p in running]
+    try:
+        if any(codes):
+            raise subprocess.CalledProcessError(next(c for c in codes if c), "hipcc")
+        subprocess.check_call([HIPCC, "-shared", "--offload-arch=gfx950"] + objs + ["-o", LIB])
+    finally:
+        for obj in objs:
+            if os.path.exists(obj):
+                os.remove(obj)
     return LIB
 
 

@@ -43,6 +43,7 @@ RecDir make_dir(const fb_graph *g, bool backward, void *out, bool out_carrier, d
     r.backward = backward ? 1 : 0;
     r.fill_pad = fill_pad ? 1 : 0;
     r.prob = backward ? g->pbwd : g->pfwd;
+    r.small = backward ? g->sbwd : g->sfwd;
     return r;
 }
 
@@ -72,6 +73,15 @@ int run_recursion(const fb_graph *g, const float *emis, const int32_t *lengths, 
     p.Ktot = g->K;
     p.Kcap = g->max_sub_K;
     p.Ecap = p.shared ? D : g->max_sub_K;
+    if (g->small) {
+        int slices = 0;
+        for (int i = 0; i < n_dir; ++i) {
+            p.dir[i] = dirs[i];
+            if (tropical) p.dir[i].small = g->strop;
+            slices = std::max(slices, (tropical ? (g->own_trop ? g->hs_trop : g->hs_fwd) : dirs[i].backward ? g->hs_bwd : g->hs_fwd).max_slices);
+        }
+        return launch_small(p, g->hs_fwd.tm, slices, tropical, stream);
+    }
     size_t lds = 0;
     for (int i = 0; i < n_dir; ++i) {
         p.dir[i] = dirs[i];
@@ -422,6 +432,7 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
     if ((rc = run_recursion(g, emis, lengths, B, N, D, &d, 1, stream, true))) return rc;
     BacktraceParams bt{};
     bt.bp = bp; bt.bp_ld = d.bp_ld; bt.last = last; bt.lengths = lengths; bt.sched = g->trop;
+    bt.small_sub = g->strop.sub;
     bt.B = B; bt.N = N; bt.shared = g->n_seq == 0; bt.Ktot = g->K; bt.Kcap = g->max_sub_K; bt.Ccap = d.Ccap;
     bt.path = path;
     return launch_backtrace(bt, stream);

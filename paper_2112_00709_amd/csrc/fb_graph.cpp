@@ -274,30 +274,52 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         bool any_parallel = false;
         bool prob_ok = n_seq == 0;   // the plans of the probability-domain kernel could be built
 
-        std::vector<int64_t> ptr;
-        std::vector<int32_t> col, vid;
-        std::vector<float> w;
+        std::vector<int64_t> ptr, mptr;
+        std::vector<int32_t> col, mcol, vid;
+        std::vector<float> w, mw;
+        // rows of the forward (dir 0) or backward matrix of sub-graph s, weights in log2 units -> ptr, col, w
+        auto rows_of = [&](int32_t s, int dir) {
+            const int32_t k0 = n_seq > 0 ? state_off[s] : 0, k1 = n_seq > 0 ? state_off[s + 1] : K, Ks = k1 - k0;
+            const std::vector<int32_t> &p = dir ? L.out_ptr : L.in_ptr, &other = dir ? L.out_dst : L.in_src;
+            const std::vector<float> &ww = dir ? L.out_w : L.in_w;
+            const int64_t e0 = p[k0], e1 = p[k1];
+            ptr.resize((size_t)Ks + 1);
+            col.resize((size_t)(e1 - e0)); w.resize((size_t)(e1 - e0));
+            for (int32_t k = 0; k <= Ks; ++k) ptr[k] = (int64_t)p[k0 + k] - e0;
+            for (int64_t e = e0; e < e1; ++e) {
+                col[(size_t)(e - e0)] = other[(size_t)e] - k0;
+                w[(size_t)(e - e0)] = to_log2(ww[(size_t)e]);
+            }
+        };
+        // The plans carry one arc per (row, column): parallel arcs are (+)-added here, once, in double
+        // (the exported layout keeps them apart).  The two semirings add differently, so the best-path
+        // plan is a plan of its own as soon as the graph has parallel arcs.
+
+        // Small graphs with vectors in double: the small-graph kernel's plans, and no others, if every sub-graph fits it.
+        g->small = g->f64 && g->nw == kNWSmall;
+        int32_t longest = 0;   // most arcs of a row, parallel ones counted apart
+        for (int32_t k = 0; k < K; ++k) longest = std::max(longest, std::max(L.in_ptr[k + 1] - L.in_ptr[k], L.out_ptr[k + 1] - L.out_ptr[k]));
+        g->hs_fwd.tm = g->hs_bwd.tm = g->hs_trop.tm = longest <= 2 ? 2 : 4;
+        for (int32_t s = 0; s < n_sub && g->small; ++s) {
+            const int32_t k0 = n_seq > 0 ? state_off[s] : 0, Ks = (n_seq > 0 ? state_off[s + 1] : K) - k0;
+            for (int dir = 0; dir < 2 && g->small; ++dir) {
+                rows_of(s, dir);
+                any_parallel |= merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
+                g->small = small_append(dir ? g->hs_bwd : g->hs_fwd, k0, Ks, mptr.data(), mcol.data(), mw.data());
+                if (dir == 0 && g->small) {
+                    merge_parallel(Ks, ptr, col, w, true, mptr, mcol, mw);
+                    g->small = small_append(g->hs_trop, k0, Ks, mptr.data(), mcol.data(), mw.data());
+                }
+            }
+        }
+        if (g->small) prob_ok = false;
+        else g->hs_fwd = g->hs_bwd = g->hs_trop = SmallHost();
         for (int32_t s = 0; s < n_sub; ++s) {
             const int32_t k0 = n_seq > 0 ? state_off[s] : 0, k1 = n_seq > 0 ? state_off[s + 1] : K, Ks = k1 - k0;
             vid.resize((size_t)Ks);
             for (int32_t k = 0; k < Ks; ++k) vid[k] = n_seq > 0 ? k : pdf[k0 + k];
-            for (int dir = 0; dir < 2; ++dir) {
-                const std::vector<int32_t> &p = dir ? L.out_ptr : L.in_ptr, &other = dir ? L.out_dst : L.in_src;
-                const std::vector<float> &ww = dir ? L.out_w : L.in_w;
-                ptr.assign((size_t)Ks + 1, 0);
-                const int64_t e0 = p[k0], e1 = p[k1];
-                col.resize((size_t)(e1 - e0)); w.resize((size_t)(e1 - e0));
-                for (int32_t k = 0; k <= Ks; ++k) ptr[k] = (int64_t)p[k0 + k] - e0;
-                for (int64_t e = e0; e < e1; ++e) {
-                    col[(size_t)(e - e0)] = other[(size_t)e] - k0;
-                    w[(size_t)(e - e0)] = to_log2(ww[(size_t)e]);
-                }
-                // The plans carry one arc per (row, column): parallel arcs are (+)-added here, once, in double
-                // (the exported layout keeps them apart).  The two semirings add differently, so the best-path
-                // plan is a plan of its own as soon as the graph has parallel arcs.
-                std::vector<int64_t> mptr;
-                std::vector<int32_t> mcol;
-                std::vector<float> mw;
+            for (int dir = 0; dir < 2 && !g->small; ++dir) {
+                rows_of(s, dir);
                 const bool dup = merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
                 sell_append(dir ? sell_bwd : sell_fwd, k0, Ks, mptr.data(), mcol.data(), mw.data(), vid.data());
                 // large shared graphs with float vectors: also the plan of the probability-domain kernel
@@ -351,7 +373,12 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             PH.sub.push_back(ps);
         }
         std::vector<Arc> lin_fwd, lin_bwd;   // the arc lists with weights as 2^w, when the graph runs that instantiation
-        {   // nothing a kernel will index may leave its array
+        if (g->small) {   // nothing a kernel will index may leave its array
+            std::string why;
+            g->own_trop = any_parallel;
+            if (!small_in_bounds(g->hs_fwd, why) || !small_in_bounds(g->hs_bwd, why) || !small_in_bounds(g->hs_trop, why))
+                rc = fail(FB_EHIP, "internal error: schedule out of bounds (" + why + ")");
+        } else {
             std::string why;
             const int32_t nv = n_seq > 0 ? -1 : D;
             if (!sell_in_bounds(sell_fwd, nv, why) || !sell_in_bounds(sell_bwd, nv, why))
@@ -415,10 +442,18 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             std::vector<int32_t> hp(pdf, pdf + K);
             const int32_t *dp = nullptr; const float *di = nullptr, *df = nullptr;
             if (!(rc = upload(g, hp, &dp)) && !(rc = upload(g, i2, &di)) && !(rc = upload(g, f2, &df)) &&
-                !(rc = upload_stream(g, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr)) &&
-                !(rc = upload_stream(g, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr)))
-                rc = upload_pdf(g, g->h_pdf, g->pdfs);
-            if (rc == FB_OK) {
+                !(rc = upload_pdf(g, g->h_pdf, g->pdfs)) && !g->small &&
+                !(rc = upload_stream(g, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr)))
+                rc = upload_stream(g, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr);
+            if (rc == FB_OK && g->small) {
+                auto up = [&](const SmallHost &h, SmallDev &d) {
+                    int r;
+                    if ((r = upload(g, h.sub, &d.sub)) || (r = upload(g, h.rows, &d.rows)) || (r = upload(g, h.lg, &d.lg))) return r;
+                    return upload(g, h.arcs, &d.arcs);
+                };
+                if (!(rc = up(g->hs_fwd, g->sfwd)) && !(rc = up(g->hs_bwd, g->sbwd)) && g->own_trop) rc = up(g->hs_trop, g->strop);
+                if (!g->own_trop) g->strop = g->sfwd;
+            } else if (rc == FB_OK) {
                 if (g->own_trop) rc = upload_stream(g, g->h_trop, g->trop);
                 else g->trop = g->fwd;
             }
@@ -493,6 +528,11 @@ int fb_graph_schedule_apply_host(const fb_graph *g, int which, int32_t sub, cons
         std::string why;
         if (!pstream_apply_host(which == 5 ? g->hp_fwd : g->hp_bwd, x, y, nullptr, nullptr, why))
             return fail(FB_EHIP, "internal error: probability-domain plan (" + why + ")");
+        return FB_OK;
+    }
+    if (g->small && which != 2) {   // the small-graph kernel's plans
+        if (which >= 3) return fail(FB_EUNSUPPORTED, "fb_graph_schedule_apply_host: this graph's plans do not take the form 2^w");
+        small_apply_host(which == 0 ? g->hs_fwd : g->hs_bwd, sub, x, y);
         return FB_OK;
     }
     if (which >= 3) {   // the forward / backward stream with weights as 2^w

@@ -256,6 +256,42 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
 bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why);
 bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why);
 
+// ---------------------------------------------------------------------------
+// Plan of the small-graph recursion kernel (fb_small.cpp, fb_small.hip): (sub-)graphs of at most kSmallStates states
+// with vectors in double.  Slice s: 64 lanes, tm arcs per lane (entry (s * tm + t) * 64 + lane; sources are byte offsets
+// of doubles), the row a lane's sum is for (kSmallNoRow: none) and log2 of the lanes a row of the slice is spread over.
+// ---------------------------------------------------------------------------
+constexpr int kSmallStates = 1024;
+constexpr int kSmallMaxSlices = 32;          // per (sub-)graph: 8 waves of 4
+constexpr uint32_t kSmallNoRow = 0xffffffffu;
+
+struct SmallSub {
+    int32_t k0, K;             // first state in the global numbering, number of states
+    int32_t slice0, n_slice;
+};
+
+struct SmallHost {
+    int32_t tm = 4;            // arcs per lane: 2 or 4
+    int32_t max_slices = 0;    // most slices of a sub-graph
+    std::vector<SmallSub> sub;
+    std::vector<uint32_t> rows;
+    std::vector<int32_t> lg;
+    std::vector<Arc> arcs;
+};
+
+struct SmallDev {
+    const SmallSub *sub = nullptr;
+    const uint32_t *rows = nullptr;
+    const int32_t *lg = nullptr;
+    const Arc *arcs = nullptr;
+};
+
+// rows [0, K) of a CSR-like matrix, weights in log2 units; appends one sub-graph's plan.  False if it does not fit the
+// kernel (too many states, a row of more than 64 lanes, too many slices).
+bool small_append(SmallHost &out, int32_t k0, int32_t K, const int64_t *ptr, const int32_t *col, const float *w);
+bool small_in_bounds(const SmallHost &S, std::string &why);
+void small_apply_host(const SmallHost &S, int32_t sub, const double *x, double *y);
+
 // States grouped by pdf for the posterior accumulation: per (sub-)graph, one row per pdf it uses
 // (every pdf for a shared graph), listing the local ids of the states tied to it.  16-bit entries:
 // a workgroup keeps its graph's table in LDS.
@@ -302,6 +338,9 @@ struct fb_graph {
     bool linear_p = false;            // the recursions run in the probability domain (linear_run): the plans below exist
     fb::PStreamHost hp_fwd, hp_bwd;   // its plans, host
     fb::PStreamDev pfwd, pbwd;        // and device
+    bool small = false;               // the recursions run in the small-graph kernel: the plans below exist and h_fwd .. do not
+    fb::SmallHost hs_fwd, hs_bwd, hs_trop;   // its plans, host (hs_trop: as h_trop, only when own_trop)
+    fb::SmallDev sfwd, sbwd, strop;   // and device (strop = sfwd unless own_trop)
     fb::PdfHost h_pdf;                // states grouped by pdf, for the posterior accumulation
     // device
     fb::StreamDev fwd, bwd, trop;     // trop = fwd unless own_trop
@@ -339,6 +378,7 @@ struct RecDir {
     uint16_t *bp;          // tropical semiring: back-pointers (see fb_viterbi in fb_api.cpp for the layout), else NULL
     int64_t bp_ld;         // elements per frame row of bp
     int32_t *last;         // tropical semiring: [B] local id of the best end state (-1: none)
+    SmallDev small;        // small-graph kernel: its plan for this direction
     PStreamDev prob;       // probability-domain kernel: its plan for this direction
     int out_linear;        // ... out takes the vectors as they are kept (entry = 2^(log2 of the true value - cum)), not their logs
     int32_t *fmt;          // ... [B], nullable: 1 if the sequence's rows in out are in that form, 0 if they are logs (the run
@@ -409,6 +449,8 @@ struct PostParams {
     const int32_t *fused;
 };
 
+// the small-graph kernel: tm, slices as the plans of the graph's directions have them (the most slices)
+int launch_small(const RecParams &p, int tm, int slices, bool tropical, void *stream);
 int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t lds_bytes, void *stream);
 bool recursion_fixed_available();   // the fixed-buffer instantiation (RecParams::xs_fixed) may be launched
 unsigned int linear_restarts();     // diagnostic: runs the probability-domain kernel gave up and redid in the log form (synchronises)
@@ -418,6 +460,7 @@ struct BacktraceParams {
     const int32_t *last;     // [B] best end state in the kernel's index space, -1: none
     const int32_t *lengths;
     StreamDev sched;         // the forward plan (sub-graphs, clones)
+    const SmallSub *small_sub;   // graphs of the small-graph kernel: their sub-graphs (sched is empty then)
     int32_t B, N, shared, Ktot, Kcap, Ccap;
     int32_t frames;          // back-pointer rows the kernel holds in LDS at a time (set by launch_backtrace)
     int32_t *path;           // [B][N]

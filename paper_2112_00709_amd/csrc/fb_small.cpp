@@ -1,0 +1,112 @@
+// Host-side construction of the plan the small-graph recursion kernel walks (fb_small.hip), its bounds check and its
+// interpretation on the host for tests.
+//
+// The product is the one of fb_sell.cpp (row j gathers the arcs that enter, or leave, state j), for (sub-)graphs of at
+// most 1024 states and a few thousand arcs with vectors in double.  Shape of the plan:
+//   * A slice is 64 lanes of which each holds `tm` arcs (2 when no row of the graph has more than two, which is every
+//     left-to-right chain; else 4) in registers for the whole time loop.  A row of up to tm arcs takes one lane, a
+//     longer one the smallest power of two of neighbouring lanes that holds it (the kernel combines them when the
+//     slice's sums are formed); all rows of a slice take the same number of lanes.
+//   * Every state is a row, also one without arcs (all its arcs weigh zero-bar): the kernel needs no list of such rows,
+//     and writing every state at every step keeps both buffers right.
+//   * Rows are sorted by the lanes they take, widest first, and keep their order otherwise; slice s goes to wave
+//     s mod NC of the workgroup.
+#include <algorithm>
+#include <cmath>
+
+#include "fb_internal.h"
+
+namespace fb {
+
+bool small_append(SmallHost &S, int32_t k0, int32_t K, const int64_t *ptr, const int32_t *col, const float *w)
+{
+    if (K > kSmallStates) return false;
+    const int32_t tm = S.tm;
+    std::vector<int32_t> by_lg[7];
+    for (int32_t r = 0; r < K; ++r) {
+        const int64_t n = ptr[r + 1] - ptr[r];
+        int lg = 0;
+        while (lg <= 6 && n > ((int64_t)tm << lg)) ++lg;
+        if (lg > 6) return false;
+        by_lg[lg].push_back(r);
+    }
+    SmallSub sd{};
+    sd.k0 = k0;
+    sd.K = K;
+    sd.slice0 = (int32_t)S.lg.size();
+    int at = kWave, lg_slice = 0;   // lanes used of the slice being filled
+    for (int lg = 6; lg >= 0; --lg)
+        for (const int32_t r : by_lg[lg]) {
+            if (at >= kWave) {   // (a row that needs fewer lanes than its slice gives takes them all the same)
+                lg_slice = lg;
+                S.lg.push_back(lg);
+                S.rows.resize(S.rows.size() + kWave, kSmallNoRow);
+                S.arcs.resize(S.arcs.size() + (size_t)tm * kWave, Arc{0, -INFINITY});
+                at = 0;
+            }
+            const size_t slice = S.lg.size() - 1;
+            S.rows[slice * kWave + (size_t)at] = (uint32_t)r;
+            for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
+                const int64_t i = e - ptr[r];
+                S.arcs[(slice * (size_t)tm + (size_t)(i % tm)) * kWave + (size_t)at + (size_t)(i / tm)] = Arc{col[e] * 8, w[e]};
+            }
+            at += 1 << lg_slice;
+        }
+    sd.n_slice = (int32_t)S.lg.size() - sd.slice0;
+    if (sd.n_slice > kSmallMaxSlices) return false;
+    S.max_slices = std::max(S.max_slices, sd.n_slice);
+    S.sub.push_back(sd);
+    return true;
+}
+
+// Every index the kernel forms stays inside what it indexes.
+bool small_in_bounds(const SmallHost &S, std::string &why)
+{
+    const size_t n = S.lg.size();
+    if (S.rows.size() != n * kWave || S.arcs.size() != n * (size_t)S.tm * kWave || (S.tm != 2 && S.tm != 4)) { why = "small plan: sizes"; return false; }
+    for (const SmallSub &sd : S.sub) {
+        if (sd.slice0 < 0 || sd.n_slice < 1 || (size_t)sd.slice0 + (size_t)sd.n_slice > n || sd.K < 1 || sd.K > kSmallStates) { why = "small plan: sub-graph"; return false; }
+        std::vector<char> seen((size_t)sd.K, 0);
+        for (int32_t s = sd.slice0; s < sd.slice0 + sd.n_slice; ++s) {
+            if (S.lg[(size_t)s] < 0 || S.lg[(size_t)s] > 6 || (S.tm == 2 && S.lg[(size_t)s] != 0)) { why = "small plan: lanes per row"; return false; }
+            for (int lane = 0; lane < kWave; ++lane) {
+                const uint32_t r = S.rows[(size_t)s * kWave + lane];
+                if (r != kSmallNoRow) {
+                    if (r >= (uint32_t)sd.K || seen[r]) { why = "small plan: row"; return false; }
+                    seen[r] = 1;
+                }
+                for (int t = 0; t < S.tm; ++t) {
+                    const Arc &a = S.arcs[((size_t)s * S.tm + t) * kWave + lane];
+                    if (a.src < 0 || a.src % 8 || a.src / 8 >= sd.K || std::isnan(a.w)) { why = "small plan: arc"; return false; }
+                }
+            }
+        }
+        for (const char c : seen)
+            if (!c) { why = "small plan: a state without a row"; return false; }
+    }
+    return true;
+}
+
+void small_apply_host(const SmallHost &S, int32_t sub, const double *x, double *y)
+{
+    const SmallSub &sd = S.sub[(size_t)sub];
+    for (int32_t s = sd.slice0; s < sd.slice0 + sd.n_slice; ++s) {
+        const int g = 1 << S.lg[(size_t)s];
+        for (int lane = 0; lane < kWave; lane += g) {
+            const uint32_t r = S.rows[(size_t)s * kWave + lane];
+            if (r == kSmallNoRow) continue;
+            double m = -INFINITY, acc = 0.0;
+            for (int pass = 0; pass < 2; ++pass)
+                for (int l = lane; l < lane + g; ++l)
+                    for (int t = 0; t < S.tm; ++t) {
+                        const Arc &a = S.arcs[((size_t)s * S.tm + t) * kWave + l];
+                        const double v = (double)a.w + x[a.src / 8];
+                        if (pass == 0) m = std::max(m, v);
+                        else if (m > -INFINITY) acc += std::exp2(v - m);
+                    }
+            y[r] = m > -INFINITY ? m + std::log2(acc) : m;
+        }
+    }
+}
+
+}  // namespace fb

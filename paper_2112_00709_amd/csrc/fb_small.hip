@@ -1,0 +1,432 @@
+// The alpha / beta recursions (Eq. 13-14) and their best-path form for small (sub-)graphs with vectors in double:
+// numerator chains, alignment and label-sequence graphs, phone loops.
+//
+// A step of such a graph is a few hundred additions; what it costs is the length of the chain of dependent
+// operations from one vector to the next.  The kernel keeps everything off that chain that need not be on it:
+//   * No normalisation.  Exponentials act on differences of two terms, and a double holds a log value of 10^4 to
+//     10^-12, so the vector is carried as it is.  The shift that makes float rows keep their resolution (a row's own
+//     largest entry) is taken by the waves that write rows out.
+//   * The arcs, targets and pdf ids of a lane sit in registers for the whole time loop (fb_small.cpp); a lane asks for
+//     the emissions of its rows kAhead frames at a time, one such group ahead, straight into registers, so a step touches LDS for the gathers
+//     and the new vector only.
+//   * Rows leave through further waves of the workgroup, which read them out of a ring of LDS rows.  With one
+//     computing wave the ring holds blocks of 8 frames and there is a barrier every 8 frames; with more of them the
+//     barrier of every step that they need among themselves serves the writers too.
+// The chain of a step is then: LDS read, add the weight, maximum / difference, one exponential, one logarithm, add
+// the emission, LDS write (and the barrier).
+//
+// Zero-bar is carried as a number that is never left: the vector is held at or above kZero = -1e30 and weights of
+// zero-bar are kZero too, so a sum of two is finite and no step meets inf - inf; what lies below kZeroOut leaves the
+// kernel as -inf.
+//
+// Measured per direction, against the general kernel with 4 waves (fb_recursion_kernel<4, double>): 32 chains of 30-120
+// states over at most 144 frames 124 -> 29 us (of which the computing wave 24); a 16-state graph over 50 frames 55 -> 12
+// (no row over several lanes) or 18 us; 701 states, 3.5 k arcs over at most 211 frames 442 -> 240 us; best path through 32
+// label-sequence graphs of 21-161 states, 209 frames, 194 -> 64 us.  What bounds it: the latency of that chain (310
+// clocks a step with one computing wave and two arcs a row); with 16 slices and more the issue of double arithmetic.
+//
+// Variants <NC, R, TM>: NC computing waves of R slices each, TM arcs per lane; the smallest that holds the batch's
+// largest sub-graph is launched.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <string>
+
+#include "fb_device.h"
+#include "fb_internal.h"
+
+namespace fb {
+
+namespace {
+
+constexpr double kZero = -1.0e30, kZeroOut = -0.5e30;
+
+template <int NC, int R>
+struct SmallShape {
+    static constexpr int NIO = NC == 1 ? 2 : 4;                          // waves that write rows out
+    static constexpr int KS = NC * R * kWave < kSmallStates ? NC * R * kWave : kSmallStates;   // states at most
+    static constexpr int XS = KS + 2;                                    // entries of a row in LDS; entry KS takes what nobody wants
+    static constexpr int RPB = NC == 1 ? 8 : 1;                          // frames between two barriers
+    static constexpr int RB = 2 * RPB;                                   // rows of the ring
+    static constexpr int kAhead = NC == 1 ? 16 : R >= 3 ? 4 : 8;         // frames whose emissions are asked for at a time
+    static constexpr int UIO = KS / kWave;                               // states per lane of a writing wave
+    static_assert(kAhead % RB == 0, "the ring row of an unrolled step is a constant");
+    // x ring, ring of the rows before the emission (backward), back-pointer ring (best path), reduction scratch
+    static constexpr size_t lds_bytes(bool backward, bool tropical)
+    {
+        return (size_t)RB * XS * 8 * (backward ? 2 : 1) + (tropical ? (size_t)RB * XS * 2 : 0) + 8 * (2 * (size_t)NC) + 16;
+    }
+};
+
+// the larger of two values that are never NaN: one instruction, without the quieting of NaNs that fmax() implies
+__device__ __forceinline__ double dmax(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+__device__ __forceinline__ void lds_barrier()   // what this wave has written to LDS is there; its global loads and stores go on
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+}  // namespace
+
+template <int NC, int R, int TM, bool TROP>
+__global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_small_kernel(const RecParams P)
+{
+    using S = SmallShape<NC, R>;
+    constexpr int NIO = S::NIO, XS = S::XS, RPB = S::RPB, RB = S::RB, A = S::kAhead;
+    extern __shared__ double lds_raw[];
+    if (P.started && threadIdx.x == 0) atomicAdd(P.started, 1u);   // this workgroup has its place on a compute unit
+    int b, which;
+    resolve_sequence<NC>(P, lds_raw, b, which);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const RecDir &D = P.dir[which];
+    const bool bwd = !TROP && D.backward != 0;
+    const SmallSub sd = D.small.sub[P.shared ? 0 : b];
+    const int K = sd.K, k0 = sd.k0;
+    const int Tn = min(max(P.lengths[b], 0), P.N);
+    auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
+
+    double *xr = lds_raw;                                   // [RB][XS]
+    double *pr = xr + (size_t)RB * XS;                      // [RB][XS], backward only
+    uint16_t *bpr = (uint16_t *)(pr + (bwd ? (size_t)RB * XS : 0));   // [RB][XS], best path only
+    double *fin = (double *)(bpr + (TROP ? (size_t)RB * XS : 0));     // [NC] + [NC] last reduction
+
+    const size_t out_ld = P.shared ? (size_t)(D.out_ld ? D.out_ld : K) : (size_t)P.Ktot;
+    const size_t out_at = P.shared ? (size_t)b * P.N * out_ld : (size_t)k0;
+    float *out_f = (D.out && !D.out_carrier) ? (float *)D.out + out_at : nullptr;
+    double *out_t = (D.out && D.out_carrier) ? (double *)D.out + out_at : nullptr;
+    double *off_seq = D.off ? D.off + (size_t)b * P.N : nullptr;
+    const int n_bar = (Tn - 1 + RPB - 1) / RPB;             // blocks of rows behind the first one
+
+    if (Tn > 0 && wave < NC) {
+        // ---- computing waves
+        uint32_t so[R][TM], tg[R];
+        double w[R][TM];
+        uint32_t po[R];                                     // the lane's place in a row of emissions, bytes
+        int lg[R];
+        char *const lds = (char *)lds_raw;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int s = wave + j * NC;
+            const bool have = s < sd.n_slice;               // (a slice that is not there: every lane adds up nothing)
+            const size_t at = (size_t)(sd.slice0 + (have ? s : 0));
+            const uint32_t row = have ? D.small.rows[at * kWave + lane] : kSmallNoRow;
+            lg[j] = have ? __builtin_amdgcn_readfirstlane(D.small.lg[at]) : 0;
+            tg[j] = row == kSmallNoRow ? (uint32_t)S::KS * 8u : row * 8u;
+            po[j] = (uint32_t)P.pdf[k0 + (row == kSmallNoRow ? 0 : (int)row)] * 4u;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) {
+                const Arc a = D.small.arcs[(at * TM + t) * kWave + lane];
+                so[j][t] = (uint32_t)a.src;
+                w[j][t] = have ? dmax((double)a.w, kZero) : kZero;
+            }
+        }
+        // the row of emissions to ask for next (uniform): the frames in order of the steps, the last one again behind the end
+        const ptrdiff_t em_step = bwd ? -(ptrdiff_t)P.D : (ptrdiff_t)P.D;
+        const float *em_row = P.emis + ((size_t)b * P.N + (size_t)frame(0)) * P.D;
+        int em_left = Tn - 1;
+        auto next_em = [&]() {
+            em_row += em_left > 0 ? em_step : 0;
+            --em_left;
+        };
+        auto emission = [&](int j) { return *(const float *)((const char *)em_row + po[j]); };
+        auto ask = [&](float(&to)[R][A]) __attribute__((always_inline)) {   // the next A frames' emissions
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+#pragma unroll
+                for (int j = 0; j < R; ++j) to[j][a] = emission(j);
+                next_em();
+            }
+        };
+        float e[R][A];
+        {   // first frame: start weight (x) emission
+            float e0[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) e0[j] = emission(j);
+            next_em();
+            ask(e);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const bool real = tg[j] != (uint32_t)S::KS * 8u;
+                const double s = real ? (double)D.bound[k0 + (int)(tg[j] >> 3)] : kZero;
+                *(double *)(lds + tg[j]) = dmax(s + (double)e0[j] * kLog2e, kZero);
+                if (bwd) *(double *)((char *)pr + tg[j]) = s;
+            }
+        }
+        lds_barrier();
+        // step i0 + a, a < A a constant
+        auto step = [&](auto ac, auto bwd_c) __attribute__((always_inline)) {
+            constexpr int a = decltype(ac)::value;
+            constexpr bool kBwd = decltype(bwd_c)::value;
+            constexpr int kRow = XS * 8, cur = (a % RB) * kRow, nxt = ((a + 1) % RB) * kRow;
+            double g[R][TM];
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+#pragma unroll
+                for (int t = 0; t < TM; ++t) g[j][t] = *(const double *)(lds + so[j][t] + cur);
+            double ed[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) ed[j] = (double)e[j][a] * kLog2e;
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                double m;
+                if constexpr (TROP) {
+                    uint32_t arg = so[j][0];
+                    m = g[j][0] + w[j][0];
+#pragma unroll
+                    for (int t = 1; t < TM; ++t) {          // (the first of equal terms)
+                        const double x = g[j][t] + w[j][t];
+                        if (x > m) { m = x; arg = so[j][t]; }
+                    }
+                    if (TM > 2 && lg[j]) {
+                        int ai = (int)arg;
+                        group_best(m, ai, lg[j], lane);
+                        arg = (uint32_t)ai;
+                    }
+                    *(double *)(lds + tg[j] + nxt) = dmax(m + ed[j], kZero);
+                    *(uint16_t *)((char *)bpr + (tg[j] >> 2) + nxt / 4) = (uint16_t)(arg >> 3);
+                } else {
+                    float l;
+                    if constexpr (TM == 2) {                // two terms: the larger + log2(1 + 2^-|difference|)
+                        const double x0 = g[j][0] + w[j][0], x1 = g[j][1] + w[j][1];
+                        m = dmax(x0, x1);
+                        l = flog2(1.0f + fexp2(-fabsf((float)(x0 - x1))));
+                    } else {
+                        double x[TM];
+#pragma unroll
+                        for (int t = 0; t < TM; ++t) x[t] = g[j][t] + w[j][t];
+                        m = dmax(dmax(x[0], x[1]), dmax(x[2], x[3]));
+                        float s = (fexp2((float)(x[0] - m)) + fexp2((float)(x[1] - m))) + (fexp2((float)(x[2] - m)) + fexp2((float)(x[3] - m)));
+                        if (lg[j]) group_total(m, s, lg[j], lane);
+                        l = flog2(s);
+                    }
+                    *(double *)(lds + tg[j] + nxt) = dmax((m + ed[j]) + (double)l, kZero);
+                    if constexpr (kBwd) *(double *)((char *)pr + tg[j] + nxt) = m + (double)l;
+                }
+            }
+            if constexpr ((a + 1) % RPB == 0) lds_barrier();
+            __builtin_amdgcn_sched_barrier(0);              // (what belongs to a step stays in it)
+        };
+        // Groups of A steps without a branch between them; a group's emissions are asked for all at once when the group
+        // before it begins.  (Asked for one step's at a time, in the place of those just used, they end up in registers of
+        // their own that the compiler moves into place at the end of the group - and has to wait for there.)
+        auto all_steps = [&](auto bwd_c) __attribute__((always_inline)) {
+            constexpr auto kA = std::make_integer_sequence<int, A>{};
+            int i0 = 1;
+            for (; i0 + A <= Tn; i0 += A) {
+                float ahead[R][A];
+                ask(ahead);
+                __builtin_amdgcn_sched_barrier(0);
+                unrolled([&](auto ac) __attribute__((always_inline)) { step(ac, bwd_c); }, kA);
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+#pragma unroll
+                    for (int a = 0; a < A; ++a) e[j][a] = ahead[j][a];
+            }
+            unrolled([&](auto ac) __attribute__((always_inline)) {
+                if (i0 + decltype(ac)::value < Tn) step(ac, bwd_c);
+            }, kA);
+        };
+        if (bwd) all_steps(std::true_type{});
+        else all_steps(std::false_type{});
+        if ((Tn - 1) % RPB != 0) lds_barrier();             // the last block's rows
+    } else if (Tn > 0) {
+        // ---- writing waves: a row is one wave's, the rows go round the waves
+        const int q = wave - NC;
+        const double *rows = bwd ? pr : xr;
+        const double scale = (double)D.out_scale;
+        const bool shifted = !out_t && (out_f || off_seq);
+        struct Row { double v[S::UIO]; uint16_t p[TROP ? S::UIO : 1]; double c; };
+        // the lane's u-th state; lanes behind the last state take that one again (and store the same value to the same place:
+        // no lane has to be masked out)
+        auto at = [&](int u) { return min(u * kWave + lane, K - 1); };
+        auto fetch = [&](int i, Row &r) __attribute__((always_inline)) {   // row i of the ring -> registers
+            const double *row = rows + (size_t)(i % RB) * XS;
+#pragma unroll
+            for (int u = 0; u < S::UIO; ++u) r.v[u] = row[at(u)];
+            if constexpr (TROP) {
+                const uint16_t *srow = bpr + (size_t)(i % RB) * XS;
+#pragma unroll
+                for (int u = 0; u < S::UIO; ++u) r.p[u] = srow[at(u)];
+            }
+        };
+        auto take_shift = [&](Row &r) __attribute__((always_inline)) {     // the row's largest entry (any number near it serves)
+            if (!shifted) return;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < S::UIO; ++u)
+                if (u * kWave < K) mx = tmax(mx, (float)r.v[u]);
+            mx = wave_max(mx);
+            r.c = (double)mx > kZeroOut ? (double)mx : 0.0;
+        };
+        auto emit = [&](int i, const Row &r, auto u0, auto u1) __attribute__((always_inline)) {   // states u0 * 64 .. u1 * 64 of row i -> global memory
+            const int f = frame(i);
+            if (shifted) {
+                if (out_f) {
+                    float *orow = out_f + (size_t)f * out_ld;
+#pragma unroll
+                    for (int u = u0; u < u1; ++u)
+                        if (u * kWave < K) orow[at(u)] = r.v[u] > kZeroOut ? (float)(r.v[u] - r.c) * D.out_scale : -INFINITY;
+                }
+                if (off_seq && u0 == 0 && lane == 0) off_seq[f] = r.c * scale;
+            } else if (out_t) {
+                double *orow = out_t + (size_t)f * out_ld;
+#pragma unroll
+                for (int u = u0; u < u1; ++u)
+                    if (u * kWave < K) orow[at(u)] = r.v[u] > kZeroOut ? r.v[u] : -INFINITY;
+            }
+            if (D.cum && u0 == 0 && lane == 0) D.cum[(size_t)b * P.N + f] = 0.0f;   // (carrier rows are not shifted)
+            if constexpr (TROP) {
+                if (D.bp && i > 0) {
+                    uint16_t *orow = D.bp + (P.shared ? ((size_t)b * P.N + f) * D.bp_ld : (size_t)f * D.bp_ld + k0);
+#pragma unroll
+                    for (int u = u0; u < u1; ++u)
+                        if (u * kWave < K) orow[at(u)] = r.p[u];
+                }
+            }
+        };
+        using N0 = std::integral_constant<int, 0>;
+        using NH = std::integral_constant<int, (S::UIO + 1) / 2>;
+        using NU = std::integral_constant<int, S::UIO>;
+        const bool any_row = shifted || out_t || D.cum || (TROP && D.bp);
+        if constexpr (NC == 1) {
+            // the rows of a block: a wave's share of them all read, then all maxima (independent chains), then all stored
+            constexpr auto kMine = std::make_integer_sequence<int, RPB / NIO>{};
+            auto block = [&](int i0, int cnt) __attribute__((always_inline)) {
+                Row r[RPB / NIO];
+                unrolled([&](auto x) __attribute__((always_inline)) { fetch(i0 + x * NIO + q, r[x]); }, kMine);   // (rows behind cnt: read and not used)
+                unrolled([&](auto x) __attribute__((always_inline)) { take_shift(r[x]); }, kMine);
+                unrolled([&](auto x) __attribute__((always_inline)) {
+                    if (x * NIO + q < cnt) emit(i0 + x * NIO + q, r[x], N0{}, NU{});
+                }, kMine);
+            };
+            lds_barrier();
+            if (any_row) block(0, 1);
+            for (int n = 1; n <= n_bar; ++n) {
+                lds_barrier();                              // block n is in the ring
+                if (any_row) block((n - 1) * RPB + 1, min(RPB, Tn - 1 - (n - 1) * RPB));
+            }
+        } else {
+            // a wave's row takes it four steps: read (it is gone two steps later), maximum, first half stored, second half
+            static_assert(NIO == 4, "stages of a row");
+            Row r;
+            auto stage = [&](int s, int i) __attribute__((always_inline)) {
+                if (s == 0) fetch(i, r);
+                else if (s == 1) take_shift(r);
+                else if (s == 2) emit(i, r, N0{}, NH{});
+                else emit(i, r, NH{}, NU{});
+            };
+            for (int n = 0; n <= n_bar; ++n) {
+                lds_barrier();                              // row n is in the ring
+                const int s = (n - q) & 3;
+                if (any_row && n >= s) stage(s, n - s);
+            }
+            const int s = (n_bar - q) & 3;
+            if (any_row && n_bar >= s)
+                for (int t = s + 1; t < 4; ++t) stage(t, n_bar - s);
+        }
+    }
+
+    if (Tn > 0) {
+        // ---- log Z (or the best score) from the last vector and the end weights, by the computing waves
+        const double *xl = xr + (size_t)((Tn - 1) % RB) * XS;
+        if (wave < NC) {
+            double m = TROP ? kZero : (double)kNegBig;
+            float s = 0.0f;
+            int at = 0x7fffffff;
+            for (int k = wave * kWave + lane; k < K; k += NC * kWave) {
+                const double t = xl[k] + (double)D.obound[k0 + k];
+                if constexpr (TROP) {
+                    if (t > m) { m = t; at = k; }
+                } else {
+                    lse_add(m, s, t);
+                }
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                const double m2 = __shfl_xor(m, o, 64);
+                if constexpr (TROP) {
+                    const int a2 = __shfl_xor(at, o, 64);
+                    if (m2 > m || (m2 == m && a2 < at)) { m = m2; at = a2; }
+                } else {
+                    lse_merge(m, s, m2, __shfl_xor(s, o, 64));
+                }
+            }
+            if (lane == 0) { fin[wave] = m; fin[NC + wave] = TROP ? (double)at : (double)s; }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double m = fin[0];
+            if constexpr (TROP) {
+                double a = fin[NC];
+                for (int v = 1; v < NC; ++v)
+                    if (fin[v] > m || (fin[v] == m && fin[NC + v] < a)) { m = fin[v]; a = fin[NC + v]; }
+                const bool none = !(m > kZeroOut);
+                if (D.logz) D.logz[b] = none ? -INFINITY : m * kLn2;
+                if (D.last) D.last[b] = none ? -1 : (int)a;
+            } else {
+                float s = (float)fin[NC];
+                for (int v = 1; v < NC; ++v) lse_merge(m, s, fin[v], (float)fin[NC + v]);
+                if (D.logz) D.logz[b] = m > kZeroOut ? (m + (double)flog2(s)) * kLn2 : -INFINITY;
+            }
+        }
+    } else if (threadIdx.x == 0) {
+        if (D.logz) D.logz[b] = -INFINITY;
+        if (TROP && D.last) D.last[b] = -1;
+    }
+
+    // ---- padded frames
+    if (D.fill_pad) {
+        constexpr int NT = (NC + NIO) * kWave;
+        const int tid = threadIdx.x;
+        if (out_f)
+            for (int f = Tn; f < P.N; ++f)
+                for (int k = tid; k < K; k += NT) out_f[(size_t)f * out_ld + k] = -INFINITY;
+        if (off_seq)
+            for (int f = Tn + tid; f < P.N; f += NT) off_seq[f] = 0.0;
+    }
+    count_done(P);
+}
+
+template <int NC, int R, int TM, bool TROP>
+static int launch_variant(const RecParams &p, void *stream)
+{
+    using S = SmallShape<NC, R>;
+    bool backward = false;
+    for (int i = 0; i < p.n_dir; ++i) backward = backward || p.dir[i].backward != 0;
+    const size_t lds = S::lds_bytes(backward, TROP);
+    static_assert(S::lds_bytes(true, TROP) <= 64 * 1024, "on-chip memory of a launch without a raised limit");
+    const int32_t n_seq = p.order ? p.n_launch : p.B;
+    hipLaunchKernelGGL((fb_small_kernel<NC, R, TM, TROP>), dim3((unsigned)(n_seq * p.n_dir)), dim3((NC + S::NIO) * kWave), lds, (hipStream_t)stream, p);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? FB_OK : fail(FB_EHIP, std::string("small-graph kernel launch: ") + hipGetErrorString(e));
+}
+
+template <int TM, bool TROP>
+static int launch_size(const RecParams &p, int slices, void *stream)
+{
+    if (slices <= 1) return launch_variant<1, 1, TM, TROP>(p, stream);
+    if (slices <= 2) return launch_variant<1, 2, TM, TROP>(p, stream);
+    if (slices <= 4) return launch_variant<2, 2, TM, TROP>(p, stream);
+    if (slices <= 8) return launch_variant<4, 2, TM, TROP>(p, stream);
+    if (slices <= 16) return launch_variant<8, 2, TM, TROP>(p, stream);
+    if (slices <= 24) return launch_variant<8, 3, TM, TROP>(p, stream);
+    if (slices <= kSmallMaxSlices) return launch_variant<8, 4, TM, TROP>(p, stream);
+    return fail(FB_EHIP, "internal error: small-graph launch");
+}
+
+int launch_small(const RecParams &p, int tm, int slices, bool tropical, void *stream)
+{
+    for (int i = 0; i < p.n_dir; ++i)
+        if (!p.dir[i].small.arcs) return fail(FB_EHIP, "internal error: small-graph launch without its plan");
+    if (p.Kcap > kSmallStates || (tm != 2 && tm != 4)) return fail(FB_EHIP, "internal error: small-graph launch");
+    if (tm == 2) return tropical ? launch_size<2, true>(p, slices, stream) : launch_size<2, false>(p, slices, stream);
+    return tropical ? launch_size<4, true>(p, slices, stream) : launch_size<4, false>(p, slices, stream);
+}
+
+}  // namespace fb

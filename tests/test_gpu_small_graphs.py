@@ -1,0 +1,109 @@
+"""The small-graph recursion kernel at the sizes where it can go wrong: around the states its waves hold, around its
+groups of frames, rows over one to 64 lanes, rows without arcs, graphs it hands to the general kernel."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2112_00709_amd as fb
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(rng, K, deg, hub, D):
+    """K states, about deg arcs each; `hub` arcs into one state and out of another; a state without arcs in."""
+    n = int(K * deg)
+    src, dst = rng.integers(0, K, n), rng.integers(0, K, n)
+    dst[dst == K // 2] = 0
+    src = np.concatenate([src, np.arange(K), np.arange(hub) % K, np.full(hub, K - 1)])
+    dst = np.concatenate([dst, (np.arange(K) + 1) % K, np.full(hub, K // 3), np.arange(hub) % K])
+    keep = dst != K // 2 if K > 3 else np.ones(dst.size, bool)
+    src, dst = src[keep].astype(np.int32), dst[keep].astype(np.int32)
+    logw = (-rng.exponential(size=src.size)).astype(np.float32)
+    logw[rng.integers(0, logw.size, max(1, logw.size // 30))] = -np.inf
+    init = (-rng.exponential(size=K)).astype(np.float32)
+    init[0] = -np.inf if K > 1 else 0.0
+    return wl.Graph(K, src, dst, logw, rng.integers(0, D, K).astype(np.int32), init, (-rng.exponential(size=K)).astype(np.float32))
+
+
+@pytest.mark.parametrize("K,deg,hub,frames", [
+    (1, 1, 0, (1, 2, 3)), (7, 2, 6, (8, 9, 10)), (64, 2, 0, (16, 17, 18)), (65, 2.2, 30, (24, 25, 33)), (128, 0.9, 0, (1, 15, 41)),
+    (129, 2, 100, (7, 26, 34)), (256, 1.5, 200, (5, 6, 50)), (257, 3, 250, (12, 13, 14)), (512, 1.8, 0, (3, 31, 32)),
+    (513, 2.5, 400, (19, 20, 21)), (900, 2, 256, (4, 11, 37)), (1024, 1, 100, (2, 10, 23)), (600, 2, 520, (9, 30, 31))])
+def test_shared_small_graphs(K, deg, hub, frames):
+    rng = np.random.default_rng(K)
+    D = 11
+    g = _graph(rng, K, deg, min(hub, K), D)
+    lengths = np.array(list(frames) + [0], dtype=np.int32)
+    B, N = lengths.size, int(lengths.max()) + 1
+    emis = (rng.standard_normal((B, N, D)) * 3).astype(np.float32)
+    for b in range(B):
+        emis[b, lengths[b]:] = np.nan
+    _check(g, emis, lengths, D)
+
+
+@pytest.mark.parametrize("kind", ["chain", "ctc"])
+def test_packed_small_graphs(kind):
+    """One batch with sub-graphs of 3 to 1020 states: the variant is the largest one's, the others leave lanes idle."""
+    D = 17
+    rng = np.random.default_rng(5)
+    if kind == "chain":
+        phones = np.array([1, 21, 22, 43, 85, 86, 170, 171, 340])
+        g = wl.chain_graphs(rng, phones, D)
+        lengths = np.array([3, 66, 66, 131, 257, 259, 511, 520, 1021], dtype=np.int32)
+    else:
+        g = wl.ctc_graphs([rng.integers(1, D, n).tolist() for n in (1, 31, 32, 63, 64)], 0)
+        lengths = np.array([1, 70, 65, 130, 140], dtype=np.int32)
+    emis = (rng.standard_normal((lengths.size, int(lengths.max()), D)) * 2).astype(np.float32)
+    _check(g, emis, lengths, D)
+
+
+def _check(g, emis, lengths, D):
+    import torch
+    B, N, _ = emis.shape
+    h = fb.graph_from(g, D)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    fb.POISON_NEW_BUFFERS = True
+    try:
+        a, ca, za = fb.fb_alpha(h, e, l)
+        b, cb, zb = fb.fb_beta(h, e, l)
+        gam, rho = fb.fb_posteriors(h, a, b, l, B, N)
+        score, path = fb.fb_viterbi(h, e, l)
+    finally:
+        fb.POISON_NEW_BUFFERS = False
+    torch.cuda.synchronize()
+    a, b, ca, cb, za, zb, gam, rho, score, path = (t.cpu().numpy() for t in (a, b, ca, cb, za, zb, gam, rho, score, path))
+    live = np.flatnonzero(lengths > 0)
+    em = np.nan_to_num(emis)
+    ref = oracle.forward_backward(g, em, lengths, sel=live)
+    best = oracle.viterbi(g, em, lengths, sel=live)
+    off = g.state_off if g.packed else None
+    for i, q in enumerate(live):
+        T = int(lengths[q])
+        rows = (lambda x: x[:T, off[q]:off[q + 1]]) if g.packed else (lambda x: x[q, :T])
+        for z in (za[q], zb[q]):
+            assert (np.isneginf(z) and np.isneginf(ref.logz[i])) or abs(z - ref.logz[i]) <= 1e-4 * max(1.0, abs(ref.logz[i]))
+        # the rows between the calls are floats: in a long chain a state that matters lies far below its frame's best, and
+        # its posterior carries half a unit of the size of its two entries
+        heavy = ref.gamma[i] > 1e-7
+        tol = 1e-5 + 2.0 ** -24 * (np.abs(rows(a)) + np.abs(rows(b)))[heavy].max(initial=0.0)
+        assert np.abs(rows(gam) - ref.gamma[i]).max() <= tol
+        assert np.abs(rho[q] - ref.rho[i]).max() <= tol
+        for x, c, want in ((rows(a), ca[q, :T], ref.alpha[i]), (rows(b), cb[q, :T], ref.beta[i])):
+            assert np.array_equal(np.isneginf(x), np.isneginf(want))
+            fin = np.isfinite(want)
+            # a stored entry is a float: half a unit of its own size, and a few units of the exponentials per frame
+            err = np.abs((x + c[:, None])[fin] - want[fin])
+            assert np.all(err <= 1e-7 * np.abs(x[fin]) + 2e-7 * T + 1e-6)
+        if np.isneginf(best.score[i]):
+            assert np.isneginf(score[q]) and np.all(path[q] == -1)
+        else:
+            # the sums are double; every weight of the path (T - 1 arcs, initial, final) was rounded to a float in log2
+            # units once: half a unit of its size, and no weight here is larger than 16
+            tol = 2.0 ** -24 * 16 * (T + 1)
+            assert abs(score[q] - best.score[i]) <= tol
+            assert abs(oracle.path_score(g, em[q], path[q, :T]) - best.score[i]) <= 2 * tol
+            assert np.all(path[q, T:] == -1)
+    for q in np.flatnonzero(lengths == 0):
+        assert np.isneginf(za[q]) and np.isneginf(zb[q]) and np.isneginf(score[q]) and np.all(path[q] == -1)
+    h.destroy()
