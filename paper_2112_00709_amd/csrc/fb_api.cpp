@@ -162,6 +162,7 @@ int run_posteriors(const PostGraph *gs, int n_graph, const int32_t *lengths, int
     p.lengths = lengths;
     p.B = B; p.N = N; p.D = D;
     p.pdf_out = pdf_out;
+    if (post_small_applies(p)) return launch_post_small(p, stream);
     p.frames_per_block = 6;
     if (gradient_kernel_applies(p)) {   // shared float denominator + small packed numerators: the specialised kernel
         const size_t glds = gradient_lds_bytes(p);

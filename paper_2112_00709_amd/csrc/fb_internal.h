@@ -467,6 +467,8 @@ struct BacktraceParams {
 };
 int launch_backtrace(const BacktraceParams &p, void *stream);
 int launch_posteriors(const PostParams &p, size_t lds_bytes, void *stream);
+bool post_small_applies(const PostParams &p);   // graphs of at most kSmallStates states each, results written (not added)
+int launch_post_small(const PostParams &p, void *stream);
 bool gradient_kernel_applies(const PostParams &p);
 size_t gradient_lds_bytes(const PostParams &p);
 int launch_gradient(const PostParams &p, size_t lds_bytes, void *stream);

@@ -107,3 +107,30 @@ def _check(g, emis, lengths, D):
     for q in np.flatnonzero(lengths == 0):
         assert np.isneginf(za[q]) and np.isneginf(zb[q]) and np.isneginf(score[q]) and np.all(path[q] == -1)
     h.destroy()
+
+
+@pytest.mark.parametrize("K,D,phones", [(3, 5, 1), (64, 7, 3), (65, 64, 12), (500, 65, 25), (1000, 300, 60)])
+def test_objective_and_gradient_with_small_denominators(K, D, phones):
+    """Both graphs' shares of a frame's gradient from one wave: few pdfs and many, sequences of one frame and of none."""
+    import torch
+    rng = np.random.default_rng(K)
+    den = _graph(rng, K, 2, 0, D)
+    num = wl.chain_graphs(rng, np.array([phones, 1, max(1, phones // 2), 1]), D)
+    lengths = np.array([3 * phones + 2, 1, 3 * max(1, phones // 2), 0], dtype=np.int32)
+    emis = (rng.standard_normal((4, int(lengths.max()) + 1, D)) * 2).astype(np.float32)
+    hd, hn = fb.graph_from(den, D), fb.graph_from(num, D)
+    fb.POISON_NEW_BUFFERS = True
+    try:
+        loss, zn, zd, grad = fb.lfmmi_loss_grad(hd, hn, torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda())
+    finally:
+        fb.POISON_NEW_BUFFERS = False
+    torch.cuda.synchronize()
+    zn, zd, grad = zn.cpu().numpy(), zd.cpu().numpy(), grad.cpu().numpy()
+    live = np.flatnonzero(lengths > 0)
+    ref = oracle.lfmmi(den, num, emis, lengths, sel=live)
+    for got, want in ((zn[live], ref.logz_num), (zd[live], ref.logz_den)):
+        both = np.isneginf(got) & np.isneginf(want)
+        assert np.all(both | (np.abs(got - want) <= 1e-4 * np.maximum(1.0, np.abs(want))))
+    assert np.abs(grad[live] - ref.grad).max() <= 1e-5
+    assert np.all(grad[3] == 0) and np.isneginf(zn[3]) and np.isneginf(zd[3])
+    hd.destroy(); hn.destroy()
