@@ -336,7 +336,7 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
  * the total probability is handed out again over the states in proportion to pi = exp(init) / sum exp(init), i.e.
  * the hidden Markov model with the transition matrix T' = (I + leak 1 pi^T) T and the graph's own initial and
  * final weights.  log Z and the pdf posteriors (Eq. 13-15 for T') of every sequence, in one call; leak = 0 gives
- * the graph itself.  Not part of lfmmi_loss_grad, and not tuned like it: a plain kernel, one workgroup per sequence.
+ * the graph itself.  Not part of lfmmi_loss_grad.
  * Vectors are float, rescaled to sum 1 in every frame, with no fallback: an entry below 2^-126 of its frame's total
  * is taken as 0 (as in any implementation of this kind; harmless unless a later frame's emissions lift such a state
  * by as much again, which takes emissions that differ by more than 87 nats between live states of one frame).
@@ -345,7 +345,7 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
  *   leak      in [0, 1]
  *   logz      out, device double [B] (-inf for a sequence without a path, whose posteriors are 0)
  *   pdf_post  out, device float [B][N][D], 0 on padded frames
- *   ws        device scratch of at least fb_leaky_workspace_bytes() (the forward vectors: 4 bytes per state and frame)
+ *   ws        device scratch of at least fb_leaky_workspace_bytes() (the vectors of one or both sweeps: 4 bytes per state and frame each)
  * FB_EINVAL: NULL arguments, a packed or host-only graph, sizes <= 0, D != the graph's D, leak outside [0, 1],
  * workspace missing or too small.  FB_EUNSUPPORTED: more than 8192 states, or four state vectors and an emission row
  * exceed the 160 KB of on-chip memory of a compute unit (16 K + 4 D bytes).

@@ -297,6 +297,48 @@ void *static_scratch()
 
 namespace fb {
 
+// See fb_internal.h.  only_ask: whether the gradient kernel takes this shape (1 or 0), nothing is launched.
+int leaky_gradient(const fb_graph *g, const float *a, const float *b, int32_t ld, const int32_t *fmt_a, const int32_t *fmt_b,
+                   const float *cum_a, const float *cum_b, const double *logz, const int32_t *lengths, int32_t B, int32_t N, int32_t D,
+                   float *pdf_out, bool only_ask, void *stream)
+{
+    PostParams p{};
+    p.n_graph = 1;
+    p.g[0] = make_post(g, a, b, false, 1.0f, 1.0f, nullptr);
+    p.g[0].ld = ld;
+    p.g[0].fmt_a = fmt_a;
+    p.g[0].fmt_b = fmt_b;
+    p.cum_a = cum_a; p.cum_b = cum_b; p.logz = logz;
+    p.lengths = lengths;
+    p.B = B; p.N = N; p.D = D;
+    p.Kcap = g->max_sub_K;
+    p.pdf_out = pdf_out;
+    p.frames_per_block = 6;
+    const size_t lds = gradient_lds_bytes(p);
+    if (only_ask) return gradient_kernel_applies(p) && lds <= kLdsBytes ? 1 : 0;
+    return launch_gradient(p, lds, stream);
+}
+
+// The recursion's parameters but for the leaky form's own (rows, offsets, flags, q).
+RecParams leaky_recursion_params(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D)
+{
+    RecParams p{};
+    p.n_dir = 2;
+    p.pdf = g->d_pdf;
+    p.emis = emis;
+    p.lengths = lengths;
+    p.B = B; p.N = N; p.D = D;
+    p.shared = 1;
+    p.Ktot = g->K;
+    p.Kcap = g->max_sub_K;
+    p.Ecap = D;
+    for (int i = 0; i < 2; ++i) {
+        p.dir[i] = make_dir(g, i == 1, nullptr, true, nullptr, nullptr, 1.0f, false);
+        p.dir[i].out_linear = 1;
+    }
+    return p;
+}
+
 void static_scratch_init() { (void)static_scratch(); }   // set-up time, this device current: later calls find the address
 
 void side_stream_init()

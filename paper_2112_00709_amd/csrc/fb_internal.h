@@ -380,6 +380,7 @@ struct RecDir {
     int32_t *last;         // tropical semiring: [B] local id of the best end state (-1: none)
     SmallDev small;        // small-graph kernel: its plan for this direction
     PStreamDev prob;       // probability-domain kernel: its plan for this direction
+    const float *rank1;    // ... leaky-HMM form: q by target (states, clone slots, dump slot), see linear_run
     int out_linear;        // ... out takes the vectors as they are kept (entry = 2^(log2 of the true value - cum)), not their logs
     int32_t *fmt;          // ... [B], nullable: 1 if the sequence's rows in out are in that form, 0 if they are logs (the run
                            //     fell back to the log form)
@@ -392,6 +393,7 @@ constexpr int kDoneFused = 16;     // ... of the word PostParams::fused of the c
 
 struct RecParams {
     RecDir dir[2];
+    float leak;            // leaky-HMM form of the probability-domain kernel: the fraction handed out again
     int n_dir;
     const int32_t *pdf;
     const float *emis;
@@ -465,7 +467,17 @@ struct BacktraceParams {
     int32_t frames;          // back-pointer rows the kernel holds in LDS at a time (set by launch_backtrace)
     int32_t *path;           // [B][N]
 };
+// The leaky-HMM form of the probability-domain kernel: its vector is kept 2^kLeakyBiasDrop lower, so that the sum over all
+// its entries and the share of it that a row gets are floats too (beyond that a run gives up as it does everywhere).
+constexpr int kLeakyBiasDrop = 22;
+size_t leaky_linear_lds_bytes(int32_t K, int32_t Ccap, int32_t D, bool backward);
+int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream);   // gave_up [n_dir][B], written
 int launch_backtrace(const BacktraceParams &p, void *stream);
+// pdf posteriors (sign +1) of a shared graph from rows of values in the workspace form (fb_api.cpp): the leaky-HMM mode
+int leaky_gradient(const fb_graph *g, const float *a, const float *b, int32_t ld, const int32_t *fmt_a, const int32_t *fmt_b,
+                   const float *cum_a, const float *cum_b, const double *logz, const int32_t *lengths, int32_t B, int32_t N, int32_t D,
+                   float *pdf_out, bool only_ask, void *stream);
+RecParams leaky_recursion_params(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D);
 int launch_posteriors(const PostParams &p, size_t lds_bytes, void *stream);
 bool post_small_applies(const PostParams &p);   // graphs of at most kSmallStates states each, results written (not added)
 int launch_post_small(const PostParams &p, void *stream);

@@ -703,6 +703,15 @@ __device__ unsigned int g_linear_restarts;   // diagnostic: sequences (x directi
 
 typedef uint32_t close_vector_t __attribute__((ext_vector_type(2 * kPMaxClose)));
 
+// LEAKY: the same recursion for the leaky-HMM of the graph (fb_leaky_posteriors), whose transition matrix is
+// (I + leak 1 pi^T) T.  The rank-one term stays apart from the sparse one and needs one number of the previous vector:
+//   forward   row j gets leak sum_k(x[k]) q[j],  q = T^t pi            (sum weights 1, share of a row q)
+//   backward  row i gets leak sum_k(q[k] x[k])                          (sum weights q, share of a row 1)
+// so a lane adds up what it writes (times its sum weight), a wave leaves its sum in a slot, and every wave adds the
+// slots of the previous step up in the same order when a step starts.  q sits in LDS by target; the entry of the slice
+// that closes next is asked for when the one before it has closed.  A clone takes no share of its own (its sign bit
+// says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
+template <bool LEAKY>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
     constexpr int NW = kNWShared, XF = kXsFixed, R = kPResident;
@@ -728,11 +737,13 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // rows on their way out that are not the vector itself: beta before the emissions are applied (backward), and
     // either direction's rows as logarithms when that is the form they leave in; two buffers that follow each other,
     // present only when used
-    const bool log_rows = R_.out != nullptr && R_.out_linear == 0;
+    const bool log_rows = !LEAKY && R_.out != nullptr && R_.out_linear == 0;
     const bool staged = bwd || log_rows;
-    float *bh = xb + Xs + XF;
-    float *red = staged ? bh + 2 * XF : bh;
-    float *er = red + 64;
+    const int XL = LEAKY ? (nX + 3) & ~3 : XF;   // floats of a buffer behind the first (leaky: q needs the room)
+    float *bh = xb + Xs + XL;
+    float *red = staged ? bh + 2 * XL : bh;
+    float *qt = red + 64;                        // leaky only: q by target
+    float *er = LEAKY ? qt + XL : red + 64;
     float *emaxw = red + 4;
 
     const float *em_seq = P.emis + (size_t)b * P.N * P.D;
@@ -744,7 +755,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         wmax = wave_max(wmax);
         if (lane == 0) __builtin_amdgcn_ds_fmaxf((__attribute__((address_space(3))) float *)(red + i % 3), wmax, 0, 0, false);
     };
-    const int kLinBias = S.bias;
+    const int kLinBias = S.bias - (LEAKY ? kLeakyBiasDrop : 0);
     const float kLinDimP = S.dim;
     const float unbias = __uint_as_float((uint32_t)(127 - kLinBias) << 23);   // 2^-bias
     // a step maximum the run cannot go on from: a lane gave up (+inf), or the vector fell more than 126 binary orders
@@ -869,6 +880,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     __syncthreads();
     if (tid < 3) er[tid * Es + P.D] = -INFINITY;   // what the dump slot "emits": its entry stays zero whatever the frame's scale
     if (tid < 8) red[tid] = (tid == 7 || tid == 3) ? -INFINITY : 0.0f;
+    if constexpr (LEAKY) {
+        for (int k = tid; k < nX; k += NT) qt[k] = R_.rank1[k];
+        if (tid < 2) red[32 + tid * 16 + NC] = 0.0f;   // (the data-moving wave writes no rows)
+    }
     __syncthreads();
     if (io_wave) {
         stage(frame(0), er);
@@ -903,7 +918,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // row needs to stay a float (the vector's entries are then smaller, and below the range the run gives up as ever).
     float base0 = M0 > -INFINITY ? M0 - (float)kLinBias : 0.0f;
     if (bwd && M0 > -INFINITY) base0 = tmax(base0, red[3] - 126.0f);
-    float wmax = 0.0f;
+    float wmax = 0.0f, wsum = 0.0f;
     for (int k = tid; k < K; k += NT) {
         const float s = R_.bound[k];
         const float y = s + fmaf(er[P.pdf[k]], (float)kLog2e, -emx0) - base0;
@@ -913,6 +928,11 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         else if (bwd) bh[k] = fexp2(s - base0);
         const bool dim = y > -INFINITY && px < kLinDimP;
         wmax = dim ? INFINITY : tmax(wmax, px);
+        if constexpr (LEAKY) wsum = bwd ? fmaf(fabsf(qt[k]), px, wsum) : wsum + px;
+    }
+    if constexpr (LEAKY) {
+        wsum = wave_sum(wsum);
+        if (lane == 0) red[32 + wave] = wsum;
     }
     for (int k = tid; k < nC; k += NT) {   // clones start empty: the state itself holds the start weight
         xb[K + k] = 0.0f;
@@ -953,8 +973,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (lane == 0) emaxw[(i + 1) % 3] = en;   // (the word of frame i - 2: read for the last time in step i - 1)
             }
             if (i + 2 < Tn) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
-            write_row(frame(i - 1), staged ? bh + cur * XF : xb + cur * Xs);
+            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
             if (lane == 0) red[(i + 1) % 3] = 0.0f;   // the word of step i + 1 starts empty
+            if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
             __syncthreads();
         }
     } else {
@@ -1028,7 +1049,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         auto step = [&](int i) __attribute__((always_inline)) -> bool {
             const int cur = (i - 1) & 1, nxt = cur ^ 1;   // which buffer holds the previous step's vector
             float *xn = xb + nxt * Xs;
-            float *bn = bh + nxt * XF;
+            float *bn = bh + nxt * XL;
             const uint32_t gbase = (uint32_t)cur * (uint32_t)kXbStride;   // (uniform) address of the buffer the gathers read
             const char *ern = (const char *)(er + (i % 3) * Es);
             const float mx = red[(i - 1) % 3];
@@ -1041,6 +1062,16 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // the order of floats that are not negative)
             uint32_t wlow = 0x7f800000u;
             float acc = 0.0f;
+            // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
+            float leaked = 0.0f, q_next = 0.0f;
+            if constexpr (LEAKY) {
+                const float4 *sl = (const float4 *)(red + 32 + ((i - 1) & 1) * 16);
+                const float4 s0 = sl[0], s1 = sl[1], s2 = sl[2], s3 = sl[3];
+                leaked = P.leak * ((((s0.x + s0.y) + (s0.z + s0.w)) + ((s1.x + s1.y) + (s1.z + s1.w))) +
+                                   (((s2.x + s2.y) + (s2.z + s2.w)) + ((s3.x + s3.y) + (s3.z + s3.w))));
+                wsum = 0.0f;
+                q_next = *(const float *)((const char *)qt + (cwv[0] & 0xffffu));
+            }
             // the wave's constants, opaque at every step: what is derived from them is computed where it is used (a
             // scalar instruction or two) instead of being kept in scalar registers that do not exist
             uint32_t m_lo = (uint32_t)mask0_w, m_hi = (uint32_t)(mask0_w >> 32), m1_lo = (uint32_t)mask1_w, m1_hi = (uint32_t)(mask1_w >> 32);
@@ -1085,8 +1116,17 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 ++nclose;
                 for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
                     acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
+                const float q = q_next;
+                if constexpr (LEAKY) {
+                    acc = bwd ? acc + ((int)__float_as_uint(q) >= 0 ? leaked : 0.0f) : fmaf(leaked, tmax(q, 0.0f), acc);
+                    q_next = *(const float *)((const char *)qt + (cwv[nclose & (kPMaxClose - 1)] & 0xffffu));
+                }
                 const float pb = acc * sc;
                 const float px = pb * pe;
+                if constexpr (LEAKY) {   // (a row spread over several lanes counts once)
+                    const float mine = (lane & ((1 << lg) - 1)) == 0 ? px : 0.0f;
+                    wsum = bwd ? fmaf(fabsf(q), mine, wsum) : wsum + mine;
+                }
                 *(float *)((char *)xn + tgt) = px;
                 if (staged) {   // (uniform) what leaves the kernel for this row
                     const float o = bwd ? pb : px;
@@ -1172,6 +1212,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // an entry below the range: the run gives up (see above)
             const bool low = wlow < __float_as_uint(kLinDimP);
             put_max(i, low ? INFINITY : wmax);
+            if constexpr (LEAKY) {
+                wsum = wave_sum(wsum);
+                if (lane == 0) red[32 + (i & 1) * 16 + wave] = wsum;
+            }
             __syncthreads();
             return true;
         };
@@ -1185,14 +1229,14 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         // to the output rows when the log form starts over
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) atomicAdd(&g_linear_restarts, 1u);
+        if (!LEAKY && tid == 0) atomicAdd(&g_linear_restarts, 1u);
         return false;
     }
 
     // ---- last frame: write it out, close log Z with the end weights
     const int last = (Tn - 1) & 1;
     const float *xl = xb + last * Xs;
-    if (io_wave) write_row(frame(Tn - 1), staged ? bh + last * XF : xl);
+    if (io_wave) write_row(frame(Tn - 1), staged ? bh + last * XL : xl);
     if (R_.logz) {
         float m = kNegBig, s = 0.0f;
         for (int k = tid; k < K; k += NT) lse_add(m, s, flog2(xl[k] * unbias) + R_.obound[k]);
@@ -1234,11 +1278,26 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
     int b, which;
     if (P.started && threadIdx.x == 0) atomicAdd(P.started, 1u);   // this workgroup has its compute unit
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    if (!linear_run(P, b, which, lds_raw)) {
+    if (!linear_run<false>(P, b, which, lds_raw)) {
         recursion_run<kNWShared, float, false, kXsFixed, false>(P, b, which, lds_raw);
         if (P.dir[which].fmt && threadIdx.x == 0) P.dir[which].fmt[b] = 0;   // this sequence's rows are in the log form
     }
     count_done(P);
+}
+
+// The leaky-HMM's recursions (both directions, one launch); gave_up[which * B + b]: the run left its range (or the
+// sequence has no frames) and is the plain kernel's.
+__global__ __launch_bounds__(kNWShared * 64) void fb_leaky_linear_kernel(const RecParams P, int32_t *gave_up)
+{
+    __builtin_amdgcn_s_setprio(3);
+    extern __shared__ double lds_raw[];
+    int b, which;
+    resolve_sequence<kNWShared>(P, lds_raw, b, which);
+    const bool ok = linear_run<true>(P, b, which, lds_raw);
+    if (threadIdx.x == 0) {
+        gave_up[which * P.B + b] = ok ? 0 : 1;
+        if (!ok) P.dir[which].fmt[b] = 1;   // (rows nobody will use, in the form the gradient kernel expects)
+    }
 }
 
 template <int NW, class T, bool TROP, int XF, bool LINW = false>
@@ -2078,12 +2137,14 @@ bool recursion_fixed_available()
     static const bool ok = [] {
         hipFuncAttributes attr{};
         hipFuncAttributes attr_lin{};
-        hipFuncAttributes attr_prob{};
+        hipFuncAttributes attr_prob{}, attr_leaky{};
         const hipError_t e = hipFuncGetAttributes(&attr, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>);
         const hipError_t e_lin =
             hipFuncGetAttributes(&attr_lin, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>);
         const hipError_t e_prob = hipFuncGetAttributes(&attr_prob, (const void *)fb_linear_kernel);
-        return e == hipSuccess && attr.sharedSizeBytes == 0 && e_lin == hipSuccess && attr_lin.sharedSizeBytes == 0 &&
+        const hipError_t e_leaky = hipFuncGetAttributes(&attr_leaky, (const void *)fb_leaky_linear_kernel);
+        return e_leaky == hipSuccess && attr_leaky.sharedSizeBytes == 0 &&
+               e == hipSuccess && attr.sharedSizeBytes == 0 && e_lin == hipSuccess && attr_lin.sharedSizeBytes == 0 &&
                e_prob == hipSuccess && attr_prob.sharedSizeBytes == 0;
     }();
     return ok;
@@ -2118,6 +2179,26 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
                    : launch_rec(fb_recursion_kernel<kNWShared, float, false, 0>, nw, p, lds_bytes, stream);
     return f64 ? launch_rec(fb_recursion_kernel<kNWSmall, double, false, 0>, nw, p, lds_bytes, stream)
                : launch_rec(fb_recursion_kernel<kNWSmall, float, false, 0>, nw, p, lds_bytes, stream);
+}
+
+size_t leaky_linear_lds_bytes(int32_t K, int32_t Ccap, int32_t D, bool backward)
+{
+    const size_t XL = ((size_t)K + (size_t)Ccap + 1 + 3) & ~(size_t)3;
+    return (size_t)kXbStride + (XL * (backward ? 4 : 2) + 64 + 3 * (((size_t)D + 1 + 3) & ~(size_t)3)) * 4;
+}
+
+int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
+{
+    size_t lds = 0;
+    for (int i = 0; i < p.n_dir; ++i) {
+        if (!p.dir[i].prob.units || !p.dir[i].rank1 || !p.dir[i].fmt) return fail(FB_EHIP, "internal error: leaky-HMM launch without its plan");
+        lds = std::max(lds, leaky_linear_lds_bytes(p.Kcap, p.dir[i].prob.Ccap, p.D, p.dir[i].backward != 0));
+    }
+    if (lds > kLdsBytes || !recursion_fixed_available()) return fail(FB_EHIP, "internal error: leaky-HMM launch beyond the on-chip memory");
+    const hipError_t e = hipFuncSetAttribute((const void *)fb_leaky_linear_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
+    hipLaunchKernelGGL(fb_leaky_linear_kernel, dim3((unsigned)(p.B * p.n_dir)), dim3(kNWShared * kWave), lds, (hipStream_t)stream, p, gave_up);
+    return check_launch("leaky-HMM recursion launch");
 }
 
 size_t probability_lds_bytes(int32_t D, bool staged)

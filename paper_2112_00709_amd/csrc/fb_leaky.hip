@@ -9,7 +9,12 @@
 // of Eq. 13-15 for T'; the rank-one term is kept apart from the sparse one:
 //     alpha_n = v_n o T^T (alpha_{n-1} + leak sum(alpha_{n-1}) pi)
 //     beta_n  = y + leak (pi . y) 1,   y = T (v_{n+1} o beta_{n+1})
-// One workgroup of 16 waves per sequence runs the forward sweep (every vector rescaled to sum 1, the logarithms of
+// Two forms.  Large shared graphs that run in the probability domain (fb_graph_linear_weights = 2), when q below and
+// the vectors fit a compute unit's memory: the recursion kernel of the exact path with the rank-one term added
+// (linear_run<true>: both sweeps side by side, arcs in registers), then the gradient kernel; it runs at the exact path's
+// speed (3022 states, 51 k arcs, 128 x 700 frames: 15.1 -> 2.87 ms a call).  A sequence one of whose sweeps
+// leaves that kernel's range, and every other graph, takes the plain kernel of this file:
+// one workgroup of 16 waves per sequence runs the forward sweep (every vector rescaled to sum 1, the logarithms of
 // the scales added up in double; the vectors go to the workspace), then the backward sweep, which forms each
 // frame's posteriors alpha_n o beta_n, normalised by their own sum, and adds them up per pdf in a fixed order.
 // Vectors are float in LDS.  The sparse products walk plain row lists in global memory (they stay in L2): rows of
@@ -17,8 +22,8 @@
 // thread, sorted by length in blocks of 1024 rows with the arcs of a block stored slot by slot, so that the threads
 // of a wave read neighbouring words.  There is no range guard and no fallback to logarithms: an entry below 2^-126 of
 // its frame's total is flushed to zero, which is this kind of method's own approximation (the exact path gives such
-// a sequence up and redoes it in the log form).  This is a simple kernel for comparison, not tuned like the exact path: no
-// arcs in registers, several barriers per frame, 8 bytes from L2 per arc and frame.
+// a sequence up and redoes it in the log form).  It is a simple kernel, not tuned: no arcs in registers, several
+// barriers per frame, 8 bytes from L2 per arc and frame.
 
 #include <hip/hip_runtime.h>
 
@@ -55,6 +60,7 @@ struct LeakyDev {
     LeakyDir fwd, bwd;           // rows = destinations (arcs by source index) / rows = sources
     const float *pi, *initp, *finalp;
     const int32_t *pdf, *pdf_ptr, *pos;   // pos[k]: the place of state k among the states in pdf order
+    const float *rank1[2];                // fast form: q by target of the forward / backward plan (linear_run), or NULL
 };
 
 struct LeakyParams {
@@ -66,6 +72,7 @@ struct LeakyParams {
     double *logz;
     float *pdf_post;
     float *rows;                 // workspace [B][N][K]: the forward vectors, each with sum 1
+    const int32_t *gave_up;      // [2][B], nullable: only the sequences one of whose recursions in the fast form gave up
 };
 
 namespace {
@@ -245,6 +252,7 @@ __global__ __launch_bounds__(kLeakyThreads) void fb_leaky_kernel(const LeakyPara
     const int Kp = (K + 3) & ~3, Dp = (D + 3) & ~3;
     float *x = lds, *y = x + Kp, *z = y + Kp, *pi = z + Kp, *er = pi + Kp, *red = er + Dp, *part = red + 2 * kLeakyWaves;
     const LeakyDev &G = P.G;
+    if (P.gave_up && P.gave_up[b] == 0 && P.gave_up[P.B + b] == 0) return;
     const int T = min(max(P.lengths[b], 0), P.N);
     const float leak = P.leak;
     const float *em = P.emis + (size_t)b * P.N * D;
@@ -467,7 +475,48 @@ int leaky_prepare(fb_graph *g, const float *init, const float *final_)
     if ((rc = up(g, pi, &dev->pi)) || (rc = up(g, ip, &dev->initp)) || (rc = up(g, fp, &dev->finalp)) ||
         (rc = up(g, pdf, &dev->pdf)) || (rc = up(g, L.pdf_ptr, &dev->pdf_ptr)) || (rc = up(g, pos, &dev->pos)))
         return rc;
+    dev->rank1[0] = dev->rank1[1] = nullptr;
+    // The fast form needs a row for every state going backward (a state without arcs out still gets the leak there).
+    if (g->linear_p && g->hp_bwd.zero_rows.empty()) {
+        std::vector<float> q((size_t)K);
+        for (int32_t j = 0; j < K; ++j) {
+            double acc = 0.0;
+            for (int32_t e = L.in_ptr[j]; e < L.in_ptr[j + 1]; ++e) acc += std::exp((double)L.in_w[e]) * (double)pi[(size_t)L.in_src[e]];
+            q[(size_t)j] = (float)acc;
+        }
+        for (int dir = 0; dir < 2; ++dir) {   // states, clone slots (sign bit: no share of their own), the dump slot (neither)
+            const PStreamHost &h = dir ? g->hp_bwd : g->hp_fwd;
+            std::vector<float> t(q);
+            t.resize((size_t)K + (size_t)h.Ccap + 1, -0.0f);
+            for (const CloneDesc &cd : h.clones)
+                for (int32_t i = 0; i < cd.count; ++i) t[(size_t)(K + cd.first + i)] = -q[(size_t)cd.state];
+            if ((rc = up(g, t, &dev->rank1[dir]))) return rc;
+        }
+    }
     return FB_OK;
+}
+
+// What the fast form keeps in the workspace; it is used if `ok`.
+struct LeakyFast {
+    bool ok = false;
+    size_t ld = 0, vec = 0, cum = 0, per_seq = 0, bytes = 0;   // row length (elements), bytes of its parts
+};
+
+static LeakyFast leaky_fast(const fb_graph *g, int32_t B, int32_t N)
+{
+    auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    LeakyFast f;
+    const LeakyDev *dev = (const LeakyDev *)g->leaky;
+    f.ld = ((size_t)g->K + 3) & ~(size_t)3;
+    f.ok = dev && dev->rank1[0] && dev->rank1[1] &&
+           leaky_linear_lds_bytes(g->K, g->hp_fwd.Ccap, g->D, false) <= kLdsBytes && leaky_linear_lds_bytes(g->K, g->hp_bwd.Ccap, g->D, true) <= kLdsBytes &&
+           leaky_gradient(g, nullptr, nullptr, (int32_t)f.ld, nullptr, nullptr, (const float *)1, (const float *)1, (const double *)1, nullptr, B, N,
+                          g->D, (float *)1, true, nullptr) != 0;   // (pointers only tested for presence)
+    f.vec = align((size_t)B * N * f.ld * sizeof(float));
+    f.cum = align((size_t)B * N * sizeof(float));
+    f.per_seq = align((size_t)B * sizeof(int32_t));
+    f.bytes = 2 * f.vec + 2 * f.cum + 2 * f.per_seq + align(2 * (size_t)B * sizeof(int32_t));
+    return f;
 }
 
 void leaky_release(fb_graph *g)
@@ -483,7 +532,9 @@ extern "C" {
 size_t fb_leaky_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 {
     if (!g || g->n_seq != 0 || B <= 0 || N <= 0) return 0;
-    return (((size_t)B * (size_t)N * (size_t)g->K * sizeof(float)) + 255) & ~(size_t)255;
+    const size_t plain = (((size_t)B * (size_t)N * (size_t)g->K * sizeof(float)) + 255) & ~(size_t)255;
+    const fb::LeakyFast f = fb::leaky_fast(g, B, N);
+    return f.ok ? std::max(plain, f.bytes) : plain;
 }
 
 int fb_leaky_posteriors(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D,
@@ -509,6 +560,32 @@ int fb_leaky_posteriors(const fb_graph *g, const float *emis, const int32_t *len
     p.B = B; p.N = N; p.D = D; p.K = g->K;
     p.leak = leak;
     p.logz = logz; p.pdf_post = pdf_post; p.rows = (float *)ws;
+    const LeakyFast fast = leaky_fast(g, B, N);
+    if (fast.ok && ((uintptr_t)ws & 15) == 0) {
+        // Both recursions of every sequence in one launch, the pdf posteriors from their rows, then what gave up
+        char *w = (char *)ws;
+        RecParams r = leaky_recursion_params(g, emis, lengths, B, N, D);
+        r.leak = leak;
+        float *cum[2];
+        int32_t *fmt[2];
+        for (int i = 0; i < 2; ++i) { r.dir[i].out = w; w += fast.vec; }
+        for (int i = 0; i < 2; ++i) { cum[i] = (float *)w; w += fast.cum; }
+        for (int i = 0; i < 2; ++i) { fmt[i] = (int32_t *)w; w += fast.per_seq; }
+        int32_t *gave_up = (int32_t *)w;
+        for (int i = 0; i < 2; ++i) {
+            r.dir[i].out_ld = (int32_t)fast.ld;
+            r.dir[i].cum = cum[i];
+            r.dir[i].fmt = fmt[i];
+            r.dir[i].rank1 = dev.rank1[i];
+        }
+        r.dir[0].logz = logz;
+        int rc = launch_leaky_linear(r, gave_up, stream);
+        if (rc == FB_OK)
+            rc = leaky_gradient(g, (const float *)r.dir[0].out, (const float *)r.dir[1].out, (int32_t)fast.ld, fmt[0], fmt[1], cum[0], cum[1],
+                                logz, lengths, B, N, D, pdf_post, false, stream);
+        if (rc != FB_OK) return rc;
+        p.gave_up = gave_up;
+    }
     if (lds_bytes > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)fb_leaky_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));

@@ -74,7 +74,7 @@ def _check(g, emis, lengths, D):
     torch.cuda.synchronize()
     a, b, ca, cb, za, zb, gam, rho, score, path = (t.cpu().numpy() for t in (a, b, ca, cb, za, zb, gam, rho, score, path))
     live = np.flatnonzero(lengths > 0)
-    em = np.nan_to_num(emis)
+    em = np.where(np.isnan(emis), np.float32(0), emis)
     ref = oracle.forward_backward(g, em, lengths, sel=live)
     best = oracle.viterbi(g, em, lengths, sel=live)
     off = g.state_off if g.packed else None
