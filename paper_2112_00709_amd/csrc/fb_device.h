@@ -167,6 +167,13 @@ __device__ __forceinline__ float wave_sum(float v)
     return group_all(v, 6, (int)(threadIdx.x & (kWave - 1)), [](float a, float b) { return a + b; });
 }
 
+// A workgroup barrier that waits for what this wave has written to LDS but lets its global loads and stores go on
+// (__syncthreads() in a wave that loads straight into LDS waits for all of them).
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ...: a loop whose counter is a compile-time constant
 template <class F, int... I>
 __device__ __forceinline__ void unrolled(F &&f, std::integer_sequence<int, I...>)

@@ -711,7 +711,8 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(2 * kPMaxClose)))
 // slots of the previous step up in the same order when a step starts.  q sits in LDS by target; the entry of the slice
 // that closes next is asked for when the one before it has closed.  A clone takes no share of its own (its sign bit
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
-template <bool LEAKY>
+// LOG: rows leave as logarithms.
+template <bool LEAKY, bool LOG>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
     constexpr int NW = kNWShared, XF = kXsFixed, R = kPResident;
@@ -737,7 +738,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // rows on their way out that are not the vector itself: beta before the emissions are applied (backward), and
     // either direction's rows as logarithms when that is the form they leave in; two buffers that follow each other,
     // present only when used
-    const bool log_rows = !LEAKY && R_.out != nullptr && R_.out_linear == 0;
+    constexpr bool log_rows = LOG;
     const bool staged = bwd || log_rows;
     const int XL = LEAKY ? (nX + 3) & ~3 : XF;   // floats of a buffer behind the first (leaky: q needs the room)
     float *bh = xb + Xs + XL;
@@ -790,6 +791,22 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
     };
     auto staged_wait = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    // The same where at least `stores` stores were issued behind the requests (memory operations of a wave complete in
+    // order): those need not have arrived, nor at the step's barrier.  (6000 states, one direction with rows over 540
+    // frames: 2295 us waiting for the stores of the step before as well, 2232 us so.)
+    auto staged_before = [&](int stores) {
+        switch (stores >> 2) {
+        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+        case 1: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+        case 2: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+        case 3: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+        case 4: asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); break;
+        case 5: asm volatile("s_waitcnt vmcnt(20)" ::: "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(24)" ::: "memory"); break;
+        }
+    };
+    // stores every wave-wide copy of a row issues at least: pieces of 16 bytes that all lanes have
+    const int n_row_stores = out_row0 ? K / (4 * kWave) : 0;
     // The largest emission of a staged frame, in log2 units (0 if there is none above zero-bar).  Over all pdfs, whether
     // a state of the graph is tied to them or not: any scale serves.  16 bytes per lane and read (the arc-walking waves
     // keep the LDS queue full: few, wide reads); what lies behind the row in its last group is -inf.
@@ -813,7 +830,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // (RecDir::out_linear: the reader has the offsets and the scale) or as log2 of (entry x 2^-bias) x out_scale, the
     // exponent and the mantissa taken apart first so that neither an entry far below the scale is lost nor the
     // entries near it are rounded at the magnitude of the bias.
-    const bool out_lin = R_.out_linear != 0;
+    constexpr bool out_lin = !LOG;
     auto to_log = [&](float v) {
         const float e = (float)(__builtin_amdgcn_frexp_expf(v) - kLinBias);   // (v = 0: -inf comes from the mantissa)
         return (e + flog2(__builtin_amdgcn_frexp_mantf(v))) * R_.out_scale;
@@ -837,17 +854,19 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             for (int u = 0; u < U; ++u) {
                 const int q = q0 + u * kWave + lane;
                 if (q < n4) {
+                    // (a streaming store: the row is read again much later, by another kernel, and what it would push out
+                    // of L2 is the arc plan every workgroup re-reads at every step)
+                    typedef float f4 __attribute__((ext_vector_type(4)));
+                    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+                    const f4 t = {v[u].x, v[u].y, v[u].z, v[u].w};
                     if (vec) {   // (the row's padding may take up to 3 values that lie behind the states)
-                        // (a streaming store: the row is read again much later, by another kernel, and what it would
-                        // push out of L2 is the arc plan every workgroup re-reads at every step)
-                        typedef float f4 __attribute__((ext_vector_type(4)));
-                        const f4 t = {v[u].x, v[u].y, v[u].z, v[u].w};
                         __builtin_nontemporal_store(t, (f4 *)orow + q);
+                    } else if (4 * q + 3 < K) {   // a row that starts anywhere: whole pieces all the same (3022 states: 2490 -> 1927 us)
+                        __builtin_nontemporal_store((f4u)t, (f4u *)(orow + 4 * q));
                     } else {
                         if (4 * q + 0 < K) orow[4 * q + 0] = v[u].x;
                         if (4 * q + 1 < K) orow[4 * q + 1] = v[u].y;
                         if (4 * q + 2 < K) orow[4 * q + 2] = v[u].z;
-                        if (4 * q + 3 < K) orow[4 * q + 3] = v[u].w;
                     }
                 }
             }
@@ -967,7 +986,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
                 if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
             }
-            staged_wait();   // frame i+1, requested a whole step ago, is in LDS
+            staged_before(i > 1 ? n_row_stores : 0);   // frame i+1, requested a whole step ago, is in LDS
             if (i + 1 < Tn) {
                 const float en = emax_of(er + ((i + 1) % 3) * Es);
                 if (lane == 0) emaxw[(i + 1) % 3] = en;   // (the word of frame i - 2: read for the last time in step i - 1)
@@ -976,7 +995,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
             if (lane == 0) red[(i + 1) % 3] = 0.0f;   // the word of step i + 1 starts empty
             if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
-            __syncthreads();
+            lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
     } else {
         const PWaveDesc wd = S.waves[wave];
@@ -1271,6 +1290,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     return true;
 }
 
+template <bool LOG>
 __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecParams P)
 {
     __builtin_amdgcn_s_setprio(3);
@@ -1278,7 +1298,7 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
     int b, which;
     if (P.started && threadIdx.x == 0) atomicAdd(P.started, 1u);   // this workgroup has its compute unit
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    if (!linear_run<false>(P, b, which, lds_raw)) {
+    if (!linear_run<false, LOG>(P, b, which, lds_raw)) {
         recursion_run<kNWShared, float, false, kXsFixed, false>(P, b, which, lds_raw);
         if (P.dir[which].fmt && threadIdx.x == 0) P.dir[which].fmt[b] = 0;   // this sequence's rows are in the log form
     }
@@ -1293,7 +1313,7 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_leaky_linear_kernel(const R
     extern __shared__ double lds_raw[];
     int b, which;
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    const bool ok = linear_run<true>(P, b, which, lds_raw);
+    const bool ok = linear_run<true, false>(P, b, which, lds_raw);
     if (threadIdx.x == 0) {
         gave_up[which * P.B + b] = ok ? 0 : 1;
         if (!ok) P.dir[which].fmt[b] = 1;   // (rows nobody will use, in the form the gradient kernel expects)
@@ -2141,7 +2161,7 @@ bool recursion_fixed_available()
         const hipError_t e = hipFuncGetAttributes(&attr, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>);
         const hipError_t e_lin =
             hipFuncGetAttributes(&attr_lin, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>);
-        const hipError_t e_prob = hipFuncGetAttributes(&attr_prob, (const void *)fb_linear_kernel);
+        const hipError_t e_prob = hipFuncGetAttributes(&attr_prob, (const void *)fb_linear_kernel<true>);
         const hipError_t e_leaky = hipFuncGetAttributes(&attr_leaky, (const void *)fb_leaky_linear_kernel);
         return e_leaky == hipSuccess && attr_leaky.sharedSizeBytes == 0 &&
                e == hipSuccess && attr.sharedSizeBytes == 0 && e_lin == hipSuccess && attr_lin.sharedSizeBytes == 0 &&
@@ -2156,12 +2176,14 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
         if (p.xs_fixed != kXsFixed || nw != kNWShared || f64 || tropical) return fail(FB_EHIP, "internal error: fixed-buffer launch");
         if (p.linear_p) {
             if (!p.shared || p.linear_w) return fail(FB_EHIP, "internal error: probability-domain launch");
+            bool logs = false;
+            for (int i = 0; i < p.n_dir; ++i) logs = logs || (p.dir[i].out && !p.dir[i].out_linear);
             for (int i = 0; i < p.n_dir; ++i) {
                 if (!p.dir[i].prob.units) return fail(FB_EHIP, "internal error: probability-domain launch without its plan");
-                lds_bytes = std::max(lds_bytes, probability_lds_bytes(p.D, p.dir[i].backward != 0 || (p.dir[i].out && !p.dir[i].out_linear)));
+                lds_bytes = std::max(lds_bytes, probability_lds_bytes(p.D, p.dir[i].backward != 0 || logs));
             }
             if (lds_bytes > kLdsBytes) return fail(FB_EHIP, "internal error: probability-domain launch beyond the on-chip memory");
-            return launch_rec(fb_linear_kernel, nw, p, lds_bytes, stream);
+            return logs ? launch_rec(fb_linear_kernel<true>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false>, nw, p, lds_bytes, stream);
         }
         if (p.linear_w) return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>, nw, p, lds_bytes, stream);
         return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed>, nw, p, lds_bytes, stream);

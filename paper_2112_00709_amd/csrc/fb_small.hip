@@ -66,11 +66,6 @@ __device__ __forceinline__ double dmax(double a, double b)
     return r;
 }
 
-__device__ __forceinline__ void lds_barrier()   // what this wave has written to LDS is there; its global loads and stores go on
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 }  // namespace
 
 template <int NC, int R, int TM, bool TROP>
