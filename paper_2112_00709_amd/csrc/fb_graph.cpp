@@ -466,6 +466,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                         return r;
                     d.n_clones = (int32_t)h.clones.size();
                     d.n_zero = (int32_t)h.zero_rows.size();
+                    for (const PWaveDesc &wd : h.waves) d.max_units = std::max(d.max_units, wd.n_units);
                     d.Ccap = h.Ccap;
                     d.bias = h.bias;
                     d.dim = h.dim;

@@ -711,11 +711,12 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(2 * kPMaxClose)))
 // slots of the previous step up in the same order when a step starts.  q sits in LDS by target; the entry of the slice
 // that closes next is asked for when the one before it has closed.  A clone takes no share of its own (its sign bit
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
-// LOG: rows leave as logarithms.
-template <bool LEAKY, bool LOG>
+// LOG: rows leave as logarithms.  FEW: no wave has more than kPFew units, so all of them stay in registers, nothing is
+// re-read, and the registers that leaves take gathers further ahead.
+template <bool LEAKY, bool LOG, bool FEW>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
-    constexpr int NW = kNWShared, XF = kXsFixed, R = kPResident;
+    constexpr int NW = kNWShared, XF = kXsFixed, R = FEW ? kPFew : kPResident;
     constexpr int NT = NW * kWave, NC = NW - 1;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1000,6 +1001,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
+        const int n_close_w = __builtin_amdgcn_readfirstlane(wd.n_close);
         auto uniform64 = [](uint64_t v) {
             return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
@@ -1019,20 +1021,20 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         // of its use; the first kPRing - 1 of a step when the step before ends.  Every place that asks does so whatever
         // the wave's unit count (for a unit that is not there, the last one again): the number of loads on their way
         // at any point of the code is then a constant, which is what the waits on them are counted by.
-        constexpr int NP = kPPatterned, H = kPHead, NG = NP - R;   // patterned positions, head, re-read ones among them
-        static_assert(NP <= 64 && NP % 16 == 0 && NG >= kPRing - 1, "close bits of the patterned part in one 64-bit word; blocks of 4, a priority level for every quarter");
+        constexpr int NP = FEW ? kPFew : kPPatterned, H = kPHead, NG = NP - R;   // patterned positions, head, re-read ones among them
+        static_assert(NP <= 64 && NP % 16 == 0 && (FEW || NG >= kPRing - 1), "close bits of the patterned part in one 64-bit word; blocks of 4, a priority level for every quarter");
         // the position of the wave's last re-read unit: what a request for a unit behind it asks for again (a wave
         // without any asks for a unit behind its own: never folded, and the plan has room behind every wave)
         int last_spos = p_streamed_pos(0);
         unrolled([&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value;
-            if constexpr (p_streamed(u)) last_spos = u < n_units_w ? u : last_spos;
+            if constexpr (!FEW && p_streamed(u)) last_spos = u < n_units_w ? u : last_spos;
         }, std::make_integer_sequence<int, NP>{});
         if (n_units_w > NP) last_spos = n_units_w - 1;
         Unit res[R];   // (units behind the wave's last one are zero words or another wave's: never folded)
         unrolled([&](auto qc) __attribute__((always_inline)) {
             constexpr int q = decltype(qc)::value;
-            load_unit(res[q], ubase + (size_t)p_resident_pos(q) * (3 * kWave));
+            load_unit(res[q], ubase + (size_t)(FEW ? q : p_resident_pos(q)) * (3 * kWave));
         }, std::make_integer_sequence<int, R>{});
         // The lane's close words and, behind them, the emission factors of the step in hand, both picked by the number
         // of the close (uniform).  One vector of sixteen: picking from a vector of eight is compiled into a chain of seven
@@ -1063,7 +1065,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         unrolled([&](auto mc) __attribute__((always_inline)) {
             constexpr int m = decltype(mc)::value;
             request_at(ring[m], p_streamed_pos(m));
-        }, std::make_integer_sequence<int, kPRing - 1>{});
+        }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
 
         auto step = [&](int i) __attribute__((always_inline)) -> bool {
             const int cur = (i - 1) & 1, nxt = cur ^ 1;   // which buffer holds the previous step's vector
@@ -1124,9 +1126,18 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // close waits for nothing but its own arcs
             typedef const __attribute__((address_space(3))) float lds_cf;
             const uint32_t ern_a = (uint32_t)(uintptr_t)ern;
-#pragma unroll
-            for (int c = 0; c < kPMaxClose; ++c)
+            auto factor = [&](auto cc) __attribute__((always_inline)) {
+                constexpr int c = decltype(cc)::value;
                 cwv[kPMaxClose + c] = __float_as_uint(fexp2(fmaf(*(lds_cf *)(uintptr_t)(ern_a + (cwv[c] >> 16)), (float)kLog2e, -emx)));
+            };
+            unrolled(factor, std::make_integer_sequence<int, FEW ? 2 : kPMaxClose>{});
+            if constexpr (FEW) {   // (a small graph's waves close a few slices: the factors of the others are not formed)
+                if (n_close_w > 2) { factor(std::integral_constant<int, 2>{}); factor(std::integral_constant<int, 3>{}); }
+                if (n_close_w > 4) {
+                    factor(std::integral_constant<int, 4>{}); factor(std::integral_constant<int, 5>{});
+                    factor(std::integral_constant<int, 6>{}); factor(std::integral_constant<int, 7>{});
+                }
+            }
             // a slice ends: the lanes of a row are added up, the row is rescaled, takes its emission, is stored
             auto close_slice = [&]() __attribute__((always_inline)) {
                 const int lg = (int)((lg_lo >> (3 * nclose)) & 7u);
@@ -1158,12 +1169,13 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // position u of the patterned part: which registers hold it
             auto unit_at = [&](auto uc) __attribute__((always_inline)) -> Unit {
                 constexpr int u = decltype(uc)::value;
-                if constexpr (p_streamed(u)) return ring[p_streamed_before(u) % kPRing];
+                if constexpr (FEW) return res[u];
+                else if constexpr (p_streamed(u)) return ring[p_streamed_before(u) % kPRing];
                 else return res[u - p_streamed_before(u)];
             };
             // gathered values of the unit being folded and of the next GD: under load a gather takes a few hundred cycles
-            constexpr int GD = 3, NGB = GD + 1;
-            static_assert(kPRing % NGB == 0 && NG % kPRing == 0 && GD <= H && GD <= kPRing - 1, "buffer names repeat with the ring; the first gathers are of resident units");
+            constexpr int GD = FEW ? 7 : 3, NGB = GD + 1;
+            static_assert(FEW || (kPRing % NGB == 0 && NG % kPRing == 0 && GD <= H && GD <= kPRing - 1), "buffer names repeat with the ring; the first gathers are of resident units");
             float2 G[NGB];
             unrolled([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
@@ -1182,7 +1194,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                         unrolled([&](auto jc) __attribute__((always_inline)) {
                             constexpr int u = u0 + decltype(jc)::value;
                             // a streamed unit: the place of the one before it in the ring is free, the unit kPRing - 1 further on goes there
-                            if constexpr (p_streamed(u)) {
+                            if constexpr (!FEW && p_streamed(u)) {
                                 constexpr int m = p_streamed_before(u);
                                 if constexpr (p_streamed_pos(m + kPRing - 1) < NP) request_at(ring[(m + kPRing - 1) % kPRing], p_streamed_pos(m + kPRing - 1));
                                 else request(ring[(m + kPRing - 1) % kPRing], p_streamed_pos(m + kPRing - 1));
@@ -1190,7 +1202,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             // (gathered whether the wave has that unit or not - its registers hold valid sources either way -
                             // so that the number of gathers on their way is a constant too)
                             if constexpr (u + GD < NP) gather(G[(u + GD) % NGB], unit_at(std::integral_constant<int, u + GD>{}).s);
-                            else gather(G[(u + GD) % NGB], ring[(NG + (u + GD - NP)) % kPRing].s);   // the first units behind the patterned part
+                            else if constexpr (!FEW) gather(G[(u + GD) % NGB], ring[(NG + (u + GD - NP)) % kPRing].s);   // the first units behind the patterned part
                             const Unit me = unit_at(std::integral_constant<int, u>{});
                             // (both values of the unit are taken at one point: one wait for the pair instead of one each)
                             asm volatile("" : "+v"(G[u % NGB].x), "+v"(G[u % NGB].y));
@@ -1205,29 +1217,31 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             block(block, std::integral_constant<int, 0>{});
             // behind the patterned part: streamed units; unit NP + t is streamed unit NG + t; kPRing positions to a round,
             // so that the names of the ring places and of the gather buffers repeat
-            static_assert(NP % NGB == 0 && NG % kPRing != -1, "rounds");
-            for (int t0 = 0; NP + t0 < n_units; t0 += kPRing) {
-#pragma unroll
-                for (int tt = 0; tt < kPRing; ++tt) {   // (a plain loop: closures inside a loop that stays a loop are not taken apart by the compiler)
-                    const int t = t0 + tt;
-                    if (NP + t < n_units) {
-                        const int mr = NG + tt;   // (t0 is a multiple of kPRing: only tt names the buffers)
-                        request(ring[(mr + kPRing - 1) % kPRing], NP + t + kPRing - 1);
-                        gather(G[(NP + tt + GD) % NGB], ring[(mr + GD) % kPRing].s);
-                        asm volatile("" : "+v"(G[(NP + tt) % NGB].x), "+v"(G[(NP + tt) % NGB].y));
-                        acc = fmaf(G[(NP + tt) % NGB].x, ring[mr % kPRing].w0, acc);
-                        acc = fmaf(G[(NP + tt) % NGB].y, ring[mr % kPRing].w1, acc);
-                        const int at = NP + t;
-                        const uint32_t word = at < 32 ? m_lo : at < 64 ? m_hi : at < 96 ? m1_lo : m1_hi;
-                        if ((word >> (at & 31)) & 1u) close_slice();
+            static_assert(FEW || NP % NGB == 0, "rounds");
+            if constexpr (!FEW) {
+                for (int t0 = 0; NP + t0 < n_units; t0 += kPRing) {
+    #pragma unroll
+                    for (int tt = 0; tt < kPRing; ++tt) {   // (a plain loop: closures inside a loop that stays a loop are not taken apart by the compiler)
+                        const int t = t0 + tt;
+                        if (NP + t < n_units) {
+                            const int mr = NG + tt;   // (t0 is a multiple of kPRing: only tt names the buffers)
+                            request(ring[(mr + kPRing - 1) % kPRing], NP + t + kPRing - 1);
+                            gather(G[(NP + tt + GD) % NGB], ring[(mr + GD) % kPRing].s);
+                            asm volatile("" : "+v"(G[(NP + tt) % NGB].x), "+v"(G[(NP + tt) % NGB].y));
+                            acc = fmaf(G[(NP + tt) % NGB].x, ring[mr % kPRing].w0, acc);
+                            acc = fmaf(G[(NP + tt) % NGB].y, ring[mr % kPRing].w1, acc);
+                            const int at = NP + t;
+                            const uint32_t word = at < 32 ? m_lo : at < 64 ? m_hi : at < 96 ? m1_lo : m1_hi;
+                            if ((word >> (at & 31)) & 1u) close_slice();
+                        }
                     }
                 }
+                // the first streamed units of the next step (every place of the ring is free now)
+                unrolled([&](auto mc) __attribute__((always_inline)) {
+                    constexpr int m = decltype(mc)::value;
+                    request_at(ring[m], p_streamed_pos(m));
+                }, std::make_integer_sequence<int, kPRing - 1>{});
             }
-            // the first streamed units of the next step (every place of the ring is free now)
-            unrolled([&](auto mc) __attribute__((always_inline)) {
-                constexpr int m = decltype(mc)::value;
-                request_at(ring[m], p_streamed_pos(m));
-            }, std::make_integer_sequence<int, kPRing - 1>{});
             // an entry below the range: the run gives up (see above)
             const bool low = wlow < __float_as_uint(kLinDimP);
             put_max(i, low ? INFINITY : wmax);
@@ -1290,7 +1304,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     return true;
 }
 
-template <bool LOG>
+template <bool LOG, bool FEW>
 __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecParams P)
 {
     __builtin_amdgcn_s_setprio(3);
@@ -1298,7 +1312,7 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
     int b, which;
     if (P.started && threadIdx.x == 0) atomicAdd(P.started, 1u);   // this workgroup has its compute unit
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    if (!linear_run<false, LOG>(P, b, which, lds_raw)) {
+    if (!linear_run<false, LOG, FEW>(P, b, which, lds_raw)) {
         recursion_run<kNWShared, float, false, kXsFixed, false>(P, b, which, lds_raw);
         if (P.dir[which].fmt && threadIdx.x == 0) P.dir[which].fmt[b] = 0;   // this sequence's rows are in the log form
     }
@@ -1307,13 +1321,14 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
 
 // The leaky-HMM's recursions (both directions, one launch); gave_up[which * B + b]: the run left its range (or the
 // sequence has no frames) and is the plain kernel's.
+template <bool FEW>
 __global__ __launch_bounds__(kNWShared * 64) void fb_leaky_linear_kernel(const RecParams P, int32_t *gave_up)
 {
     __builtin_amdgcn_s_setprio(3);
     extern __shared__ double lds_raw[];
     int b, which;
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    const bool ok = linear_run<true, false>(P, b, which, lds_raw);
+    const bool ok = linear_run<true, false, FEW>(P, b, which, lds_raw);
     if (threadIdx.x == 0) {
         gave_up[which * P.B + b] = ok ? 0 : 1;
         if (!ok) P.dir[which].fmt[b] = 1;   // (rows nobody will use, in the form the gradient kernel expects)
@@ -2155,19 +2170,26 @@ bool recursion_fixed_available()
     // the fixed-buffer instantiation addresses LDS from 0: usable only while the kernel has no static LDS in front
     // of its dynamic array (a property of the build, looked up once)
     static const bool ok = [] {
-        hipFuncAttributes attr{};
-        hipFuncAttributes attr_lin{};
-        hipFuncAttributes attr_prob{}, attr_leaky{};
-        const hipError_t e = hipFuncGetAttributes(&attr, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>);
-        const hipError_t e_lin =
-            hipFuncGetAttributes(&attr_lin, (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>);
-        const hipError_t e_prob = hipFuncGetAttributes(&attr_prob, (const void *)fb_linear_kernel<true>);
-        const hipError_t e_leaky = hipFuncGetAttributes(&attr_leaky, (const void *)fb_leaky_linear_kernel);
-        return e_leaky == hipSuccess && attr_leaky.sharedSizeBytes == 0 &&
-               e == hipSuccess && attr.sharedSizeBytes == 0 && e_lin == hipSuccess && attr_lin.sharedSizeBytes == 0 &&
-               e_prob == hipSuccess && attr_prob.sharedSizeBytes == 0;
+        const void *kernels[] = {(const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>,
+                                 (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>,
+                                 (const void *)fb_linear_kernel<false, false>, (const void *)fb_linear_kernel<false, true>,
+                                 (const void *)fb_linear_kernel<true, false>, (const void *)fb_linear_kernel<true, true>,
+                                 (const void *)fb_leaky_linear_kernel<false>, (const void *)fb_leaky_linear_kernel<true>};
+        for (const void *k : kernels) {
+            hipFuncAttributes attr{};
+            if (hipFuncGetAttributes(&attr, k) != hipSuccess || attr.sharedSizeBytes != 0) return false;
+        }
+        return true;
     }();
     return ok;
+}
+
+// every direction's plan keeps its units in registers
+static bool few_units(const RecParams &p)
+{
+    bool few = true;
+    for (int i = 0; i < p.n_dir; ++i) few = few && p.dir[i].prob.max_units <= kPFew;
+    return few;
 }
 
 int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t lds_bytes, void *stream)
@@ -2183,7 +2205,9 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
                 lds_bytes = std::max(lds_bytes, probability_lds_bytes(p.D, p.dir[i].backward != 0 || logs));
             }
             if (lds_bytes > kLdsBytes) return fail(FB_EHIP, "internal error: probability-domain launch beyond the on-chip memory");
-            return logs ? launch_rec(fb_linear_kernel<true>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false>, nw, p, lds_bytes, stream);
+            if (few_units(p))
+                return logs ? launch_rec(fb_linear_kernel<true, true>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false, true>, nw, p, lds_bytes, stream);
+            return logs ? launch_rec(fb_linear_kernel<true, false>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false, false>, nw, p, lds_bytes, stream);
         }
         if (p.linear_w) return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>, nw, p, lds_bytes, stream);
         return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed>, nw, p, lds_bytes, stream);
@@ -2217,9 +2241,10 @@ int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
         lds = std::max(lds, leaky_linear_lds_bytes(p.Kcap, p.dir[i].prob.Ccap, p.D, p.dir[i].backward != 0));
     }
     if (lds > kLdsBytes || !recursion_fixed_available()) return fail(FB_EHIP, "internal error: leaky-HMM launch beyond the on-chip memory");
-    const hipError_t e = hipFuncSetAttribute((const void *)fb_leaky_linear_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    auto kern = few_units(p) ? fb_leaky_linear_kernel<true> : fb_leaky_linear_kernel<false>;
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
-    hipLaunchKernelGGL(fb_leaky_linear_kernel, dim3((unsigned)(p.B * p.n_dir)), dim3(kNWShared * kWave), lds, (hipStream_t)stream, p, gave_up);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.n_dir)), dim3(kNWShared * kWave), lds, (hipStream_t)stream, p, gave_up);
     return check_launch("leaky-HMM recursion launch");
 }
 
