@@ -127,7 +127,7 @@ size_t recursion_lds_bytes(int32_t Kcap, int32_t Ccap, int32_t Ecap, bool backwa
     // carrier-typed: state buffers (states, clone slots, a dump slot) and reduction slots;
     // then three emission rows (float, plus a zero slot), for packed graphs a pdf id per state, the emission index table
     const size_t xs = xs_fixed ? (size_t)xs_fixed : (size_t)Kcap + (size_t)Ccap + 1;
-    return (xs * (backward ? 4 : 2) + 4 * kNWShared + 2) * (f64 ? 8 : 4) + ((size_t)Ecap + 1) * 12 +
+    return (xs * (backward && !tropical ? 4 : 2) + 4 * kNWShared + 2) * (f64 ? 8 : 4) + ((size_t)Ecap + 1) * 12 +
            (shared ? 0 : (size_t)Ecap * 4) + (tropical ? xs * 4 : 0) + ((xs + 1) & ~(size_t)1) * 2 +
            kLdsReserve;   // tropical: two rows of 16-bit back-pointers; always: the 16-bit emission index of every target
 }
@@ -269,8 +269,8 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         }
         g->nw = (max_sub_E >= 4096 || g->max_sub_K > 1024) ? kNWShared : kNWSmall;
         g->f64 = (flags & FB_GRAPH_WIDE_STATE) ? true : (flags & FB_GRAPH_NARROW_STATE) ? false : g->nw == kNWSmall;
-        SellHost sell_fwd, sell_bwd, sell_trop;   // sliced plans of the recursions, flattened into streams below
-        sell_fwd.nw = sell_bwd.nw = sell_trop.nw = g->nw - 1;   // the last wave of a workgroup moves data, the others walk arcs
+        SellHost sell_fwd, sell_bwd;   // sliced plans of the recursions, flattened into streams below
+        sell_fwd.nw = sell_bwd.nw = g->nw - 1;   // the last wave of a workgroup moves data, the others walk arcs
         bool any_parallel = false;
         bool prob_ok = n_seq == 0;   // the plans of the probability-domain kernel could be built
 
@@ -299,21 +299,25 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         g->small = g->f64 && g->nw == kNWSmall;
         int32_t longest = 0;   // most arcs of a row, parallel ones counted apart
         for (int32_t k = 0; k < K; ++k) longest = std::max(longest, std::max(L.in_ptr[k + 1] - L.in_ptr[k], L.out_ptr[k + 1] - L.out_ptr[k]));
-        g->hs_fwd.tm = g->hs_bwd.tm = g->hs_trop.tm = longest <= 2 ? 2 : 4;
+        g->hs_fwd.tm = g->hs_bwd.tm = g->hs_trop.tm = g->hs_btrop.tm = longest <= 2 ? 2 : 4;
         for (int32_t s = 0; s < n_sub && g->small; ++s) {
             const int32_t k0 = n_seq > 0 ? state_off[s] : 0, Ks = (n_seq > 0 ? state_off[s + 1] : K) - k0;
             for (int dir = 0; dir < 2 && g->small; ++dir) {
                 rows_of(s, dir);
                 any_parallel |= merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
                 g->small = small_append(dir ? g->hs_bwd : g->hs_fwd, k0, Ks, mptr.data(), mcol.data(), mw.data());
-                if (dir == 0 && g->small) {
-                    merge_parallel(Ks, ptr, col, w, true, mptr, mcol, mw);
-                    g->small = small_append(g->hs_trop, k0, Ks, mptr.data(), mcol.data(), mw.data());
-                }
             }
         }
         if (g->small) prob_ok = false;
-        else g->hs_fwd = g->hs_bwd = g->hs_trop = SmallHost();
+        else g->hs_fwd = g->hs_bwd = g->hs_trop = g->hs_btrop = SmallHost();
+        for (int32_t s = 0; s < n_sub && g->small && any_parallel && rc == FB_OK; ++s)   // (as many arcs a row as above)
+            for (int dir = 0; dir < 2; ++dir) {
+                const int32_t k0 = n_seq > 0 ? state_off[s] : 0, Ks = (n_seq > 0 ? state_off[s + 1] : K) - k0;
+                rows_of(s, dir);
+                merge_parallel(Ks, ptr, col, w, true, mptr, mcol, mw);
+                if (!small_append(dir ? g->hs_btrop : g->hs_trop, k0, Ks, mptr.data(), mcol.data(), mw.data()))
+                    rc = fail(FB_EHIP, "internal error: best-path plan of a small graph");
+            }
         for (int32_t s = 0; s < n_sub; ++s) {
             const int32_t k0 = n_seq > 0 ? state_off[s] : 0, k1 = n_seq > 0 ? state_off[s + 1] : K, Ks = k1 - k0;
             vid.resize((size_t)Ks);
@@ -331,11 +335,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 } else {
                     prob_ok = false;
                 }
-                if (dir == 0) {
-                    any_parallel = any_parallel || dup;
-                    merge_parallel(Ks, ptr, col, w, true, mptr, mcol, mw);
-                    sell_append(sell_trop, k0, Ks, mptr.data(), mcol.data(), mw.data(), vid.data());
-                }
+                any_parallel = any_parallel || dup;
             }
             // states grouped by pdf: one row per pdf (every pdf for a shared graph, the pdfs the
             // sub-graph uses for packed graphs), states in ascending order inside a row
@@ -376,7 +376,8 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         if (g->small) {   // nothing a kernel will index may leave its array
             std::string why;
             g->own_trop = any_parallel;
-            if (!small_in_bounds(g->hs_fwd, why) || !small_in_bounds(g->hs_bwd, why) || !small_in_bounds(g->hs_trop, why))
+            if (rc == FB_OK && (!small_in_bounds(g->hs_fwd, why) || !small_in_bounds(g->hs_bwd, why) ||
+                                !small_in_bounds(g->hs_trop, why) || !small_in_bounds(g->hs_btrop, why)))
                 rc = fail(FB_EHIP, "internal error: schedule out of bounds (" + why + ")");
         } else {
             std::string why;
@@ -415,12 +416,23 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             }
             if (g->host_only && prob_ok) g->linear_p = true;   // (host-only handles keep the plans for fb_graph_schedule_apply_host)
             g->own_trop = any_parallel || g->linear_w;
-            if (rc == FB_OK && g->own_trop) {
+            for (int dir = 0; dir < 2 && rc == FB_OK && g->own_trop; ++dir) {
+                SellHost sell_trop;
+                sell_trop.nw = g->nw - 1;
+                for (int32_t s = 0; s < n_sub; ++s) {
+                    const int32_t k0 = n_seq > 0 ? state_off[s] : 0, Ks = (n_seq > 0 ? state_off[s + 1] : K) - k0;
+                    vid.resize((size_t)Ks);
+                    for (int32_t k = 0; k < Ks; ++k) vid[k] = n_seq > 0 ? k : pdf[k0 + k];
+                    rows_of(s, dir);
+                    merge_parallel(Ks, ptr, col, w, true, mptr, mcol, mw);
+                    sell_append(sell_trop, k0, Ks, mptr.data(), mcol.data(), mw.data(), vid.data());
+                }
+                StreamHost &trop = dir ? g->h_btrop : g->h_trop;
                 if (!sell_in_bounds(sell_trop, nv, why))
                     rc = fail(FB_EHIP, "internal error: schedule out of bounds (" + why + ")");
-                else if (!stream_from_sell(sell_trop, g->max_sub_K, n_seq > 0 ? g->max_sub_K : D, g->f64 ? 8 : 4, g->h_trop, why))
+                else if (!stream_from_sell(sell_trop, g->max_sub_K, n_seq > 0 ? g->max_sub_K : D, g->f64 ? 8 : 4, trop, why))
                     rc = fail(FB_EUNSUPPORTED, "graph too large: " + why);
-                else if (!stream_in_bounds(g->h_trop, nv, why))
+                else if (!stream_in_bounds(trop, nv, why))
                     rc = fail(FB_EHIP, "internal error: stream out of bounds (" + why + ")");
             }
         }
@@ -451,11 +463,13 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     if ((r = upload(g, h.sub, &d.sub)) || (r = upload(g, h.rows, &d.rows)) || (r = upload(g, h.lg, &d.lg))) return r;
                     return upload(g, h.arcs, &d.arcs);
                 };
-                if (!(rc = up(g->hs_fwd, g->sfwd)) && !(rc = up(g->hs_bwd, g->sbwd)) && g->own_trop) rc = up(g->hs_trop, g->strop);
-                if (!g->own_trop) g->strop = g->sfwd;
+                if (!(rc = up(g->hs_fwd, g->sfwd)) && !(rc = up(g->hs_bwd, g->sbwd)) && g->own_trop &&
+                    !(rc = up(g->hs_trop, g->strop)))
+                    rc = up(g->hs_btrop, g->sbtrop);
+                if (!g->own_trop) { g->strop = g->sfwd; g->sbtrop = g->sbwd; }
             } else if (rc == FB_OK) {
-                if (g->own_trop) rc = upload_stream(g, g->h_trop, g->trop);
-                else g->trop = g->fwd;
+                if (!g->own_trop) { g->trop = g->fwd; g->btrop = g->bwd; }
+                else if (!(rc = upload_stream(g, g->h_trop, g->trop))) rc = upload_stream(g, g->h_btrop, g->btrop);
             }
             if (rc == FB_OK && g->linear_p) {
                 auto up = [&](const PStreamHost &h, PStreamDev &d) {

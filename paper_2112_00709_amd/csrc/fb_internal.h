@@ -337,18 +337,18 @@ struct fb_graph {
     fb::HostLayout lay;
     std::vector<int32_t> state_off;   // packed only
     fb::StreamHost h_fwd, h_bwd;      // host schedules of the two recursions
-    fb::StreamHost h_trop;            // forward schedule of the tropical semiring, when it differs (own_trop)
+    fb::StreamHost h_trop, h_btrop;   // schedules of the tropical semiring (forward, backward), when they differ (own_trop)
     bool own_trop = false;            // the graph has parallel arcs: they combine by max there, not by (+)
     bool linear_w = false;            // the device copies of fwd / bwd carry weights as 2^w (see stream_linear_weights)
     bool linear_p = false;            // the recursions run in the probability domain (linear_run): the plans below exist
     fb::PStreamHost hp_fwd, hp_bwd;   // its plans, host
     fb::PStreamDev pfwd, pbwd;        // and device
     bool small = false;               // the recursions run in the small-graph kernel: the plans below exist and h_fwd .. do not
-    fb::SmallHost hs_fwd, hs_bwd, hs_trop;   // its plans, host (hs_trop: as h_trop, only when own_trop)
-    fb::SmallDev sfwd, sbwd, strop;   // and device (strop = sfwd unless own_trop)
+    fb::SmallHost hs_fwd, hs_bwd, hs_trop, hs_btrop;   // its plans, host (the last two: as h_trop, only when own_trop)
+    fb::SmallDev sfwd, sbwd, strop, sbtrop;   // and device (the last two = the first two unless own_trop)
     fb::PdfHost h_pdf;                // states grouped by pdf, for the posterior accumulation
     // device
-    fb::StreamDev fwd, bwd, trop;     // trop = fwd unless own_trop
+    fb::StreamDev fwd, bwd, trop, btrop;     // the last two = the first two unless own_trop
     fb::PdfDev pdfs;
     int32_t *d_pdf = nullptr;         // [K]
     float *d_init2 = nullptr;         // [K] init * log2(e)
@@ -382,7 +382,10 @@ struct RecDir {
     int32_t out_ld;        // shared graph: elements between the rows of consecutive frames of out (0: the state count)
     uint16_t *bp;          // tropical semiring: back-pointers (see fb_viterbi in fb_api.cpp for the layout), else NULL
     int64_t bp_ld;         // elements per frame row of bp
-    int32_t *last;         // tropical semiring: [B] local id of the best end state (-1: none)
+    int32_t bp_ccap;       // clone slots a row of bp has room for, per sequence (both directions write rows of one form)
+    void *mid;             // tropical semiring: [B][mid_ld] the vector this direction ends with (carrier type; states, then clone slots)
+    int64_t mid_ld;
+    double *mid_off;       // ... [B] its shift (log2 units)
     SmallDev small;        // small-graph kernel: its plan for this direction
     PStreamDev prob;       // probability-domain kernel: its plan for this direction
     const float *rank1;    // ... leaky-HMM form: q by target (states, clone slots, dump slot), see linear_run
@@ -399,7 +402,7 @@ constexpr int kDoneFused = 16;     // ... of the word PostParams::fused of the c
 struct RecParams {
     RecDir dir[2];
     float leak;            // leaky-HMM form of the probability-domain kernel: the fraction handed out again
-    int n_dir;
+    int n_dir;             // tropical semiring: with two directions each goes half way (see path_middle)
     const int32_t *pdf;
     const float *emis;
     const int32_t *lengths;
@@ -464,11 +467,17 @@ unsigned int linear_restarts();     // diagnostic: runs the probability-domain k
 struct BacktraceParams {
     const uint16_t *bp;      // back-pointers written by the recursion kernel
     int64_t bp_ld;           // elements per frame row
-    const int32_t *last;     // [B] best end state in the kernel's index space, -1: none
     const int32_t *lengths;
-    StreamDev sched;         // the forward plan (sub-graphs, clones)
+    StreamDev sched[2];      // the forward and the backward plan (sub-graphs, clones)
     const SmallSub *small_sub;   // graphs of the small-graph kernel: their sub-graphs (sched is empty then)
-    int32_t B, N, shared, Ktot, Kcap, Ccap;
+    int32_t n_dir;           // 2: the recursions met in the middle; 1: there was only the forward one
+    const void *mid[2];      // the vectors they ended with (RecDir::mid), double if f64
+    const double *mid_off[2];
+    const float *end;        // end weights, log2 units (n_dir == 1)
+    int64_t mid_ld;
+    int32_t f64;
+    double *score;           // [B]
+    int32_t B, N, shared, Ktot, Kcap, Ccap;   // Ccap: clone slots a row of bp has room for
     int32_t frames;          // back-pointer rows the kernel holds in LDS at a time (set by launch_backtrace)
     int32_t *path;           // [B][N]
 };

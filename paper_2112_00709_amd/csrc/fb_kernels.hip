@@ -84,17 +84,19 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
     const bool io_wave = wave == NC;
     const RecDir &R = P.dir[which];
     const StreamDev &S = R.sched;
-    const bool bwd = R.backward != 0;
+    const bool bwd = R.backward != 0, keep_pre = bwd && !TROP;   // keep_pre: rows leave before the emission is applied
     const SubDesc sd = S.sub[P.shared ? 0 : b];
     const int K = sd.K, k0 = sd.k0, nC = sd.n_slot;
     const int Tn = min(max(P.lengths[b], 0), P.N);
+    const int mid = path_middle(Tn, TROP ? P.n_dir : 1);
+    const int Ts = Tn > 0 && TROP ? (bwd ? Tn - mid : mid + 1) : Tn;   // frames this direction visits
     const int nE = P.shared ? P.D : K;           // entries of a staged emission vector
     const int nX = P.Kcap + R.Ccap + 1;          // states, clone slots, dump slot
     const int Xs = XF ? XF : nX, Es = P.Ecap + 1;
 
     T *xb = (T *)lds_raw;
     T *bh = xb + 2 * Xs;
-    T *red = bh + (bwd ? 2 * Xs : 0);
+    T *red = bh + (keep_pre ? 2 * Xs : 0);
     float *er = (float *)(red + 4 * NW + 2);
     int32_t *pix = (int32_t *)(er + 3 * Es);
     uint16_t *vix = (uint16_t *)(pix + (P.shared ? 0 : P.Ecap));   // emission index of every target
@@ -230,13 +232,14 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
             }
     };
 
-    // tropical semiring: the back-pointers of frame f (f >= 1) -> global memory; a row holds the states
+    // tropical semiring: the back-pointers of step i (i >= 1) -> global memory; a row holds the states
     // and, behind them, the clone slots (a back-pointer is an index into the state buffer: a state, or
     // Kcap + slot for a clone)
-    auto write_bp = [&](int f, const uint16_t *srcb) {
+    auto write_bp = [&](int i, const uint16_t *srcb) {
         if (TROP && R.bp) {
+            const int f = bwd ? Tn - i : i;   // (row f joins frames f - 1 and f, see path_middle)
             uint16_t *orow = R.bp + (P.shared ? ((size_t)b * P.N + f) * R.bp_ld : (size_t)f * R.bp_ld);
-            uint16_t *ost = orow + (P.shared ? 0 : k0), *ocl = orow + (P.shared ? K : P.Ktot + b * R.Ccap);
+            uint16_t *ost = orow + (P.shared ? 0 : k0), *ocl = orow + (P.shared ? K : P.Ktot + b * R.bp_ccap);
             copy_out(ost, srcb, K, [](uint16_t x) { return x; });
             copy_out(ocl, srcb + P.Kcap, nC, [](uint16_t x) { return x; });
         }
@@ -256,9 +259,9 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                 for (int u = 0; u < kPixRegs; ++u) pixr[u] = u * kWave + lane < nE ? pix[u * kWave + lane] : 0;
             }
             stage(frame(0), er);
-            if (Tn > 1) stage(frame(1), er + Es);
+            if (Ts > 1) stage(frame(1), er + Es);
             staged_wait();
-            if (Tn > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
+            if (Ts > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
             if (off_seq && lane == 0) off_seq[frame(0)] = 0.0;
             if (R.cum && lane == 0) R.cum[(size_t)b * P.N + frame(0)] = 0.0f;
         }
@@ -266,14 +269,15 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
         T wmax = kNegInf;
         for (int k = tid; k < K; k += NT) {
             const T s = (T)R.bound[k0 + k];
-            const T x = s + (T)er[P.shared ? P.pdf[k0 + k] : k] * (T)kLog2e;
+            // (a best path's backward recursion ends before the emission of its last frame, which may be this one)
+            const T x = TROP && bwd && Ts == 1 ? s : s + (T)er[P.shared ? P.pdf[k0 + k] : k] * (T)kLog2e;
             xb[k] = x;
-            if (bwd) bh[k] = s;
+            if (keep_pre) bh[k] = s;
             wmax = tmax(wmax, x);
         }
         for (int k = tid; k < nC; k += NT) {   // clones start empty: the state itself holds the start weight
             xb[P.Kcap + k] = kNegInf;
-            if (bwd) bh[P.Kcap + k] = kNegInf;
+            if (keep_pre) bh[P.Kcap + k] = kNegInf;
         }
         if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = kNegInf;   // the dump slot holds zero-bar in both buffers, always
         put_max(0, wmax);
@@ -281,7 +285,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
 
         double csum = 0.0;
         if (io_wave) {
-            for (int i = 1; i < Tn; ++i) {
+            for (int i = 1; i < Ts; ++i) {
                 const int cur = (i - 1) & 1;
                 const T M = get_max(i - 1);
                 const T c = (M == kNegInf) ? (T)0 : M;
@@ -289,8 +293,8 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                 if (off_seq && lane == 0) off_seq[frame(i)] = csum * (double)R.out_scale;
                 if (R.cum && lane == 0) R.cum[(size_t)b * P.N + frame(i)] = (float)csum;
                 staged_wait();   // frame i+1, requested a whole step ago, is in LDS
-                if (i + 2 < Tn) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
-                write_row(frame(i - 1), bwd ? bh + cur * Xs : xb + cur * Xs);
+                if (i + 2 < Ts) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
+                write_row(frame(i - 1), keep_pre ? bh + cur * Xs : xb + cur * Xs);
                 if (TROP && i >= 2) write_bp(i - 1, bpb + cur * Xs);
                 if (lane == 0) {   // its own slot counts for nothing / the word of step i + 1 starts empty
                     if (kAtomMax) red[(i + 1) % 3] = kNegInf;
@@ -404,6 +408,8 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                 const T M = get_max(i - 1);
                 const T c = (M == kNegInf) ? (T)0 : M;
                 wmax = kNegInf;
+                const bool no_em = TROP && bwd && i == Ts - 1;   // (see the first frame)
+                auto emitted = [&](float e) { return TROP && no_em ? (T)0 : (T)e * (T)kLog2e; };
                 T m = TROP ? kNegInf : (T)kNegBig;
                 float sum = 0.0f;
                 int arg = 0;                         // tropical semiring: the state the best term so far came from
@@ -413,7 +419,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                     for (int z = tid; z < sd.n_zero; z += NC * kWave) {
                         const int k = S.zero_rows[sd.zero0 + z];
                         xn[k] = kNegInf;
-                        if (bwd) bn[k] = kNegInf;
+                        if (keep_pre) bn[k] = kNegInf;
                     }
                 // fold one batch: a, gv = its entries and gathered values; next = the batch after it (its
                 // gathers are issued before this batch's arithmetic), has_next: there is one
@@ -445,10 +451,10 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                         auto close_part = [&](T val, int parg, int r) {   // r: a row of the part that names its target
                             const uint32_t tgt = ptgt[r];
                             const T pre = val - c;
-                            const T x = pre + (T)pem[r] * (T)kLog2e;
+                            const T x = pre + emitted(pem[r]);
                             xn[tgt] = x;
                             if constexpr (TROP) bpn[tgt] = (uint16_t)(parg >> kSrcShift);
-                            else if (bwd) bn[tgt] = pre;
+                            else if (keep_pre) bn[tgt] = pre;
                             wmax = tmax(wmax, x);
                         };
                         T xs[kBatchRows];
@@ -499,7 +505,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                                 const T pre = m + (T)flog2(sum) - c;   // sum == 0 -> -inf
                                 const T x = pre + (T)ern[vix[tgt]] * (T)kLog2e;
                                 xn[tgt] = x;
-                                if (bwd) bn[tgt] = pre;
+                                if (keep_pre) bn[tgt] = pre;
                                 wmax = tmax(wmax, x);
                                 m = (T)kNegBig;
                                 sum = 0.0f;
@@ -520,7 +526,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                                 const int lg = (int)((f >> kFlagLgShift) & 7u);
                                 if (lg) group_best(m, arg, lg, lane);
                                 const uint32_t tgt = target();
-                                const T x = (m - c) + (T)ern[vix[tgt]] * (T)kLog2e;
+                                const T x = (m - c) + emitted(ern[vix[tgt]]);
                                 xn[tgt] = x;
                                 bpn[tgt] = (uint16_t)(arg >> kSrcShift);
                                 wmax = tmax(wmax, x);
@@ -536,7 +542,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                                 const T pre = m + (T)flog2(sum) - c;   // sum == 0 -> -inf
                                 const T x = pre + (T)ern[vix[tgt]] * (T)kLog2e;
                                 xn[tgt] = x;
-                                if (bwd) bn[tgt] = pre;
+                                if (keep_pre) bn[tgt] = pre;
                                 wmax = tmax(wmax, x);
                                 m = (T)kNegBig;
                                 sum = 0.0f;
@@ -581,51 +587,25 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                 __syncthreads();
             };
             if constexpr (XF != 0) {
-                for (int i = 1; i < Tn; i += 2) {
+                for (int i = 1; i < Ts; i += 2) {
                     step(i, std::integral_constant<int, 0>{});
-                    if (i + 1 < Tn) step(i + 1, std::integral_constant<int, 1>{});
+                    if (i + 1 < Ts) step(i + 1, std::integral_constant<int, 1>{});
                 }
             } else {
-                for (int i = 1; i < Tn; ++i) step(i, (i - 1) & 1);
+                for (int i = 1; i < Ts; ++i) step(i, (i - 1) & 1);
             }
         }
 
         // ---- last frame: write it out, close log Z with the end weights
-        const int last = (Tn - 1) & 1;
+        const int last = (Ts - 1) & 1;
         const T *xl = xb + last * Xs;
-        if (io_wave) write_row(frame(Tn - 1), bwd ? bh + last * Xs : xl);
-        if (TROP) {
-            if (io_wave && Tn >= 2) write_bp(Tn - 1, bpb + last * Xs);
-            // score = max_k (x[k] + end weight) and a state that attains it (the smallest such k)
-            T m = kNegInf;
-            int at = 0x7fffffff;
-            for (int k = tid; k < K; k += NT) {
-                const T t = xl[k] + (T)R.obound[k0 + k];
-                if (t > m) { m = t; at = k; }
-            }
-            for (int j = tid; j < sd.n_cdesc; j += NT) {   // clones end with their state's weight
-                const CloneDesc cd = cdesc[j];
-                for (int i = 0; i < cd.count; ++i) {
-                    const T t = xl[P.Kcap + cd.first + i] + (T)R.obound[k0 + cd.state];
-                    if (t > m || (t == m && P.Kcap + cd.first + i < at)) { m = t; at = P.Kcap + cd.first + i; }
-                }
-            }
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                const T m2 = (T)__shfl_xor(m, o, 64);
-                const int a2 = __shfl_xor(at, o, 64);
-                if (m2 > m || (m2 == m && a2 < at)) { m = m2; at = a2; }
-            }
-            T *rm = red + 2 * NW, *rs = rm + NW;
-            if (lane == 0) { rm[wave] = m; rs[wave] = (T)at; }
-            __syncthreads();
-            if (io_wave && lane == 0) {   // the lane that holds the sum of the offsets
-                m = rm[0]; T a = rs[0];
-                for (int w = 1; w < NW; ++w)
-                    if (rm[w] > m || (rm[w] == m && rs[w] < a)) { m = rm[w]; a = rs[w]; }
-                if (R.logz) R.logz[b] = (csum + (double)m) * kLn2;
-                if (R.last) R.last[b] = m == kNegInf ? -1 : (int)a;
-            }
+        if (io_wave) write_row(frame(Ts - 1), keep_pre ? bh + last * Xs : xl);
+        if (TROP) {   // the last vector and its shift, for the kernel that joins the two halves
+            if (io_wave && Ts >= 2) write_bp(Ts - 1, bpb + last * Xs);
+            T *mrow = (T *)R.mid + (size_t)b * R.mid_ld;
+            for (int k = tid; k < K; k += NT) mrow[k] = xl[k];
+            for (int k = tid; k < nC; k += NT) mrow[P.Kcap + k] = xl[P.Kcap + k];
+            if (io_wave && lane == 0) R.mid_off[b] = csum;
         } else if (R.logz) {
             T m = (T)kNegBig;
             float s = 0.0f;
@@ -646,8 +626,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
             }
         }
     } else if (tid == 0) {
-        if (R.logz) R.logz[b] = -INFINITY;
-        if (TROP && R.last) R.last[b] = -1;
+        if (!TROP && R.logz) R.logz[b] = -INFINITY;
     }
 
     // ---- padded frames
@@ -2059,35 +2038,50 @@ __global__ __launch_bounds__(256) void fb_loss_kernel(const double *zn, const do
     if (threadIdx.x == 0) *loss = acc[0];
 }
 
-// Best path from the back-pointers: one thread per sequence walks from the best end state to frame 0.
-// Indices are those of the state buffer (a state, or Kcap + slot for a clone of a very long row); a clone
-// is reported as the state it belongs to.
-// One workgroup per sequence.  A path is a chain of dependent reads (the back-pointer of frame n names the row
-// entry to read at frame n - 1), each a trip to HBM if taken one by one; so the workgroup copies the sequence's
-// back-pointer rows of kBtFrames frames at a time into LDS (whole rows: which entry is needed is only known once the
-// chain gets there), the next block travelling while one thread walks the frames of this one there.
-constexpr int kBtThreads = 256, kBtFrames = 8;
+// Best path: the two halves joined and followed.  The recursions have left, at the frame m where they met (path_middle),
+// the best score from the start to every state there and from every state there to the end; their largest sum is the
+// score, the state that attains it the path's at frame m (of equal ones the smallest), and the back-pointers lead from
+// there to both ends.  One workgroup per sequence and half.
+// A path is a chain of dependent reads (the back-pointer of a frame names the row entry to read at the next one), each
+// a trip to HBM if taken one by one; so the workgroup copies the sequence's back-pointer rows of several frames at a
+// time into LDS (whole rows: which entry is needed is only known once the chain gets there), the next block travelling
+// while one thread walks the frames of this one there.  Bound: reading the rows once (466 MB for 128 sequences of at
+// most 500 frames over 6000 states: 250 us as one chain per sequence, on half as many compute units; 161 us as two).
+// Indices are those of the state buffers (a state, or Kcap + slot for a clone of a very long row, which each direction
+// has for itself); a clone is reported as the state it belongs to.
+constexpr int kBtThreads = 256, kBtFrames = 64;
+constexpr size_t kBtSmallBytes = 64 * 1024;   // rows in LDS beyond this only as far as kBtLargeFrames
+constexpr int kBtLargeFrames = 8;
 
 __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const BacktraceParams P)
 {
-    extern __shared__ uint16_t bt_rows[];   // [frames][W]: the 16-byte pieces that hold the states' columns, then the clone slots'
-    const int b = blockIdx.x, tid = threadIdx.x;
-    SubDesc sd{};
-    if (P.small_sub) {
-        sd.k0 = P.small_sub[P.shared ? 0 : b].k0;
-        sd.K = P.small_sub[P.shared ? 0 : b].K;
-    } else {
-        sd = P.sched.sub[P.shared ? 0 : b];
-    }
-    const CloneDesc *cdesc = P.sched.clones + sd.clone0;
-    const int T = min(max(P.lengths[b], 0), P.N);
+    extern __shared__ uint16_t bt_rows[];   // [2][frames][W]: the 16-byte pieces that hold the states' columns, then the clone slots'
+    const int b = blockIdx.x % P.B, half = blockIdx.x / P.B, tid = threadIdx.x;   // half 0: frames m .. 0, 1: m + 1 .. T - 1
+    auto sub_of = [&](int h) {
+        SubDesc sd{};
+        if (P.small_sub) {
+            sd.k0 = P.small_sub[P.shared ? 0 : b].k0;
+            sd.K = P.small_sub[P.shared ? 0 : b].K;
+        } else {
+            sd = P.sched[h].sub[P.shared ? 0 : b];
+        }
+        return sd;
+    };
+    const SubDesc sd0 = sub_of(0), sd1 = sub_of(P.n_dir - 1);
+    const CloneDesc *const cd0 = P.sched[0].clones + sd0.clone0, *const cd1 = P.sched[P.n_dir - 1].clones + sd1.clone0;
+    const int n_cd0 = sd0.n_cdesc, n_cd1 = P.n_dir == 2 ? sd1.n_cdesc : 0;
+    const int T = min(max(P.lengths[b], 0), P.N), m = path_middle(T, P.n_dir);
+    const int k0 = sd0.k0, K = sd0.K, F = P.frames;
     int32_t *prow = P.path + (size_t)b * P.N;
-    for (int n = T + tid; n < P.N; n += kBtThreads) prow[n] = -1;
-    if (T == 0) return;
-    const int K = sd.K, F = P.frames;
+    if (half == 0)
+        for (int n = T + tid; n < P.N; n += kBtThreads) prow[n] = -1;
+    if (T == 0) {
+        if (half == 0 && tid == 0) P.score[b] = -INFINITY;
+        return;
+    }
     // where the sequence's columns lie in a row of back-pointers, and the 16-byte pieces of the row that hold them
     // (rows are a multiple of 8 entries long and start on 16-byte boundaries)
-    const int64_t col_states = P.shared ? 0 : sd.k0;
+    const int64_t col_states = P.shared ? 0 : k0;
     const int64_t col_clones = P.shared ? (int64_t)K : (int64_t)P.Ktot + (int64_t)b * P.Ccap;
     const int64_t ps0 = col_states >> 3, ps1 = (col_states + K + 7) >> 3;
     const int64_t pc0 = col_clones >> 3, pc1 = (col_clones + P.Ccap + 7) >> 3;
@@ -2095,51 +2089,112 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     const int W = (ns + nc) * 8;
     const int at_states = (int)(col_states - ps0 * 8), at_clones = ns * 8 + (int)(col_clones - pc0 * 8);
     const int lane = tid & (kWave - 1), wave = tid >> 6;
-    int s = P.last[b];   // index in the kernel's index space: a state, or Kcap + a clone slot (thread 0 follows it)
-    if (s < 0) {
-        for (int n = tid; n < T; n += kBtThreads) prow[n] = -1;
+    // the half's rows in the order it takes them: m, m - 1, .. 1 or m + 1, .. T - 1; in blocks of F, in two buffers: the
+    // next block is on its way from global memory while thread 0 walks this one
+    const int n_rows = half ? T - 1 - m : m;
+    auto row_of = [&](int i) { return half ? m + 1 + i : m - i; };
+    auto issue = [&](int i0, int buf) {   // rows row_of(i0), ..., straight into LDS, 16 bytes per lane, nothing waits in between
+        const int cnt = min(F, n_rows - i0);
+        for (int f = 0; f < cnt; ++f) {
+            const uint4 *row = (const uint4 *)(P.bp + (P.shared ? ((size_t)b * P.N + row_of(i0 + f)) : (size_t)row_of(i0 + f)) * P.bp_ld);
+            uint4 *dst = (uint4 *)(bt_rows + ((size_t)buf * F + f) * W);
+            for (int p = wave * kWave; p < ns; p += kBtThreads)
+                if (p + lane < ns)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + ps0 + p + lane),
+                                                     (__attribute__((address_space(3))) void *)(dst + p), 16, 0, 0);
+            for (int p = wave * kWave; p < nc; p += kBtThreads)
+                if (p + lane < nc)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + pc0 + p + lane),
+                                                     (__attribute__((address_space(3))) void *)(dst + ns + p), 16, 0, 0);
+        }
+    };
+    if (n_rows > 0) issue(0, 0);
+
+    // ---- the score and the places of its path in both directions' vectors (both workgroups of a sequence find the same)
+    const size_t mid_at = (size_t)b * P.mid_ld;
+    auto value = [&](int h, int idx) {
+        return P.f64 ? ((const double *)P.mid[h])[mid_at + idx] : (double)((const float *)P.mid[h])[mid_at + idx];
+    };
+    auto value1 = [&](int idx) { return P.n_dir == 2 ? value(1, idx) : (double)P.end[k0 + idx]; };
+    double best = -INFINITY;
+    uint32_t at = 0xffffffffu;   // place in the forward vector << 16 | place in the backward vector
+    auto take = [&](double v, uint32_t a) {
+        if (v > best || (v == best && a < at)) { best = v; at = a; }
+    };
+    for (int k = tid; k < K; k += kBtThreads) {
+        const double v = value(0, k) + value1(k);
+        if (v > best) { best = v; at = (uint32_t)k << 16 | (uint32_t)k; }   // (a lane's states come in ascending order)
+    }
+    // a cloned state's value is the largest of its own and its clones'; a clone's way on starts where its state's does
+    for (int j = tid; j < n_cd0; j += kBtThreads) {
+        const CloneDesc c = cd0[j];
+        for (int i = 0; i < c.count; ++i) {
+            const uint32_t f = (uint32_t)(P.Kcap + c.first + i);
+            const double v = value(0, (int)f);
+            take(v + value1(c.state), f << 16 | (uint32_t)c.state);
+            for (int j1 = 0; j1 < n_cd1; ++j1)
+                if (cd1[j1].state == c.state)
+                    for (int i1 = 0; i1 < cd1[j1].count; ++i1) {
+                        const uint32_t f1 = (uint32_t)(P.Kcap + cd1[j1].first + i1);
+                        take(v + value1((int)f1), f << 16 | f1);
+                    }
+        }
+    }
+    for (int j = tid; j < n_cd1; j += kBtThreads) {
+        const CloneDesc c = cd1[j];
+        const double v = value(0, c.state);
+        for (int i = 0; i < c.count; ++i) {
+            const uint32_t f1 = (uint32_t)(P.Kcap + c.first + i);
+            take(v + value1((int)f1), (uint32_t)c.state << 16 | f1);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double v = __shfl_xor(best, o, 64);
+        const uint32_t a = (uint32_t)__shfl_xor((int)at, o, 64);
+        take(v, a);
+    }
+    double *red_v = (double *)(bt_rows + (size_t)2 * F * W);   // [waves] the waves' best, [waves] their places
+    uint32_t *red_a = (uint32_t *)(red_v + kBtThreads / kWave);
+    if (lane == 0) { red_v[wave] = best; red_a[wave] = at; }
+    __syncthreads();
+    best = red_v[0]; at = red_a[0];
+#pragma unroll
+    for (int w = 1; w < kBtThreads / kWave; ++w) take(red_v[w], red_a[w]);
+    const bool none = best == -INFINITY;
+    if (half == 0 && tid == 0)
+        P.score[b] = none ? -INFINITY : (P.mid_off[0][b] + (P.n_dir == 2 ? P.mid_off[1][b] : 0.0) + best) * kLn2;
+    if (none) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (rows on their way into this workgroup's LDS)
+        for (int i = tid; i < (half ? n_rows : m + 1); i += kBtThreads) prow[half ? m + 1 + i : i] = -1;
         return;
     }
+
+    // ---- along the back-pointers
+    const CloneDesc *const cdesc = half ? cd1 : cd0;
+    const int n_cdesc = half ? n_cd1 : n_cd0;
     auto state_of = [&](int idx) {
         if (idx < P.Kcap) return idx;
         const int slot = idx - P.Kcap;
         int state = 0;
-        for (int j = 0; j < sd.n_cdesc; ++j)
+        for (int j = 0; j < n_cdesc; ++j)
             if (slot >= cdesc[j].first && slot < cdesc[j].first + cdesc[j].count) state = cdesc[j].state;
         return state;
     };
-    // frames T-1 .. 1 take their predecessor from their own row; blocks of F rows, highest frame first, in two
-    // buffers: the next block is on its way from global memory while thread 0 walks this one
-    auto issue = [&](int hi, int buf) {   // rows hi, hi - 1, ..., straight into LDS, 16 bytes per lane, nothing waits in between
-        const int cnt = min(F, hi);
-        for (int f = 0; f < cnt; ++f) {
-            const uint4 *row = (const uint4 *)(P.bp + (P.shared ? ((size_t)b * P.N + (hi - f)) : (size_t)(hi - f)) * P.bp_ld);
-            uint4 *dst = (uint4 *)(bt_rows + ((size_t)buf * F + f) * W);
-            for (int i0 = wave * kWave; i0 < ns; i0 += kBtThreads)
-                if (i0 + lane < ns)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + ps0 + i0 + lane),
-                                                     (__attribute__((address_space(3))) void *)(dst + i0), 16, 0, 0);
-            for (int i0 = wave * kWave; i0 < nc; i0 += kBtThreads)
-                if (i0 + lane < nc)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + pc0 + i0 + lane),
-                                                     (__attribute__((address_space(3))) void *)(dst + ns + i0), 16, 0, 0);
-        }
-    };
-    if (T > 1) issue(T - 1, 0);
-    int buf = 0;
-    for (int hi = T - 1; hi >= 1; hi -= F, buf ^= 1) {
-        const int cnt = min(F, hi);
+    int s = half ? (int)(at & 0xffffu) : (int)(at >> 16);
+    if (half == 0 && tid == 0) prow[m] = k0 + state_of(s);
+    for (int i0 = 0, buf = 0; i0 < n_rows; i0 += F, buf ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();   // this block is in LDS; thread 0 has left the other buffer
-        if (hi - F >= 1) issue(hi - F, buf ^ 1);
+        if (i0 + F < n_rows) issue(i0 + F, buf ^ 1);
         if (tid == 0) {
+            const int cnt = min(F, n_rows - i0);
             for (int f = 0; f < cnt; ++f) {
-                prow[hi - f] = sd.k0 + state_of(s);
                 s = bt_rows[((size_t)buf * F + f) * W + (s < P.Kcap ? at_states + s : at_clones + (s - P.Kcap))];
+                prow[half ? row_of(i0 + f) : row_of(i0 + f) - 1] = k0 + state_of(s);
             }
         }
     }
-    if (tid == 0) prow[0] = sd.k0 + state_of(s);
 }
 
 
@@ -2266,14 +2321,18 @@ int launch_backtrace(const BacktraceParams &p, void *stream)
     BacktraceParams q = p;
     if ((p.bp_ld & 7) != 0 || ((uintptr_t)p.bp & 15) != 0) return fail(FB_EHIP, "internal error: back-pointer rows are not in 16-byte pieces");
     const size_t row_bytes = ((size_t)p.Kcap + (size_t)p.Ccap + 32) * sizeof(uint16_t);   // both spans rounded out to whole pieces
-    q.frames = (int32_t)std::max<size_t>(1, std::min<size_t>(kBtFrames, (kLdsBytes - kLdsReserve) / (2 * std::max<size_t>(row_bytes, 1))));   // two buffers
-    const size_t lds_bytes = 2 * (size_t)q.frames * row_bytes;
+    const size_t extra = kBtThreads / kWave * (sizeof(double) + sizeof(uint32_t));
+    auto fit = [&](size_t room, int most) { return (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)most, (room - extra) / (2 * row_bytes))); };   // two buffers
+    // Short rows: as many as 64 KB hold, since a block costs a trip to memory whatever it holds; long ones: a block of
+    // 8 frames keeps a compute unit's share of the memory rate busy, more only take LDS.
+    q.frames = std::max(fit(kBtSmallBytes, kBtFrames), fit(kLdsBytes - kLdsReserve, kBtLargeFrames));
+    const size_t lds_bytes = 2 * (size_t)q.frames * row_bytes + extra;
     if (lds_bytes > kLdsBytes) return fail(FB_EUNSUPPORTED, "backtrace: a row of back-pointers exceeds the on-chip memory");
     if (lds_bytes > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)fb_backtrace_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(fb_backtrace_kernel, dim3((unsigned)p.B), dim3(kBtThreads), lds_bytes, (hipStream_t)stream, q);
+    hipLaunchKernelGGL(fb_backtrace_kernel, dim3((unsigned)(p.B * p.n_dir)), dim3(kBtThreads), lds_bytes, (hipStream_t)stream, q);
     return check_launch("backtrace kernel launch");
 }
 

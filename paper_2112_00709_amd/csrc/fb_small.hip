@@ -22,7 +22,7 @@
 // Measured per direction, against the general kernel with 4 waves (fb_recursion_kernel<4, double>): 32 chains of 30-120
 // states over at most 144 frames 124 -> 29 us (of which the computing wave 24); a 16-state graph over 50 frames 55 -> 12
 // (no row over several lanes) or 18 us; 701 states, 3.5 k arcs over at most 211 frames 442 -> 240 us; best path through 32
-// label-sequence graphs of 21-161 states, 209 frames, 194 -> 64 us.  What bounds it: the latency of that chain (310
+// label-sequence graphs of 21-161 states, 209 frames, 194 -> 64 us, and 40 us from both ends (fb_viterbi).  What bounds it: the latency of that chain (310
 // clocks a step with one computing wave and two arcs a row); with 16 slices and more the issue of double arithmetic.
 //
 // Variants <NC, R, TM>: NC computing waves of R slices each, TM arcs per lane; the smallest that holds the batch's
@@ -54,7 +54,7 @@ struct SmallShape {
     // x ring, ring of the rows before the emission (backward), back-pointer ring (best path), reduction scratch
     static constexpr size_t lds_bytes(bool backward, bool tropical)
     {
-        return (size_t)RB * XS * 8 * (backward ? 2 : 1) + (tropical ? (size_t)RB * XS * 2 : 0) + 8 * (2 * (size_t)NC) + 16;
+        return (size_t)RB * XS * 8 * (backward && !tropical ? 2 : 1) + (tropical ? (size_t)RB * XS * 2 : 0) + 8 * (2 * (size_t)NC) + 16;
     }
 };
 
@@ -80,15 +80,17 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const RecDir &D = P.dir[which];
-    const bool bwd = !TROP && D.backward != 0;
+    const bool bwd = D.backward != 0, pre = bwd && !TROP;   // pre: rows leave before the emission is applied
     const SmallSub sd = D.small.sub[P.shared ? 0 : b];
     const int K = sd.K, k0 = sd.k0;
     const int Tn = min(max(P.lengths[b], 0), P.N);
+    const int mid = path_middle(Tn, TROP ? P.n_dir : 1);
+    const int Ts = Tn > 0 && TROP ? (bwd ? Tn - mid : mid + 1) : Tn;   // frames this direction visits
     auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
 
     double *xr = lds_raw;                                   // [RB][XS]
     double *pr = xr + (size_t)RB * XS;                      // [RB][XS], backward only
-    uint16_t *bpr = (uint16_t *)(pr + (bwd ? (size_t)RB * XS : 0));   // [RB][XS], best path only
+    uint16_t *bpr = (uint16_t *)(pr + (pre ? (size_t)RB * XS : 0));   // [RB][XS], best path only
     double *fin = (double *)(bpr + (TROP ? (size_t)RB * XS : 0));     // [NC] + [NC] last reduction
 
     const size_t out_ld = P.shared ? (size_t)(D.out_ld ? D.out_ld : K) : (size_t)P.Ktot;
@@ -96,7 +98,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
     float *out_f = (D.out && !D.out_carrier) ? (float *)D.out + out_at : nullptr;
     double *out_t = (D.out && D.out_carrier) ? (double *)D.out + out_at : nullptr;
     double *off_seq = D.off ? D.off + (size_t)b * P.N : nullptr;
-    const int n_bar = (Tn - 1 + RPB - 1) / RPB;             // blocks of rows behind the first one
+    const int n_bar = (Ts - 1 + RPB - 1) / RPB;             // blocks of rows behind the first one
 
     if (Tn > 0 && wave < NC) {
         // ---- computing waves
@@ -124,7 +126,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
         // the row of emissions to ask for next (uniform): the frames in order of the steps, the last one again behind the end
         const ptrdiff_t em_step = bwd ? -(ptrdiff_t)P.D : (ptrdiff_t)P.D;
         const float *em_row = P.emis + ((size_t)b * P.N + (size_t)frame(0)) * P.D;
-        int em_left = Tn - 1;
+        int em_left = Ts - 1;
         auto next_em = [&]() {
             em_row += em_left > 0 ? em_step : 0;
             --em_left;
@@ -149,13 +151,14 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
             for (int j = 0; j < R; ++j) {
                 const bool real = tg[j] != (uint32_t)S::KS * 8u;
                 const double s = real ? (double)D.bound[k0 + (int)(tg[j] >> 3)] : kZero;
-                *(double *)(lds + tg[j]) = dmax(s + (double)e0[j] * kLog2e, kZero);
-                if (bwd) *(double *)((char *)pr + tg[j]) = s;
+                // (a best path's backward recursion ends before the emission of its last frame, which may be this one)
+                *(double *)(lds + tg[j]) = dmax(s + (TROP && bwd && Ts == 1 ? 0.0 : (double)e0[j] * kLog2e), kZero);
+                if (pre) *(double *)((char *)pr + tg[j]) = s;
             }
         }
         lds_barrier();
         // step i0 + a, a < A a constant
-        auto step = [&](auto ac, auto bwd_c) __attribute__((always_inline)) {
+        auto step = [&](auto ac, auto bwd_c, int i0) __attribute__((always_inline)) {
             constexpr int a = decltype(ac)::value;
             constexpr bool kBwd = decltype(bwd_c)::value;
             constexpr int kRow = XS * 8, cur = (a % RB) * kRow, nxt = ((a + 1) % RB) * kRow;
@@ -166,7 +169,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                 for (int t = 0; t < TM; ++t) g[j][t] = *(const double *)(lds + so[j][t] + cur);
             double ed[R];
 #pragma unroll
-            for (int j = 0; j < R; ++j) ed[j] = (double)e[j][a] * kLog2e;
+            for (int j = 0; j < R; ++j) ed[j] = TROP && kBwd && i0 + a == Ts - 1 ? 0.0 : (double)e[j][a] * kLog2e;   // (see above)
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 double m;
@@ -213,27 +216,27 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
         auto all_steps = [&](auto bwd_c) __attribute__((always_inline)) {
             constexpr auto kA = std::make_integer_sequence<int, A>{};
             int i0 = 1;
-            for (; i0 + A <= Tn; i0 += A) {
+            for (; i0 + A <= Ts; i0 += A) {
                 float ahead[R][A];
                 ask(ahead);
                 __builtin_amdgcn_sched_barrier(0);
-                unrolled([&](auto ac) __attribute__((always_inline)) { step(ac, bwd_c); }, kA);
+                unrolled([&](auto ac) __attribute__((always_inline)) { step(ac, bwd_c, i0); }, kA);
 #pragma unroll
                 for (int j = 0; j < R; ++j)
 #pragma unroll
                     for (int a = 0; a < A; ++a) e[j][a] = ahead[j][a];
             }
             unrolled([&](auto ac) __attribute__((always_inline)) {
-                if (i0 + decltype(ac)::value < Tn) step(ac, bwd_c);
+                if (i0 + decltype(ac)::value < Ts) step(ac, bwd_c, i0);
             }, kA);
         };
         if (bwd) all_steps(std::true_type{});
         else all_steps(std::false_type{});
-        if ((Tn - 1) % RPB != 0) lds_barrier();             // the last block's rows
+        if ((Ts - 1) % RPB != 0) lds_barrier();             // the last block's rows
     } else if (Tn > 0) {
         // ---- writing waves: a row is one wave's, the rows go round the waves
         const int q = wave - NC;
-        const double *rows = bwd ? pr : xr;
+        const double *rows = pre ? pr : xr;
         const double scale = (double)D.out_scale;
         const bool shifted = !out_t && (out_f || off_seq);
         struct Row { double v[S::UIO]; uint16_t p[TROP ? S::UIO : 1]; double c; };
@@ -278,7 +281,8 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
             if (D.cum && u0 == 0 && lane == 0) D.cum[(size_t)b * P.N + f] = 0.0f;   // (carrier rows are not shifted)
             if constexpr (TROP) {
                 if (D.bp && i > 0) {
-                    uint16_t *orow = D.bp + (P.shared ? ((size_t)b * P.N + f) * D.bp_ld : (size_t)f * D.bp_ld + k0);
+                    const int row = bwd ? f + 1 : f;         // (path_middle)
+                    uint16_t *orow = D.bp + (P.shared ? ((size_t)b * P.N + row) * D.bp_ld : (size_t)row * D.bp_ld + k0);
 #pragma unroll
                     for (int u = u0; u < u1; ++u)
                         if (u * kWave < K) orow[at(u)] = r.p[u];
@@ -304,7 +308,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
             if (any_row) block(0, 1);
             for (int n = 1; n <= n_bar; ++n) {
                 lds_barrier();                              // block n is in the ring
-                if (any_row) block((n - 1) * RPB + 1, min(RPB, Tn - 1 - (n - 1) * RPB));
+                if (any_row) block((n - 1) * RPB + 1, min(RPB, Ts - 1 - (n - 1) * RPB));
             }
         } else {
             // a wave's row takes it four steps: read (it is gone two steps later), maximum, first half stored, second half
@@ -328,51 +332,33 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
     }
 
     if (Tn > 0) {
-        // ---- log Z (or the best score) from the last vector and the end weights, by the computing waves
-        const double *xl = xr + (size_t)((Tn - 1) % RB) * XS;
-        if (wave < NC) {
-            double m = TROP ? kZero : (double)kNegBig;
-            float s = 0.0f;
-            int at = 0x7fffffff;
-            for (int k = wave * kWave + lane; k < K; k += NC * kWave) {
-                const double t = xl[k] + (double)D.obound[k0 + k];
-                if constexpr (TROP) {
-                    if (t > m) { m = t; at = k; }
-                } else {
-                    lse_add(m, s, t);
-                }
-            }
+        const double *xl = xr + (size_t)((Ts - 1) % RB) * XS;
+        if constexpr (TROP) {
+            // ---- the last vector, for the kernel that joins the two halves
+            double *mrow = (double *)D.mid + (size_t)b * D.mid_ld;
+            if (wave < NC)
+                for (int k = wave * kWave + lane; k < K; k += NC * kWave) mrow[k] = xl[k] > kZeroOut ? xl[k] : -INFINITY;
+            if (threadIdx.x == 0) D.mid_off[b] = 0.0;
+        } else {
+            // ---- log Z from the last vector and the end weights, by the computing waves
+            if (wave < NC) {
+                double m = (double)kNegBig;
+                float s = 0.0f;
+                for (int k = wave * kWave + lane; k < K; k += NC * kWave) lse_add(m, s, xl[k] + (double)D.obound[k0 + k]);
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                const double m2 = __shfl_xor(m, o, 64);
-                if constexpr (TROP) {
-                    const int a2 = __shfl_xor(at, o, 64);
-                    if (m2 > m || (m2 == m && a2 < at)) { m = m2; at = a2; }
-                } else {
-                    lse_merge(m, s, m2, __shfl_xor(s, o, 64));
-                }
+                for (int o = 32; o >= 1; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
+                if (lane == 0) { fin[wave] = m; fin[NC + wave] = (double)s; }
             }
-            if (lane == 0) { fin[wave] = m; fin[NC + wave] = TROP ? (double)at : (double)s; }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double m = fin[0];
-            if constexpr (TROP) {
-                double a = fin[NC];
-                for (int v = 1; v < NC; ++v)
-                    if (fin[v] > m || (fin[v] == m && fin[NC + v] < a)) { m = fin[v]; a = fin[NC + v]; }
-                const bool none = !(m > kZeroOut);
-                if (D.logz) D.logz[b] = none ? -INFINITY : m * kLn2;
-                if (D.last) D.last[b] = none ? -1 : (int)a;
-            } else {
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double m = fin[0];
                 float s = (float)fin[NC];
                 for (int v = 1; v < NC; ++v) lse_merge(m, s, fin[v], (float)fin[NC + v]);
                 if (D.logz) D.logz[b] = m > kZeroOut ? (m + (double)flog2(s)) * kLn2 : -INFINITY;
             }
         }
-    } else if (threadIdx.x == 0) {
-        if (D.logz) D.logz[b] = -INFINITY;
-        if (TROP && D.last) D.last[b] = -1;
+    } else if (threadIdx.x == 0 && D.logz) {
+        D.logz[b] = -INFINITY;
     }
 
     // ---- padded frames

@@ -93,3 +93,32 @@ def test_viterbi_edge_cases(fb):
     g2 = wl.tiny_graph(9, 6, 4)
     e2 = rng.normal(size=(2, 7, 4)).astype(np.float32)
     check(fb, g2, 4, e2, np.array([7, 5], np.int32), "tiny graph with -inf entries")
+
+
+@pytest.mark.parametrize("kind", ["small", "small, parallel arcs", "large", "large, hub rows both ways", "large, parallel arcs, double vectors", "packed"])
+def test_viterbi_halves_meet(fb, kind):
+    """The two recursions meet at frame (T - 1) / 2: the shortest lengths, odd and even ones, clones in either plan."""
+    rng = np.random.default_rng(len(kind))
+    D, lengths = 13, np.array([1, 2, 3, 4, 0, 5, 16, 17, 18, 33], np.int32)
+    K = 70 if kind.startswith("small") else 2400 if "hub" in kind else 1300
+    if kind == "packed":
+        phones = np.array([1, 1, 1, 1, 2, 1, 5, 5, 6, 11])
+        g = wl.chain_graphs(rng, phones, D)
+        g.final[:] = np.log(0.5)   # every state may end: a frame is enough
+    else:
+        g = wl.random_graph(rng, K, D)
+        if "hub" in kind:   # rows of more than 2048 arcs in both plans, one state's among them
+            every = np.arange(K, dtype=np.int32)
+            g.src = np.concatenate([g.src, every, np.full(K, 9, np.int32), every, np.full(K, 40, np.int32)])
+            g.dst = np.concatenate([g.dst, np.full(K, 9, np.int32), every, np.full(K, 77, np.int32), every])
+            g.logw = np.concatenate([g.logw, (-rng.exponential(size=4 * K)).astype(np.float32)])
+        if "parallel" in kind:
+            n = g.src.size // 5
+            g.src, g.dst = np.concatenate([g.src, g.src[:n]]), np.concatenate([g.dst, g.dst[:n]])
+            g.logw = np.concatenate([g.logw, (-rng.exponential(size=n)).astype(np.float32)])
+    emis = (rng.standard_normal((lengths.size, 34, D)) * 2).astype(np.float32)
+    for b, T in enumerate(lengths):
+        emis[b, T:] = np.nan
+    emis[3, 1, :] = -np.inf       # no path through frame 1
+    score, path = check(fb, g, D, emis, lengths, kind, sel=np.flatnonzero(lengths), state="wide" if "double" in kind else "auto")
+    assert np.isneginf(score[4]) and np.all(path[4] == -1)
