@@ -50,9 +50,19 @@ bool merge_parallel(int32_t K, const std::vector<int64_t> &ptr, const std::vecto
     mptr.assign((size_t)K + 1, 0);
     mcol.clear();
     mw.clear();
+    mcol.reserve(col.size());
+    mw.reserve(col.size());
     bool any = false;
     std::vector<std::pair<int32_t, float>> row;
     for (int32_t r = 0; r < K; ++r) {
+        bool ascending = true;   // every column once, in order: nothing to sort or combine
+        for (int64_t e = ptr[r] + 1; e < ptr[r + 1] && ascending; ++e) ascending = col[(size_t)e - 1] < col[(size_t)e];
+        if (ascending) {
+            mcol.insert(mcol.end(), col.begin() + ptr[r], col.begin() + ptr[r + 1]);
+            mw.insert(mw.end(), w.begin() + ptr[r], w.begin() + ptr[r + 1]);
+            mptr[(size_t)r + 1] = (int64_t)mcol.size();
+            continue;
+        }
         row.clear();
         for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) row.emplace_back(col[(size_t)e], w[(size_t)e]);
         std::stable_sort(row.begin(), row.end(), [](const std::pair<int32_t, float> &a, const std::pair<int32_t, float> &b) {
@@ -80,43 +90,85 @@ bool merge_parallel(int32_t K, const std::vector<int64_t> &ptr, const std::vecto
     return any;
 }
 
-template <class T>
-int upload(fb_graph *g, const std::vector<T> &h, const T **dev)
+// What a graph keeps on the device goes there as one allocation and one copy: every array takes its place in `bytes`
+// (256-byte steps), and finish() gives the pointers their values.  A copy of its own per array cost a packed graph 25
+// allocations and 25 synchronous copies of some 15 us each: creating and destroying 64 chains of 45 to 135 states took
+// 790 us, and takes 340 us so.
+struct Arena {
+    std::vector<unsigned char> bytes;
+    std::vector<std::pair<void *, size_t>> at;   // where a pointer is kept, and the offset it gets
+
+    template <class T>
+    void put(const std::vector<T> &h, const T **dev)
+    {
+        *dev = nullptr;
+        if (h.empty()) return;
+        const size_t off = (bytes.size() + 255) & ~(size_t)255;
+        bytes.resize(off + h.size() * sizeof(T));
+        std::memcpy(bytes.data() + off, h.data(), h.size() * sizeof(T));
+        at.emplace_back((void *)dev, off);
+    }
+
+    int finish(fb_graph *g)
+    {
+        if (bytes.empty()) return FB_OK;
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, bytes.size());
+        if (e != hipSuccess)
+            return fail(e == hipErrorOutOfMemory ? FB_ENOMEM : FB_EHIP, std::string("hipMalloc: ") + hipGetErrorString(e));
+        g->allocs.push_back(p);
+        e = hipMemcpy(p, bytes.data(), bytes.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return fail(FB_EHIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
+        for (const auto &a : at) {
+            const void *v = (const char *)p + a.second;
+            std::memcpy(a.first, &v, sizeof v);
+        }
+        return FB_OK;
+    }
+};
+
+void put_pdf(Arena &A, const PdfHost &h, PdfDev &d)
 {
-    *dev = nullptr;
-    if (h.empty()) return FB_OK;
-    void *p = nullptr;
-    hipError_t e = hipMalloc(&p, h.size() * sizeof(T));
-    if (e != hipSuccess)
-        return fail(e == hipErrorOutOfMemory ? FB_ENOMEM : FB_EHIP, std::string("hipMalloc: ") + hipGetErrorString(e));
-    g->allocs.push_back(p);
-    e = hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return fail(FB_EHIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
-    *dev = (const T *)p;
-    return FB_OK;
+    A.put(h.sub, &d.sub);
+    A.put(h.row_pdf, &d.row_pdf);
+    A.put(h.row_ptr, &d.row_ptr);
+    A.put(h.pos, &d.pos);
+    A.put(h.states, &d.states);
 }
 
-int upload_pdf(fb_graph *g, const PdfHost &h, PdfDev &d)
+// arcs: the list to put in place of h.arcs (same length), or nullptr
+void put_stream(Arena &A, const StreamHost &h, StreamDev &d, const std::vector<Arc> *arcs = nullptr)
 {
-    int rc;
-    if ((rc = upload(g, h.sub, &d.sub))) return rc;
-    if ((rc = upload(g, h.row_pdf, &d.row_pdf))) return rc;
-    if ((rc = upload(g, h.row_ptr, &d.row_ptr))) return rc;
-    if ((rc = upload(g, h.pos, &d.pos))) return rc;
-    return upload(g, h.states, &d.states);
+    A.put(h.sub, &d.sub);
+    A.put(h.waves, &d.waves);
+    A.put(h.flagwords, &d.flagwords);
+    A.put(h.vix, &d.vix);
+    A.put(h.clones, &d.clones);
+    A.put(h.zero_rows, &d.zero_rows);
+    A.put(arcs ? *arcs : h.arcs, &d.arcs);
 }
 
-// arcs: the list to upload in place of h.arcs (same length), or nullptr
-int upload_stream(fb_graph *g, const StreamHost &h, StreamDev &d, const std::vector<Arc> *arcs = nullptr)
+void put_small(Arena &A, const SmallHost &h, SmallDev &d)
 {
-    int rc;
-    if ((rc = upload(g, h.sub, &d.sub))) return rc;
-    if ((rc = upload(g, h.waves, &d.waves))) return rc;
-    if ((rc = upload(g, h.flagwords, &d.flagwords))) return rc;
-    if ((rc = upload(g, h.vix, &d.vix))) return rc;
-    if ((rc = upload(g, h.clones, &d.clones))) return rc;
-    if ((rc = upload(g, h.zero_rows, &d.zero_rows))) return rc;
-    return upload(g, arcs ? *arcs : h.arcs, &d.arcs);
+    A.put(h.sub, &d.sub);
+    A.put(h.rows, &d.rows);
+    A.put(h.lg, &d.lg);
+    A.put(h.arcs, &d.arcs);
+}
+
+void put_pstream(Arena &A, const PStreamHost &h, PStreamDev &d)
+{
+    A.put(h.waves, &d.waves);
+    A.put(h.units, &d.units);
+    A.put(h.close_words, &d.close_words);
+    A.put(h.clones, &d.clones);
+    A.put(h.zero_rows, &d.zero_rows);
+    d.n_clones = (int32_t)h.clones.size();
+    d.n_zero = (int32_t)h.zero_rows.size();
+    for (const PWaveDesc &wd : h.waves) d.max_units = std::max(d.max_units, wd.n_units);
+    d.Ccap = h.Ccap;
+    d.bias = h.bias;
+    d.dim = h.dim;
 }
 
 }  // namespace
@@ -300,6 +352,12 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         int32_t longest = 0;   // most arcs of a row, parallel ones counted apart
         for (int32_t k = 0; k < K; ++k) longest = std::max(longest, std::max(L.in_ptr[k + 1] - L.in_ptr[k], L.out_ptr[k + 1] - L.out_ptr[k]));
         g->hs_fwd.tm = g->hs_bwd.tm = g->hs_trop.tm = g->hs_btrop.tm = longest <= 2 ? 2 : 4;
+        for (SmallHost *h : {&g->hs_fwd, &g->hs_bwd}) {   // (as much as graphs need whose rows take a lane each)
+            const size_t slices = g->small ? (size_t)K / kWave + (size_t)n_sub : 0;
+            h->lg.reserve(slices);
+            h->rows.reserve(slices * kWave);
+            h->arcs.reserve(slices * kWave * (size_t)h->tm);
+        }
         for (int32_t s = 0; s < n_sub && g->small; ++s) {
             const int32_t k0 = n_seq > 0 ? state_off[s] : 0, Ks = (n_seq > 0 ? state_off[s + 1] : K) - k0;
             for (int dir = 0; dir < 2 && g->small; ++dir) {
@@ -318,10 +376,23 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 if (!small_append(dir ? g->hs_btrop : g->hs_trop, k0, Ks, mptr.data(), mcol.data(), mw.data()))
                     rc = fail(FB_EHIP, "internal error: best-path plan of a small graph");
             }
+        // packed graphs: every sub-graph's states by (pdf, state), at the places of the sub-graph's states: the
+        // grouping of all states by pdf, dealt out to the sub-graphs in its order
+        std::vector<int32_t> by_pdf;
+        if (n_seq > 0) {
+            by_pdf.resize((size_t)K);
+            std::vector<int32_t> at(state_off, state_off + n_seq);
+            for (int32_t i = 0; i < K; ++i) {
+                const int32_t k = L.pdf_states[(size_t)i];
+                by_pdf[(size_t)at[(size_t)seq_of[(size_t)k]]++] = k;
+            }
+        }
         for (int32_t s = 0; s < n_sub; ++s) {
             const int32_t k0 = n_seq > 0 ? state_off[s] : 0, k1 = n_seq > 0 ? state_off[s + 1] : K, Ks = k1 - k0;
-            vid.resize((size_t)Ks);
-            for (int32_t k = 0; k < Ks; ++k) vid[k] = n_seq > 0 ? k : pdf[k0 + k];
+            if (!g->small) {
+                vid.resize((size_t)Ks);
+                for (int32_t k = 0; k < Ks; ++k) vid[k] = n_seq > 0 ? k : pdf[k0 + k];
+            }
             for (int dir = 0; dir < 2 && !g->small; ++dir) {
                 rows_of(s, dir);
                 const bool dup = merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
@@ -356,16 +427,16 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 for (int32_t i = Ks; i < ((Ks + 3) & ~3); ++i) PH.pos[(size_t)i] = (uint16_t)i;
                 ps.n_rows = D;
             } else {
-                std::vector<int32_t> order((size_t)Ks);
-                std::iota(order.begin(), order.end(), 0);
-                std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return pdf[k0 + a] < pdf[k0 + b]; });
-                for (size_t i = 0; i < order.size(); ++i) {
-                    if (i == 0 || pdf[k0 + order[i]] != pdf[k0 + order[i - 1]]) {
-                        PH.row_pdf.push_back((uint16_t)pdf[k0 + order[i]]);
+                int32_t last = -1;
+                for (int32_t i = 0; i < Ks; ++i) {
+                    const int32_t k = by_pdf[(size_t)(k0 + i)];
+                    if (pdf[k] != last) {
+                        last = pdf[k];
+                        PH.row_pdf.push_back((uint16_t)last);
                         PH.row_ptr.push_back((uint16_t)i);
                         ++ps.n_rows;
                     }
-                    PH.states.push_back((uint16_t)order[i]);
+                    PH.states.push_back((uint16_t)(k - k0));
                 }
                 PH.row_ptr.push_back((uint16_t)Ks);
             }
@@ -451,43 +522,26 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             if (n_seq != 0) side_stream_init();
             std::vector<float> i2((size_t)K), f2((size_t)K);
             for (int32_t k = 0; k < K; ++k) { i2[k] = to_log2(init[k]); f2[k] = to_log2(final_[k]); }
-            std::vector<int32_t> hp(pdf, pdf + K);
+            const std::vector<int32_t> hp(pdf, pdf + K);
             const int32_t *dp = nullptr; const float *di = nullptr, *df = nullptr;
-            if (!(rc = upload(g, hp, &dp)) && !(rc = upload(g, i2, &di)) && !(rc = upload(g, f2, &df)) &&
-                !(rc = upload_pdf(g, g->h_pdf, g->pdfs)) && !g->small &&
-                !(rc = upload_stream(g, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr)))
-                rc = upload_stream(g, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr);
-            if (rc == FB_OK && g->small) {
-                auto up = [&](const SmallHost &h, SmallDev &d) {
-                    int r;
-                    if ((r = upload(g, h.sub, &d.sub)) || (r = upload(g, h.rows, &d.rows)) || (r = upload(g, h.lg, &d.lg))) return r;
-                    return upload(g, h.arcs, &d.arcs);
-                };
-                if (!(rc = up(g->hs_fwd, g->sfwd)) && !(rc = up(g->hs_bwd, g->sbwd)) && g->own_trop &&
-                    !(rc = up(g->hs_trop, g->strop)))
-                    rc = up(g->hs_btrop, g->sbtrop);
-                if (!g->own_trop) { g->strop = g->sfwd; g->sbtrop = g->sbwd; }
-            } else if (rc == FB_OK) {
-                if (!g->own_trop) { g->trop = g->fwd; g->btrop = g->bwd; }
-                else if (!(rc = upload_stream(g, g->h_trop, g->trop))) rc = upload_stream(g, g->h_btrop, g->btrop);
+            Arena A;
+            A.put(hp, &dp);
+            A.put(i2, &di);
+            A.put(f2, &df);
+            put_pdf(A, g->h_pdf, g->pdfs);
+            if (g->small) {
+                put_small(A, g->hs_fwd, g->sfwd);
+                put_small(A, g->hs_bwd, g->sbwd);
+                if (g->own_trop) { put_small(A, g->hs_trop, g->strop); put_small(A, g->hs_btrop, g->sbtrop); }
+            } else {
+                put_stream(A, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr);
+                put_stream(A, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr);
+                if (g->own_trop) { put_stream(A, g->h_trop, g->trop); put_stream(A, g->h_btrop, g->btrop); }
+                if (g->linear_p) { put_pstream(A, g->hp_fwd, g->pfwd); put_pstream(A, g->hp_bwd, g->pbwd); }
             }
-            if (rc == FB_OK && g->linear_p) {
-                auto up = [&](const PStreamHost &h, PStreamDev &d) {
-                    int r;
-                    if ((r = upload(g, h.waves, &d.waves)) || (r = upload(g, h.units, &d.units)) ||
-                        (r = upload(g, h.close_words, &d.close_words)) || (r = upload(g, h.clones, &d.clones)) ||
-                        (r = upload(g, h.zero_rows, &d.zero_rows)))
-                        return r;
-                    d.n_clones = (int32_t)h.clones.size();
-                    d.n_zero = (int32_t)h.zero_rows.size();
-                    for (const PWaveDesc &wd : h.waves) d.max_units = std::max(d.max_units, wd.n_units);
-                    d.Ccap = h.Ccap;
-                    d.bias = h.bias;
-                    d.dim = h.dim;
-                    return (int)FB_OK;
-                };
-                if (!(rc = up(g->hp_fwd, g->pfwd))) rc = up(g->hp_bwd, g->pbwd);
-            }
+            rc = A.finish(g);
+            if (!g->own_trop && g->small) { g->strop = g->sfwd; g->sbtrop = g->sbwd; }
+            else if (!g->own_trop) { g->trop = g->fwd; g->btrop = g->bwd; }
             g->d_pdf = const_cast<int32_t *>(dp); g->d_init2 = const_cast<float *>(di); g->d_final2 = const_cast<float *>(df);
             if (rc == FB_OK && n_seq == 0) rc = leaky_prepare(g, init, final_);
         }

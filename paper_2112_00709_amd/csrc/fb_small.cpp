@@ -22,36 +22,44 @@ bool small_append(SmallHost &S, int32_t k0, int32_t K, const int64_t *ptr, const
 {
     if (K > kSmallStates) return false;
     const int32_t tm = S.tm;
-    std::vector<int32_t> by_lg[7];
+    // rows by the lanes they take, widest first, in ascending order otherwise (a counting sort)
+    std::vector<int32_t> order((size_t)K);
+    std::vector<int8_t> lg_of((size_t)K);
+    int32_t at_lg[8] = {0};
     for (int32_t r = 0; r < K; ++r) {
         const int64_t n = ptr[r + 1] - ptr[r];
         int lg = 0;
         while (lg <= 6 && n > ((int64_t)tm << lg)) ++lg;
         if (lg > 6) return false;
-        by_lg[lg].push_back(r);
+        lg_of[(size_t)r] = (int8_t)lg;
+        ++at_lg[6 - lg + 1];
     }
+    for (int i = 1; i < 8; ++i) at_lg[i] += at_lg[i - 1];
+    for (int32_t r = 0; r < K; ++r) order[(size_t)at_lg[6 - lg_of[(size_t)r]]++] = r;
     SmallSub sd{};
     sd.k0 = k0;
     sd.K = K;
     sd.slice0 = (int32_t)S.lg.size();
     int at = kWave, lg_slice = 0;   // lanes used of the slice being filled
-    for (int lg = 6; lg >= 0; --lg)
-        for (const int32_t r : by_lg[lg]) {
-            if (at >= kWave) {   // (a row that needs fewer lanes than its slice gives takes them all the same)
-                lg_slice = lg;
-                S.lg.push_back(lg);
-                S.rows.resize(S.rows.size() + kWave, kSmallNoRow);
-                S.arcs.resize(S.arcs.size() + (size_t)tm * kWave, Arc{0, -INFINITY});
-                at = 0;
-            }
-            const size_t slice = S.lg.size() - 1;
-            S.rows[slice * kWave + (size_t)at] = (uint32_t)r;
-            for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
-                const int64_t i = e - ptr[r];
-                S.arcs[(slice * (size_t)tm + (size_t)(i % tm)) * kWave + (size_t)at + (size_t)(i / tm)] = Arc{col[e] * 8, w[e]};
-            }
-            at += 1 << lg_slice;
+    for (const int32_t r : order) {
+        const int lg = lg_of[(size_t)r];
+        if (at >= kWave) {   // (a row that needs fewer lanes than its slice gives takes them all the same)
+            lg_slice = lg;
+            S.lg.push_back(lg);
+            S.rows.resize(S.rows.size() + kWave, kSmallNoRow);
+            S.arcs.resize(S.arcs.size() + (size_t)tm * kWave, Arc{0, -INFINITY});
+            at = 0;
         }
+        const size_t slice = S.lg.size() - 1;
+        S.rows[slice * kWave + (size_t)at] = (uint32_t)r;
+        const int64_t n = ptr[r + 1] - ptr[r];
+        Arc *a = S.arcs.data() + slice * (size_t)tm * kWave + (size_t)at;
+        for (int64_t i = 0; i < n; ++i) {
+            const int64_t e = ptr[r] + i;
+            a[(size_t)(i % tm) * kWave + (size_t)(i / tm)] = Arc{col[e] * 8, w[e]};
+        }
+        at += 1 << lg_slice;
+    }
     sd.n_slice = (int32_t)S.lg.size() - sd.slice0;
     if (sd.n_slice > kSmallMaxSlices) return false;
     S.max_slices = std::max(S.max_slices, sd.n_slice);
