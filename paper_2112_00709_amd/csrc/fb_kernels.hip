@@ -2045,13 +2045,18 @@ __global__ __launch_bounds__(256) void fb_loss_kernel(const double *zn, const do
 // A path is a chain of dependent reads (the back-pointer of a frame names the row entry to read at the next one), each
 // a trip to HBM if taken one by one; so the workgroup copies the sequence's back-pointer rows of several frames at a
 // time into LDS (whole rows: which entry is needed is only known once the chain gets there), the next block travelling
-// while one thread walks the frames of this one there.  Bound: reading the rows once (466 MB for 128 sequences of at
+// while one thread walks the frames of this one there.  That thread's wave asks for nothing and stores nothing: a wait
+// for an LDS read is also one for every load and store its wave has on the way (the copies write LDS), and a store per
+// frame made a step of the walk 0.3 us.  Whole calls of fb_viterbi, before and after: 32 label-sequence graphs over 209
+// frames 70.7 -> 53.4 us; 6000 states, 128 sequences of at most 500 frames 1670 -> 1644 us (with 3 instead of 7 copying
+// waves 1681).  Bound: reading the rows once (466 MB for 128 sequences of at
 // most 500 frames over 6000 states: 250 us as one chain per sequence, on half as many compute units; 161 us as two).
 // Indices are those of the state buffers (a state, or Kcap + slot for a clone of a very long row, which each direction
 // has for itself); a clone is reported as the state it belongs to.
-constexpr int kBtThreads = 256, kBtFrames = 64;
+constexpr int kBtThreads = 512, kBtFrames = 64;
 constexpr size_t kBtSmallBytes = 64 * 1024;   // rows in LDS beyond this only as far as kBtLargeFrames
 constexpr int kBtLargeFrames = 8;
+static_assert(kBtFrames <= kWave, "a lane hands over a frame");
 
 __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const BacktraceParams P)
 {
@@ -2088,25 +2093,31 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     const int ns = (int)(ps1 - ps0), nc = P.Ccap > 0 ? (int)(pc1 - pc0) : 0;   // pieces
     const int W = (ns + nc) * 8;
     const int at_states = (int)(col_states - ps0 * 8), at_clones = ns * 8 + (int)(col_clones - pc0 * 8);
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the half's rows in the order it takes them: m, m - 1, .. 1 or m + 1, .. T - 1; in blocks of F, in two buffers: the
     // next block is on its way from global memory while thread 0 walks this one
     const int n_rows = half ? T - 1 - m : m;
     auto row_of = [&](int i) { return half ? m + 1 + i : m - i; };
-    auto issue = [&](int i0, int buf) {   // rows row_of(i0), ..., straight into LDS, 16 bytes per lane, nothing waits in between
+    // rows row_of(i0), ..., straight into LDS, 16 bytes per lane, nothing waits in between; by all waves but the first, a
+    // wave's worth of pieces of a row each in turn
+    auto issue = [&](int i0, int buf) {
+        if (wave == 0) return;
         const int cnt = min(F, n_rows - i0);
-        for (int f = 0; f < cnt; ++f) {
-            const uint4 *row = (const uint4 *)(P.bp + (P.shared ? ((size_t)b * P.N + row_of(i0 + f)) : (size_t)row_of(i0 + f)) * P.bp_ld);
-            uint4 *dst = (uint4 *)(bt_rows + ((size_t)buf * F + f) * W);
-            for (int p = wave * kWave; p < ns; p += kBtThreads)
-                if (p + lane < ns)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + ps0 + p + lane),
+        auto span = [&](int64_t piece0, int n, int to) {
+            const int nr = (n + kWave - 1) & ~(kWave - 1);
+            if (nr == 0) return;
+            for (int f = 0, p = (wave - 1) * kWave; ; p += kBtThreads - kWave) {
+                while (p >= nr) { p -= nr; ++f; }
+                if (f >= cnt) break;
+                const uint4 *row = (const uint4 *)(P.bp + (P.shared ? ((size_t)b * P.N + row_of(i0 + f)) : (size_t)row_of(i0 + f)) * P.bp_ld);
+                uint4 *dst = (uint4 *)(bt_rows + ((size_t)buf * F + f) * W) + to;
+                if (p + lane < n)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + piece0 + p + lane),
                                                      (__attribute__((address_space(3))) void *)(dst + p), 16, 0, 0);
-            for (int p = wave * kWave; p < nc; p += kBtThreads)
-                if (p + lane < nc)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + pc0 + p + lane),
-                                                     (__attribute__((address_space(3))) void *)(dst + ns + p), 16, 0, 0);
-        }
+            }
+        };
+        span(ps0, ns, 0);
+        span(pc0, nc, ns);
     };
     if (n_rows > 0) issue(0, 0);
 
@@ -2156,6 +2167,7 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     }
     double *red_v = (double *)(bt_rows + (size_t)2 * F * W);   // [waves] the waves' best, [waves] their places
     uint32_t *red_a = (uint32_t *)(red_v + kBtThreads / kWave);
+    uint16_t *const walked = (uint16_t *)(red_a + kBtThreads / kWave);   // [2][kBtFrames] what thread 0 has found in a block
     if (lane == 0) { red_v[wave] = best; red_a[wave] = at; }
     __syncthreads();
     best = red_v[0]; at = red_a[0];
@@ -2183,18 +2195,27 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     };
     int s = half ? (int)(at & 0xffffu) : (int)(at >> 16);
     if (half == 0 && tid == 0) prow[m] = k0 + state_of(s);
+    // thread 0 keeps what it finds in LDS and a lane each of the second wave hands it over once the block is done
+    auto hand_over = [&](int i0, int buf) {
+        if (wave == 1 && lane < min(F, n_rows - i0))
+            prow[half ? row_of(i0 + lane) : row_of(i0 + lane) - 1] = k0 + state_of(walked[buf * kBtFrames + lane]);
+    };
     for (int i0 = 0, buf = 0; i0 < n_rows; i0 += F, buf ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();   // this block is in LDS; thread 0 has left the other buffer
+        if (i0 > 0) hand_over(i0 - F, buf ^ 1);
         if (i0 + F < n_rows) issue(i0 + F, buf ^ 1);
         if (tid == 0) {
             const int cnt = min(F, n_rows - i0);
-            for (int f = 0; f < cnt; ++f) {
-                s = bt_rows[((size_t)buf * F + f) * W + (s < P.Kcap ? at_states + s : at_clones + (s - P.Kcap))];
-                prow[half ? row_of(i0 + f) : row_of(i0 + f) - 1] = k0 + state_of(s);
+            const uint16_t *r = bt_rows + (size_t)buf * F * W;
+            for (int f = 0; f < cnt; ++f, r += W) {
+                s = r[s < P.Kcap ? at_states + s : at_clones + (s - P.Kcap)];
+                walked[buf * kBtFrames + f] = (uint16_t)s;
             }
         }
     }
+    __syncthreads();
+    if (n_rows > 0) hand_over((n_rows - 1) / F * F, (n_rows - 1) / F & 1);
 }
 
 
@@ -2321,7 +2342,7 @@ int launch_backtrace(const BacktraceParams &p, void *stream)
     BacktraceParams q = p;
     if ((p.bp_ld & 7) != 0 || ((uintptr_t)p.bp & 15) != 0) return fail(FB_EHIP, "internal error: back-pointer rows are not in 16-byte pieces");
     const size_t row_bytes = ((size_t)p.Kcap + (size_t)p.Ccap + 32) * sizeof(uint16_t);   // both spans rounded out to whole pieces
-    const size_t extra = kBtThreads / kWave * (sizeof(double) + sizeof(uint32_t));
+    const size_t extra = kBtThreads / kWave * (sizeof(double) + sizeof(uint32_t)) + 2 * kBtFrames * sizeof(uint16_t);
     auto fit = [&](size_t room, int most) { return (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)most, (room - extra) / (2 * row_bytes))); };   // two buffers
     // Short rows: as many as 64 KB hold, since a block costs a trip to memory whatever it holds; long ones: a block of
     // 8 frames keeps a compute unit's share of the memory rate busy, more only take LDS.

@@ -122,3 +122,15 @@ def test_viterbi_halves_meet(fb, kind):
     emis[3, 1, :] = -np.inf       # no path through frame 1
     score, path = check(fb, g, D, emis, lengths, kind, sel=np.flatnonzero(lengths), state="wide" if "double" in kind else "auto")
     assert np.isneginf(score[4]) and np.all(path[4] == -1)
+
+
+@pytest.mark.parametrize("K", [70, 1300])
+def test_viterbi_backtrace_block_edges(fb, K):
+    """Halves of whole blocks of back-pointer rows and one row more or fewer (64 rows a block in the small graph, 12 in
+    the large one)."""
+    rng = np.random.default_rng(K)
+    D, F = 11, 64 if K == 70 else 12
+    lengths = np.array([2 * r + d for r in (F, 2 * F) for d in (-1, 0, 1, 2, 3)], np.int32)
+    g = wl.random_graph(rng, K, D)
+    emis = (rng.standard_normal((lengths.size, int(lengths.max()), D)) * 2).astype(np.float32)
+    check(fb, g, D, emis, lengths, f"block edges K={K}")
