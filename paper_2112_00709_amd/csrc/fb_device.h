@@ -226,6 +226,10 @@ __device__ __forceinline__ void resolve_sequence(const RecParams &P, double *lds
 __device__ __forceinline__ int path_middle(int T, int n_dir) { return n_dir == 2 ? (T - 1) >> 1 : T - 1; }
 
 // Progress counter of a launch: everything this workgroup writes is on its way; make it visible device-wide, then count.
+// Every wave waits for its own stores first: the barrier alone waits for no global store on this chip, and the fence of
+// the thread that counts covers the stores its own wave has made and what has reached the L2 by then - a row that another
+// wave still has under way would get there behind the write-back, and a kernel released by the counter on another XCD
+// could read what was in memory before.  (One wait per workgroup and launch.)
 __device__ __forceinline__ void count_done(const RecParams &P)
 {
     if (P.done) {
@@ -233,6 +237,7 @@ __device__ __forceinline__ void count_done(const RecParams &P)
         int slot = 0;
 #pragma unroll
         for (int i = 0; i < kDoneCuts; ++i) slot += rank >= P.done_from[i] ? 1 : 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0 && slot > 0) {
             __threadfence();
