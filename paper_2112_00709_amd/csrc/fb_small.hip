@@ -15,9 +15,11 @@
 // The chain of a step is then: LDS read, add the weight, maximum / difference, one exponential, one logarithm, add
 // the emission, LDS write (and the barrier).
 //
-// Zero-bar is carried as a number that is never left: the vector is held at or above kZero = -1e30 and weights of
-// zero-bar are kZero too, so a sum of two is finite and no step meets inf - inf; what lies below kZeroOut leaves the
-// kernel as -inf.
+// Zero-bar is carried as a number: start weights, arc weights and emissions of zero-bar (or below) are kZero = -1e30, so
+// every sum is finite and no step meets inf - inf (a state that stays at zero-bar falls by that much a step, which a
+// double takes); what lies below kZeroOut leaves the kernel as -inf.  Nothing is clamped behind the emissions: a NaN among
+// them (not a legal input, but what a diverged network hands over) is in log Z and the rows as it is in the general
+// kernel's.  The best path never takes a state whose score is NaN, there as here, and clamps its sums.
 //
 // Measured per direction, against the general kernel with 4 waves (fb_recursion_kernel<4, double>): 32 chains of 30-120
 // states over at most 144 frames 124 -> 29 us (of which the computing wave 24); a 16-state graph over 50 frames 55 -> 12
@@ -40,6 +42,11 @@ namespace fb {
 namespace {
 
 constexpr double kZero = -1.0e30, kZeroOut = -0.5e30;
+
+__device__ __forceinline__ bool is_zero(double v) { return v <= kZeroOut; }   // (false for a NaN)
+
+// an emission in log2 units, zero-bar as kZero; a NaN stays one
+__device__ __forceinline__ double emitted(float e) { return (double)(e < (float)kZero ? (float)kZero : e) * kLog2e; }
 
 template <int NC, int R>
 struct SmallShape {
@@ -152,7 +159,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                 const bool real = tg[j] != (uint32_t)S::KS * 8u;
                 const double s = real ? (double)D.bound[k0 + (int)(tg[j] >> 3)] : kZero;
                 // (a best path's backward recursion ends before the emission of its last frame, which may be this one)
-                *(double *)(lds + tg[j]) = dmax(s + (TROP && bwd && Ts == 1 ? 0.0 : (double)e0[j] * kLog2e), kZero);
+                *(double *)(lds + tg[j]) = TROP ? dmax(s + (bwd && Ts == 1 ? 0.0 : (double)e0[j] * kLog2e), kZero) : dmax(s, kZero) + emitted(e0[j]);
                 if (pre) *(double *)((char *)pr + tg[j]) = s;
             }
         }
@@ -169,7 +176,8 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                 for (int t = 0; t < TM; ++t) g[j][t] = *(const double *)(lds + so[j][t] + cur);
             double ed[R];
 #pragma unroll
-            for (int j = 0; j < R; ++j) ed[j] = TROP && kBwd && i0 + a == Ts - 1 ? 0.0 : (double)e[j][a] * kLog2e;   // (see above)
+            for (int j = 0; j < R; ++j)                     // (best path: see above)
+                ed[j] = !TROP ? emitted(e[j][a]) : kBwd && i0 + a == Ts - 1 ? 0.0 : (double)e[j][a] * kLog2e;
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 double m;
@@ -203,7 +211,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                         if (lg[j]) group_total(m, s, lg[j], lane);
                         l = flog2(s);
                     }
-                    *(double *)(lds + tg[j] + nxt) = dmax((m + ed[j]) + (double)l, kZero);
+                    *(double *)(lds + tg[j] + nxt) = (m + ed[j]) + (double)l;
                     if constexpr (kBwd) *(double *)((char *)pr + tg[j] + nxt) = m + (double)l;
                 }
             }
@@ -269,14 +277,14 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                     float *orow = out_f + (size_t)f * out_ld;
 #pragma unroll
                     for (int u = u0; u < u1; ++u)
-                        if (u * kWave < K) orow[at(u)] = r.v[u] > kZeroOut ? (float)(r.v[u] - r.c) * D.out_scale : -INFINITY;
+                        if (u * kWave < K) orow[at(u)] = is_zero(r.v[u]) ? -INFINITY : (float)(r.v[u] - r.c) * D.out_scale;
                 }
                 if (off_seq && u0 == 0 && lane == 0) off_seq[f] = r.c * scale;
             } else if (out_t) {
                 double *orow = out_t + (size_t)f * out_ld;
 #pragma unroll
                 for (int u = u0; u < u1; ++u)
-                    if (u * kWave < K) orow[at(u)] = r.v[u] > kZeroOut ? r.v[u] : -INFINITY;
+                    if (u * kWave < K) orow[at(u)] = is_zero(r.v[u]) ? -INFINITY : r.v[u];
             }
             if (D.cum && u0 == 0 && lane == 0) D.cum[(size_t)b * P.N + f] = 0.0f;   // (carrier rows are not shifted)
             if constexpr (TROP) {
@@ -337,7 +345,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
             // ---- the last vector, for the kernel that joins the two halves
             double *mrow = (double *)D.mid + (size_t)b * D.mid_ld;
             if (wave < NC)
-                for (int k = wave * kWave + lane; k < K; k += NC * kWave) mrow[k] = xl[k] > kZeroOut ? xl[k] : -INFINITY;
+                for (int k = wave * kWave + lane; k < K; k += NC * kWave) mrow[k] = is_zero(xl[k]) ? -INFINITY : xl[k];
             if (threadIdx.x == 0) D.mid_off[b] = 0.0;
         } else {
             // ---- log Z from the last vector and the end weights, by the computing waves
@@ -354,7 +362,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
                 double m = fin[0];
                 float s = (float)fin[NC];
                 for (int v = 1; v < NC; ++v) lse_merge(m, s, fin[v], (float)fin[NC + v]);
-                if (D.logz) D.logz[b] = m > kZeroOut ? (m + (double)flog2(s)) * kLn2 : -INFINITY;
+                if (D.logz) D.logz[b] = is_zero(m) && s == s ? -INFINITY : (m + (double)flog2(s)) * kLn2;   // (a NaN is in s)
             }
         }
     } else if (threadIdx.x == 0 && D.logz) {

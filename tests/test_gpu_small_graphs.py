@@ -134,3 +134,37 @@ def test_objective_and_gradient_with_small_denominators(K, D, phones):
     assert np.abs(grad[live] - ref.grad).max() <= 1e-5
     assert np.all(grad[3] == 0) and np.isneginf(zn[3]) and np.isneginf(zd[3])
     hd.destroy(); hn.destroy()
+
+
+@pytest.mark.parametrize("K,D", [(3, 2), (40, 9), (300, 20), (1000, 40)])
+def test_nan_emissions_show(K, D):
+    """NaN is not a legal emission, but a diverged network's must not come back as a finite loss and gradient: it is in
+    both log Z, the state posteriors, the loss and the gradient of its sequence, and nowhere else."""
+    import torch
+    rng = np.random.default_rng(K)
+    den = _graph(rng, K, 2, 0, D)
+    den.init[:] = 0.0                                        # (every state is alive at every frame)
+    num = wl.chain_graphs(rng, np.array([2, 3, 2]), D)
+    lengths = np.array([20, 21, 19], dtype=np.int32)
+    emis = (rng.standard_normal((3, 21, D)) * 2).astype(np.float32)
+    hd, hn = fb.graph_from(den, D), fb.graph_from(num, D)
+    l = torch.from_numpy(lengths).cuda()
+    for frame, pdf in ((0, int(den.pdf[0])), (7, int(den.pdf[0])), (20, int(den.pdf[0])), (9, slice(None))):
+        e = emis.copy()
+        e[1, frame, pdf] = np.nan
+        e = torch.from_numpy(e).cuda()
+        a, _, za = fb.fb_alpha(hd, e, l)
+        b, _, zb = fb.fb_beta(hd, e, l)
+        gam, _ = fb.fb_posteriors(hd, a, b, l, 3, 21)
+        loss, zn, zd, grad = fb.lfmmi_loss_grad(hd, hn, e, l)
+        torch.cuda.synchronize()
+        for z in (za, zb, zd):
+            assert np.array_equal(np.isnan(z.cpu().numpy()), [False, True, False])
+        assert np.isnan(loss.cpu().numpy()).all()
+        if not isinstance(pdf, slice):                      # (a frame without a finite sum has posteriors 0, as in the general kernel)
+            assert np.isnan(gam.cpu().numpy()[1]).any() and np.isnan(grad.cpu().numpy()[1]).any()
+        else:
+            assert np.isnan(zn.cpu().numpy()[1])
+        for i in (0, 2):
+            assert np.isfinite(gam.cpu().numpy()[i]).all() and np.isfinite(grad.cpu().numpy()[i]).all()
+    hd.destroy(); hn.destroy()
