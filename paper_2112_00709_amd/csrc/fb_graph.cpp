@@ -541,6 +541,19 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             }
             rc = A.finish(g);
             if (!g->own_trop && g->small) { g->strop = g->sfwd; g->sbtrop = g->sbwd; }
+            if (g->small) {   // (in the sums what is below -1e30, in log2 units, is zero-bar and not a large weight)
+                bool sums = false, paths = false;
+                auto look = [&](const float *x, int64_t n) {
+                    for (int64_t i = 0; i < n; ++i) {
+                        if (!(std::fabs(x[i]) > 65536.0f) || !std::isfinite(to_log2(x[i]))) continue;
+                        paths = true;
+                        if (to_log2(x[i]) > -1.0e30f) sums = true;
+                    }
+                };
+                look(logw, E); look(init, K); look(final_, K);
+                g->sfwd.large = g->sbwd.large = sums ? ~0u : 0u;
+                g->strop.large = g->sbtrop.large = paths ? ~0u : 0u;
+            }
             else if (!g->own_trop) { g->trop = g->fwd; g->btrop = g->bwd; }
             g->d_pdf = const_cast<int32_t *>(dp); g->d_init2 = const_cast<float *>(di); g->d_final2 = const_cast<float *>(df);
             if (rc == FB_OK && n_seq == 0) rc = leaky_prepare(g, init, final_);

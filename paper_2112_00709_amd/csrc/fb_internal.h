@@ -289,6 +289,7 @@ struct SmallDev {
     const uint32_t *rows = nullptr;
     const int32_t *lg = nullptr;
     const Arc *arcs = nullptr;
+    uint32_t large = 0;        // ~0 if some weight, start or end weight is finite and larger than 65536 in size: runs take the plain form
 };
 
 // rows [0, K) of a CSR-like matrix, weights in log2 units; appends one sub-graph's plan.  False if it does not fit the

@@ -168,3 +168,108 @@ def test_nan_emissions_show(K, D):
         for i in (0, 2):
             assert np.isfinite(gam.cpu().numpy()[i]).all() and np.isfinite(grad.cpu().numpy()[i]).all()
     hd.destroy(); hn.destroy()
+
+
+def _dense_ring(rng, K, arcs, D, weight=0.0):
+    """Every state alive at every frame: `arcs` arcs out of and into every state, the self-loop among them; the end
+    weights spread, the start weights all alike."""
+    src = np.tile(np.arange(K), arcs)
+    dst = (src + np.repeat(np.arange(arcs), K)) % K
+    logw = (weight - rng.exponential(size=src.size)).astype(np.float32)
+    return wl.Graph(K, src.astype(np.int32), dst.astype(np.int32), logw, rng.integers(0, D, K).astype(np.int32),
+                    np.zeros(K, np.float32), (-rng.exponential(size=K)).astype(np.float32))
+
+
+@pytest.mark.parametrize("K,arcs", [(9, 2), (16, 4), (100, 2), (100, 9), (200, 2), (230, 6), (400, 3), (701, 2), (701, 5), (1000, 3)])
+def test_masked_frames(K, arcs):
+    """A frame whose emissions are all some large mask: the same posteriors on either side of it as those of the two
+    pieces by themselves (what joins the pieces is lost in a sum of that size in any arithmetic, but neither the frames
+    before nor the ones behind may lose their resolution), at the edges of the kernel's groups of frames."""
+    import torch
+    rng = np.random.default_rng(K + arcs)
+    D, T = 13, 53
+    g = _dense_ring(rng, K, arcs, D)
+    masked = np.array([0, 1, 4, 7, 8, 9, 15, 16, 17, 24, 26, 27, 33, 48, 49, 51, 52], dtype=np.int64)
+    B = masked.size
+    lengths = np.full(B, T, dtype=np.int32)
+    emis = (rng.standard_normal((B, T, D)) * 2).astype(np.float32)
+    rows = np.arange(B)
+    h = fb.graph_from(g, D)
+    l = torch.from_numpy(lengths).cuda()
+    before, behind = wl.Graph(**{**g.__dict__, "final": np.zeros(K, np.float32)}), wl.Graph(**{**g.__dict__, "init": np.zeros(K, np.float32)})
+    zero = emis.copy()
+    zero[rows, masked] = 0
+    pieces = []
+    for b, n in enumerate(masked):
+        a = oracle.forward_backward(before, np.ascontiguousarray(zero[b:b + 1, :n + 1]), np.array([n + 1], np.int32))
+        c = oracle.forward_backward(behind, np.ascontiguousarray(zero[b:b + 1, n:]), np.array([T - n], np.int32))
+        # the piece that the place where the two halves of a best path meet lies in
+        first = n > (T - 1) // 2
+        part = zero[b:b + 1, :n + 1] if first else zero[b:b + 1, n:]
+        best = oracle.viterbi(before if first else behind, np.ascontiguousarray(part), np.array([part.shape[1]], np.int32))
+        pieces.append((a, c, first, best.score[0]))
+    for mask in (np.float32(-1e20), np.float32(-1e25), np.finfo(np.float32).min):
+        e = emis.copy()
+        e[rows, masked] = mask
+        e = torch.from_numpy(e).cuda()
+        alpha, _, z = fb.fb_alpha(h, e, l)
+        beta, cb, zb = fb.fb_beta(h, e, l)
+        gam, _ = fb.fb_posteriors(h, alpha, beta, l, B, T)
+        score, path = fb.fb_viterbi(h, e, l)
+        torch.cuda.synchronize()
+        z, zb, gam, score, path = (t.cpu().numpy() for t in (z, zb, gam, score, path))
+        assert np.all(np.abs(score / float(mask) - 1) <= 1e-6)
+        for b, n in enumerate(masked):
+            a, c, first, best = pieces[b]
+            p = path[b, :n + 1] if first else path[b, n:]
+            part = zero[b, :n + 1] if first else zero[b, n:]
+            # the sums are double, every weight is rounded to a float in log2 units once (none is larger than 16)
+            assert abs(oracle.path_score(before if first else behind, part, p) - best) <= 2.0 ** -24 * 16 * (T + 1)
+            assert np.isfinite(oracle.path_score(g, zero[b], path[b]))
+            if mask > -1e30:                                # (below that a value counts as zero-bar in the sums)
+                assert abs(z[b] / float(mask) - 1) <= 1e-6 and abs(zb[b] / float(mask) - 1) <= 1e-6
+                assert np.abs(gam[b, :n] - a.gamma[0][:n]).max(initial=0.0) <= 1e-5
+                assert np.abs(gam[b, n:] - c.gamma[0]).max() <= 1e-5
+            else:
+                assert np.isneginf(z[b]) and np.isneginf(zb[b]) and np.all(gam[b] == 0)
+    h.destroy()
+
+
+@pytest.mark.parametrize("K,arcs", [(16, 4), (230, 6), (701, 2)])
+def test_large_weights(K, arcs):
+    """The same where the large numbers are weights: start and end weights all -1e20 (or the lowest float, best path only)
+    are a shift and nothing else, but for the emissions of the two frames that they are added to."""
+    import torch
+    rng = np.random.default_rng(K)
+    D, T, B = 13, 40, 3
+    g = _dense_ring(rng, K, arcs, D)
+    g.final[:] = 0
+    lengths = np.array([T, 17, 2], dtype=np.int32)
+    emis = (rng.standard_normal((B, T, D)) * 2).astype(np.float32)
+    emis[:, 0] = 0
+    emis[np.arange(B), lengths - 1] = 0
+    ref = oracle.forward_backward(g, emis, lengths)
+    best = oracle.viterbi(g, emis, lengths)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    for size in (np.float32(-1e20), np.float32(-2e38)):
+        ends = np.full(K, size, np.float32)
+        h = fb.graph_from(wl.Graph(**{**g.__dict__, "init": ends, "final": ends}), D)
+        alpha, _, z = fb.fb_alpha(h, e, l)
+        beta, _, zb = fb.fb_beta(h, e, l)
+        gam, _ = fb.fb_posteriors(h, alpha, beta, l, B, T)
+        score, path = fb.fb_viterbi(h, e, l)
+        torch.cuda.synchronize()
+        z, zb, gam, score, path = (t.cpu().numpy() for t in (z, zb, gam, score, path))
+        for b in range(B):
+            Tb = int(lengths[b])
+            if size > -1e30:
+                assert abs(z[b] / (2 * float(size)) - 1) <= 1e-6 and abs(zb[b] / (2 * float(size)) - 1) <= 1e-6
+                assert np.abs(gam[b, :Tb] - ref.gamma[b]).max() <= 1e-5
+            else:
+                assert np.isneginf(z[b]) and np.isneginf(zb[b]) and np.all(gam[b] == 0)
+            # (the two halves of a path meet in the middle: each is the best one from there, whatever the ends' size)
+            assert abs(score[b] / (2 * float(size)) - 1) <= 1e-6
+            assert np.all(path[b, :Tb] >= 0) and np.isfinite(oracle.path_score(g, emis[b], path[b, :Tb]))
+            if size > -1e30:
+                assert abs(oracle.path_score(g, emis[b], path[b, :Tb]) - best.score[b]) <= 2.0 ** -24 * 16 * (T + 1)
+        h.destroy()
