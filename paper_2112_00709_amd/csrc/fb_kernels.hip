@@ -600,12 +600,15 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
         const int last = (Ts - 1) & 1;
         const T *xl = xb + last * Xs;
         if (io_wave) write_row(frame(Ts - 1), keep_pre ? bh + last * Xs : xl);
-        if (TROP) {   // the last vector and its shift, for the kernel that joins the two halves
+        if (TROP) {   // the last vector and its shift, for the kernel that joins the two halves: without its largest entry, or
+                      // the other half's entries would be lost in it where this frame's emissions are some large mask
             if (io_wave && Ts >= 2) write_bp(Ts - 1, bpb + last * Xs);
+            const T M = get_max(Ts - 1);
+            const T c = (M == kNegInf) ? (T)0 : M;
             T *mrow = (T *)R.mid + (size_t)b * R.mid_ld;
-            for (int k = tid; k < K; k += NT) mrow[k] = xl[k];
-            for (int k = tid; k < nC; k += NT) mrow[P.Kcap + k] = xl[P.Kcap + k];
-            if (io_wave && lane == 0) R.mid_off[b] = csum;
+            for (int k = tid; k < K; k += NT) mrow[k] = xl[k] - c;
+            for (int k = tid; k < nC; k += NT) mrow[P.Kcap + k] = xl[P.Kcap + k] - c;
+            if (io_wave && lane == 0) R.mid_off[b] = csum + (double)c;
         } else if (R.logz) {
             T m = (T)kNegBig;
             float s = 0.0f;

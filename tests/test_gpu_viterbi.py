@@ -134,3 +134,32 @@ def test_viterbi_backtrace_block_edges(fb, K):
     g = wl.random_graph(rng, K, D)
     emis = (rng.standard_normal((lengths.size, int(lengths.max()), D)) * 2).astype(np.float32)
     check(fb, g, D, emis, lengths, f"block edges K={K}")
+
+
+@pytest.mark.parametrize("state", ["auto", "wide"])
+def test_viterbi_masked_meeting_frame(fb, state):
+    """The frame where the halves meet masked with -1e20 in every pdf: what is behind it is the best path of that piece
+    (a half's vector of that size must not swallow the other half's entries)."""
+    import torch
+    rng = np.random.default_rng(2)
+    D, lengths = 13, np.array([1, 2, 3, 8, 9, 30, 31], np.int32)
+    g = wl.random_graph(rng, 1300, D)
+    B = lengths.size
+    emis = (rng.standard_normal((B, 31, D)) * 2).astype(np.float32)
+    meet = (lengths - 1) // 2
+    plain = emis.copy()
+    plain[np.arange(B), meet] = 0
+    emis[np.arange(B), meet] = -1e20
+    h = fb.graph_from(g, D, state=state)
+    score, path = fb.fb_viterbi(h, torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda())
+    torch.cuda.synchronize()
+    score, path = score.cpu().numpy(), path.cpu().numpy()
+    rest = wl.Graph(**{**g.__dict__, "init": np.zeros(g.K, np.float32)})
+    for b in range(B):
+        piece = np.ascontiguousarray(plain[b:b + 1, meet[b]:lengths[b]])
+        best = oracle.viterbi(rest, piece, np.array([piece.shape[1]], np.int32)).score[0]
+        got = oracle.path_score(rest, piece[0], path[b, meet[b]:lengths[b]])
+        # a float carrier: a step rounds at half a unit of its entries, which are below 64 in size
+        assert abs(got - best) <= (2.0 ** -24 * 16 if state == "wide" else 2.0 ** -24 * 64) * 2 * (piece.shape[1] + 1)
+        assert abs(score[b] / -1e20 - 1) <= 1e-6 and np.isfinite(oracle.path_score(g, plain[b], path[b, :lengths[b]]))
+    h.destroy()
