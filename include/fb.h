@@ -62,14 +62,14 @@
  * precision keeps its resolution on long sequences:
  *   true alpha_n[k] = alpha[..n..][k] + alpha_cum[b][n]
  *   true beta_n[k]  = beta[..n..][k]  + beta_cum[b][n]
- * (the shift of frame n, accumulated in double over the frames the recursion has passed: from
- * the first frame for alpha, from the last for beta).  The shifts cancel in Eq. 15, so
- * posteriors do not depend on them.  Rows of padded frames hold -inf (alpha, beta) or 0
+ * (the shift of frame n, a double: accumulated over the frames the recursion has passed - from
+ * the first for alpha, from the last for beta - or the true row's own largest entry; which,
+ * depends on the graph).  The shifts cancel in Eq. 15, so posteriors do not depend on them.  Rows of padded frames hold -inf (alpha, beta) or 0
  * (shifts, posteriors, grad).
  *
  * Precision.  Exponentials and logarithms are single precision everywhere.
- * The normalised state vector of the recursions is carried either in single or
- * in double precision.  A single-precision log value x carries a rounding error
+ * The state vector of the recursions is carried either in single precision,
+ * normalised, or in double precision, normalised where its size asks for it.  A single-precision log value x carries a rounding error
  * of about 3e-8 * |x| per time step, so single carriers are accurate when the
  * states that matter for the posterior lie within a few tens of the frame's
  * best state (densely connected graphs such as the denominator); in long
@@ -323,7 +323,8 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N);
  * input (results do not depend on timing) but otherwise unspecified.
  *   score  out, device double [B];  path  out, device int32 [B][N]
  *   ws     device scratch of at least fb_viterbi_workspace_bytes(), 256-byte aligned
- *          (the back-pointers: 2 bytes per state and frame, a little more for graphs with very long rows)
+ *          (the back-pointers: 2 bytes per state and frame, a little more for graphs with very long rows; and per
+ *          sequence two vectors, of 4 or 8 bytes per state of the largest (sub-)graph, and two numbers)
  * Errors as fb_alpha.
  */
 int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D,
@@ -345,7 +346,9 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
  *   leak      in [0, 1]
  *   logz      out, device double [B] (-inf for a sequence without a path, whose posteriors are 0)
  *   pdf_post  out, device float [B][N][D], 0 on padded frames
- *   ws        device scratch of at least fb_leaky_workspace_bytes() (the vectors of one or both sweeps: 4 bytes per state and frame each)
+ *   ws        device scratch of fb_leaky_workspace_bytes() (the vectors of one or both sweeps: 4 bytes per state and frame
+ *             each).  With less, but room for one sweep's (4 B N K bytes, rounded up to a multiple of 256), the call takes a
+ *             plain kernel, which is several times slower on large graphs
  * FB_EINVAL: NULL arguments, a packed or host-only graph, sizes <= 0, D != the graph's D, leak outside [0, 1],
  * workspace missing or too small.  FB_EUNSUPPORTED: more than 8192 states, or four state vectors and an emission row
  * exceed the 160 KB of on-chip memory of a compute unit (16 K + 4 D bytes).

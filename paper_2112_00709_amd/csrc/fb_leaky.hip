@@ -529,10 +529,16 @@ void leaky_release(fb_graph *g)
 
 extern "C" {
 
+// the plain kernel's rows
+static size_t leaky_plain_bytes(const fb_graph *g, int32_t B, int32_t N)
+{
+    return (((size_t)B * (size_t)N * (size_t)g->K * sizeof(float)) + 255) & ~(size_t)255;
+}
+
 size_t fb_leaky_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 {
     if (!g || g->n_seq != 0 || B <= 0 || N <= 0) return 0;
-    const size_t plain = (((size_t)B * (size_t)N * (size_t)g->K * sizeof(float)) + 255) & ~(size_t)255;
+    const size_t plain = leaky_plain_bytes(g, B, N);
     const fb::LeakyFast f = fb::leaky_fast(g, B, N);
     return f.ok ? std::max(plain, f.bytes) : plain;
 }
@@ -548,7 +554,7 @@ int fb_leaky_posteriors(const fb_graph *g, const float *emis, const int32_t *len
     if (B <= 0 || N <= 0 || D <= 0) return fail(FB_EINVAL, "fb_leaky_posteriors: B, N and D must be positive");
     if (D != g->D) return fail(FB_EINVAL, "fb_leaky_posteriors: D differs from the graph's D");
     if (!(leak >= 0.0f) || !(leak <= 1.0f)) return fail(FB_EINVAL, "fb_leaky_posteriors: leak must lie in [0, 1]");
-    if (!ws || ws_bytes < fb_leaky_workspace_bytes(g, B, N)) return fail(FB_EINVAL, "fb_leaky_posteriors: workspace missing or too small");
+    if (!ws || ws_bytes < leaky_plain_bytes(g, B, N)) return fail(FB_EINVAL, "fb_leaky_posteriors: workspace missing or too small");
     if (!g->leaky) return fail(FB_EUNSUPPORTED, "fb_leaky_posteriors: the graph has no row lists for this mode");
     const LeakyDev &dev = *(const LeakyDev *)g->leaky;
     const size_t lds_bytes = leaky_lds_bytes(g->K, D, std::max(dev.fwd.n_piece, dev.bwd.n_piece));
@@ -561,7 +567,7 @@ int fb_leaky_posteriors(const fb_graph *g, const float *emis, const int32_t *len
     p.leak = leak;
     p.logz = logz; p.pdf_post = pdf_post; p.rows = (float *)ws;
     const LeakyFast fast = leaky_fast(g, B, N);
-    if (fast.ok && ((uintptr_t)ws & 15) == 0) {
+    if (fast.ok && ws_bytes >= fast.bytes && ((uintptr_t)ws & 15) == 0) {
         // Both recursions of every sequence in one launch, the pdf posteriors from their rows, then what gave up
         char *w = (char *)ws;
         RecParams r = leaky_recursion_params(g, emis, lengths, B, N, D);

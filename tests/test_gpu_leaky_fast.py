@@ -68,3 +68,31 @@ def test_states_without_arcs_out():
     g = wl.Graph(g.K, g.src[keep], g.dst[keep], g.logw[keep], g.pdf, g.init, g.final)
     emis = (rng.standard_normal((3, 10, 30)) * 2).astype(np.float32)
     _compare(g, 30, emis, np.array([10, 4, 8], dtype=np.int32), 0.01)
+
+
+def test_workspace_for_one_sweep_is_enough():
+    """Room for the plain kernel's rows only: that kernel serves the call; one byte less is refused."""
+    import torch
+
+    import paper_2112_00709_amd as fb
+    rng = np.random.default_rng(6)
+    g = wl.random_graph(rng, 1301, 30, mean_extra_deg=5.0)
+    lengths = np.array([10, 4, 0], dtype=np.int32)
+    emis = (rng.standard_normal((3, 10, 30)) * 2).astype(np.float32)
+    G = fb.graph_from(g, 30)
+    assert fb.fb_graph_linear_weights(G) == 2
+    one = (4 * 3 * 10 * 1301 + 255) // 256 * 256
+    assert one < fb.fb_leaky_workspace_bytes(G, 3, 10)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    ws = torch.full((one + 4096,), 77, dtype=torch.uint8, device="cuda")
+    logz, post = fb.fb_leaky_posteriors(G, e, l, 1e-3, ws=ws[:one])
+    torch.cuda.synchronize()
+    assert bool((ws[one:] == 77).all())
+    ref = oleaky.forward_backward(g, emis, lengths, 1e-3)
+    for b, T in enumerate(lengths[:2]):
+        assert abs(float(logz[b]) - ref.logz[b]) <= 1e-4 * max(1.0, abs(ref.logz[b]))
+        assert np.abs(post[b].cpu().numpy() - ref.rho[b]).max() <= 1e-5
+    with pytest.raises(fb.FBError) as err:
+        fb.fb_leaky_posteriors(G, e, l, 1e-3, ws=ws[:one - 1])
+    assert err.value.code == fb.FB_EINVAL
+    G.destroy()
