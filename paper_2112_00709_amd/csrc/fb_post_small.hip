@@ -7,7 +7,8 @@
 // wave, the exponentials go to the wave's own LDS in pdf order (a pdf's states are neighbours, the place of a lane's
 // states is kept in registers for all its frames), and no barrier follows the one behind the tables.  Four waves share
 // the tables; a wave takes F frames, as many as leave about two workgroups per compute unit.  Sums are formed in a fixed
-// order.  Measured (three-call forward-backward, this call alone): 16 states, 1 x 50 frames, 19 -> 5.8 us; 32
+// order.  A shared graph has a row for every pdf and needs no list of the rows it has: 300 states, 3000 pdfs, 128 x 300 frames
+// 369 -> 185 us without the room for one (half the chip's waves had no place).  Measured (three-call forward-backward, this call alone): 16 states, 1 x 50 frames, 19 -> 5.8 us; 32
 // chains of 30-120 states, 3.0 k frames, with state posteriors 39 -> 7.6 us; 701 states, 97 pdfs, 3.1 k frames,
 // with state posteriors 46 -> 20 us.  Bound: launch and HBM latency in the first, the row traffic in the last.
 #include <hip/hip_runtime.h>
@@ -29,13 +30,13 @@ struct PostSmallLds {      // bytes of the parts of a workgroup's LDS; the kerne
     __host__ __device__ explicit PostSmallLds(const PostParams &P)
     {
         size_t at = 0;
-        const bool two = P.n_graph == 2;
+        const bool two = P.n_graph == 2, packed = two || !P.g[0].shared;   // packed: the last graph's rows are a selection of the pdfs
         ptr[0] = 0; at = ((size_t)P.g[0].Rcap + 2) / 2 * 4;
         ptr[1] = at; at += two ? ((size_t)P.g[1].Rcap + 2) / 2 * 4 : 0;
-        nidx = at; at += ((size_t)P.D + 1) / 2 * 4;
+        nidx = at; at += packed ? ((size_t)P.D + 1) / 2 * 4 : 0;
         tb[0] = at; at += (size_t)kPostWaves * (size_t)P.g[0].Kcap * 4;
         tb[1] = at; at += two ? (size_t)kPostWaves * (size_t)P.g[1].Kcap * 4 : 0;
-        nval = at; at += (size_t)kPostWaves * (size_t)(two ? P.g[1].Rcap : P.g[0].Rcap) * 4;
+        nval = at; at += packed ? (size_t)kPostWaves * (size_t)(two ? P.g[1].Rcap : P.g[0].Rcap) * 4 : 0;
         total = at;
     }
 };
@@ -207,6 +208,12 @@ bool post_small_applies(const PostParams &p)
     if (p.n_graph == 2 && (!p.g[0].shared || p.g[1].shared)) return false;
     for (int i = 0; i < p.n_graph; ++i)
         if (p.g[i].Kcap > kSmallStates || p.g[i].fmt_a || p.g[i].fmt_b) return false;
+    // One shared graph of many states and pdfs, many frames: the workgroup-wide kernels read a row wider and keep fewer copies of
+    // it.  128 x 300 frames, this kernel / the one that takes the call otherwise: 1000 states, 2000 pdfs 317 / 288 us; 600, 3000
+    // 331 / 303; on this side of the line 600, 2000 264 / 288; 1000, 1000 239 / 275; 300, 3000 185 / 293.  16 x 200 frames, 1000
+    // states, 3000 pdfs: 32 / 36.
+    const int64_t frames = (int64_t)(p.order ? p.n_launch : p.B) * p.N;
+    if (p.n_graph == 1 && p.g[0].shared && (int64_t)p.g[0].Kcap * p.D > 1500000 && frames > 8192) return false;
     return PostSmallLds(p).total <= 64 * 1024;              // (two workgroups and more on a compute unit)
 }
 

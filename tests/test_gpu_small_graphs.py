@@ -273,3 +273,27 @@ def test_large_weights(K, arcs):
             if size > -1e30:
                 assert abs(oracle.path_score(g, emis[b], path[b, :Tb]) - best.score[b]) <= 2.0 ** -24 * 16 * (T + 1)
         h.destroy()
+
+
+@pytest.mark.parametrize("D", [2400, 2600])
+def test_posteriors_of_many_pdfs(D):
+    """600 states and D pdfs lie on either side of the size where large batches go to the workgroup-wide kernel: a
+    sequence's posteriors are those it has by itself (the wave-wide kernel's), and sum to 1."""
+    import torch
+    rng = np.random.default_rng(D)
+    g = _dense_ring(rng, 600, 3, D)
+    B, N = 40, 210
+    lengths = rng.integers(1, N + 1, B).astype(np.int32)
+    lengths[0] = N
+    emis = torch.from_numpy((rng.standard_normal((B, N, D)) * 2).astype(np.float32)).cuda()
+    l = torch.from_numpy(lengths).cuda()
+    h = fb.graph_from(g, D)
+    alpha, beta = fb.fb_alpha(h, emis, l)[0], fb.fb_beta(h, emis, l)[0]
+    gam, rho = fb.fb_posteriors(h, alpha, beta, l, B, N)
+    for b in (0, 7, 39):
+        gam1, rho1 = fb.fb_posteriors(h, alpha[b:b + 1].contiguous(), beta[b:b + 1].contiguous(), l[b:b + 1].contiguous(), 1, N)
+        # the same sums in another order: a few units of single precision of numbers below 1
+        assert float((gam1[0] - gam[b]).abs().max()) <= 1e-6 and float((rho1[0] - rho[b]).abs().max()) <= 1e-6
+        real = rho[b, :lengths[b]].sum(dim=1).cpu().numpy()
+        assert np.abs(real - 1).max() <= 1e-5 and float(rho[b, lengths[b]:].abs().sum()) == 0
+    h.destroy()
