@@ -471,7 +471,7 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 // recursion is a chain of steps that only one workgroup works on, so half the steps are half the time: best path
 // through 6000 states, 60 k arcs, 128 sequences of at most 500 frames 3456 -> 1671 us; 32 label-sequence graphs of at
 // most 161 states over 209 frames 122 -> 71 us (a call).  A batch that fills the chip twice does the same number of steps
-// either way.  One direction alone when the backward plan's vectors (its clone slots) do not fit beside the rest.
+// either way.  (The backward plan fits wherever the graph could be created: the sums' form of it takes more memory.)
 int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D, double *score,
                int32_t *path, void *ws, size_t ws_bytes, fb_stream stream)
 {
@@ -482,14 +482,11 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
     if (((uintptr_t)ws & 255) != 0) return fail(FB_EINVAL, "fb_viterbi: workspace must be 256-byte aligned");
     const size_t rows = (g->n_seq == 0 ? (size_t)B * N : (size_t)N) * viterbi_bp_ld(g);
     const size_t mid_ld = viterbi_mid_ld(g), mid_bytes = align256((size_t)B * mid_ld * (g->f64 ? 8 : 4));
-    const int32_t Ecap = g->n_seq == 0 ? D : g->max_sub_K;
-    const bool both = g->small || recursion_lds_bytes(g->max_sub_K, viterbi_ccap(g, true), Ecap, true, g->f64, g->n_seq == 0, true) <= kLdsBytes;
     BacktraceParams bt{};
     bt.bp = (const uint16_t *)ws;
     bt.bp_ld = (int64_t)viterbi_bp_ld(g);
-    bt.n_dir = both ? 2 : 1;
     RecDir d[2] = {};
-    for (int i = 0; i < bt.n_dir; ++i) {
+    for (int i = 0; i < 2; ++i) {
         char *w = (char *)ws + align256(rows * sizeof(uint16_t)) + (size_t)i * (mid_bytes + align256((size_t)B * sizeof(double)));
         d[i] = make_dir(g, i == 1, nullptr, false, nullptr, nullptr, 1.0f, false);
         d[i].sched = bt.sched[i] = i ? g->btrop : g->trop;
@@ -503,10 +500,9 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
         bt.mid[i] = d[i].mid;
         bt.mid_off[i] = d[i].mid_off;
     }
-    if ((rc = run_recursion(g, emis, lengths, B, N, D, d, bt.n_dir, stream, true))) return rc;
+    if ((rc = run_recursion(g, emis, lengths, B, N, D, d, 2, stream, true))) return rc;
     bt.lengths = lengths;
     bt.small_sub = g->strop.sub;
-    bt.end = g->d_final2;
     bt.mid_ld = (int64_t)mid_ld;
     bt.f64 = g->f64 ? 1 : 0;
     bt.score = score;

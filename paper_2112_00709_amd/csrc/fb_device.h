@@ -220,10 +220,9 @@ __device__ __forceinline__ void resolve_sequence(const RecParams &P, double *lds
 }
 
 // Best path: the frame at which the forward and the backward recursion of a sequence of T > 0 frames meet.  The forward
-// one covers frames 0 .. m and the backward one T-1 .. m, side by side; alone (one direction) the forward one goes all
-// the way.  Row f of the back-pointers joins frame f - 1 and frame f: written by the forward recursion for f <= m, by the
+// one covers frames 0 .. m and the backward one T-1 .. m, side by side.  Row f of the back-pointers joins frame f - 1 and frame f: written by the forward recursion for f <= m, by the
 // backward one for f > m.
-__device__ __forceinline__ int path_middle(int T, int n_dir) { return n_dir == 2 ? (T - 1) >> 1 : T - 1; }
+__device__ __forceinline__ int path_middle(int T) { return (T - 1) >> 1; }
 
 // Progress counter of a launch: everything this workgroup writes is on its way; make it visible device-wide, then count.
 // Every wave waits for its own stores first: the barrier alone waits for no global store on this chip, and the fence of

@@ -403,7 +403,7 @@ constexpr int kDoneFused = 16;     // ... of the word PostParams::fused of the c
 struct RecParams {
     RecDir dir[2];
     float leak;            // leaky-HMM form of the probability-domain kernel: the fraction handed out again
-    int n_dir;             // tropical semiring: with two directions each goes half way (see path_middle)
+    int n_dir;             // tropical semiring: two, each goes half way (see path_middle)
     const int32_t *pdf;
     const float *emis;
     const int32_t *lengths;
@@ -471,10 +471,8 @@ struct BacktraceParams {
     const int32_t *lengths;
     StreamDev sched[2];      // the forward and the backward plan (sub-graphs, clones)
     const SmallSub *small_sub;   // graphs of the small-graph kernel: their sub-graphs (sched is empty then)
-    int32_t n_dir;           // 2: the recursions met in the middle; 1: there was only the forward one
     const void *mid[2];      // the vectors they ended with (RecDir::mid), double if f64
     const double *mid_off[2];
-    const float *end;        // end weights, log2 units (n_dir == 1)
     int64_t mid_ld;
     int32_t f64;
     double *score;           // [B]

@@ -88,7 +88,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
     const SubDesc sd = S.sub[P.shared ? 0 : b];
     const int K = sd.K, k0 = sd.k0, nC = sd.n_slot;
     const int Tn = min(max(P.lengths[b], 0), P.N);
-    const int mid = path_middle(Tn, TROP ? P.n_dir : 1);
+    const int mid = path_middle(Tn);
     const int Ts = Tn > 0 && TROP ? (bwd ? Tn - mid : mid + 1) : Tn;   // frames this direction visits
     const int nE = P.shared ? P.D : K;           // entries of a staged emission vector
     const int nX = P.Kcap + R.Ccap + 1;          // states, clone slots, dump slot
@@ -2075,10 +2075,10 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
         }
         return sd;
     };
-    const SubDesc sd0 = sub_of(0), sd1 = sub_of(P.n_dir - 1);
-    const CloneDesc *const cd0 = P.sched[0].clones + sd0.clone0, *const cd1 = P.sched[P.n_dir - 1].clones + sd1.clone0;
-    const int n_cd0 = sd0.n_cdesc, n_cd1 = P.n_dir == 2 ? sd1.n_cdesc : 0;
-    const int T = min(max(P.lengths[b], 0), P.N), m = path_middle(T, P.n_dir);
+    const SubDesc sd0 = sub_of(0), sd1 = sub_of(1);
+    const CloneDesc *const cd0 = P.sched[0].clones + sd0.clone0, *const cd1 = P.sched[1].clones + sd1.clone0;
+    const int n_cd0 = sd0.n_cdesc, n_cd1 = sd1.n_cdesc;
+    const int T = min(max(P.lengths[b], 0), P.N), m = path_middle(T);
     const int k0 = sd0.k0, K = sd0.K, F = P.frames;
     int32_t *prow = P.path + (size_t)b * P.N;
     if (half == 0)
@@ -2129,7 +2129,7 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     auto value = [&](int h, int idx) {
         return P.f64 ? ((const double *)P.mid[h])[mid_at + idx] : (double)((const float *)P.mid[h])[mid_at + idx];
     };
-    auto value1 = [&](int idx) { return P.n_dir == 2 ? value(1, idx) : (double)P.end[k0 + idx]; };
+    auto value1 = [&](int idx) { return value(1, idx); };
     double best = -INFINITY;
     uint32_t at = 0xffffffffu;   // place in the forward vector << 16 | place in the backward vector
     auto take = [&](double v, uint32_t a) {
@@ -2178,7 +2178,7 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     for (int w = 1; w < kBtThreads / kWave; ++w) take(red_v[w], red_a[w]);
     const bool none = best == -INFINITY;
     if (half == 0 && tid == 0)
-        P.score[b] = none ? -INFINITY : (P.mid_off[0][b] + (P.n_dir == 2 ? P.mid_off[1][b] : 0.0) + best) * kLn2;
+        P.score[b] = none ? -INFINITY : (P.mid_off[0][b] + P.mid_off[1][b] + best) * kLn2;
     if (none) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (rows on their way into this workgroup's LDS)
         for (int i = tid; i < (half ? n_rows : m + 1); i += kBtThreads) prow[half ? m + 1 + i : i] = -1;
@@ -2356,7 +2356,7 @@ int launch_backtrace(const BacktraceParams &p, void *stream)
         const hipError_t e = hipFuncSetAttribute((const void *)fb_backtrace_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(fb_backtrace_kernel, dim3((unsigned)(p.B * p.n_dir)), dim3(kBtThreads), lds_bytes, (hipStream_t)stream, q);
+    hipLaunchKernelGGL(fb_backtrace_kernel, dim3((unsigned)(2 * p.B)), dim3(kBtThreads), lds_bytes, (hipStream_t)stream, q);
     return check_launch("backtrace kernel launch");
 }
 

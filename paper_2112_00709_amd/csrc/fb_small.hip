@@ -285,7 +285,7 @@ __global__ __launch_bounds__((NC + SmallShape<NC, R>::NIO) * kWave) void fb_smal
     const SmallSub sd = D.small.sub[P.shared ? 0 : b];
     const int K = sd.K, k0 = sd.k0;
     const int Tn = min(max(P.lengths[b], 0), P.N);
-    const int mid = path_middle(Tn, TROP ? P.n_dir : 1);
+    const int mid = path_middle(Tn);
     const int Ts = Tn > 0 && TROP ? (bwd ? Tn - mid : mid + 1) : Tn;   // frames this direction visits
     auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
 
