@@ -41,7 +41,6 @@ namespace fb {
 namespace {
 
 constexpr int kBanks = 32, kHalf = 32;
-constexpr double kPLastSimdShare = 1.0;
 
 inline int bank_of(int32_t state) { return state & (kBanks - 1); }
 
@@ -52,10 +51,10 @@ struct PItem {
     std::vector<float> w;      // 2^w
 };
 
-int lanes_log2(int64_t n)
+int lanes_log2(int64_t n, int chunk)
 {
     int lg = 0;
-    while (lg < 6 && (n + (1 << lg) - 1) / (1 << lg) > kPChunk) ++lg;
+    while (lg < 6 && (n + (1 << lg) - 1) / (1 << lg) > chunk) ++lg;
     return lg;
 }
 
@@ -64,6 +63,84 @@ struct PSlice {
     int trip = 0;                 // arcs per lane (even)
     std::vector<int32_t> items;   // indices into the item list, at most 64 >> lg
 };
+
+// What a wave's step costs, in units: a close costs about as much as a unit, one that adds up lanes about two.
+constexpr int kPCloseCost = 1, kPLanesCost = 1;
+int slice_cost(const PSlice &sl) { return sl.trip / 2 + kPCloseCost + (sl.lg > 0 ? kPLanesCost : 0); }
+
+// Slices of the items (in order of length, longest first): a slice takes its lanes per row from its first row, whose
+// arcs are dealt to as many lanes as keeps each at `chunk` arcs or less.
+std::vector<PSlice> make_slices(const std::vector<PItem> &items, const std::vector<int32_t> &order, int chunk)
+{
+    std::vector<PSlice> slices;
+    for (size_t i = 0; i < order.size();) {
+        PSlice sl;
+        const int64_t n0 = (int64_t)items[order[i]].col.size();
+        sl.lg = lanes_log2(n0, chunk);
+        const int count = (int)std::min<size_t>((size_t)(kWave >> sl.lg), order.size() - i);
+        sl.trip = (int)((n0 + (1 << sl.lg) - 1) >> sl.lg);
+        sl.trip += sl.trip & 1;
+        for (int j = 0; j < count; ++j) sl.items.push_back(order[i + j]);
+        slices.push_back(std::move(sl));
+        i += (size_t)count;
+    }
+    return slices;
+}
+
+// Deals slices to nw waves so that the largest wave's cost, which is what every other wave waits for at the end of a
+// step, is as small as moves and swaps get it: the costliest slice first to the wave that is cheapest so far, then, while
+// it helps, a slice of the costliest wave moved to another wave or swapped for one of another wave's.  (3022 states, 51 k
+// arcs: the costliest of 15 waves has 28 units, the average, instead of 32; its walk took 5000 clocks of a step of 6900
+// beside 3850 for the others.)  Returns that cost, or -1 if the waves do not have close words for all slices.
+int deal_slices(const std::vector<PSlice> &slices, int nw, std::vector<std::vector<int>> &mine)
+{
+    std::vector<int> by_cost(slices.size());
+    std::iota(by_cost.begin(), by_cost.end(), 0);
+    std::stable_sort(by_cost.begin(), by_cost.end(), [&](int a, int b) { return slice_cost(slices[a]) > slice_cost(slices[b]); });
+    mine.assign((size_t)nw, {});
+    std::vector<int> load((size_t)nw, 0);
+    for (int s : by_cost) {
+        int best = -1;
+        for (int wv = 0; wv < nw; ++wv)
+            if ((int)mine[wv].size() < kPMaxClose && (best < 0 || load[wv] < load[best])) best = wv;
+        if (best < 0) return -1;
+        mine[best].push_back(s);
+        load[best] += slice_cost(slices[s]);
+    }
+    for (;;) {
+        const int top = (int)(std::max_element(load.begin(), load.end()) - load.begin());
+        int least = load[top], to = -1, give = -1, take = -1;   // (every pass lowers the top wave's cost: it ends)
+        for (int wv = 0; wv < nw; ++wv) {
+            if (wv == top) continue;
+            for (int i = 0; i < (int)mine[top].size(); ++i) {
+                const int a = slice_cost(slices[mine[top][i]]);
+                if ((int)mine[wv].size() < kPMaxClose && std::max(load[top] - a, load[wv] + a) < least) {
+                    least = std::max(load[top] - a, load[wv] + a);
+                    to = wv; give = i; take = -1;
+                }
+                for (int j = 0; j < (int)mine[wv].size(); ++j) {
+                    const int b = slice_cost(slices[mine[wv][j]]);
+                    const int after = std::max(load[top] - a + b, load[wv] + a - b);
+                    if (after < least) { least = after; to = wv; give = i; take = j; }
+                }
+            }
+        }
+        if (to < 0) return load[top];
+        const int sa = mine[top][give], a = slice_cost(slices[sa]);
+        if (take >= 0) {
+            const int sb = mine[to][take], b = slice_cost(slices[sb]);
+            mine[top][give] = sb;
+            mine[to][take] = sa;
+            load[top] += b - a;
+            load[to] += a - b;
+        } else {
+            mine[top].erase(mine[top].begin() + give);
+            mine[to].push_back(sa);
+            load[top] -= a;
+            load[to] += a;
+        }
+    }
+}
 
 // cycles one half of a gather takes: the largest number of distinct addresses any bank has to serve (at least 1)
 int half_cycles(const int32_t *addr, int n)
@@ -331,22 +408,26 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
         S.dim = (float)std::exp2((double)(-124 - w2));
     }
 
-    // ---- slices: longest rows first; a slice takes its lanes per row from its first (longest) row
+    // ---- slices, longest rows first, and the waves that walk them
     std::vector<int32_t> order(items.size());
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return items[a].col.size() > items[b].col.size(); });
+    // (how many arcs a lane takes before a row gets more lanes: fewer make slices that are easier to deal evenly, but
+    // fill lanes less well.  2000 states, 20 k arcs: 16 is best, 1200 skewed: 16, 3022 states, 51 k arcs and more: 32.)
     std::vector<PSlice> slices;
-    for (size_t i = 0; i < order.size();) {
-        PSlice sl;
-        const int64_t n0 = (int64_t)items[order[i]].col.size();
-        sl.lg = lanes_log2(n0);
-        const int count = (int)std::min<size_t>((size_t)(kWave >> sl.lg), order.size() - i);
-        sl.trip = (int)((n0 + (1 << sl.lg) - 1) >> sl.lg);
-        sl.trip += sl.trip & 1;
-        for (int j = 0; j < count; ++j) sl.items.push_back(order[i + j]);
-        slices.push_back(std::move(sl));
-        i += (size_t)count;
+    std::vector<std::vector<int>> mine;
+    int cost = -1;
+    for (int chunk : {kPChunk, kPChunk * 5 / 8, kPChunk / 2, kPChunk * 3 / 8}) {
+        std::vector<PSlice> sl = make_slices(items, order, chunk);
+        std::vector<std::vector<int>> dealt;
+        const int c = deal_slices(sl, nw, dealt);
+        if (c >= 0 && (cost < 0 || c < cost)) {
+            cost = c;
+            slices.swap(sl);
+            mine.swap(dealt);
+        }
     }
+    if (cost < 0) { why = "more slices than the waves have close words for"; return false; }
 
     // ---- trade rows between the halves of slices that both rows fit until each half's arcs are spread evenly over the banks
     // (one lane per row only: the rows of a slice of wider rows share their half anyway)
@@ -398,24 +479,6 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
                 for (int32_t c : rb.col) { --ha[bank_of(c)]; ++hb[bank_of(c)]; }
             }
         }
-    }
-
-    // ---- deal slices to the waves: most units first, to the wave that would finish first and still has a close word free
-    std::vector<int> sorder(slices.size());
-    std::iota(sorder.begin(), sorder.end(), 0);
-    std::stable_sort(sorder.begin(), sorder.end(), [&](int a, int b) { return slices[a].trip > slices[b].trip; });
-    std::vector<std::vector<int>> mine((size_t)nw);
-    std::vector<int64_t> load((size_t)nw, 0);
-    for (int s : sorder) {
-        // (waves go round the four SIMDs of a compute unit; the last SIMD hosts the data-moving wave in place of a fourth
-        // arc-walking one, so its three arc-walking waves get more of its issue slots and take more units)
-        auto finish = [&](int wv) { return (double)(load[wv] + slices[s].trip / 2) / (wv % 4 == 3 ? kPLastSimdShare : 1.0); };
-        int best = -1;
-        for (int wv = 0; wv < nw; ++wv)
-            if ((int)mine[wv].size() < kPMaxClose && (best < 0 || finish(wv) < finish(best))) best = wv;
-        if (best < 0) { why = "more slices than the waves have close words for"; return false; }
-        mine[best].push_back(s);
-        load[best] += slices[s].trip / 2;
     }
 
     // ---- emit
