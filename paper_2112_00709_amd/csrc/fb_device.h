@@ -167,6 +167,30 @@ __device__ __forceinline__ float wave_sum(float v)
     return group_all(v, 6, (int)(threadIdx.x & (kWave - 1)), [](float a, float b) { return a + b; });
 }
 
+// The largest of a wave's values, in lane 63 (the other lanes hold partial maxima): six maxima that read their neighbour's
+// value directly, a lane without one keeping its own.  (wave_max takes a move, a maximum and, across rows, reads into
+// scalars instead: 20 instructions and their waits.)
+__device__ __forceinline__ float wave_max_last(float v)
+{
+    asm volatile("s_nop 1\n\t"   // (a value just written may be read from another lane two instructions later)
+                 "v_max_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_max_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_max_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_max_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_max_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_max_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 1"
+                 : "+v"(v));
+    return v;
+}
+
+// The word in LDS raised to v, by the lanes that call.  In assembly: for the builtin the compiler first reduces over the
+// lanes that are on, in a loop, although a single one is.  The caller's next barrier has to be lds_barrier(), whose wait
+// does not depend on what the compiler knows of.
+__device__ __forceinline__ void lds_raise(float *word, float v)
+{
+    asm volatile("ds_max_f32 %0, %1" :: "v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)word), "v"(v) : "memory");
+}
+
 // A workgroup barrier that waits for what this wave has written to LDS but lets its global loads and stores go on
 // (__syncthreads() in a wave that loads straight into LDS waits for all of them).
 __device__ __forceinline__ void lds_barrier()

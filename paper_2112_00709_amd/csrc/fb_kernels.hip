@@ -115,13 +115,12 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
     auto put_max = [&](int i, T wmax) {
         // (a double carrier's maximum is reduced as a float rounded up: what the next step subtracts from every entry
         // need only be near the largest, the same for all, and not below it by more than rounding)
-        if constexpr (sizeof(T) == 8) wmax = (T)wave_max(__double2float_ru((double)wmax));
-        else wmax = wave_max(wmax);
-        if (lane == 0) {   // (one lane per wave: atomics of many lanes on one word are served one at a time)
-            if constexpr (kAtomMax)
-                __builtin_amdgcn_ds_fmaxf((__attribute__((address_space(3))) float *)(red + i % 3), (float)wmax, 0, 0, false);
-            else
-                red[(i & 1) * NW + wave] = wmax;
+        float wm;
+        if constexpr (sizeof(T) == 8) wm = wave_max_last(__double2float_ru((double)wmax));
+        else wm = wave_max_last(wmax);
+        if (lane == kWave - 1) {   // (one lane per wave: atomics of many lanes on one word are served one at a time)
+            if constexpr (kAtomMax) lds_raise((float *)red + i % 3, wm);
+            else red[(i & 1) * NW + wave] = (T)wm;
         }
     };
     auto get_max = [&](int i) {
@@ -281,7 +280,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
         }
         if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = kNegInf;   // the dump slot holds zero-bar in both buffers, always
         put_max(0, wmax);
-        __syncthreads();
+        lds_barrier();
 
         double csum = 0.0;
         if (io_wave) {
@@ -584,7 +583,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
                     fw = fwn;
                 }
                 put_max(i, wmax);
-                __syncthreads();
+                lds_barrier();
             };
             if constexpr (XF != 0) {
                 for (int i = 1; i < Ts; i += 2) {
@@ -736,8 +735,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     double *off_seq = R_.off ? R_.off + (size_t)b * P.N : nullptr;
     auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
     auto put_max = [&](int i, float wmax) {
-        wmax = wave_max(wmax);
-        if (lane == 0) __builtin_amdgcn_ds_fmaxf((__attribute__((address_space(3))) float *)(red + i % 3), wmax, 0, 0, false);
+        wmax = wave_max_last(wmax);
+        if (lane == kWave - 1) lds_raise(red + i % 3, wmax);
     };
     const int kLinBias = S.bias - (LEAKY ? kLeakyBiasDrop : 0);
     const float kLinDimP = S.dim;
@@ -805,7 +804,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
 #pragma unroll
             for (int u = 0; u < U; ++u) m = tmax3(tmax3(m, v[u].x, v[u].y), v[u].z, v[u].w);
         }
-        m = wave_max(m) * (float)kLog2e;
+        m = lane_value(wave_max_last(m), kWave - 1) * (float)kLog2e;
         return m > -INFINITY ? m : 0.0f;
     };
     const CloneDesc *cdesc = S.clones;
@@ -905,14 +904,14 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             ymax = tmax(ymax, s + fmaf(er[P.pdf[k]], (float)kLog2e, -emx0));
             smax = tmax(smax, s);
         }
-        ymax = wave_max(ymax);
-        smax = wave_max(smax);
-        if (lane == 0) {
-            __builtin_amdgcn_ds_fmaxf((__attribute__((address_space(3))) float *)(red + 7), ymax, 0, 0, false);
-            __builtin_amdgcn_ds_fmaxf((__attribute__((address_space(3))) float *)(red + 3), smax, 0, 0, false);
+        ymax = wave_max_last(ymax);
+        smax = wave_max_last(smax);
+        if (lane == kWave - 1) {
+            lds_raise(red + 7, ymax);
+            lds_raise(red + 3, smax);
         }
     }
-    __syncthreads();
+    lds_barrier();
     const float M0 = red[7];
     // log2 of the first vector = log2 of its entries + base0 (+ the emission maximum).  The largest entry goes to
     // 2^bias; backward, the row that leaves is the start weights before the frame's emissions, which lie above the
@@ -942,7 +941,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     }
     if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = 0.0f;   // the dump slot holds zero in both buffers, always
     put_max(0, wmax);
-    __syncthreads();
+    lds_barrier();
 
     // offsets: log2 of the true row of step i = log2 of (the row in LDS x 2^-bias: what is written out) + sum_{j <= i} c_j,
     // with c_0 = base0 + bias (+ the emission maximum of the frame, forward) and c_i = -log2(scale of step i) + the
@@ -1231,7 +1230,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 wsum = wave_sum(wsum);
                 if (lane == 0) red[32 + (i & 1) * 16 + wave] = wsum;
             }
-            __syncthreads();
+            lds_barrier();
             return true;
         };
         for (int i = 1; i < Tn && ok; ++i) ok = step(i);
