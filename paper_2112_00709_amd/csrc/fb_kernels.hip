@@ -682,7 +682,7 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
 // ---------------------------------------------------------------------------
 __device__ unsigned int g_linear_restarts;   // diagnostic: sequences (x directions) given up by linear_run since the library was loaded
 
-typedef uint32_t close_vector_t __attribute__((ext_vector_type(2 * kPMaxClose)));
+typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)));
 
 // LEAKY: the same recursion for the leaky-HMM of the graph (fb_leaky_posteriors), whose transition matrix is
 // (I + leak 1 pi^T) T.  The rank-one term stays apart from the sparse one and needs one number of the previous vector:
@@ -741,16 +741,17 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const int kLinBias = S.bias - (LEAKY ? kLeakyBiasDrop : 0);
     const float kLinDimP = S.dim;
     const float unbias = __uint_as_float((uint32_t)(127 - kLinBias) << 23);   // 2^-bias
-    // a step maximum the run cannot go on from: a lane gave up (+inf), or the vector fell more than 126 binary orders
-    // in one step (its rescaling would not be a float)
-    const float mx_floor = __uint_as_float((uint32_t)max(kLinBias - 126 + 127, 1) << 23);
-    auto gives_up = [&](float mx) { return !(mx < INFINITY) || (mx > 0.0f && mx < mx_floor); };
-    // the power of two that brings mx (finite, 0 or >= mx_floor) to [2^bias, 2^(bias + 1)), and minus its log2
-    auto rescale = [&](float mx, float &sc, float &neg_log2_sc) {
-        const int ex = (int)((__float_as_uint(mx) >> 23) & 0xffu);
-        const bool live = mx > 0.0f;
-        sc = live ? __uint_as_float((uint32_t)(254 + kLinBias - ex) << 23) : 1.0f;
-        neg_log2_sc = live ? (float)(ex - 127 - kLinBias) : 0.0f;
+    // A step maximum, as its bits: it is never negative, and the bits of such floats have their order.  One the run cannot
+    // go on from: a lane gave up (+inf), or the vector fell more than 126 binary orders in one step (its rescaling would
+    // not be a float).
+    const uint32_t mx_floor = (uint32_t)max(kLinBias - 126 + 127, 1) << 23;
+    auto step_max = [&](int i) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(red[i])); };
+    auto gives_up = [&](uint32_t mx) { return mx >= 0x7f800000u || (mx > 0u && mx < mx_floor); };
+    // the power of two that brings mx (0 or >= mx_floor) to [2^bias, 2^(bias + 1)), and minus its log2
+    auto rescale = [&](uint32_t mx, float &sc, float &neg_log2_sc) {
+        const int ex = (int)(mx >> 23);
+        sc = mx > 0u ? __uint_as_float((uint32_t)(254 + kLinBias - ex) << 23) : 1.0f;
+        neg_log2_sc = mx > 0u ? (float)(ex - 127 - kLinBias) : 0.0f;
     };
 
     // ---- duties of the data-moving wave
@@ -773,39 +774,87 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
     };
     auto staged_wait = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-    // The same where at least `stores` stores were issued behind the requests (memory operations of a wave complete in
-    // order): those need not have arrived, nor at the step's barrier.  (6000 states, one direction with rows over 540
-    // frames: 2295 us waiting for the stores of the step before as well, 2232 us so.)
-    auto staged_before = [&](int stores) {
-        switch (stores >> 2) {
+    // The same for the requests of the step before, where at least `later` memory operations were issued behind them (those
+    // of a wave complete in order): the later ones need not have arrived, nor at the step's barrier.  (6000 states, one
+    // direction with rows over 540 frames: 2295 us waiting for the stores of the step before as well, 2232 us so.)
+    auto staged_before = [&](int later) {
+        switch (min(later, 60) >> 2) {
         case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
         case 1: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
         case 2: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
         case 3: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
         case 4: asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); break;
         case 5: asm volatile("s_waitcnt vmcnt(20)" ::: "memory"); break;
-        default: asm volatile("s_waitcnt vmcnt(24)" ::: "memory"); break;
+        case 6: asm volatile("s_waitcnt vmcnt(24)" ::: "memory"); break;
+        case 7: asm volatile("s_waitcnt vmcnt(28)" ::: "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(32)" ::: "memory"); break;
         }
     };
-    // stores every wave-wide copy of a row issues at least: pieces of 16 bytes that all lanes have
+    // pieces of 16 bytes a lane: body(constant n, q) for the n <= 8 pieces from piece q on, until all n_pieces are done
+    auto in_groups = [&](int n_pieces, auto body) __attribute__((always_inline)) {
+        constexpr int U = 8;
+        int q = 0;
+        for (; q + U <= n_pieces; q += U) body(std::integral_constant<int, U>{}, q);
+        const int rest = n_pieces - q;
+        unrolled([&](auto rc) __attribute__((always_inline)) {
+            constexpr int n = decltype(rc)::value + 1;
+            if (rest == n) body(std::integral_constant<int, n>{}, q);
+        }, std::make_integer_sequence<int, U - 1>{});
+    };
+    // stores and requests a step issues at least: pieces that all lanes have, and a frame's emissions
     const int n_row_stores = out_row0 ? K / (4 * kWave) : 0;
-    // The largest emission of a staged frame, in log2 units (0 if there is none above zero-bar).  Over all pdfs, whether
-    // a state of the graph is tied to them or not: any scale serves.  16 bytes per lane and read (the arc-walking waves
-    // keep the LDS queue full: few, wide reads); what lies behind the row in its last group is -inf.
+    const bool em_pieces16 = (P.D & 3) == 0 && ((uintptr_t)em_seq & 15) == 0;
+    const int n_requests = em_pieces16 ? (P.D + 4 * kWave - 1) / (4 * kWave) : (P.D + kWave - 1) / kWave;
+    // A staged frame's row of emissions -> the factors its states take, 2^(emission - the largest), in place; returns the
+    // largest, in log2 units (0 if there is none above zero-bar).  The largest over all pdfs, whether a state of the graph is
+    // tied to them or not: any scale serves.  16 bytes per lane and read (the arc-walking waves keep the LDS queue full: few,
+    // wide reads); what lies behind the row in its last group becomes zero.  By this wave, which has the time, so that an
+    // exponential is taken per pdf and not per state and a row's close waits for nothing but one read.
+    auto last_piece = [&](const float *row, int e0) {
+        const int e = e0 + 4 * lane;
+        float4 v = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if (e < nE) {
+            v = *(const float4 *)(row + e);
+            v.y = e + 1 < nE ? v.y : -INFINITY;
+            v.z = e + 2 < nE ? v.z : -INFINITY;
+            v.w = e + 3 < nE ? v.w : -INFINITY;
+        }
+        return v;
+    };
     auto emax_of = [&](const float *row) {
         float m = -INFINITY;
-        const float4 *r4 = (const float4 *)row;
-        const int n4e = Es / 4;
-        constexpr int U = 8;
-        for (int j0 = 0; j0 * kWave < n4e; j0 += U) {
-            float4 v[U];
+        const float4 *r4 = (const float4 *)row + lane;
+        const int n_full = nE / (4 * kWave);
+        in_groups(n_full, [&](auto nc, int q) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            float4 v[n];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = r4[min((j0 + u) * kWave + lane, n4e - 1)];
+            for (int u = 0; u < n; ++u) v[u] = r4[(q + u) * kWave];
 #pragma unroll
-            for (int u = 0; u < U; ++u) m = tmax3(tmax3(m, v[u].x, v[u].y), v[u].z, v[u].w);
-        }
+            for (int u = 0; u < n; ++u) m = tmax3(tmax3(m, v[u].x, v[u].y), v[u].z, v[u].w);
+        });
+        const float4 v = last_piece(row, n_full * 4 * kWave);
+        m = tmax3(tmax3(m, v.x, v.y), v.z, v.w);
         m = lane_value(wave_max_last(m), kWave - 1) * (float)kLog2e;
         return m > -INFINITY ? m : 0.0f;
+    };
+    auto to_factors = [&](float *row, float em) {
+        auto raised = [&](float4 v) {
+            return float4{fexp2(fmaf(v.x, (float)kLog2e, -em)), fexp2(fmaf(v.y, (float)kLog2e, -em)),
+                          fexp2(fmaf(v.z, (float)kLog2e, -em)), fexp2(fmaf(v.w, (float)kLog2e, -em))};
+        };
+        float4 *r4 = (float4 *)row + lane;
+        const int n_full = nE / (4 * kWave);
+        in_groups(n_full, [&](auto nc, int q) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            float4 v[n];
+#pragma unroll
+            for (int u = 0; u < n; ++u) v[u] = r4[(q + u) * kWave];
+#pragma unroll
+            for (int u = 0; u < n; ++u) r4[(q + u) * kWave] = raised(v[u]);
+        });
+        const float4 v = last_piece(row, n_full * 4 * kWave);
+        if (n_full * 4 * kWave + 4 * lane < Es) r4[n_full * kWave] = raised(v);
     };
     const CloneDesc *cdesc = S.clones;
     // a finished vector -> global memory, coalesced; a cloned state leaves as the sum of its clones.  Either as it is
@@ -821,36 +870,40 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     auto write_row = [&](int f, const float *srcv) {
         if (!out_row0) return;
         float *orow = out_row0 + (size_t)f * out_ld;
-        const float4 *s4 = (const float4 *)srcv;
-        const int n4 = (K + 3) / 4;
-        const bool vec = (out_ld & 3) == 0 && (size_t)(n4 * 4) <= out_ld && ((uintptr_t)orow & 15) == 0;
-        constexpr int U = 8;
-        for (int q0 = 0; q0 < n4; q0 += U * kWave) {
-            float4 v[U];
+        // (streaming stores: the row is read again much later, by another kernel, and what it would push out of L2 is the arc
+        // plan every workgroup re-reads at every step.  Pieces that all lanes have go out without a mask, through a buffer
+        // descriptor: an instruction each; with a mask and an address per store this wave took 200 - 280 clocks a piece and
+        // was what a step waited for.  The piece's offset is the lane's, not the scalar one: behind a 16-byte store with a scalar
+        // offset register the compiler sees no need for a pause before the data registers are written again, and this chip
+        // then stored the new value in the first word of a quarter of the lanes.)
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        const f4 *s4 = (const f4 *)srcv + lane;
+        const int n_full = K / (4 * kWave);
+        auto dst = __builtin_amdgcn_make_buffer_rsrc((void *)orow, 0, K * 4, 0x00027000);
+        const int lane16 = lane * 16;
+        constexpr int kStreaming = 2;
+        in_groups(n_full, [&](auto nc, int q) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            f4 v[n];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = s4[min(q0 + u * kWave + lane, n4 - 1)];
+            for (int u = 0; u < n; ++u) v[u] = s4[(q + u) * kWave];
 #pragma unroll
-            for (int u = 0; u < U; ++u)   // every read and conversion stays in front of the stores
-                asm volatile("" : "+v"(v[u].x), "+v"(v[u].y), "+v"(v[u].z), "+v"(v[u].w));
+            for (int u = 0; u < n; ++u) asm volatile("" : "+v"(v[u]));   // every read stays in front of the stores
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int q = q0 + u * kWave + lane;
-                if (q < n4) {
-                    // (a streaming store: the row is read again much later, by another kernel, and what it would push out
-                    // of L2 is the arc plan every workgroup re-reads at every step)
-                    typedef float f4 __attribute__((ext_vector_type(4)));
-                    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-                    const f4 t = {v[u].x, v[u].y, v[u].z, v[u].w};
-                    if (vec) {   // (the row's padding may take up to 3 values that lie behind the states)
-                        __builtin_nontemporal_store(t, (f4 *)orow + q);
-                    } else if (4 * q + 3 < K) {   // a row that starts anywhere: whole pieces all the same (3022 states: 2490 -> 1927 us)
-                        __builtin_nontemporal_store((f4u)t, (f4u *)(orow + 4 * q));
-                    } else {
-                        if (4 * q + 0 < K) orow[4 * q + 0] = v[u].x;
-                        if (4 * q + 1 < K) orow[4 * q + 1] = v[u].y;
-                        if (4 * q + 2 < K) orow[4 * q + 2] = v[u].z;
-                    }
-                }
+            for (int u = 0; u < n; ++u) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v[u]), dst, lane16 + (q + u) * kWave * 16, 0, kStreaming);
+        });
+        const int at = n_full * 4 * kWave + 4 * lane;   // the last states, fewer than 256
+        if (at < K) {
+            const f4 v = s4[n_full * kWave];
+            // (a padded row may take up to 3 values that lie behind the states)
+            if (at + 3 < K || ((out_ld & 3) == 0 && (size_t)(at + 4) <= out_ld)) {
+                __builtin_nontemporal_store((f4u)v, (f4u *)(orow + at));
+            } else {
+                orow[at] = v.x;
+                if (at + 1 < K) orow[at + 1] = v.y;
+                if (at + 2 < K) orow[at + 2] = v.z;
             }
         }
         for (int j = lane; j < S.n_clones; j += kWave) {   // stores of one wave to one address keep their order
@@ -893,6 +946,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         const float e0 = emax_of(er);
         const float e1 = Tn > 1 ? emax_of(er + Es) : 0.0f;
         if (lane == 0) { emaxw[0] = e0; emaxw[1] = e1; }
+        if (Tn > 1) to_factors(er + Es, e1);
         if (Tn > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
     }
     __syncthreads();
@@ -958,7 +1012,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
         for (int i = 1; i < Tn; ++i) {
             const int cur = (i - 1) & 1;
-            const float mx = red[(i - 1) % 3];
+            const uint32_t mx = step_max((i - 1) % 3);
             if (gives_up(mx)) { ok = false; break; }
             float sc, nls;
             rescale(mx, sc, nls);
@@ -968,13 +1022,15 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
                 if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
             }
-            staged_before(i > 1 ? n_row_stores : 0);   // frame i+1, requested a whole step ago, is in LDS
+            const bool more = i + 2 < Tn;
+            if (more) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
+            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
             if (i + 1 < Tn) {
+                staged_before(n_row_stores + (more ? n_requests : 0));   // frame i+1, requested a whole step ago, is in LDS
                 const float en = emax_of(er + ((i + 1) % 3) * Es);
                 if (lane == 0) emaxw[(i + 1) % 3] = en;   // (the word of frame i - 2: read for the last time in step i - 1)
+                to_factors(er + ((i + 1) % 3) * Es, en);
             }
-            if (i + 2 < Tn) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
-            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
             if (lane == 0) red[(i + 1) % 3] = 0.0f;   // the word of step i + 1 starts empty
             if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
             lds_barrier();   // (the row's stores and the emissions asked for go on)
@@ -982,20 +1038,26 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
-        const int n_close_w = __builtin_amdgcn_readfirstlane(wd.n_close);
         auto uniform64 = [](uint64_t v) {
             return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
         };
         const uint64_t mask0_w = uniform64(wd.close_mask[0]), mask1_w = uniform64(wd.close_mask[1]), lgs_w = uniform64(wd.lgs);
-        struct Unit { uint32_t s; float w0, w1; };
-        // unit u of the wave: a wave-uniform base (three words per lane) plus the lane's 12 bytes
-        const uint32_t *const ubase = S.units + (size_t)uniform64((uint64_t)wd.unit_base) * (3 * kWave);
-        const uint32_t lane3 = (uint32_t)lane * 3u;
-        auto load_unit = [&](Unit &dst, const uint32_t *base) __attribute__((always_inline)) {
-            dst.s = base[lane3];
-            dst.w0 = __uint_as_float(base[lane3 + 1]);
-            dst.w1 = __uint_as_float(base[lane3 + 2]);
+        // (s1: the second source apart from the first, where registers allow it: an address then needs no instruction)
+        struct Unit { uint32_t s, s1; float w0, w1; };
+        // Unit u of the wave: three words per lane, read through a buffer descriptor, whose scalar offset is the unit's: a
+        // request takes no vector instruction (an address formed from a scalar base and a large constant takes four).
+        constexpr int kUnitBytes = 3 * kWave * 4;
+        auto units = __builtin_amdgcn_make_buffer_rsrc((void *)(S.units + (size_t)uniform64((uint64_t)wd.unit_base) * (3 * kWave)), 0,
+                                                       max(n_units_w, FEW ? kPFew : kPPatterned) * kUnitBytes, 0x00027000);
+        const int lane12 = lane * 12;
+        auto load_unit = [&](Unit &dst, int u) __attribute__((always_inline)) {
+            typedef uint32_t u3 __attribute__((ext_vector_type(3)));
+            const u3 v = __builtin_amdgcn_raw_buffer_load_b96(units, lane12, u * kUnitBytes, 0);
+            dst.s = FEW ? v.x & 0xffffu : v.x;
+            dst.s1 = FEW ? v.x >> 16 : 0u;
+            dst.w0 = __uint_as_float(v.y);
+            dst.w1 = __uint_as_float(v.z);
         };
         // The wave's units in walking order (see kPPatterned): which positions stay in registers, which are re-read.
         // Re-read ("streamed") unit m of a step sits in ring[m % kPRing] and is asked for kPRing - 1 streamed units ahead
@@ -1015,31 +1077,23 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         Unit res[R];   // (units behind the wave's last one are zero words or another wave's: never folded)
         unrolled([&](auto qc) __attribute__((always_inline)) {
             constexpr int q = decltype(qc)::value;
-            load_unit(res[q], ubase + (size_t)(FEW ? q : p_resident_pos(q)) * (3 * kWave));
+            load_unit(res[q], FEW ? q : p_resident_pos(q));
         }, std::make_integer_sequence<int, R>{});
-        // The lane's close words and, behind them, the emission factors of the step in hand, both picked by the number
-        // of the close (uniform).  One vector of sixteen: picking from a vector of eight is compiled into a chain of seven
-        // selects, from a longer one into one indexed register move.
+        // The lane's close words, picked by the number of the close (uniform).  One vector of nine: picking from a vector of
+        // eight is compiled into a chain of seven selects, from a longer one into one indexed register move.
         close_vector_t cwv;
 #pragma unroll
         for (int c = 0; c < kPMaxClose; ++c) cwv[c] = S.close_words[((size_t)wd.cw_base + c) * kWave + lane];
+        cwv[kPMaxClose] = cwv[0];   // (what is asked for when the last slice has closed)
         // (everything asked for so far has arrived: the waits inside the loop then count the loop's own loads only)
         __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
         Unit ring[kPRing];
         // streamed unit m -> its ring place (in the patterned part streamed unit m is position H + 3 m + 2; behind it, unit
         // NP + t is streamed unit NG + t)
-        // (the base the requests add to is made opaque at every step: an address formed at the place of the request is a
-        // scalar base plus the lane's offset, while addresses kept over the whole loop, as the compiler would have them,
-        // take a register pair each)
-        uint32_t ub_lo = (uint32_t)(uintptr_t)ubase, ub_hi = (uint32_t)((uintptr_t)ubase >> 32);
         // (a position inside the patterned part is asked for as it is, whatever the wave's unit count: the plan has
         // room for kPPatterned units behind every wave's first; positions behind it are held to the wave's last unit)
         auto request_at = [&](Unit &dst, int u) __attribute__((always_inline)) {
-            typedef const __attribute__((address_space(1))) uint32_t global_u32;   // (an address built from integers: say that it is global memory)
-            global_u32 *ub = (global_u32 *)((uintptr_t)ub_lo | ((uintptr_t)ub_hi << 32)) + (size_t)u * (3 * kWave);
-            dst.s = ub[lane3];
-            dst.w0 = __uint_as_float(ub[lane3 + 1]);
-            dst.w1 = __uint_as_float(ub[lane3 + 2]);
+            load_unit(dst, u);
             __builtin_amdgcn_sched_barrier(0);   // keep the issue order: waits count loads in order
         };
         auto request = [&](Unit &dst, int pos) __attribute__((always_inline)) { request_at(dst, min(pos, last_spos)); };
@@ -1048,21 +1102,28 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             request_at(ring[m], p_streamed_pos(m));
         }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
 
-        auto step = [&](int i) __attribute__((always_inline)) -> bool {
-            const int cur = (i - 1) & 1, nxt = cur ^ 1;   // which buffer holds the previous step's vector
+        // Two steps, one after the other, are two copies of the code: which buffer holds the previous step's vector is then
+        // known, and its address is the constant offset of an LDS instruction.  (With the address OR-ed into a source by the
+        // instruction that takes the source out of its word, that instruction is one of sub-words, which issue at little
+        // more than half the rate.)
+        auto step = [&](int i, auto parity) __attribute__((always_inline)) -> bool {
+            constexpr int cur = decltype(parity)::value, nxt = cur ^ 1;   // (i - 1) & 1: the buffer of the previous step's vector
             float *xn = xb + nxt * Xs;
             float *bn = bh + nxt * XL;
-            const uint32_t gbase = (uint32_t)cur * (uint32_t)kXbStride;   // (uniform) address of the buffer the gathers read
-            const char *ern = (const char *)(er + (i % 3) * Es);
-            const float mx = red[(i - 1) % 3];
+            typedef __attribute__((address_space(3))) float lds_f;
+            // (the workgroup's LDS starts at address 0)
+            const uint32_t bn_at = (uint32_t)((Xs + XL) * 4) + (uint32_t)nxt * (uint32_t)(XL * 4);
+            typedef const __attribute__((address_space(3))) float lds_cf;
+            const uint32_t ern = (uint32_t)(uintptr_t)(lds_cf *)(er + (i % 3) * Es);   // the frame's emission factors
+            const uint32_t mx = step_max((i - 1) % 3);
             if (gives_up(mx)) return false;   // (the same word in every wave: all of them leave here)
             float sc, nls;
             rescale(mx, sc, nls);
-            const float emx = emaxw[i % 3];
+            // the close word in use, and the emission factor of its rows: asked for when the slice before has closed
+            uint32_t cw = cwv[0];
+            float pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
             wmax = 0.0f;
-            // the smallest entry this lane has written for a row whose sum is above zero, as its bit pattern (which keeps
-            // the order of floats that are not negative)
-            uint32_t wlow = 0x7f800000u;
+            uint64_t low = 0;   // lanes that have written an entry below the range for a row whose sum is above zero
             float acc = 0.0f;
             // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
             float leaked = 0.0f, q_next = 0.0f;
@@ -1072,79 +1133,59 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 leaked = P.leak * ((((s0.x + s0.y) + (s0.z + s0.w)) + ((s1.x + s1.y) + (s1.z + s1.w))) +
                                    (((s2.x + s2.y) + (s2.z + s2.w)) + ((s3.x + s3.y) + (s3.z + s3.w))));
                 wsum = 0.0f;
-                q_next = *(const float *)((const char *)qt + (cwv[0] & 0xffffu));
+                q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
             }
             // the wave's constants, opaque at every step: what is derived from them is computed where it is used (a
             // scalar instruction or two) instead of being kept in scalar registers that do not exist
             uint32_t m_lo = (uint32_t)mask0_w, m_hi = (uint32_t)(mask0_w >> 32), m1_lo = (uint32_t)mask1_w, m1_hi = (uint32_t)(mask1_w >> 32);
             uint32_t lg_lo = (uint32_t)lgs_w;
             int n_units = n_units_w;
-            asm volatile("" : "+s"(m_lo), "+s"(m_hi), "+s"(m1_lo), "+s"(m1_hi), "+s"(lg_lo), "+s"(n_units), "+s"(ub_lo), "+s"(ub_hi), "+s"(last_spos));
+            asm volatile("" : "+s"(m_lo), "+s"(m_hi), "+s"(m1_lo), "+s"(m1_hi), "+s"(lg_lo), "+s"(n_units), "+s"(last_spos));
             int nclose = 0;   // slices closed so far in this step (uniform)
-            if (i <= 2)   // rows without arcs: zero from the second frame on, in both buffers
+            if (i == cur + 1)   // rows without arcs: zero from the second frame on, in both buffers
                 for (int z = tid; z < S.n_zero; z += NC * kWave) {
                     const int k = S.zero_rows[z];
                     xn[k] = 0.0f;
                     if (staged) bn[k] = log_rows ? -INFINITY : 0.0f;
                 }
-            // the two values a unit gathers; sources are byte offsets, the workgroup's LDS starts at address 0
-            auto gather = [&](float2 &g, uint32_t s) __attribute__((always_inline)) {
+            // the two values a unit gathers; sources are byte offsets.  (In assembly so that the addresses are formed at every
+            // step: left to itself the compiler keeps every resident unit's two in registers of their own.)
+            uint32_t low_half = 0xffffu;
+            asm volatile("" : "+s"(low_half));
+            auto gather = [&](float2 &g, const Unit &un) __attribute__((always_inline)) {
                 typedef const __attribute__((address_space(3))) float lds_ct;
-                // one instruction per address: a half of the word, zero-extended, OR the buffer's address.  (In assembly
-                // also so that the addresses are formed at every step: left to itself the compiler keeps every resident
-                // unit's two addresses in registers of their own.)
-                uint32_t lo, hi;
-                asm volatile("v_or_b32_sdwa %0, %3, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"
-                             "v_or_b32_sdwa %1, %3, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
-                             : "=&v"(lo), "=v"(hi) : "v"(s), "s"(gbase));
-                g.x = *(lds_ct *)(uintptr_t)lo;
-                g.y = *(lds_ct *)(uintptr_t)hi;
+                uint32_t lo = un.s, hi = un.s1;
+                if constexpr (!FEW)
+                    asm volatile("v_and_b32 %0, %3, %2\n\tv_lshrrev_b32 %1, 16, %2" : "=&v"(lo), "=v"(hi) : "v"(un.s), "s"(low_half));
+                g.x = *(lds_ct *)(uintptr_t)(lo + (uint32_t)(cur * kXbStride));
+                g.y = *(lds_ct *)(uintptr_t)(hi + (uint32_t)(cur * kXbStride));
             };
-            // a slice ends: the lanes of a row are added up, the row is rescaled, takes its emission, is stored.  The
-            // emission of the slice that ends next is asked for as soon as the one before it has ended, so that it has
-            // arrived when it is needed (LDS answers in order: asked for at the end, it would wait behind the gathers).
-            // the emission factors of the wave's closes, relative to the frame's best: read and raised here, so that a
-            // close waits for nothing but its own arcs
-            typedef const __attribute__((address_space(3))) float lds_cf;
-            const uint32_t ern_a = (uint32_t)(uintptr_t)ern;
-            auto factor = [&](auto cc) __attribute__((always_inline)) {
-                constexpr int c = decltype(cc)::value;
-                cwv[kPMaxClose + c] = __float_as_uint(fexp2(fmaf(*(lds_cf *)(uintptr_t)(ern_a + (cwv[c] >> 16)), (float)kLog2e, -emx)));
-            };
-            unrolled(factor, std::make_integer_sequence<int, FEW ? 2 : kPMaxClose>{});
-            if constexpr (FEW) {   // (a small graph's waves close a few slices: the factors of the others are not formed)
-                if (n_close_w > 2) { factor(std::integral_constant<int, 2>{}); factor(std::integral_constant<int, 3>{}); }
-                if (n_close_w > 4) {
-                    factor(std::integral_constant<int, 4>{}); factor(std::integral_constant<int, 5>{});
-                    factor(std::integral_constant<int, 6>{}); factor(std::integral_constant<int, 7>{});
-                }
-            }
             // a slice ends: the lanes of a row are added up, the row is rescaled, takes its emission, is stored
             auto close_slice = [&]() __attribute__((always_inline)) {
                 const int lg = (int)((lg_lo >> (3 * nclose)) & 7u);
-                const uint32_t tgt = cwv[nclose] & 0xffffu;
-                const float pe = __uint_as_float(cwv[kPMaxClose + nclose]);
-                ++nclose;
+                const uint32_t tgt = cw & 0xffffu;
+                cw = cwv[++nclose];
                 for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
                     acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
                 const float q = q_next;
                 if constexpr (LEAKY) {
                     acc = bwd ? acc + ((int)__float_as_uint(q) >= 0 ? leaked : 0.0f) : fmaf(leaked, tmax(q, 0.0f), acc);
-                    q_next = *(const float *)((const char *)qt + (cwv[nclose & (kPMaxClose - 1)] & 0xffffu));
+                    q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
                 }
                 const float pb = acc * sc;
                 const float px = pb * pe;
+                pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
                 if constexpr (LEAKY) {   // (a row spread over several lanes counts once)
                     const float mine = (lane & ((1 << lg) - 1)) == 0 ? px : 0.0f;
                     wsum = bwd ? fmaf(fabsf(q), mine, wsum) : wsum + mine;
                 }
-                *(float *)((char *)xn + tgt) = px;
+                *(lds_f *)(uintptr_t)(tgt + (uint32_t)(nxt * kXbStride)) = px;
                 if (staged) {   // (uniform) what leaves the kernel for this row
                     const float o = bwd ? pb : px;
-                    *(float *)((char *)bn + tgt) = log_rows ? to_log(o) : o;
+                    *(lds_f *)(uintptr_t)(tgt + bn_at) = log_rows ? to_log(o) : o;
                 }
                 wmax = tmax(wmax, px);
-                wlow = min(wlow, __float_as_uint(pb > 0.0f ? px : INFINITY));
+                low |= __ballot(pb > 0.0f && px < kLinDimP);
                 acc = 0.0f;
             };
             // position u of the patterned part: which registers hold it
@@ -1160,7 +1201,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             float2 G[NGB];
             unrolled([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                gather(G[u], unit_at(std::integral_constant<int, u>{}).s);
+                gather(G[u], unit_at(std::integral_constant<int, u>{}));
             }, std::make_integer_sequence<int, GD>{});
             // Waves of equal priority are served oldest first, so with one fixed priority the younger waves of a SIMD
             // would do most of their step alone after the older ones have finished theirs.  A wave's priority therefore
@@ -1182,14 +1223,14 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             }
                             // (gathered whether the wave has that unit or not - its registers hold valid sources either way -
                             // so that the number of gathers on their way is a constant too)
-                            if constexpr (u + GD < NP) gather(G[(u + GD) % NGB], unit_at(std::integral_constant<int, u + GD>{}).s);
-                            else if constexpr (!FEW) gather(G[(u + GD) % NGB], ring[(NG + (u + GD - NP)) % kPRing].s);   // the first units behind the patterned part
+                            if constexpr (u + GD < NP) gather(G[(u + GD) % NGB], unit_at(std::integral_constant<int, u + GD>{}));
+                            else if constexpr (!FEW) gather(G[(u + GD) % NGB], ring[(NG + (u + GD - NP)) % kPRing]);   // the first units behind the patterned part
                             const Unit me = unit_at(std::integral_constant<int, u>{});
                             // (both values of the unit are taken at one point: one wait for the pair instead of one each)
                             asm volatile("" : "+v"(G[u % NGB].x), "+v"(G[u % NGB].y));
                             acc = fmaf(G[u % NGB].x, me.w0, acc);
                             acc = fmaf(G[u % NGB].y, me.w1, acc);
-                            if (((u < 32 ? m_lo : m_hi) >> (u & 31)) & 1u) close_slice();
+                            if (__builtin_expect(((u < 32 ? m_lo : m_hi) >> (u & 31)) & 1u, 0)) close_slice();
                         }, std::make_integer_sequence<int, 4>{});
                         self(self, std::integral_constant<int, decltype(kc)::value + 1>{});
                     }
@@ -1207,13 +1248,13 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                         if (NP + t < n_units) {
                             const int mr = NG + tt;   // (t0 is a multiple of kPRing: only tt names the buffers)
                             request(ring[(mr + kPRing - 1) % kPRing], NP + t + kPRing - 1);
-                            gather(G[(NP + tt + GD) % NGB], ring[(mr + GD) % kPRing].s);
+                            gather(G[(NP + tt + GD) % NGB], ring[(mr + GD) % kPRing]);
                             asm volatile("" : "+v"(G[(NP + tt) % NGB].x), "+v"(G[(NP + tt) % NGB].y));
                             acc = fmaf(G[(NP + tt) % NGB].x, ring[mr % kPRing].w0, acc);
                             acc = fmaf(G[(NP + tt) % NGB].y, ring[mr % kPRing].w1, acc);
                             const int at = NP + t;
                             const uint32_t word = at < 32 ? m_lo : at < 64 ? m_hi : at < 96 ? m1_lo : m1_hi;
-                            if ((word >> (at & 31)) & 1u) close_slice();
+                            if (__builtin_expect((word >> (at & 31)) & 1u, 0)) close_slice();
                         }
                     }
                 }
@@ -1224,7 +1265,6 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 }, std::make_integer_sequence<int, kPRing - 1>{});
             }
             // an entry below the range: the run gives up (see above)
-            const bool low = wlow < __float_as_uint(kLinDimP);
             put_max(i, low ? INFINITY : wmax);
             if constexpr (LEAKY) {
                 wsum = wave_sum(wsum);
@@ -1233,7 +1273,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_barrier();
             return true;
         };
-        for (int i = 1; i < Tn && ok; ++i) ok = step(i);
+        for (int i = 1; ok && i < Tn; ++i) {
+            ok = step(i, std::integral_constant<int, 0>{});
+            if (ok && ++i < Tn) ok = step(i, std::integral_constant<int, 1>{});
+        }
     }
     // a state below the range in the last step: give up as well (every wave reads the same word)
     if (ok && !(red[(Tn - 1) % 3] < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
