@@ -191,6 +191,13 @@ __device__ __forceinline__ void lds_raise(float *word, float v)
     asm volatile("ds_max_f32 %0, %1" :: "v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)word), "v"(v) : "memory");
 }
 
+// The same for the value that lane 63 holds, in a wave all of whose lanes are on; at: the word's address in LDS.  (A mask
+// set and put back instead of a branch around one lane.)
+__device__ __forceinline__ void lds_raise_last(uint32_t at, float v)
+{
+    asm volatile("s_brev_b64 exec, 1\n\tds_max_f32 %0, %1\n\ts_mov_b64 exec, -1" :: "v"(at), "v"(v) : "memory");
+}
+
 // A workgroup barrier that waits for what this wave has written to LDS but lets its global loads and stores go on
 // (__syncthreads() in a wave that loads straight into LDS waits for all of them).
 __device__ __forceinline__ void lds_barrier()

@@ -713,7 +713,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // an arc's source (an offset into a buffer) and the buffer's address then combine by OR
     constexpr int Xs = kXbStride / 4;
     static_assert(kXbStride >= XF * 4 && (kXbStride & (kXbStride - 1)) == 0 && 2 * kXbStride <= 0x10000, "buffer stride");
-    const int Es = (P.D + 1 + 3) & ~3;
+    const int Es = prob_row_floats(P.D);
     if (Tn <= 0) return false;                   // (nothing to run: the log form writes the empty results)
 
     float *xb = (float *)lds_raw;
@@ -734,25 +734,20 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     float *out_row0 = R_.out ? (float *)R_.out + (size_t)b * P.N * out_ld : nullptr;
     double *off_seq = R_.off ? R_.off + (size_t)b * P.N : nullptr;
     auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
-    auto put_max = [&](int i, float wmax) {
-        wmax = wave_max_last(wmax);
-        if (lane == kWave - 1) lds_raise(red + i % 3, wmax);
-    };
+    // the word of step i: the largest entry of its vector, in the last place of the emission row that is in use then (cleared
+    // when that row is made ready, read for the last time before the next frame's row is made ready there)
+    auto step_word = [&](int i) { return er + (i % 3) * Es + Es - 1; };
     const int kLinBias = S.bias - (LEAKY ? kLeakyBiasDrop : 0);
     const float kLinDimP = S.dim;
     const float unbias = __uint_as_float((uint32_t)(127 - kLinBias) << 23);   // 2^-bias
-    // A step maximum, as its bits: it is never negative, and the bits of such floats have their order.  One the run cannot
-    // go on from: a lane gave up (+inf), or the vector fell more than 126 binary orders in one step (its rescaling would
-    // not be a float).
+    // A step maximum, as its bits: it is never negative, and the bits of such floats have their order.  The run cannot go on
+    // from one that is not finite: a lane has given up (+inf).  Below mx_floor the vector fell more than 126 binary orders in
+    // one step and its rescaling would not be a float: the data-moving wave then gives up for the step that follows.
     const uint32_t mx_floor = (uint32_t)max(kLinBias - 126 + 127, 1) << 23;
-    auto step_max = [&](int i) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(red[i])); };
-    auto gives_up = [&](uint32_t mx) { return mx >= 0x7f800000u || (mx > 0u && mx < mx_floor); };
-    // the power of two that brings mx (0 or >= mx_floor) to [2^bias, 2^(bias + 1)), and minus its log2
-    auto rescale = [&](uint32_t mx, float &sc, float &neg_log2_sc) {
-        const int ex = (int)(mx >> 23);
-        sc = mx > 0u ? __uint_as_float((uint32_t)(254 + kLinBias - ex) << 23) : 1.0f;
-        neg_log2_sc = mx > 0u ? (float)(ex - 127 - kLinBias) : 0.0f;
-    };
+    // The power of two that brings mx (0 or >= mx_floor) to [2^bias, 2^(bias + 1)).  (For 0 a negative number, which leaves
+    // every sum of that step, all zero, a zero.)
+    const uint32_t sc_top = (uint32_t)(254 + kLinBias) << 23;
+    auto rescale = [&](uint32_t mx) { return __uint_as_float(sc_top - (mx & 0x7f800000u)); };
 
     // ---- duties of the data-moving wave
     // a frame's emissions -> LDS, 16 bytes a lane where the row allows it; the lane's address is formed once and every
@@ -930,9 +925,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const double cum_shift = out_lin ? (double)kLinBias : 0.0;
 
     // ---- first frame of this direction: the start weights and the frame's emissions, relative to their maximum
-    if (tid < 12) er[(tid >> 2) * Es + Es - 4 + (tid & 3)] = -INFINITY;   // behind the rows (staging never writes there; the row's own last entries are rewritten)
-    __syncthreads();
-    if (tid < 3) er[tid * Es + P.D] = -INFINITY;   // what the dump slot "emits": its entry stays zero whatever the frame's scale
+    if (tid < 3) *step_word(tid) = 0.0f;
     if (tid < 8) red[tid] = (tid == 7 || tid == 3) ? -INFINITY : 0.0f;
     if constexpr (LEAKY) {
         for (int k = tid; k < nX; k += NT) qt[k] = R_.rank1[k];
@@ -994,7 +987,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         if (staged) bh[K + k] = log_rows ? -INFINITY : 0.0f;
     }
     if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = 0.0f;   // the dump slot holds zero in both buffers, always
-    put_max(0, wmax);
+    wmax = wave_max_last(wmax);
+    if (lane == kWave - 1) lds_raise(step_word(0), wmax);
     lds_barrier();
 
     // offsets: log2 of the true row of step i = log2 of (the row in LDS x 2^-bias: what is written out) + sum_{j <= i} c_j,
@@ -1012,10 +1006,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
         for (int i = 1; i < Tn; ++i) {
             const int cur = (i - 1) & 1;
-            const uint32_t mx = step_max((i - 1) % 3);
-            if (gives_up(mx)) { ok = false; break; }
-            float sc, nls;
-            rescale(mx, sc, nls);
+            const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(*step_word(i - 1)));
+            if (mx > 0x7f7fffffu) { ok = false; break; }
+            const float nls = mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
             c = nls + emaxw[(bwd ? i - 1 : i) % 3];
             csum += (double)c;
             if (lane == 0) {
@@ -1031,7 +1024,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (lane == 0) emaxw[(i + 1) % 3] = en;   // (the word of frame i - 2: read for the last time in step i - 1)
                 to_factors(er + ((i + 1) % 3) * Es, en);
             }
-            if (lane == 0) red[(i + 1) % 3] = 0.0f;   // the word of step i + 1 starts empty
+            if (mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(step_word(i), INFINITY);
             if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
             lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
@@ -1076,8 +1069,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         if (n_units_w > NP) last_spos = n_units_w - 1;
         Unit res[R];   // (units behind the wave's last one are zero words or another wave's: never folded)
         unrolled([&](auto qc) __attribute__((always_inline)) {
-            constexpr int q = decltype(qc)::value;
-            load_unit(res[q], FEW ? q : p_resident_pos(q));
+            constexpr int q = decltype(qc)::value, pos = FEW ? q : p_resident_pos(q);
+            load_unit(res[q], pos);
         }, std::make_integer_sequence<int, R>{});
         // The lane's close words, picked by the number of the close (uniform).  One vector of nine: picking from a vector of
         // eight is compiled into a chain of seven selects, from a longer one into one indexed register move.
@@ -1098,9 +1091,26 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         };
         auto request = [&](Unit &dst, int pos) __attribute__((always_inline)) { request_at(dst, min(pos, last_spos)); };
         unrolled([&](auto mc) __attribute__((always_inline)) {
-            constexpr int m = decltype(mc)::value;
-            request_at(ring[m], p_streamed_pos(m));
+            constexpr int m = decltype(mc)::value, first = p_streamed_pos(m);
+            request_at(ring[m], first);
         }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
+
+        // Scalar instructions and branches are what a step is short of: a SIMD issues one in about 5.5 clocks whatever the
+        // number of its waves (a plain vector instruction in 2.4), and a step of 3022 states, 51 k arcs took 2900 of them
+        // over its 16 waves beside 3200 vector instructions, in 5100 clocks.  Hence: what a step needs of the rotating rows is
+        // one running address, and scales and the range guard are vector arithmetic.  (Asked once for every four units whether
+        // a slice ends among them, a step takes 700 scalar instructions fewer, but 800 moves more where the two paths meet.)
+        uint32_t m_lo = (uint32_t)mask0_w, m_hi = (uint32_t)(mask0_w >> 32), m1_lo = (uint32_t)mask1_w, m1_hi = (uint32_t)(mask1_w >> 32);
+        uint32_t lg_lo = (uint32_t)lgs_w;
+        int n_units = n_units_w, n_wide = 0;   // slices whose rows take several lanes: the plan has them in front
+#pragma unroll
+        for (int c = 0; c < kPMaxClose; ++c) n_wide = ((lg_lo >> (3 * c)) & 7u) ? c + 1 : n_wide;
+        typedef __attribute__((address_space(3))) float lds_f;
+        typedef const __attribute__((address_space(3))) float lds_cf;
+        const uint32_t row_bytes = (uint32_t)Es * 4u, row_first = (uint32_t)(uintptr_t)(lds_cf *)er, row_end = row_first + 3u * row_bytes;
+        uint32_t row_cur = row_first;   // the emission row of the frame in hand
+        uint32_t to_word = row_bytes - 4u;
+        asm volatile("" : "+v"(to_word));   // (a vector register: what is added to it is then no scalar addition)
 
         // Two steps, one after the other, are two copies of the code: which buffer holds the previous step's vector is then
         // known, and its address is the constant offset of an LDS instruction.  (With the address OR-ed into a source by the
@@ -1110,20 +1120,23 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             constexpr int cur = decltype(parity)::value, nxt = cur ^ 1;   // (i - 1) & 1: the buffer of the previous step's vector
             float *xn = xb + nxt * Xs;
             float *bn = bh + nxt * XL;
-            typedef __attribute__((address_space(3))) float lds_f;
             // (the workgroup's LDS starts at address 0)
             const uint32_t bn_at = (uint32_t)((Xs + XL) * 4) + (uint32_t)nxt * (uint32_t)(XL * 4);
-            typedef const __attribute__((address_space(3))) float lds_cf;
-            const uint32_t ern = (uint32_t)(uintptr_t)(lds_cf *)(er + (i % 3) * Es);   // the frame's emission factors
-            const uint32_t mx = step_max((i - 1) % 3);
-            if (gives_up(mx)) return false;   // (the same word in every wave: all of them leave here)
-            float sc, nls;
-            rescale(mx, sc, nls);
+            // the wave's constants, opaque at every step: what is derived from them is computed where it is used (a
+            // scalar instruction or two) instead of being kept in scalar registers that do not exist
+            asm volatile("" : "+s"(m_lo), "+s"(m_hi), "+s"(m1_lo), "+s"(m1_hi), "+s"(lg_lo), "+s"(n_units), "+s"(last_spos));
+            const float mxv = *(lds_cf *)(uintptr_t)(row_cur + to_word);
+            row_cur += row_bytes;
+            row_cur = row_cur == row_end ? row_first : row_cur;
+            const uint32_t ern = row_cur;   // the frame's emission factors
             // the close word in use, and the emission factor of its rows: asked for when the slice before has closed
             uint32_t cw = cwv[0];
             float pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
+            float sc = 1.0f;
             wmax = 0.0f;
-            uint64_t low = 0;   // lanes that have written an entry below the range for a row whose sum is above zero
+            // the smallest entry this lane has written for a row whose sum is above zero, as its bit pattern (which keeps
+            // the order of floats that are not negative)
+            uint32_t wlow = 0x7f800000u;
             float acc = 0.0f;
             // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
             float leaked = 0.0f, q_next = 0.0f;
@@ -1135,12 +1148,6 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 wsum = 0.0f;
                 q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
             }
-            // the wave's constants, opaque at every step: what is derived from them is computed where it is used (a
-            // scalar instruction or two) instead of being kept in scalar registers that do not exist
-            uint32_t m_lo = (uint32_t)mask0_w, m_hi = (uint32_t)(mask0_w >> 32), m1_lo = (uint32_t)mask1_w, m1_hi = (uint32_t)(mask1_w >> 32);
-            uint32_t lg_lo = (uint32_t)lgs_w;
-            int n_units = n_units_w;
-            asm volatile("" : "+s"(m_lo), "+s"(m_hi), "+s"(m1_lo), "+s"(m1_hi), "+s"(lg_lo), "+s"(n_units), "+s"(last_spos));
             int nclose = 0;   // slices closed so far in this step (uniform)
             if (i == cur + 1)   // rows without arcs: zero from the second frame on, in both buffers
                 for (int z = tid; z < S.n_zero; z += NC * kWave) {
@@ -1162,11 +1169,14 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             };
             // a slice ends: the lanes of a row are added up, the row is rescaled, takes its emission, is stored
             auto close_slice = [&]() __attribute__((always_inline)) {
-                const int lg = (int)((lg_lo >> (3 * nclose)) & 7u);
                 const uint32_t tgt = cw & 0xffffu;
+                int lg = 0;
+                if (__builtin_expect(nclose < n_wide, 0)) {
+                    lg = (int)((lg_lo >> (3 * nclose)) & 7u);
+                    for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
+                        acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
+                }
                 cw = cwv[++nclose];
-                for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
-                    acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
                 const float q = q_next;
                 if constexpr (LEAKY) {
                     acc = bwd ? acc + ((int)__float_as_uint(q) >= 0 ? leaked : 0.0f) : fmaf(leaked, tmax(q, 0.0f), acc);
@@ -1185,15 +1195,18 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                     *(lds_f *)(uintptr_t)(tgt + bn_at) = log_rows ? to_log(o) : o;
                 }
                 wmax = tmax(wmax, px);
-                low |= __ballot(pb > 0.0f && px < kLinDimP);
+                wlow = min(wlow, __float_as_uint(pb > 0.0f ? px : INFINITY));
                 acc = 0.0f;
             };
             // position u of the patterned part: which registers hold it
             auto unit_at = [&](auto uc) __attribute__((always_inline)) -> Unit {
                 constexpr int u = decltype(uc)::value;
                 if constexpr (FEW) return res[u];
-                else if constexpr (p_streamed(u)) return ring[p_streamed_before(u) % kPRing];
-                else return res[u - p_streamed_before(u)];
+                else {
+                    constexpr int before = p_streamed_before(u);
+                    if constexpr (p_streamed(u)) return ring[before % kPRing];
+                    else return res[u - before];
+                }
             };
             // gathered values of the unit being folded and of the next GD: under load a gather takes a few hundred cycles
             constexpr int GD = FEW ? 7 : 3, NGB = GD + 1;
@@ -1203,6 +1216,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 constexpr int u = decltype(uc)::value;
                 gather(G[u], unit_at(std::integral_constant<int, u>{}));
             }, std::make_integer_sequence<int, GD>{});
+            const uint32_t mx = __float_as_uint(mxv);
+            if (__builtin_expect((uint32_t)__builtin_amdgcn_readfirstlane((int)mx) > 0x7f7fffffu, 0)) return false;   // (the same word in every wave: all of them leave here)
+            sc = rescale(mx);
             // Waves of equal priority are served oldest first, so with one fixed priority the younger waves of a SIMD
             // would do most of their step alone after the older ones have finished theirs.  A wave's priority therefore
             // falls as its step advances, a level for every quarter: whoever has more left goes first.
@@ -1217,9 +1233,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             constexpr int u = u0 + decltype(jc)::value;
                             // a streamed unit: the place of the one before it in the ring is free, the unit kPRing - 1 further on goes there
                             if constexpr (!FEW && p_streamed(u)) {
-                                constexpr int m = p_streamed_before(u);
-                                if constexpr (p_streamed_pos(m + kPRing - 1) < NP) request_at(ring[(m + kPRing - 1) % kPRing], p_streamed_pos(m + kPRing - 1));
-                                else request(ring[(m + kPRing - 1) % kPRing], p_streamed_pos(m + kPRing - 1));
+                                constexpr int m = p_streamed_before(u), ahead = p_streamed_pos(m + kPRing - 1);
+                                if constexpr (ahead < NP) request_at(ring[(m + kPRing - 1) % kPRing], ahead);
+                                else request(ring[(m + kPRing - 1) % kPRing], ahead);
                             }
                             // (gathered whether the wave has that unit or not - its registers hold valid sources either way -
                             // so that the number of gathers on their way is a constant too)
@@ -1258,14 +1274,15 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                         }
                     }
                 }
-                // the first streamed units of the next step (every place of the ring is free now)
-                unrolled([&](auto mc) __attribute__((always_inline)) {
-                    constexpr int m = decltype(mc)::value;
-                    request_at(ring[m], p_streamed_pos(m));
-                }, std::make_integer_sequence<int, kPRing - 1>{});
             }
+            // the first streamed units of the next step (every place of the ring is free now)
+            unrolled([&](auto mc) __attribute__((always_inline)) {
+                constexpr int m = decltype(mc)::value, first = p_streamed_pos(m);
+                request_at(ring[m], first);
+            }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
             // an entry below the range: the run gives up (see above)
-            put_max(i, low ? INFINITY : wmax);
+            wmax = wave_max_last(wlow < __float_as_uint(kLinDimP) ? INFINITY : wmax);
+            lds_raise_last(ern + to_word, wmax);
             if constexpr (LEAKY) {
                 wsum = wave_sum(wsum);
                 if (lane == 0) red[32 + (i & 1) * 16 + wave] = wsum;
@@ -1279,7 +1296,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
     }
     // a state below the range in the last step: give up as well (every wave reads the same word)
-    if (ok && !(red[(Tn - 1) % 3] < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
+    if (ok && !(*step_word(Tn - 1) < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
     __builtin_amdgcn_s_setprio(3);
     if (!ok) {
         // every wave has left the time loop at the same step; nothing of this run may still be on its way to LDS or
@@ -2351,7 +2368,7 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
 size_t leaky_linear_lds_bytes(int32_t K, int32_t Ccap, int32_t D, bool backward)
 {
     const size_t XL = ((size_t)K + (size_t)Ccap + 1 + 3) & ~(size_t)3;
-    return (size_t)kXbStride + (XL * (backward ? 4 : 2) + 64 + 3 * (((size_t)D + 1 + 3) & ~(size_t)3)) * 4;
+    return (size_t)kXbStride + (XL * (backward ? 4 : 2) + 64 + 3 * (size_t)prob_row_floats(D)) * 4;
 }
 
 int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
@@ -2371,7 +2388,7 @@ int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
 
 size_t probability_lds_bytes(int32_t D, bool staged)
 {
-    return (size_t)kXbStride + ((size_t)kXsFixed * (staged ? 3 : 1) + 64 + 3 * (((size_t)D + 1 + 3) & ~(size_t)3)) * 4;
+    return (size_t)kXbStride + ((size_t)kXsFixed * (staged ? 3 : 1) + 64 + 3 * (size_t)prob_row_floats(D)) * 4;
 }
 
 unsigned int linear_restarts()

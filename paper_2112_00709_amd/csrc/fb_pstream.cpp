@@ -428,6 +428,8 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
         }
     }
     if (cost < 0) { why = "more slices than the waves have close words for"; return false; }
+    // (a wave's slices whose rows take several lanes come first: the kernel then knows them by their number)
+    for (auto &m : mine) std::stable_partition(m.begin(), m.end(), [&](int sl) { return slices[sl].lg > 0; });
 
     // ---- trade rows between the halves of slices that both rows fit until each half's arcs are spread evenly over the banks
     // (one lane per row only: the rows of a slice of wider rows share their half anyway)
