@@ -220,8 +220,8 @@ static_assert(kPPatterned - p_streamed_before(kPPatterned) == kPResident, "the p
 constexpr int kPFew = 16;
 constexpr int kPMaxClose = 8;     // slices per wave and step
 constexpr int kPMaxUnits = 128;   // units per wave and step
-// its emission rows in LDS: D entries, the one that the dump slot takes, ..., the word of a step's maximum in the last place
-constexpr int prob_row_floats(int D) { return (D + 2 + 3) & ~3; }
+// its emission rows in LDS: D entries, the one that the dump slot takes, ..., the row's largest emission, the step's maximum
+constexpr int prob_row_floats(int D) { return (D + 3 + 3) & ~3; }
 
 struct PWaveDesc {
     int64_t unit_base;            // first unit of the wave in `units` (units of 3 x 64 words)

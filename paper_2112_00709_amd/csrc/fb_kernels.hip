@@ -675,10 +675,10 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
 // data-moving wave copies rows out either way); shifts and log Z as there.
 // LDS: xb, the previous / current vector, kXsFixed floats each at addresses 0 and kXbStride; bh 2 x kXsFixed behind
 // them (rows on their way out that are not the vector itself: beta before the emission is applied, or either
-// direction's rows as logarithms; absent otherwise); red 64 floats (0-2 step maxima, 4-6 the frames' emission maxima
-// in log2 units, 3 and 7 scratch of the first frame, 32-63 the last reduction); er 3 x Es floats, Es = D + 1
-// rounded up to 4: the emissions as given of the frame in use and of the next two, entry D = -inf (what the dump
-// slot "emits").
+// direction's rows as logarithms; absent otherwise); red 64 floats (3 and 7 scratch of the first frame, 4 the largest
+// emission of the first, later of the last frame, 32-63 the last reduction); er 3 x Es floats, Es = D + 3 rounded up
+// to 4: the emissions as given of the frame in use and of the next two, entry D = -inf (what the dump slot "emits"), in
+// the last two places the row's largest emission in log2 units and the largest entry of the vector of its step.
 // ---------------------------------------------------------------------------
 __device__ unsigned int g_linear_restarts;   // diagnostic: sequences (x directions) given up by linear_run since the library was loaded
 
@@ -800,11 +800,11 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const int n_row_stores = out_row0 ? K / (4 * kWave) : 0;
     const bool em_pieces16 = (P.D & 3) == 0 && ((uintptr_t)em_seq & 15) == 0;
     const int n_requests = em_pieces16 ? (P.D + 4 * kWave - 1) / (4 * kWave) : (P.D + kWave - 1) / kWave;
-    // A staged frame's row of emissions -> the factors its states take, 2^(emission - the largest), in place; returns the
-    // largest, in log2 units (0 if there is none above zero-bar).  The largest over all pdfs, whether a state of the graph is
-    // tied to them or not: any scale serves.  16 bytes per lane and read (the arc-walking waves keep the LDS queue full: few,
-    // wide reads); what lies behind the row in its last group becomes zero.  By this wave, which has the time, so that an
-    // exponential is taken per pdf and not per state and a row's close waits for nothing but one read.
+    // The largest emission of a staged frame, in log2 units (0 if there is none above zero-bar).  Over all pdfs, whether a
+    // state of the graph is tied to them or not: any scale serves.  16 bytes per lane and read (the arc-walking waves keep
+    // the LDS queue full: few, wide reads).  (The factors 2^(emission - largest) are raised where a row closes.  Raised here
+    // as well, an exponential per pdf and not per state, a step of 3022 states is 1 % faster with 84 pdfs, but one of 6000
+    // states 9 % slower with 3000, and one of 2000 states 7 %: this wave is then what the others wait for.)
     auto last_piece = [&](const float *row, int e0) {
         const int e = e0 + 4 * lane;
         float4 v = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -832,24 +832,6 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         m = tmax3(tmax3(m, v.x, v.y), v.z, v.w);
         m = lane_value(wave_max_last(m), kWave - 1) * (float)kLog2e;
         return m > -INFINITY ? m : 0.0f;
-    };
-    auto to_factors = [&](float *row, float em) {
-        auto raised = [&](float4 v) {
-            return float4{fexp2(fmaf(v.x, (float)kLog2e, -em)), fexp2(fmaf(v.y, (float)kLog2e, -em)),
-                          fexp2(fmaf(v.z, (float)kLog2e, -em)), fexp2(fmaf(v.w, (float)kLog2e, -em))};
-        };
-        float4 *r4 = (float4 *)row + lane;
-        const int n_full = nE / (4 * kWave);
-        in_groups(n_full, [&](auto nc, int q) __attribute__((always_inline)) {
-            constexpr int n = decltype(nc)::value;
-            float4 v[n];
-#pragma unroll
-            for (int u = 0; u < n; ++u) v[u] = r4[(q + u) * kWave];
-#pragma unroll
-            for (int u = 0; u < n; ++u) r4[(q + u) * kWave] = raised(v[u]);
-        });
-        const float4 v = last_piece(row, n_full * 4 * kWave);
-        if (n_full * 4 * kWave + 4 * lane < Es) r4[n_full * kWave] = raised(v);
     };
     const CloneDesc *cdesc = S.clones;
     // a finished vector -> global memory, coalesced; a cloned state leaves as the sum of its clones.  Either as it is
@@ -925,7 +907,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const double cum_shift = out_lin ? (double)kLinBias : 0.0;
 
     // ---- first frame of this direction: the start weights and the frame's emissions, relative to their maximum
-    if (tid < 3) *step_word(tid) = 0.0f;
+    if (tid < 3) {
+        *step_word(tid) = 0.0f;
+        er[tid * Es + P.D] = -INFINITY;   // what the dump slot "emits" (staging never writes there): its entry stays zero
+    }
     if (tid < 8) red[tid] = (tid == 7 || tid == 3) ? -INFINITY : 0.0f;
     if constexpr (LEAKY) {
         for (int k = tid; k < nX; k += NT) qt[k] = R_.rank1[k];
@@ -939,7 +924,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         const float e0 = emax_of(er);
         const float e1 = Tn > 1 ? emax_of(er + Es) : 0.0f;
         if (lane == 0) { emaxw[0] = e0; emaxw[1] = e1; }
-        if (Tn > 1) to_factors(er + Es, e1);
+        if (Tn > 1 && lane == 0) er[Es + Es - 2] = e1;
         if (Tn > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
     }
     __syncthreads();
@@ -1004,30 +989,39 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             if (off_seq) off_seq[frame(0)] = csum * (double)R_.out_scale;
             if (R_.cum) R_.cum[(size_t)b * P.N + frame(0)] = (float)(csum - cum_shift);
         }
+        float e_prev = emx0, e_cur = Tn > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
+        float *row_a = er, *row_b = er + Es, *row_c = er + 2 * Es;   // rows of frame i - 1 (from step i on: i + 2), i, i + 1
         for (int i = 1; i < Tn; ++i) {
             const int cur = (i - 1) & 1;
-            const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(*step_word(i - 1)));
+            const float mxv = row_a[Es - 1];
+            const bool more = i + 2 < Tn;
+            // (the word of step i - 1 lies behind what is staged)
+            if (more) stage(frame(i + 2), row_a);   // buffer of frame i-1: no longer read
+            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
+            const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(mxv));
             if (mx > 0x7f7fffffu) { ok = false; break; }
             const float nls = mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
-            c = nls + emaxw[(bwd ? i - 1 : i) % 3];
+            c = nls + (bwd ? e_prev : e_cur);
             csum += (double)c;
             if (lane == 0) {
                 if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
                 if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
             }
-            const bool more = i + 2 < Tn;
-            if (more) stage(frame(i + 2), er + ((i + 2) % 3) * Es);   // buffer of frame i-1: no longer read
-            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
+            if (mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
+            e_prev = e_cur;
             if (i + 1 < Tn) {
                 staged_before(n_row_stores + (more ? n_requests : 0));   // frame i+1, requested a whole step ago, is in LDS
-                const float en = emax_of(er + ((i + 1) % 3) * Es);
-                if (lane == 0) emaxw[(i + 1) % 3] = en;   // (the word of frame i - 2: read for the last time in step i - 1)
-                to_factors(er + ((i + 1) % 3) * Es, en);
+                e_cur = emax_of(row_c);
+                if (lane < 2) row_c[Es - 2 + lane] = lane ? 0.0f : e_cur;   // and the word of step i + 1 starts empty
             }
-            if (mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(step_word(i), INFINITY);
             if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
+            float *const t = row_a;
+            row_a = row_b;
+            row_b = row_c;
+            row_c = t;
             lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
+        if (lane == 0) emaxw[0] = e_prev;   // that of the last frame, for log Z
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
@@ -1109,7 +1103,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         typedef const __attribute__((address_space(3))) float lds_cf;
         const uint32_t row_bytes = (uint32_t)Es * 4u, row_first = (uint32_t)(uintptr_t)(lds_cf *)er, row_end = row_first + 3u * row_bytes;
         uint32_t row_cur = row_first;   // the emission row of the frame in hand
-        uint32_t to_word = row_bytes - 4u;
+        uint32_t to_word = row_bytes - 8u;   // of a row: its largest emission, then the word of the step's maximum
         asm volatile("" : "+v"(to_word));   // (a vector register: what is added to it is then no scalar addition)
 
         // Two steps, one after the other, are two copies of the code: which buffer holds the previous step's vector is then
@@ -1125,11 +1119,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // the wave's constants, opaque at every step: what is derived from them is computed where it is used (a
             // scalar instruction or two) instead of being kept in scalar registers that do not exist
             asm volatile("" : "+s"(m_lo), "+s"(m_hi), "+s"(m1_lo), "+s"(m1_hi), "+s"(lg_lo), "+s"(n_units), "+s"(last_spos));
-            const float mxv = *(lds_cf *)(uintptr_t)(row_cur + to_word);
+            const float mxv = *(lds_cf *)(uintptr_t)(row_cur + to_word + 4u);
             row_cur += row_bytes;
             row_cur = row_cur == row_end ? row_first : row_cur;
-            const uint32_t ern = row_cur;   // the frame's emission factors
-            // the close word in use, and the emission factor of its rows: asked for when the slice before has closed
+            const uint32_t ern = row_cur;   // the frame's emissions
+            const float emx = *(lds_cf *)(uintptr_t)(ern + to_word);
+            // the close word in use, and the emission of its rows: asked for when the slice before has closed
             uint32_t cw = cwv[0];
             float pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
             float sc = 1.0f;
@@ -1183,7 +1178,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                     q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
                 }
                 const float pb = acc * sc;
-                const float px = pb * pe;
+                const float px = pb * fexp2(fmaf(pe, (float)kLog2e, -emx));
                 pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
                 if constexpr (LEAKY) {   // (a row spread over several lanes counts once)
                     const float mine = (lane & ((1 << lg) - 1)) == 0 ? px : 0.0f;
@@ -1282,7 +1277,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
             // an entry below the range: the run gives up (see above)
             wmax = wave_max_last(wlow < __float_as_uint(kLinDimP) ? INFINITY : wmax);
-            lds_raise_last(ern + to_word, wmax);
+            lds_raise_last(ern + to_word + 4u, wmax);
             if constexpr (LEAKY) {
                 wsum = wave_sum(wsum);
                 if (lane == 0) red[32 + (i & 1) * 16 + wave] = wsum;
@@ -1321,7 +1316,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
         float *rm = red + 32, *rs = rm + NW;
-        const float em_last = emaxw[(Tn - 1) % 3];
+        const float em_last = emaxw[0];
         if (lane == 0) { rm[wave] = m; rs[wave] = s; }
         __syncthreads();
         if (io_wave && lane == 0) {   // the lane that holds the sum of the offsets
