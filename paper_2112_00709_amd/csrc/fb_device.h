@@ -183,6 +183,26 @@ __device__ __forceinline__ float wave_max_last(float v)
     return v;
 }
 
+// Sums likewise, always in the same order: of 16 lanes in the last of them, of the wave in lane 63.
+__device__ __forceinline__ float row_sum_last(float v)
+{
+    asm volatile("s_nop 1\n\t"
+                 "v_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\ts_nop 1"
+                 : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ float wave_sum_last(float v)
+{
+    v = row_sum_last(v);
+    asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1\n\t"
+                 "v_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf\n\ts_nop 1"
+                 : "+v"(v));
+    return v;
+}
+
 // The word in LDS raised to v, by the lanes that call.  In assembly: for the builtin the compiler first reduces over the
 // lanes that are on, in a loop, although a single one is.  The caller's next barrier has to be lds_barrier(), whose wait
 // does not depend on what the compiler knows of.

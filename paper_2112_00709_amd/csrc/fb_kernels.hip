@@ -1134,12 +1134,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             uint32_t wlow = 0x7f800000u;
             float acc = 0.0f;
             // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
-            float leaked = 0.0f, q_next = 0.0f;
+            float leaked = 0.0f, q_next = 0.0f, slot = 0.0f;
             if constexpr (LEAKY) {
-                const float4 *sl = (const float4 *)(red + 32 + ((i - 1) & 1) * 16);
-                const float4 s0 = sl[0], s1 = sl[1], s2 = sl[2], s3 = sl[3];
-                leaked = P.leak * ((((s0.x + s0.y) + (s0.z + s0.w)) + ((s1.x + s1.y) + (s1.z + s1.w))) +
-                                   (((s2.x + s2.y) + (s2.z + s2.w)) + ((s3.x + s3.y) + (s3.z + s3.w))));
+                slot = red[32 + cur * 16 + (lane & 15)];
                 wsum = 0.0f;
                 q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
             }
@@ -1165,9 +1162,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // a slice ends: the lanes of a row are added up, the row is rescaled, takes its emission, is stored
             auto close_slice = [&]() __attribute__((always_inline)) {
                 const uint32_t tgt = cw & 0xffffu;
-                int lg = 0;
+                float share = 1.0f;   // (leaky: a row spread over several lanes, all of which hold it, counts once)
                 if (__builtin_expect(nclose < n_wide, 0)) {
-                    lg = (int)((lg_lo >> (3 * nclose)) & 7u);
+                    const int lg = (int)((lg_lo >> (3 * nclose)) & 7u);
+                    if constexpr (LEAKY) share = __uint_as_float((uint32_t)(127 - lg) << 23);
                     for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
                         acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
                 }
@@ -1180,10 +1178,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 const float pb = acc * sc;
                 const float px = pb * fexp2(fmaf(pe, (float)kLog2e, -emx));
                 pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
-                if constexpr (LEAKY) {   // (a row spread over several lanes counts once)
-                    const float mine = (lane & ((1 << lg) - 1)) == 0 ? px : 0.0f;
-                    wsum = bwd ? fmaf(fabsf(q), mine, wsum) : wsum + mine;
-                }
+                if constexpr (LEAKY) wsum = fmaf(bwd ? fabsf(q) * share : share, px, wsum);
                 *(lds_f *)(uintptr_t)(tgt + (uint32_t)(nxt * kXbStride)) = px;
                 if (staged) {   // (uniform) what leaves the kernel for this row
                     const float o = bwd ? pb : px;
@@ -1214,6 +1209,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             const uint32_t mx = __float_as_uint(mxv);
             if (__builtin_expect((uint32_t)__builtin_amdgcn_readfirstlane((int)mx) > 0x7f7fffffu, 0)) return false;   // (the same word in every wave: all of them leave here)
             sc = rescale(mx);
+            if constexpr (LEAKY) leaked = P.leak * lane_value(row_sum_last(slot), 15);
             // Waves of equal priority are served oldest first, so with one fixed priority the younger waves of a SIMD
             // would do most of their step alone after the older ones have finished theirs.  A wave's priority therefore
             // falls as its step advances, a level for every quarter: whoever has more left goes first.
@@ -1279,8 +1275,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             wmax = wave_max_last(wlow < __float_as_uint(kLinDimP) ? INFINITY : wmax);
             lds_raise_last(ern + to_word + 4u, wmax);
             if constexpr (LEAKY) {
-                wsum = wave_sum(wsum);
-                if (lane == 0) red[32 + (i & 1) * 16 + wave] = wsum;
+                wsum = wave_sum_last(wsum);
+                if (lane == kWave - 1) red[32 + nxt * 16 + wave] = wsum;
             }
             lds_barrier();
             return true;
