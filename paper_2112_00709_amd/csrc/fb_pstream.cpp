@@ -412,6 +412,18 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
     std::vector<int32_t> order(items.size());
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return items[a].col.size() > items[b].col.size(); });
+    // (among rows of one length: a row of every bank in turn, so that the 32 lanes of half a slice store to different banks)
+    for (size_t i = 0; i < order.size();) {
+        size_t j = i;
+        while (j < order.size() && items[order[j]].col.size() == items[order[i]].col.size()) ++j;
+        std::vector<std::vector<int32_t>> of_bank(kBanks);
+        for (size_t q = i; q < j; ++q) of_bank[bank_of(items[order[q]].out)].push_back(order[q]);
+        size_t at = i;
+        for (size_t r = 0; at < j; ++r)
+            for (int bk = 0; bk < kBanks; ++bk)
+                if (r < of_bank[bk].size()) order[at++] = of_bank[bk][r];
+        i = j;
+    }
     // (how many arcs a lane takes before a row gets more lanes: fewer make slices that are easier to deal evenly, but
     // fill lanes less well.  2000 states, 20 k arcs: 16 is best, 1200 skewed: 16, 3022 states, 51 k arcs and more: 32.)
     std::vector<PSlice> slices;
@@ -434,12 +446,19 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
     // ---- trade rows between the halves of slices that both rows fit until each half's arcs are spread evenly over the banks
     // (one lane per row only: the rows of a slice of wider rows share their half anyway)
     {
-        auto half_hist = [&](const PSlice &sl, int h, int *hist) {
-            std::fill(hist, hist + kBanks, 0);
-            for (int j = h * kHalf; j < std::min<int>((h + 1) * kHalf, (int)sl.items.size()); ++j)
+        // (first kBanks places: arcs by the bank of their source, then rows by the bank of their target)
+        auto half_hist = [&](const PSlice &sl, int h, int16_t *hist) {
+            std::fill(hist, hist + 2 * kBanks, (int16_t)0);
+            for (int j = h * kHalf; j < std::min<int>((h + 1) * kHalf, (int)sl.items.size()); ++j) {
                 for (int32_t c : items[sl.items[j]].col) ++hist[bank_of(c)];
+                ++hist[kBanks + bank_of(items[sl.items[j]].out)];
+            }
         };
-        auto peak = [&](const int *hist) { return *std::max_element(hist, hist + kBanks); };
+        auto peak = [&](const int16_t *hist) {
+            int16_t m = hist[0];
+            for (int k = 1; k < kBanks; ++k) m = std::max(m, hist[k]);
+            return (int)m;
+        };
         // groups of (slice, half) with the same trip and one lane per row
         std::vector<std::pair<int, int>> halves;
         for (int s = 0; s < (int)slices.size(); ++s)
@@ -447,7 +466,7 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
                 for (int h = 0; h * kHalf < (int)slices[s].items.size(); ++h) halves.push_back({s, h});
         uint64_t rng = 0x9E3779B97F4A7C15ull;
         auto next = [&]() { rng ^= rng << 13; rng ^= rng >> 7; rng ^= rng << 17; return rng; };
-        std::vector<std::vector<int>> hist(halves.size(), std::vector<int>(kBanks));
+        std::vector<std::vector<int16_t>> hist(halves.size(), std::vector<int16_t>(2 * kBanks));
         for (size_t i = 0; i < halves.size(); ++i) half_hist(slices[halves[i].first], halves[i].second, hist[i].data());
         const int64_t tries = std::min<int64_t>(400000, 200 * (int64_t)items.size());
         for (int64_t it = 0; it < tries && halves.size() > 1; ++it) {
@@ -464,14 +483,22 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
             const PItem &ra = items[sa.items[ia]], &rb = items[sb.items[ib]];
             if ((int)ra.col.size() > sb.trip || (int)rb.col.size() > sa.trip) continue;   // each row must fit the other slice
             // what the two halves cost before and after the swap: a half whose fullest bank serves no more arcs than
-            // the slice has steps can be walked without conflicts, the surplus is what counts
-            std::vector<int> &ha = hist[a], &hb = hist[b2];
-            auto cost = [&]() { return std::max(peak(ha.data()), sa.trip) + std::max(peak(hb.data()), sb.trip); };
+            // the slice has steps can be walked without conflicts, the surplus is what counts; and the stores of a close
+            // (to the vector and, backward or where rows leave as logarithms, to the row on its way out) take as many
+            // turns as the fullest bank has targets.  (Counted: of the conflict cycles of a step of 3022 states half were
+            // those of stores, which the arcs' order cannot help.)
+            std::vector<int16_t> &ha = hist[a], &hb = hist[b2];
+            auto cost = [&]() {
+                return std::max(peak(ha.data()), sa.trip) + std::max(peak(hb.data()), sb.trip) +
+                       2 * (peak(ha.data() + kBanks) + peak(hb.data() + kBanks));
+            };
+            const int ta = kBanks + bank_of(ra.out), tb = kBanks + bank_of(rb.out);
             const int before = cost();
             long sq_before = 0, sq_after = 0;
             for (int k = 0; k < kBanks; ++k) sq_before += (long)ha[k] * ha[k] + (long)hb[k] * hb[k];
             for (int32_t c : ra.col) { --ha[bank_of(c)]; ++hb[bank_of(c)]; }
             for (int32_t c : rb.col) { ++ha[bank_of(c)]; --hb[bank_of(c)]; }
+            --ha[ta]; ++hb[ta]; ++ha[tb]; --hb[tb];
             const int after = cost();
             for (int k = 0; k < kBanks; ++k) sq_after += (long)ha[k] * ha[k] + (long)hb[k] * hb[k];
             if (after < before || (after == before && sq_after < sq_before)) {
@@ -479,6 +506,7 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
             } else {   // undo
                 for (int32_t c : ra.col) { ++ha[bank_of(c)]; --hb[bank_of(c)]; }
                 for (int32_t c : rb.col) { --ha[bank_of(c)]; ++hb[bank_of(c)]; }
+                ++ha[ta]; --hb[ta]; --ha[tb]; ++hb[tb];
             }
         }
     }
