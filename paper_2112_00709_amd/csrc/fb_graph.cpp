@@ -163,6 +163,7 @@ void put_pstream(Arena &A, const PStreamHost &h, PStreamDev &d)
     A.put(h.close_words, &d.close_words);
     A.put(h.clones, &d.clones);
     A.put(h.zero_rows, &d.zero_rows);
+    d.paired = h.paired ? 1 : 0;
     d.n_clones = (int32_t)h.clones.size();
     d.n_zero = (int32_t)h.zero_rows.size();
     for (const PWaveDesc &wd : h.waves) d.max_units = std::max(d.max_units, wd.n_units);

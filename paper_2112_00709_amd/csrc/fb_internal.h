@@ -214,10 +214,12 @@ constexpr int p_resident_pos(int q)   // position of the q-th unit that stays in
     return -1;
 }
 static_assert(kPPatterned - p_streamed_before(kPPatterned) == kPResident, "the pattern keeps kPResident units");
-// A plan none of whose waves has more than kPFew units (about 30 k arcs) runs the instantiation that keeps them all in
-// registers: nothing is re-read and gathers run 7 units ahead instead of 3, which is what fits beside 16 units.  2000
-// states, 20 k arcs, 64 x 150 frames, a direction with rows: 297 us in the general instantiation, 260 us in this one.
-constexpr int kPFew = 16;
+// A plan none of whose waves has more than kPFew units (about 26 k arcs), all in pairs, runs the instantiation that keeps
+// them all in registers, their sources taken apart beforehand: nothing is re-read and gathers run 7 units ahead instead of
+// 3, which is what fits beside 16 units.  Up to kPFewMost (about 33 k) one that keeps them as they come.  64 x 150 frames, a
+// direction with rows: 2600 states, 26 k arcs 183 us in the first, 206 in the second; 3000 states, 31 k arcs 215 us in the
+// second, 252 in the general one.
+constexpr int kPFew = 16, kPFewMost = 20;
 constexpr int kPMaxClose = 8;     // slices per wave and step
 constexpr int kPMaxUnits = 128;   // units per wave and step
 // its emission rows in LDS: D entries, the one that the dump slot takes, ..., the row's largest emission, the step's maximum
@@ -235,6 +237,7 @@ struct PWaveDesc {
 
 struct PStreamHost {
     int32_t K = 0, Ccap = 0;      // states, clone slots (the dump slot is K + Ccap)
+    bool paired = false;          // every slice is a whole number of pairs of units, and no wave has more than kPFewMost
     int32_t bias = 0;             // log2 of the scale the kernel keeps its vector at (see linear_run)
     float dim = 0.0f;             // the value below which an entry that is not zero makes a run give up
     std::vector<PWaveDesc> waves; // kNWShared - 1
@@ -252,6 +255,7 @@ struct PStreamDev {
     const int32_t *zero_rows = nullptr;
     int32_t n_clones = 0, n_zero = 0, Ccap = 0, bias = 0;
     int32_t max_units = 0;        // most units of a wave
+    int32_t paired = 0;           // as PStreamHost::paired
     float dim = 0.0f;
 };
 

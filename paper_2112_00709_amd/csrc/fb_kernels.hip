@@ -692,12 +692,12 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)))
 // slots of the previous step up in the same order when a step starts.  q sits in LDS by target; the entry of the slice
 // that closes next is asked for when the one before it has closed.  A clone takes no share of its own (its sign bit
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
-// LOG: rows leave as logarithms.  FEW: no wave has more than kPFew units, so all of them stay in registers, nothing is
-// re-read, and the registers that leaves take gathers further ahead.
-template <bool LEAKY, bool LOG, bool FEW>
+// LOG: rows leave as logarithms.  FEW (kPFew, kPFewMost or 0): no wave has more than that many units, so all of them stay in
+// registers, nothing is re-read, and the registers that leaves take gathers further ahead.
+template <bool LEAKY, bool LOG, int FEW>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
-    constexpr int NW = kNWShared, XF = kXsFixed, R = FEW ? kPFew : kPResident;
+    constexpr int NW = kNWShared, XF = kXsFixed, R = FEW ? FEW : kPResident;
     constexpr int NT = NW * kWave, NC = NW - 1;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1031,18 +1031,19 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         };
         const uint64_t mask0_w = uniform64(wd.close_mask[0]), mask1_w = uniform64(wd.close_mask[1]), lgs_w = uniform64(wd.lgs);
         // (s1: the second source apart from the first, where registers allow it: an address then needs no instruction)
+        constexpr bool kApart = FEW == kPFew;
         struct Unit { uint32_t s, s1; float w0, w1; };
         // Unit u of the wave: three words per lane, read through a buffer descriptor, whose scalar offset is the unit's: a
         // request takes no vector instruction (an address formed from a scalar base and a large constant takes four).
         constexpr int kUnitBytes = 3 * kWave * 4;
         auto units = __builtin_amdgcn_make_buffer_rsrc((void *)(S.units + (size_t)uniform64((uint64_t)wd.unit_base) * (3 * kWave)), 0,
-                                                       max(n_units_w, FEW ? kPFew : kPPatterned) * kUnitBytes, 0x00027000);
+                                                       max(n_units_w, FEW ? FEW : kPPatterned) * kUnitBytes, 0x00027000);
         const int lane12 = lane * 12;
         auto load_unit = [&](Unit &dst, int u) __attribute__((always_inline)) {
             typedef uint32_t u3 __attribute__((ext_vector_type(3)));
             const u3 v = __builtin_amdgcn_raw_buffer_load_b96(units, lane12, u * kUnitBytes, 0);
-            dst.s = FEW ? v.x & 0xffffu : v.x;
-            dst.s1 = FEW ? v.x >> 16 : 0u;
+            dst.s = kApart ? v.x & 0xffffu : v.x;
+            dst.s1 = kApart ? v.x >> 16 : 0u;
             dst.w0 = __uint_as_float(v.y);
             dst.w1 = __uint_as_float(v.z);
         };
@@ -1051,8 +1052,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         // of its use; the first kPRing - 1 of a step when the step before ends.  Every place that asks does so whatever
         // the wave's unit count (for a unit that is not there, the last one again): the number of loads on their way
         // at any point of the code is then a constant, which is what the waits on them are counted by.
-        constexpr int NP = FEW ? kPFew : kPPatterned, H = kPHead, NG = NP - R;   // patterned positions, head, re-read ones among them
-        static_assert(NP <= 64 && NP % 16 == 0 && (FEW || NG >= kPRing - 1), "close bits of the patterned part in one 64-bit word; blocks of 4, a priority level for every quarter");
+        constexpr int NP = FEW ? FEW : kPPatterned, H = kPHead, NG = NP - R;   // patterned positions, head, re-read ones among them
+        static_assert(NP <= 64 && NP % 4 == 0 && (FEW || NG >= kPRing - 1), "close bits of the patterned part in one 64-bit word; blocks of 4");
+        constexpr int kQuarter = (NP / 4 + 3) / 4 * 4;   // a priority level for every quarter, in whole blocks
         // the position of the wave's last re-read unit: what a request for a unit behind it asks for again (a wave
         // without any asks for a unit behind its own: never folded, and the plan has room behind every wave)
         int last_spos = p_streamed_pos(0);
@@ -1154,7 +1156,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             auto gather = [&](float2 &g, const Unit &un) __attribute__((always_inline)) {
                 typedef const __attribute__((address_space(3))) float lds_ct;
                 uint32_t lo = un.s, hi = un.s1;
-                if constexpr (!FEW)
+                if constexpr (!kApart)
                     asm volatile("v_and_b32 %0, %3, %2\n\tv_lshrrev_b32 %1, 16, %2" : "=&v"(lo), "=v"(hi) : "v"(un.s), "s"(low_half));
                 g.x = *(lds_ct *)(uintptr_t)(lo + (uint32_t)(cur * kXbStride));
                 g.y = *(lds_ct *)(uintptr_t)(hi + (uint32_t)(cur * kXbStride));
@@ -1219,7 +1221,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 constexpr int u0 = decltype(kc)::value * 4;
                 if constexpr (u0 < NP) {
                     if (n_units > u0) {
-                        if constexpr (u0 % (NP / 4) == 0 && u0 > 0) __builtin_amdgcn_s_setprio(3 - u0 / (NP / 4));
+                        if constexpr (u0 % kQuarter == 0 && u0 > 0) __builtin_amdgcn_s_setprio(3 - u0 / kQuarter);
                         unrolled([&](auto jc) __attribute__((always_inline)) {
                             constexpr int u = u0 + decltype(jc)::value;
                             // a streamed unit: the place of the one before it in the ring is free, the unit kPRing - 1 further on goes there
@@ -1237,7 +1239,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             asm volatile("" : "+v"(G[u % NGB].x), "+v"(G[u % NGB].y));
                             acc = fmaf(G[u % NGB].x, me.w0, acc);
                             acc = fmaf(G[u % NGB].y, me.w1, acc);
-                            if (__builtin_expect(((u < 32 ? m_lo : m_hi) >> (u & 31)) & 1u, 0)) close_slice();
+                            if constexpr (!FEW || (u & 1)) {   // (slices of pairs of units: PStreamHost::paired)
+                                if (__builtin_expect(((u < 32 ? m_lo : m_hi) >> (u & 31)) & 1u, 0)) close_slice();
+                            }
                         }, std::make_integer_sequence<int, 4>{});
                         self(self, std::integral_constant<int, decltype(kc)::value + 1>{});
                     }
@@ -1336,7 +1340,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     return true;
 }
 
-template <bool LOG, bool FEW>
+template <bool LOG, int FEW>
 __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecParams P)
 {
     __builtin_amdgcn_s_setprio(3);
@@ -1353,7 +1357,7 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
 
 // The leaky-HMM's recursions (both directions, one launch); gave_up[which * B + b]: the run left its range (or the
 // sequence has no frames) and is the plain kernel's.
-template <bool FEW>
+template <int FEW>
 __global__ __launch_bounds__(kNWShared * 64) void fb_leaky_linear_kernel(const RecParams P, int32_t *gave_up)
 {
     __builtin_amdgcn_s_setprio(3);
@@ -2301,9 +2305,11 @@ bool recursion_fixed_available()
     static const bool ok = [] {
         const void *kernels[] = {(const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>,
                                  (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>,
-                                 (const void *)fb_linear_kernel<false, false>, (const void *)fb_linear_kernel<false, true>,
-                                 (const void *)fb_linear_kernel<true, false>, (const void *)fb_linear_kernel<true, true>,
-                                 (const void *)fb_leaky_linear_kernel<false>, (const void *)fb_leaky_linear_kernel<true>};
+                                 (const void *)fb_linear_kernel<false, 0>, (const void *)fb_linear_kernel<false, kPFew>,
+                                 (const void *)fb_linear_kernel<false, kPFewMost>, (const void *)fb_linear_kernel<true, 0>,
+                                 (const void *)fb_linear_kernel<true, kPFew>, (const void *)fb_linear_kernel<true, kPFewMost>,
+                                 (const void *)fb_leaky_linear_kernel<0>, (const void *)fb_leaky_linear_kernel<kPFew>,
+                                 (const void *)fb_leaky_linear_kernel<kPFewMost>};
         for (const void *k : kernels) {
             hipFuncAttributes attr{};
             if (hipFuncGetAttributes(&attr, k) != hipSuccess || attr.sharedSizeBytes != 0) return false;
@@ -2313,12 +2319,12 @@ bool recursion_fixed_available()
     return ok;
 }
 
-// every direction's plan keeps its units in registers
-static bool few_units(const RecParams &p)
+// kPFew or kPFewMost if every direction's plan keeps its units in that many places in registers, else 0
+static int few_units(const RecParams &p)
 {
-    bool few = true;
-    for (int i = 0; i < p.n_dir; ++i) few = few && p.dir[i].prob.max_units <= kPFew;
-    return few;
+    int most = 0;
+    for (int i = 0; i < p.n_dir; ++i) most = p.dir[i].prob.paired ? std::max(most, p.dir[i].prob.max_units) : kPMaxUnits;
+    return most <= kPFew ? kPFew : most <= kPFewMost ? kPFewMost : 0;
 }
 
 int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t lds_bytes, void *stream)
@@ -2334,9 +2340,11 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
                 lds_bytes = std::max(lds_bytes, probability_lds_bytes(p.D, p.dir[i].backward != 0 || logs));
             }
             if (lds_bytes > kLdsBytes) return fail(FB_EHIP, "internal error: probability-domain launch beyond the on-chip memory");
-            if (few_units(p))
-                return logs ? launch_rec(fb_linear_kernel<true, true>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false, true>, nw, p, lds_bytes, stream);
-            return logs ? launch_rec(fb_linear_kernel<true, false>, nw, p, lds_bytes, stream) : launch_rec(fb_linear_kernel<false, false>, nw, p, lds_bytes, stream);
+            const int few = few_units(p);
+            auto kern = few == kPFew ? (logs ? fb_linear_kernel<true, kPFew> : fb_linear_kernel<false, kPFew>)
+                        : few        ? (logs ? fb_linear_kernel<true, kPFewMost> : fb_linear_kernel<false, kPFewMost>)
+                                     : (logs ? fb_linear_kernel<true, 0> : fb_linear_kernel<false, 0>);
+            return launch_rec(kern, nw, p, lds_bytes, stream);
         }
         if (p.linear_w) return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>, nw, p, lds_bytes, stream);
         return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed>, nw, p, lds_bytes, stream);
@@ -2370,7 +2378,8 @@ int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
         lds = std::max(lds, leaky_linear_lds_bytes(p.Kcap, p.dir[i].prob.Ccap, p.D, p.dir[i].backward != 0));
     }
     if (lds > kLdsBytes || !recursion_fixed_available()) return fail(FB_EHIP, "internal error: leaky-HMM launch beyond the on-chip memory");
-    auto kern = few_units(p) ? fb_leaky_linear_kernel<true> : fb_leaky_linear_kernel<false>;
+    const int few = few_units(p);
+    auto kern = few == kPFew ? fb_leaky_linear_kernel<kPFew> : few ? fb_leaky_linear_kernel<kPFewMost> : fb_leaky_linear_kernel<0>;
     const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
     hipLaunchKernelGGL(kern, dim3((unsigned)(p.B * p.n_dir)), dim3(kNWShared * kWave), lds, (hipStream_t)stream, p, gave_up);
