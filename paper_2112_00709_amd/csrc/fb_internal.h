@@ -224,6 +224,8 @@ constexpr int kPMaxClose = 8;     // slices per wave and step
 constexpr int kPMaxUnits = 128;   // units per wave and step
 // its emission rows in LDS: D entries, the one that the dump slot takes, ..., the row's largest emission, the step's maximum
 constexpr int prob_row_floats(int D) { return (D + 3 + 3) & ~3; }
+// the words in front of those rows: 8 of the first and the last frame, two slots a wave
+constexpr int kProbWords = 8 + 2 * kNWShared;
 
 struct PWaveDesc {
     int64_t unit_base;            // first unit of the wave in `units` (units of 3 x 64 words)

@@ -675,9 +675,9 @@ __device__ __forceinline__ void recursion_run(const RecParams &P, const int b, c
 // data-moving wave copies rows out either way); shifts and log Z as there.
 // LDS: xb, the previous / current vector, kXsFixed floats each at addresses 0 and kXbStride; bh 2 x kXsFixed behind
 // them (rows on their way out that are not the vector itself: beta before the emission is applied, or either
-// direction's rows as logarithms; absent otherwise); red 64 floats (3 and 7 scratch of the first frame, 4 the largest
-// emission of the first, later of the last frame, 32-63 the last reduction); er 3 x Es floats, Es = D + 3 rounded up
-// to 4: the emissions as given of the frame in use and of the next two, entry D = -inf (what the dump slot "emits"), in
+// direction's rows as logarithms; absent otherwise); red kProbWords floats (3 and 7 scratch of the first frame, 4 the
+// largest emission of the first, later of the last frame, 5 that of the second, behind them the slots: the leaky mode's
+// sums, at the end the last reduction); er 3 x Es floats, Es = D + 3 rounded up to 4: the emissions as given of the frame in use and of the next two, entry D = -inf (what the dump slot "emits"), in
 // the last two places the row's largest emission in log2 units and the largest entry of the vector of its step.
 // ---------------------------------------------------------------------------
 __device__ unsigned int g_linear_restarts;   // diagnostic: sequences (x directions) given up by linear_run since the library was loaded
@@ -725,8 +725,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const int XL = LEAKY ? (nX + 3) & ~3 : XF;   // floats of a buffer behind the first (leaky: q needs the room)
     float *bh = xb + Xs + XL;
     float *red = staged ? bh + 2 * XL : bh;
-    float *qt = red + 64;                        // leaky only: q by target
-    float *er = LEAKY ? qt + XL : red + 64;
+    float *slots = red + 8;
+    float *qt = red + kProbWords;                // leaky only: q by target
+    float *er = LEAKY ? qt + XL : red + kProbWords;
     float *emaxw = red + 4;
 
     const float *em_seq = P.emis + (size_t)b * P.N * P.D;
@@ -914,7 +915,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     if (tid < 8) red[tid] = (tid == 7 || tid == 3) ? -INFINITY : 0.0f;
     if constexpr (LEAKY) {
         for (int k = tid; k < nX; k += NT) qt[k] = R_.rank1[k];
-        if (tid < 2) red[32 + tid * 16 + NC] = 0.0f;   // (the data-moving wave writes no rows)
+        if (tid < 2) slots[tid * NW + NC] = 0.0f;   // (the data-moving wave writes no rows)
     }
     __syncthreads();
     if (io_wave) {
@@ -965,7 +966,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     }
     if constexpr (LEAKY) {
         wsum = wave_sum(wsum);
-        if (lane == 0) red[32 + wave] = wsum;
+        if (lane == 0) slots[wave] = wsum;
     }
     for (int k = tid; k < nC; k += NT) {   // clones start empty: the state itself holds the start weight
         xb[K + k] = 0.0f;
@@ -1014,7 +1015,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 e_cur = emax_of(row_c);
                 if (lane < 2) row_c[Es - 2 + lane] = lane ? 0.0f : e_cur;   // and the word of step i + 1 starts empty
             }
-            if (LEAKY && lane == 0) red[32 + (i & 1) * 16 + NC] = 0.0f;
+            if (LEAKY && lane == 0) slots[(i & 1) * NW + NC] = 0.0f;
             float *const t = row_a;
             row_a = row_b;
             row_b = row_c;
@@ -1138,7 +1139,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
             float leaked = 0.0f, q_next = 0.0f, slot = 0.0f;
             if constexpr (LEAKY) {
-                slot = red[32 + cur * 16 + (lane & 15)];
+                slot = slots[cur * NW + (lane & (NW - 1))];
                 wsum = 0.0f;
                 q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
             }
@@ -1280,7 +1281,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_raise_last(ern + to_word + 4u, wmax);
             if constexpr (LEAKY) {
                 wsum = wave_sum_last(wsum);
-                if (lane == kWave - 1) red[32 + nxt * 16 + wave] = wsum;
+                if (lane == kWave - 1) slots[nxt * NW + wave] = wsum;
             }
             lds_barrier();
             return true;
@@ -1315,7 +1316,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
-        float *rm = red + 32, *rs = rm + NW;
+        float *rm = slots, *rs = rm + NW;
         const float em_last = emaxw[0];
         if (lane == 0) { rm[wave] = m; rs[wave] = s; }
         __syncthreads();
@@ -2367,7 +2368,7 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
 size_t leaky_linear_lds_bytes(int32_t K, int32_t Ccap, int32_t D, bool backward)
 {
     const size_t XL = ((size_t)K + (size_t)Ccap + 1 + 3) & ~(size_t)3;
-    return (size_t)kXbStride + (XL * (backward ? 4 : 2) + 64 + 3 * (size_t)prob_row_floats(D)) * 4;
+    return (size_t)kXbStride + (XL * (backward ? 4 : 2) + kProbWords + 3 * (size_t)prob_row_floats(D)) * 4;
 }
 
 int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
@@ -2388,7 +2389,7 @@ int launch_leaky_linear(const RecParams &p, int32_t *gave_up, void *stream)
 
 size_t probability_lds_bytes(int32_t D, bool staged)
 {
-    return (size_t)kXbStride + ((size_t)kXsFixed * (staged ? 3 : 1) + 64 + 3 * (size_t)prob_row_floats(D)) * 4;
+    return (size_t)kXbStride + ((size_t)kXsFixed * (staged ? 3 : 1) + kProbWords + 3 * (size_t)prob_row_floats(D)) * 4;
 }
 
 unsigned int linear_restarts()

@@ -48,6 +48,20 @@ def test_large_graphs(K, D, kind, leak):
     _compare(g, D, emis, lengths, leak)
 
 
+@pytest.mark.parametrize("K,D", [(6000, 2895), (6000, 2894), (5998, 2898)])
+def test_the_largest_rows_that_fit_on_chip_memory(K, D):
+    """Four vectors of K + 1 floats and three emission rows behind the first vector's 32 KB: 160 KB is what a workgroup
+    has.  The fast form's workspace, larger than the plain kernel's, says that it serves the call."""
+    import paper_2112_00709_amd as fb
+    rng = np.random.default_rng(K + D)
+    g = wl.random_graph(rng, K, D, mean_extra_deg=3.0)
+    G = fb.graph_from(g, D)
+    assert fb.fb_leaky_workspace_bytes(G, 2, 6) > (4 * 2 * 6 * K + 255) // 256 * 256
+    G.destroy()
+    emis = (rng.standard_normal((2, 6, D)) * 2).astype(np.float32)
+    _compare(g, D, emis, np.array([6, 3], dtype=np.int32), 1e-3)
+
+
 def test_sequences_that_leave_the_range():
     """An unused pdf far above the others: the fast form gives those sequences up, the plain kernel redoes them, the
     rest stay; a frame nobody can emit has no path."""
