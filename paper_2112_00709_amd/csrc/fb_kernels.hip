@@ -740,7 +740,6 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     auto step_word = [&](int i) { return er + (i % 3) * Es + Es - 1; };
     const int kLinBias = S.bias - (LEAKY ? kLeakyBiasDrop : 0);
     const float kLinDimP = S.dim;
-    const float unbias = __uint_as_float((uint32_t)(127 - kLinBias) << 23);   // 2^-bias
     // A step maximum, as its bits: it is never negative, and the bits of such floats have their order.  The run cannot go on
     // from one that is not finite: a lane has given up (+inf).  Below mx_floor the vector fell more than 126 binary orders in
     // one step and its rescaling would not be a float: the data-moving wave then gives up for the step that follows.
@@ -840,10 +839,11 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // exponent and the mantissa taken apart first so that neither an entry far below the scale is lost nor the
     // entries near it are rounded at the magnitude of the bias.
     constexpr bool out_lin = !LOG;
-    auto to_log = [&](float v) {
+    auto log2_of = [&](float v) {
         const float e = (float)(__builtin_amdgcn_frexp_expf(v) - kLinBias);   // (v = 0: -inf comes from the mantissa)
-        return (e + flog2(__builtin_amdgcn_frexp_mantf(v))) * R_.out_scale;
+        return e + flog2(__builtin_amdgcn_frexp_mantf(v));
     };
+    auto to_log = [&](float v) { return log2_of(v) * R_.out_scale; };
     // (rows that leave as logarithms were staged in that form by the waves that formed them: a plain copy either way)
     auto write_row = [&](int f, const float *srcv) {
         if (!out_row0) return;
@@ -1308,11 +1308,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const float *xl = xb + last * Xs;
     if (io_wave) write_row(frame(Tn - 1), staged ? bh + last * XL : xl);
     if (R_.logz) {
+        // (the last vector has not been rescaled: its entries x 2^-bias need not be floats)
         float m = kNegBig, s = 0.0f;
-        for (int k = tid; k < K; k += NT) lse_add(m, s, flog2(xl[k] * unbias) + R_.obound[k]);
+        for (int k = tid; k < K; k += NT) lse_add(m, s, log2_of(xl[k]) + R_.obound[k]);
         for (int j = tid; j < S.n_clones; j += NT) {   // clones end with their state's weight
             const CloneDesc cd = cdesc[j];
-            for (int i = 0; i < cd.count; ++i) lse_add(m, s, flog2(xl[K + cd.first + i] * unbias) + R_.obound[cd.state]);
+            for (int i = 0; i < cd.count; ++i) lse_add(m, s, log2_of(xl[K + cd.first + i]) + R_.obound[cd.state]);
         }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
