@@ -34,10 +34,13 @@ def _compare(g, D, emis, lengths, leak):
 
 
 @pytest.mark.parametrize("leak", [0.0, 1e-5, 0.3, 1.0])
-@pytest.mark.parametrize("K,D,kind", [(1025, 5, "uniform"), (1501, 84, "hubs"), (3500, 1000, "clones")])
+@pytest.mark.parametrize("K,D,kind", [(1025, 5, "uniform"), (1501, 84, "hubs"), (3500, 1000, "clones"), (1537, 84, "dense"), (3003, 90, "many")])
 def test_large_graphs(K, D, kind, leak):
+    """The kernel of up to 16 units a wave (the first two), the general one, and that of up to 20: rows over two lanes
+    in both directions (dense), rows of one lane (many)."""
     rng = np.random.default_rng(K)
-    g = wl.random_graph(rng, K, D, mean_extra_deg=9.0 if kind == "clones" else 4.0, zipf_s={"uniform": None, "hubs": 1.1, "clones": 1.1}[kind])
+    deg = {"clones": 9.0, "dense": 19.0, "many": 9.6}.get(kind, 4.0)
+    g = wl.random_graph(rng, K, D, mean_extra_deg=deg, zipf_s=1.1 if kind in ("hubs", "clones") else None)
     if kind == "clones":
         assert np.bincount(g.dst, minlength=K).max() > 2048       # a row of several clones
     g.init[:] = np.log(rng.dirichlet(np.full(K, 0.05))).astype(np.float32)    # most of the leak goes to a few states

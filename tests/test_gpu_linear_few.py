@@ -1,5 +1,6 @@
-"""The probability-domain recursion where a wave's units all stay in registers (at most 16 per wave) and just beyond:
-the edges of that rule, one arc a row and rows over many lanes, both row forms, against the oracle."""
+"""The probability-domain recursion where a wave's units all stay in registers: at most 16 per wave (the first four
+graphs and the last) or at most 20 (the others), slices of whole pairs of units; one arc a row and rows over many lanes,
+both row forms, against the oracle."""
 import numpy as np
 import pytest
 

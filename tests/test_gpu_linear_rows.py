@@ -53,20 +53,26 @@ def test_emission_rows_and_rows_of_states(K, deg, zipf, D):
     G.destroy()
 
 
-def test_rows_of_a_stream_of_frames_stay_what_they_were():
-    """Rows leave by 16-byte stores whose registers are used again at once: three calls give the same bytes, and the same
-    as a batch of one gives."""
+@pytest.mark.parametrize("K,deg", [(2500, 9.0), (3003, 9.6), (2303, 14.0), (3500, 13.0)])
+def test_rows_of_a_stream_of_frames_stay_what_they_were(K, deg):
+    """Rows leave by 16-byte stores whose registers are used again at once: they are the oracle's, three calls give the same
+    bytes, and a batch of one gives the same.  The kernels of up to 16 and up to 20 units a wave and, twice, the general one;
+    rows of whole groups of eight pieces, with and without a partial group behind them."""
     import torch
 
     import paper_2112_00709_amd as fb
     rng = np.random.default_rng(8)
     D = 84
-    den = wl.random_graph(rng, 2303, D, mean_extra_deg=14.0)
+    den = wl.random_graph(rng, K, D, mean_extra_deg=deg)
     emis = (rng.standard_normal((8, 60, D)) * 2).astype(np.float32)
-    e, l = torch.from_numpy(emis).cuda(), torch.full((8,), 60, dtype=torch.int32).cuda()
+    lengths = np.full(8, 60, dtype=np.int32)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    ref = oracle.forward_backward(den, emis, lengths)
     G = fb.graph_from(den, D)
-    for call in (fb.fb_alpha, fb.fb_beta):
-        first = call(G, e, l)[0].clone()
+    for call, want in ((fb.fb_alpha, ref.alpha), (fb.fb_beta, ref.beta)):
+        first, shift, _ = call(G, e, l)
+        first = first.clone()
+        _rows_agree(first.cpu().numpy(), shift.cpu().numpy(), want, lengths)
         for _ in range(2):
             assert torch.equal(call(G, e, l)[0], first)
         for q in (0, 7):
