@@ -709,10 +709,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const int Tn = min(max(P.lengths[b], 0), P.N);
     const int nE = P.D;
     const int nX = K + nC + 1;                   // states, clone slots, dump slot
-    // the two buffers of the vector in use lie kXbStride bytes apart, further than a buffer is long and a power of two:
-    // an arc's source (an offset into a buffer) and the buffer's address then combine by OR
+    // the two buffers of the vector in use lie kXbStride bytes apart, at least a buffer's length: a source or a target is
+    // an offset into a buffer, and which buffer is the constant offset of an LDS instruction, 16 bits
     constexpr int Xs = kXbStride / 4;
-    static_assert(kXbStride >= XF * 4 && (kXbStride & (kXbStride - 1)) == 0 && 2 * kXbStride <= 0x10000, "buffer stride");
+    static_assert(kXbStride >= XF * 4 && kXbStride < 0x10000, "buffer stride");
     const int Es = prob_row_floats(P.D);
     if (Tn <= 0) return false;                   // (nothing to run: the log form writes the empty results)
 

@@ -7,15 +7,17 @@
 // ordinary arithmetic: the stream carries 2^w.
 //
 // Shape of the plan.
-//   * A slice is 64 lanes walking arcs in lockstep.  A row of up to kPChunk arcs takes one lane, a longer
+//   * A slice is 64 lanes walking arcs in lockstep.  A row of up to `chunk` arcs takes one lane, a longer
 //     one 2, 4, ... 64 lanes of one slice (all rows of a slice take the same number of lanes, the kernel
-//     adds the lanes of a row up when the slice ends); a row too long even for 64 lanes is cloned as in
+//     adds the lanes of a row up when the slice ends); chunk is kPChunk or, where that deals the slices to the
+//     waves more evenly, 5/8, 1/2 or 3/8 of it.  A row too long even for 64 lanes of kPChunk is cloned as in
 //     fb_sell.cpp.  Rows are sorted by length; rows without arcs of non-zero weight are left out.
 //   * Arcs travel in pairs: a unit is, per lane, three 32-bit words {source of arc 0 | source of arc 1 << 16,
 //     2^w of arc 0, 2^w of arc 1} (6 bytes per arc), sources being byte offsets into the state buffer.  A
-//     slice is a whole number of units (its lanes are padded with arcs of weight 0), and a wave's time step
-//     is the units of its slices one after the other.  Of a wave's first kPPatterned units kPResident stay
-//     in registers for the whole time loop (which ones: p_streamed), the rest is re-read from L2 every step.
+//     slice is a whole number of units (its lanes are padded with arcs of weight 0), of pairs of units where no
+//     wave has more than kPFewMost, and a wave's time step is the units of its slices one after the other.
+//     Those few units all stay in registers for the whole time loop; of a longer wave's first kPPatterned units
+//     kPResident do (which ones: p_streamed), the rest is re-read from L2 every step.
 //   * When a slice ends, every lane holds a row's sum (or a share of it) and needs to know where it goes and
 //     which emission it takes: one 32-bit "close word" per lane and slice {target byte offset | emission
 //     byte offset << 16}, kept in registers too (at most kPMaxClose slices per wave).  Which units end a
@@ -432,7 +434,12 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
     // (Slices of four arcs a lane, i.e. of pairs of units, where all of a wave's units then stay in registers: the kernel
     // asks at every other unit only whether a slice ends, a scalar instruction and a branch each, which is worth more there
     // than the arcs of padding.  2000 states, 20 k arcs, 64 x 150 frames 199 -> 179 us a direction; in the general
-    // instantiation, 3022 states, 51 k arcs, 128 x 300 frames, 572 -> 627.)
+    // instantiation, 3022 states, 51 k arcs, 128 x 300 frames, 572 -> 627.  Against the same kernels asking at every unit,
+    // backward: rows of few arcs, which are padded most, 6000 states, 18 k arcs 257 / 274, 5000, 20 k 241 / 256, 1200,
+    // 3.6 k 188 / 186; 3000, 30 k 225 / 238; 5400, 25 k 267 / 266; the worst met, 6000, 30 k, 313 / 296.
+    // The directions of a graph decide apart.  Where one of them has pairs and the other not, a launch of both takes
+    // the general kernel, the padding along: with hub states, 3000 to 5400 states, 32 to 36 k arcs, LF-MMI and the leaky
+    // mode take the same time with both unpaired, since the unpaired direction is what the launch lasts.)
     for (int whole = 4; whole >= 2 && cost < 0; whole -= 2) {
         for (int chunk : {kPChunk, kPChunk * 5 / 8, kPChunk / 2, kPChunk * 3 / 8}) {
             std::vector<PSlice> sl = make_slices(items, order, chunk, whole);
@@ -498,7 +505,8 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
             // what the two halves cost before and after the swap: a half whose fullest bank serves no more arcs than
             // the slice has steps can be walked without conflicts, the surplus is what counts; and the stores of a close
             // (to the vector and, backward or where rows leave as logarithms, to the row on its way out) take as many
-            // turns as the fullest bank has targets.  (Counted: of the conflict cycles of a step of 3022 states half were
+            // turns as the fullest bank has targets, counted twice.  (Forward, LF-MMI and the leaky mode store once: the
+            // plan is the same for all.)  (Counted: of the conflict cycles of a step of 3022 states half were
             // those of stores, which the arcs' order cannot help.)
             std::vector<int16_t> &ha = hist[a], &hb = hist[b2];
             auto cost = [&]() {
