@@ -1,6 +1,6 @@
 """HBM traffic of the LF-MMI call's kernels from two rocprofv3 counter runs.
 
-Usage (on the GPU machine, from the repository root; one counter per run):
+Usage (from the repository root, on a machine with the GPU; one counter per run):
 
     export FB_AMD_SERIAL=1
     rocprofv3 --pmc FETCH_SIZE -d out/pmc_fetch -o p --output-format csv -- \\
