@@ -371,9 +371,13 @@ int32_t fb_limits_max_states(int32_t D, int shared);
  * the same to rounding either way. */
 int fb_graph_linear_weights(const fb_graph *g);
 
-/* Diagnostic: how many (sequence, direction) runs the probability-domain recursion kernel has given up and
- * redone in the log form since the library was loaded (see fb_graph_linear_weights: form 2).  Synchronises
- * the device. */
+/* Diagnostic: 1 if g is a small shared graph (vectors in double, at most 1024 states) whose sums run on probabilities: every state lies
+ * on or near the one strongly connected part, and the weights are of ordinary size; 0: any other graph; -1: g is NULL. */
+int fb_graph_small_linear(const fb_graph *g);
+
+/* Diagnostic: how many (sequence, direction) runs the probability-domain recursion kernels have given up and
+ * redone in the log form since the library was loaded (see fb_graph_linear_weights: form 2, and
+ * fb_graph_small_linear).  Synchronises the device. */
 int64_t fb_debug_linear_restarts(void);
 
 /* Diagnostic, host only: the cycles the gathers of one time step of the probability-domain kernel take in the

@@ -29,7 +29,7 @@ SYMBOLS = ["fb_graph_create", "fb_graph_destroy", "fb_graph_layout_size", "fb_gr
            "fb_alpha", "fb_beta", "fb_posteriors", "fb_lfmmi_workspace_bytes", "lfmmi_loss_grad", "lfmmi_loss_grad_ragged",
            "fb_limits_max_states", "fb_strerror", "fb_last_error", "fb_graph_schedule_apply_host",
            "fb_profile_enable", "fb_profile_read", "fb_viterbi_workspace_bytes", "fb_viterbi", "fb_graph_linear_weights",
-           "fb_debug_linear_restarts", "fb_graph_plan_cycles", "lfmmi_loss_grad_static", "fb_static_scratch_bytes",
+           "fb_debug_linear_restarts", "fb_graph_small_linear", "fb_graph_plan_cycles", "lfmmi_loss_grad_static", "fb_static_scratch_bytes",
            "fb_leaky_workspace_bytes", "fb_leaky_posteriors"]
 
 
@@ -85,6 +85,8 @@ def lib() -> ctypes.CDLL:
         L.fb_graph_linear_weights.restype = ctypes.c_int
         L.fb_graph_plan_cycles.argtypes = [vp, ctypes.c_int, vp, vp]
         L.fb_graph_plan_cycles.restype = ctypes.c_int
+        L.fb_graph_small_linear.argtypes = [vp]
+        L.fb_graph_small_linear.restype = ctypes.c_int
         L.fb_debug_linear_restarts.argtypes = []
         L.fb_debug_linear_restarts.restype = i64
         L.fb_limits_max_states.argtypes = [i32, ctypes.c_int]
@@ -214,8 +216,13 @@ def fb_graph_plan_cycles(g: Graph, backward: bool):
     return int(c.value), int(f.value)
 
 
+def fb_graph_small_linear(g: Graph) -> int:
+    """Diagnostic: 1 a small shared graph whose sums run on probabilities, 0 any other."""
+    return int(lib().fb_graph_small_linear(g.handle))
+
+
 def fb_debug_linear_restarts() -> int:
-    """Diagnostic: runs the probability-domain kernel has redone in the log form so far (synchronises)."""
+    """Diagnostic: runs the probability-domain kernels have redone in the log form so far (synchronises)."""
     return int(lib().fb_debug_linear_restarts())
 
 

@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfb_amd.so")
 SOURCES = ["fb_kernels.hip", "fb_graph.cpp", "fb_sell.cpp", "fb_stream.cpp", "fb_pstream.cpp", "fb_small.cpp", "fb_api.cpp", "fb_leaky.hip",
-           "fb_small.hip", "fb_post_small.hip"]
+           "fb_small.hip", "fb_small_linear.hip", "fb_post_small.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -26,7 +26,7 @@ def is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "fb_internal.h"), os.path.join(CSRC, "fb_device.h"), os.path.join(HERE, "..", "include", "fb.h")]
+    deps = sources() + [os.path.join(CSRC, h) for h in ("fb_internal.h", "fb_device.h", "fb_small_run.h")] + [os.path.join(HERE, "..", "include", "fb.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

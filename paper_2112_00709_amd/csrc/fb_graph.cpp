@@ -216,7 +216,9 @@ const char *fb_strerror(int code)
 
 int fb_graph_linear_weights(const fb_graph *g) { return g ? (g->linear_p ? 2 : g->linear_w ? 1 : 0) : -1; }
 
-int64_t fb_debug_linear_restarts(void) { return (int64_t)linear_restarts(); }
+int64_t fb_debug_linear_restarts(void) { return (int64_t)linear_restarts() + (int64_t)small_linear_restarts(); }
+
+int fb_graph_small_linear(const fb_graph *g) { return g ? (g->small_linear ? 1 : 0) : -1; }
 
 int fb_graph_plan_cycles(const fb_graph *g, int backward, int64_t *cycles, int64_t *cycles_floor)
 {
@@ -365,6 +367,22 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 rows_of(s, dir);
                 any_parallel |= merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
                 g->small = small_append(dir ? g->hs_bwd : g->hs_fwd, k0, Ks, mptr.data(), mcol.data(), mw.data());
+            }
+        }
+        if (g->small && n_seq == 0 && g->hs_fwd.tm == 4) {   // the sums in the probability domain, if the graph mixes
+            std::vector<int64_t> iptr;
+            std::vector<int32_t> icol;
+            std::vector<float> iw, i2((size_t)K), f2((size_t)K);
+            rows_of(0, 0);   // (mptr .. hold the backward rows)
+            merge_parallel(K, ptr, col, w, false, iptr, icol, iw);
+            for (int32_t k = 0; k < K; ++k) { i2[(size_t)k] = to_log2(init[k]); f2[(size_t)k] = to_log2(final_[k]); }
+            g->small_linear = small_mixes(K, iptr, icol, iw, mptr, mcol, mw, i2, f2);
+            g->small_place.resize((size_t)K);
+            for (int32_t d = 0; d < D && g->small_linear; ++d) {
+                if (L.pdf_ptr[(size_t)d] == L.pdf_ptr[(size_t)d + 1]) continue;
+                for (int32_t i = L.pdf_ptr[(size_t)d]; i < L.pdf_ptr[(size_t)d + 1]; ++i)
+                    g->small_place[(size_t)L.pdf_states[(size_t)i]] = (uint16_t)g->small_places.size();
+                g->small_places.push_back(d);
             }
         }
         if (g->small) prob_ok = false;
@@ -534,6 +552,12 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 put_small(A, g->hs_fwd, g->sfwd);
                 put_small(A, g->hs_bwd, g->sbwd);
                 if (g->own_trop) { put_small(A, g->hs_trop, g->strop); put_small(A, g->hs_btrop, g->sbtrop); }
+                if (g->small_linear)
+                    for (SmallDev *d : {&g->sfwd, &g->sbwd}) {
+                        A.put(g->small_places, &d->places);
+                        A.put(g->small_place, &d->place);
+                        d->n_place = (int32_t)g->small_places.size();
+                    }
             } else {
                 put_stream(A, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr);
                 put_stream(A, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr);

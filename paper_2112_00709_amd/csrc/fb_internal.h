@@ -297,6 +297,10 @@ struct SmallDev {
     const uint32_t *rows = nullptr;
     const int32_t *lg = nullptr;
     const Arc *arcs = nullptr;
+    // Graphs that small_mixes() takes (nullptr: others): the pdfs some state is tied to, ascending, and the place of every state's pdf among them
+    const int32_t *places = nullptr;
+    const uint16_t *place = nullptr;
+    int32_t n_place = 0;
     uint32_t large = 0;        // ~0 if some weight, start or end weight is finite and larger than 65536 in size: runs take the plain form
 };
 
@@ -304,6 +308,11 @@ struct SmallDev {
 // kernel (too many states, a row of more than 64 lanes, too many slices).
 bool small_append(SmallHost &out, int32_t k0, int32_t K, const int64_t *ptr, const int32_t *col, const float *w);
 bool small_in_bounds(const SmallHost &S, std::string &why);
+// Whether a shared small graph runs in the probability domain (fb_small_linear.hip): in_*, out_* = its rows forward and backward,
+// parallel arcs merged, weights in log2 units as start and end weights are.
+bool small_mixes(int32_t K, const std::vector<int64_t> &in_ptr, const std::vector<int32_t> &in_src, const std::vector<float> &in_w,
+                 const std::vector<int64_t> &out_ptr, const std::vector<int32_t> &out_dst, const std::vector<float> &out_w,
+                 const std::vector<float> &init2, const std::vector<float> &final2);
 void small_apply_host(const SmallHost &S, int32_t sub, const double *x, double *y);
 
 // States grouped by pdf for the posterior accumulation: per (sub-)graph, one row per pdf it uses
@@ -354,6 +363,9 @@ struct fb_graph {
     fb::PStreamDev pfwd, pbwd;        // and device
     bool small = false;               // the recursions run in the small-graph kernel: the plans below exist and h_fwd .. do not
     fb::SmallHost hs_fwd, hs_bwd, hs_trop, hs_btrop;   // its plans, host (the last two: as h_trop, only when own_trop)
+    bool small_linear = false;        // ... the sums in the probability domain (small_mixes)
+    std::vector<int32_t> small_places;
+    std::vector<uint16_t> small_place;
     fb::SmallDev sfwd, sbwd, strop, sbtrop;   // and device (the last two = the first two unless own_trop)
     fb::PdfHost h_pdf;                // states grouped by pdf, for the posterior accumulation
     // device
@@ -470,6 +482,8 @@ struct PostParams {
 
 // the small-graph kernel: tm, slices as the plans of the graph's directions have them (the most slices)
 int launch_small(const RecParams &p, int tm, int slices, bool tropical, void *stream);
+int launch_small_linear(const RecParams &p, int slices, void *stream);   // ... in the probability domain (four arcs a lane)
+unsigned int small_linear_restarts();   // diagnostic: as linear_restarts, for that kernel
 int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t lds_bytes, void *stream);
 bool recursion_fixed_available();   // the fixed-buffer instantiation (RecParams::xs_fixed) may be launched
 unsigned int linear_restarts();     // diagnostic: runs the probability-domain kernel gave up and redid in the log form (synchronises)

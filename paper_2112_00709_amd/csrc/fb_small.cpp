@@ -95,6 +95,84 @@ bool small_in_bounds(const SmallHost &S, std::string &why)
     return true;
 }
 
+// Whether the vectors of a graph's recursions keep within a double's range (fb_small_linear.hip).  Mass that lies far behind the
+// frame's largest entry comes from states that get theirs from elsewhere and pass it on over many steps, or that nobody refreshes: a
+// cycle beside the main one whose states decay (or are left behind) by some binary orders every frame.  So: finite weights of
+// ordinary size, one cycle-bearing component, and every state on it or hanging off it within kDeep steps either way - an
+// entry then lies at most kDeep arcs and emissions behind the largest (twice 24 steps of 20 nats each are 1400 of the 1100
+// binary orders there are up to the largest: met by no emissions but masks, and a run that leaves the range is only slower).
+// Measured, a direction in the log form -> in the probability domain, us: 701 states, 3.5 k arcs, 97 pdfs, 23 x 211 frames 253 -> 139
+// (300 pdfs 259 -> 176); 1000 states, 4 k arcs, 16 x 200 242 -> 142; 300 states, 1.2 k arcs, 8 x 200 131 -> 64; 120 states 97 -> 67; 60
+// states 80 -> 46; 30 states 65 -> 37.
+bool small_mixes(int32_t K, const std::vector<int64_t> &in_ptr, const std::vector<int32_t> &in_src, const std::vector<float> &in_w,
+                 const std::vector<int64_t> &out_ptr, const std::vector<int32_t> &out_dst, const std::vector<float> &out_w,
+                 const std::vector<float> &init2, const std::vector<float> &final2)
+{
+    constexpr int kDeep = 24;
+    constexpr float kNone = -1.0e30f, kLow = -100.0f, kHigh = 40.0f;
+    auto ordinary = [&](float x) { return x <= kNone || (x >= kLow && x <= kHigh); };   // (false for a NaN)
+    auto rows_ok = [&](const std::vector<int64_t> &ptr, const std::vector<float> &w) {
+        for (int32_t r = 0; r < K; ++r) {
+            float top = kNone;
+            for (int64_t i = ptr[(size_t)r]; i < ptr[(size_t)r + 1]; ++i) {
+                if (!ordinary(w[(size_t)i])) return false;
+                top = std::max(top, w[(size_t)i]);
+            }
+            // (a sum of n weights is at most n times the largest)
+            if (top > kNone && (double)top + std::log2((double)(ptr[(size_t)r + 1] - ptr[(size_t)r])) > (double)kHigh) return false;
+        }
+        return true;
+    };
+    if (!rows_ok(in_ptr, in_w) || !rows_ok(out_ptr, out_w)) return false;
+    for (int32_t k = 0; k < K; ++k)
+        if (!ordinary(init2[(size_t)k]) || !ordinary(final2[(size_t)k])) return false;
+
+    // steps from `from` to every state it reaches (-1: none) along the arcs of rows
+    auto steps = [&](int32_t from, const std::vector<int64_t> &ptr, const std::vector<int32_t> &to, const std::vector<float> &w) {
+        std::vector<int32_t> d((size_t)K, -1), queue{from};
+        d[(size_t)from] = 0;
+        for (size_t h = 0; h < queue.size(); ++h)
+            for (int64_t i = ptr[(size_t)queue[h]]; i < ptr[(size_t)queue[h] + 1]; ++i) {
+                const int32_t t = to[(size_t)i];
+                if (w[(size_t)i] > kNone && d[(size_t)t] < 0) {
+                    d[(size_t)t] = d[(size_t)queue[h]] + 1;
+                    queue.push_back(t);
+                }
+            }
+        return d;
+    };
+    // what is left when states without an arc in (or out) from what is left are taken away again and again holds all cycles,
+    // and is the one component if its states all reach each other
+    std::vector<char> left((size_t)K, 1);
+    std::vector<int32_t> n_in((size_t)K, 0), n_out((size_t)K, 0), gone;
+    for (int32_t r = 0; r < K; ++r)
+        for (int64_t i = out_ptr[(size_t)r]; i < out_ptr[(size_t)r + 1]; ++i)
+            if (out_w[(size_t)i] > kNone) { ++n_out[(size_t)r]; ++n_in[(size_t)out_dst[(size_t)i]]; }
+    for (int32_t k = 0; k < K; ++k)
+        if (n_in[(size_t)k] == 0 || n_out[(size_t)k] == 0) { left[(size_t)k] = 0; gone.push_back(k); }
+    while (!gone.empty()) {
+        const int32_t k = gone.back();
+        gone.pop_back();
+        auto take = [&](const std::vector<int64_t> &ptr, const std::vector<int32_t> &to, const std::vector<float> &w, std::vector<int32_t> &count) {
+            for (int64_t i = ptr[(size_t)k]; i < ptr[(size_t)k + 1]; ++i) {
+                const int32_t t = to[(size_t)i];
+                if (w[(size_t)i] > kNone && --count[(size_t)t] == 0 && left[(size_t)t]) { left[(size_t)t] = 0; gone.push_back(t); }
+            }
+        };
+        take(out_ptr, out_dst, out_w, n_in);
+        take(in_ptr, in_src, in_w, n_out);
+    }
+    int32_t root = 0;
+    while (root < K && !left[(size_t)root]) ++root;
+    if (root == K) return false;                            // (no cycle: the mass dies after at most K frames)
+    const std::vector<int32_t> from = steps(root, out_ptr, out_dst, out_w), to = steps(root, in_ptr, in_src, in_w);
+    for (int32_t k = 0; k < K; ++k) {
+        if (left[(size_t)k] && (from[(size_t)k] < 0 || to[(size_t)k] < 0)) return false;
+        if (from[(size_t)k] > kDeep || to[(size_t)k] > kDeep) return false;
+    }
+    return true;
+}
+
 void small_apply_host(const SmallHost &S, int32_t sub, const double *x, double *y)
 {
     const SmallSub &sd = S.sub[(size_t)sub];

@@ -1,0 +1,122 @@
+"""The small-graph recursion on probabilities at the sizes where it can go wrong: around what its variants hold (states,
+slices, pdfs per lane), rows over one to 64 lanes, sequences shorter than the rounds of its waves, and runs that leave
+the range or meet masks, which the log form does over."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2112_00709_amd as fb
+import workloads as wl
+from test_gpu_small_graphs import _check
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(rng, K, deg, hub, D):
+    """One strongly connected part: a cycle through every state but the last two, which hang off it (one without an arc in)."""
+    n = int(K * deg)
+    core = max(1, K - 2)
+    src, dst = rng.integers(0, core, n), rng.integers(0, core, n)
+    order = rng.permutation(core)
+    for lead in (1, 7):                                      # (a cycle, and a shorter way round it)
+        src, dst = np.concatenate([src, order]), np.concatenate([dst, np.roll(order, -lead)])
+    src, dst = np.concatenate([src, np.arange(hub) % core, np.full(hub, core - 1)]), np.concatenate([dst, np.full(hub, core // 3), np.arange(hub) % core])
+    if K > 2:
+        src, dst = np.concatenate([src, [K - 2, 0, 0]]), np.concatenate([dst, [0, K - 1, K - 1]])
+    logw = (-rng.exponential(size=src.size)).astype(np.float32)
+    init = (-rng.exponential(size=K)).astype(np.float32)
+    init[rng.integers(0, K)] = -np.inf
+    return wl.Graph(K, src.astype(np.int32), dst.astype(np.int32), logw, rng.integers(0, D, K).astype(np.int32), init if K > 1 else init * 0,
+                    (-rng.exponential(size=K)).astype(np.float32))
+
+
+SIZES = [(4, 3, 0, 3, (1, 2, 3, 4)), (16, 2, 6, 16, (5, 7, 8, 9)), (30, 3, 0, 40, (15, 16, 17, 24)), (63, 1.5, 60, 5, (1, 8, 25, 33)),
+         (64, 0.5, 0, 70, (31, 32, 34, 40)), (100, 1.5, 90, 128, (2, 9, 10, 11)), (128, 2, 0, 129, (6, 12, 13, 48)), (250, 1.5, 240, 130, (14, 18, 19, 20)),
+         (257, 4, 100, 300, (21, 22, 23, 3)), (500, 3, 64, 512, (1, 3, 4, 5)), (513, 3, 200, 600, (6, 7, 8, 26)), (700, 2.5, 100, 97, (2, 27, 28, 29)),
+         (769, 2, 33, 320, (9, 10, 11, 12)), (900, 2, 40, 321, (13, 14, 15, 16)), (1024, 1.2, 120, 1500, (4, 5, 6, 35))]
+
+
+@pytest.mark.parametrize("K,deg,hub,D,frames", SIZES)
+def test_parity(K, deg, hub, D, frames):
+    rng = np.random.default_rng(K)
+    g = _graph(rng, K, deg, hub, D)
+    lengths = np.array(list(frames) + [0], dtype=np.int32)
+    emis = (rng.standard_normal((lengths.size, int(lengths.max()) + 1, D)) * 2).astype(np.float32)
+    for b in range(lengths.size):
+        emis[b, lengths[b]:] = np.nan
+    emis[1, 0, :] -= 100.0                                   # (what all pdfs of a frame share is taken off it)
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_small_linear(h) == 1
+    h.destroy()
+    before = fb.fb_debug_linear_restarts()
+    _check(g, emis, lengths, D)
+    assert fb.fb_debug_linear_restarts() == before
+
+
+@pytest.mark.parametrize("K,deg,hub,D,frames", [SIZES[i] for i in (1, 3, 5, 7, 9, 11, 14)])
+def test_runs_that_leave_the_range(K, deg, hub, D, frames):
+    """Emissions hundreds of nats apart: one sequence all along, one in a single frame, one a masked state, one not at all."""
+    import torch
+    rng = np.random.default_rng(K)
+    g = _graph(rng, K, deg, hub, D)
+    T = 26
+    lengths = np.array([T, T, T, T], dtype=np.int32)
+    emis = (rng.standard_normal((4, T, D)) * 2).astype(np.float32)
+    emis[0] *= 100.0
+    emis[1, 11] *= 150.0
+    emis[2, :, int(g.pdf[1])] = -1.0e4
+    before = fb.fb_debug_linear_restarts()
+    h = fb.graph_from(g, D)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    a, ca, za = fb.fb_alpha(h, e, l)
+    b, cb, zb = fb.fb_beta(h, e, l)
+    gam, rho = fb.fb_posteriors(h, a, b, l, 4, T)
+    assert fb.fb_debug_linear_restarts() - before == 6       # both directions of three of them
+    a, b, ca, cb, za, zb, gam, rho = (t.cpu().numpy() for t in (a, b, ca, cb, za, zb, gam, rho))
+    ref = oracle.forward_backward(g, emis, lengths)
+    for q in range(4):
+        for z in (za[q], zb[q]):
+            assert abs(z - ref.logz[q]) <= 1e-4 * max(1.0, abs(ref.logz[q]))
+        tol = 1e-5 + 2.0 ** -24 * (np.abs(a[q]) + np.abs(b[q]))[ref.gamma[q] > 1e-7].max(initial=0.0)
+        assert np.abs(gam[q] - ref.gamma[q]).max() <= tol and np.abs(rho[q] - ref.rho[q]).max() <= tol
+        for x, c, want in ((a[q], ca[q], ref.alpha[q]), (b[q], cb[q], ref.beta[q])):
+            assert np.array_equal(np.isneginf(x), np.isneginf(want))
+            fin = np.isfinite(want)
+            # as in _check, and the float ln 2 that shifts are multiplied by
+            err = np.abs((x + c[:, None])[fin] - want[fin])
+            assert np.all(err <= 1e-7 * np.abs(x[fin]) + 2e-7 * T + 1e-6 + 3e-9 * np.abs(c).max())
+    h.destroy()
+
+
+@pytest.mark.parametrize("K,arcs", [(9, 3), (20, 4), (23, 9)])
+def test_masked_frames_and_nan(K, arcs):
+    """A frame of masks, one of zero-bar for all, one of zero-bar for some, a NaN: as the general kernel has them."""
+    import torch
+    rng = np.random.default_rng(K)
+    D, T = 5, 33
+    src = np.tile(np.arange(K), arcs)
+    dst = (src + np.repeat(np.arange(arcs), K)) % K
+    g = wl.Graph(K, src.astype(np.int32), dst.astype(np.int32), (-rng.exponential(size=src.size)).astype(np.float32),
+                 rng.integers(0, D, K).astype(np.int32), np.zeros(K, np.float32), np.zeros(K, np.float32))
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_small_linear(h) == 1
+    emis = (rng.standard_normal((5, T, D)) * 2).astype(np.float32)
+    emis[0, 9] = -1e20
+    emis[1, 13] = -np.inf
+    emis[2, 17, 1:] = -np.inf
+    emis[3, 4, int(g.pdf[0])] = np.nan
+    lengths = np.full(5, T, dtype=np.int32)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    a, _, za = fb.fb_alpha(h, e, l)
+    b, _, zb = fb.fb_beta(h, e, l)
+    gam, _ = fb.fb_posteriors(h, a, b, l, 5, T)
+    za, zb, gam = za.cpu().numpy(), zb.cpu().numpy(), gam.cpu().numpy()
+    ref = oracle.forward_backward(g, emis, lengths, sel=np.array([2, 4]))
+    for i, q in enumerate((2, 4)):
+        both = np.isneginf(za[q]) and np.isneginf(ref.logz[i])
+        assert both or (abs(za[q] - ref.logz[i]) <= 1e-4 * abs(ref.logz[i]) and abs(zb[q] - ref.logz[i]) <= 1e-4 * abs(ref.logz[i]))
+        assert np.abs(gam[q] - ref.gamma[i]).max() <= 1e-5
+    assert abs(za[0] / -1e20 - 1) <= 1e-6 and abs(zb[0] / -1e20 - 1) <= 1e-6 and np.isfinite(gam[0]).all()
+    assert np.isneginf(za[1]) and np.isneginf(zb[1]) and np.all(gam[1] == 0)
+    assert np.isnan(za[3]) and np.isnan(zb[3]) and np.isnan(gam[3]).any()
+    h.destroy()
