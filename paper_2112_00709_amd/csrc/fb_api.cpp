@@ -458,9 +458,14 @@ static size_t viterbi_bp_ld(const fb_graph *g)
 
 static size_t viterbi_mid_ld(const fb_graph *g) { return (size_t)g->max_sub_K + (size_t)std::max(viterbi_ccap(g, false), viterbi_ccap(g, true)); }
 
+// Graphs in the probability domain keep their vectors instead: a float a state and frame, rows in 16-byte pieces.
+static size_t best_ld(const fb_graph *g) { return ((size_t)g->K + 3) & ~(size_t)3; }
+static size_t best_rows_bytes(const fb_graph *g, int32_t B, int32_t N) { return align256((size_t)B * N * best_ld(g) * sizeof(float)); }
+
 size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 {
     if (!g || B <= 0 || N <= 0) return 0;
+    if (g->linear_p) return best_rows_bytes(g, B, N) + 2 * (align256((size_t)B * best_ld(g) * sizeof(float)) + align256((size_t)B * sizeof(double)));
     const size_t rows = (g->n_seq == 0 ? (size_t)B * N : (size_t)N) * viterbi_bp_ld(g);
     // the back-pointers, then per direction the vector it ends with and that vector's shift
     return align256(rows * sizeof(uint16_t)) + 2 * (align256((size_t)B * viterbi_mid_ld(g) * (g->f64 ? 8 : 4)) + align256((size_t)B * sizeof(double)));
@@ -473,6 +478,50 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 // through 6000 states, 60 k arcs, 128 sequences of at most 500 frames 3456 -> 1671 us; 32 label-sequence graphs of at
 // most 161 states over 209 frames 122 -> 71 us (a call).  A batch that fills the chip twice does the same number of steps
 // either way.  (The backward plan fits wherever the graph could be created: the sums' form of it takes more memory.)
+//
+// Graphs that have probability-domain plans (fb_pstream.cpp) walk them with weights in log2 units and keep no back-pointers at
+// all: a row's largest term costs two additions and a maximum of three for every two arcs, where finding out which one it is as
+// well takes a comparison and two selects an arc.  The vectors leave as they are, and the trace forms the terms of the one row a
+// frame that the path takes anew.  (6000 states, 60 k arcs, 128 sequences of at most 500 frames: 1606 -> 1210 us a call, the workspace twice as large.)
+static int best_path(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D, double *score,
+                     int32_t *path, void *ws, fb_stream stream)
+{
+    RecParams p{};
+    BestTraceParams bt{};
+    p.pdf = g->d_pdf;
+    p.emis = emis;
+    p.lengths = lengths;
+    p.B = B; p.N = N; p.D = D;
+    p.shared = 1;
+    p.Ktot = p.Kcap = g->K;
+    p.Ecap = D;
+    p.n_dir = 2;
+    bt.rows = (const float *)ws;
+    bt.ld = (int64_t)best_ld(g);
+    const size_t mid_bytes = align256((size_t)B * best_ld(g) * sizeof(float));
+    for (int i = 0; i < 2; ++i) {
+        char *w = (char *)ws + best_rows_bytes(g, B, N) + (size_t)i * (mid_bytes + align256((size_t)B * sizeof(double)));
+        p.dir[i] = make_dir(g, i == 1, ws, false, nullptr, nullptr, 1.0f, false);
+        p.dir[i].prob = g->best[i];
+        p.dir[i].out_linear = 1;
+        p.dir[i].out_ld = (int32_t)best_ld(g);
+        p.dir[i].mid = w;
+        p.dir[i].mid_ld = bt.mid_ld = (int64_t)best_ld(g);
+        p.dir[i].mid_off = (double *)(w + mid_bytes);
+        bt.mid[i] = (const float *)w;
+        bt.mid_off[i] = p.dir[i].mid_off;
+        bt.ptr[i] = g->d_best_ptr[i];
+        bt.arcs[i] = g->d_best_arcs[i];
+    }
+    const int rc = launch_best_linear(p, stream);
+    if (rc) return rc;
+    bt.lengths = lengths;
+    bt.score = score;
+    bt.path = path;
+    bt.B = B; bt.N = N; bt.K = g->K;
+    return launch_best_trace(bt, stream);
+}
+
 int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D, double *score,
                int32_t *path, void *ws, size_t ws_bytes, fb_stream stream)
 {
@@ -481,6 +530,7 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
     if (!score || !path) return fail(FB_EINVAL, "fb_viterbi: score or path is NULL");
     if (!ws || ws_bytes < fb_viterbi_workspace_bytes(g, B, N)) return fail(FB_EINVAL, "fb_viterbi: workspace missing or too small");
     if (((uintptr_t)ws & 255) != 0) return fail(FB_EINVAL, "fb_viterbi: workspace must be 256-byte aligned");
+    if (g->linear_p) return best_path(g, emis, lengths, B, N, D, score, path, ws, stream);
     const size_t rows = (g->n_seq == 0 ? (size_t)B * N : (size_t)N) * viterbi_bp_ld(g);
     const size_t mid_ld = viterbi_mid_ld(g), mid_bytes = align256((size_t)B * mid_ld * (g->f64 ? 8 : 4));
     BacktraceParams bt{};

@@ -505,7 +505,20 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 g->linear_w = false;   // the log form it falls back to adds in the exponent
             }
             if (g->host_only && prob_ok) g->linear_p = true;   // (host-only handles keep the plans for fb_graph_schedule_apply_host)
-            g->own_trop = any_parallel || g->linear_w;
+            // (graphs in the probability domain: the best path runs on their plans, with weights of its own)
+            const bool best = g->linear_p && !g->host_only;
+            for (int dir = 0; dir < 2 && rc == FB_OK && best; ++dir) {
+                rows_of(0, dir);
+                merge_parallel(K, ptr, col, w, true, mptr, mcol, mw);
+                if (!pstream_best_units(dir ? g->hp_bwd : g->hp_fwd, mptr.data(), mcol.data(), mw.data(), g->best_units[dir])) {
+                    rc = fail(FB_EHIP, "internal error: best-path weights of a probability-domain plan");
+                    break;
+                }
+                g->best_ptr[dir].assign(mptr.begin(), mptr.end());
+                g->best_arcs[dir].reserve(mcol.size());
+                for (size_t i = 0; i < mcol.size(); ++i) g->best_arcs[dir].push_back(Arc{mcol[i], mw[i]});
+            }
+            g->own_trop = !best && (any_parallel || g->linear_w);
             for (int dir = 0; dir < 2 && rc == FB_OK && g->own_trop; ++dir) {
                 SellHost sell_trop;
                 sell_trop.nw = g->nw - 1;
@@ -562,9 +575,23 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 put_stream(A, g->h_fwd, g->fwd, g->linear_w ? &lin_fwd : nullptr);
                 put_stream(A, g->h_bwd, g->bwd, g->linear_w ? &lin_bwd : nullptr);
                 if (g->own_trop) { put_stream(A, g->h_trop, g->trop); put_stream(A, g->h_btrop, g->btrop); }
-                if (g->linear_p) { put_pstream(A, g->hp_fwd, g->pfwd); put_pstream(A, g->hp_bwd, g->pbwd); }
+                if (g->linear_p) {
+                    put_pstream(A, g->hp_fwd, g->pfwd);
+                    put_pstream(A, g->hp_bwd, g->pbwd);
+                    for (int dir = 0; dir < 2; ++dir) {
+                        A.put(g->best_units[dir], &g->best[dir].units);
+                        A.put(g->best_ptr[dir], &g->d_best_ptr[dir]);
+                        A.put(g->best_arcs[dir], &g->d_best_arcs[dir]);
+                    }
+                }
             }
             rc = A.finish(g);
+            if (g->linear_p)
+                for (int dir = 0; dir < 2; ++dir) {
+                    const uint32_t *units = g->best[dir].units;
+                    g->best[dir] = dir ? g->pbwd : g->pfwd;
+                    g->best[dir].units = units;
+                }
             if (!g->own_trop && g->small) { g->strop = g->sfwd; g->sbtrop = g->sbwd; }
             if (g->small) {   // (in the sums what is below -1e30, in log2 units, is zero-bar and not a large weight)
                 bool sums = false, paths = false;

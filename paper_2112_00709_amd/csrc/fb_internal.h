@@ -266,6 +266,7 @@ struct PStreamDev {
 // why, if the matrix does not fit the kernel (weights out of range, too many slices, ...).
 bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const float *w, const int32_t *row_vidx, int32_t n_vidx,
                    PStreamHost &out, std::string &why);
+bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units);
 bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why);
 bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why);
 
@@ -361,6 +362,12 @@ struct fb_graph {
     bool linear_p = false;            // the recursions run in the probability domain (linear_run): the plans below exist
     fb::PStreamHost hp_fwd, hp_bwd;   // its plans, host
     fb::PStreamDev pfwd, pbwd;        // and device
+    std::vector<uint32_t> best_units[2];      // the best path's: those plans with its weights, and the rows forward and backward
+    std::vector<int32_t> best_ptr[2];
+    std::vector<fb::Arc> best_arcs[2];
+    fb::PStreamDev best[2];           // (device; linear_p only)
+    const int32_t *d_best_ptr[2] = {nullptr, nullptr};
+    const fb::Arc *d_best_arcs[2] = {nullptr, nullptr};
     bool small = false;               // the recursions run in the small-graph kernel: the plans below exist and h_fwd .. do not
     fb::SmallHost hs_fwd, hs_bwd, hs_trop, hs_btrop;   // its plans, host (the last two: as h_trop, only when own_trop)
     bool small_linear = false;        // ... the sums in the probability domain (small_mixes)
@@ -502,6 +509,23 @@ struct BacktraceParams {
     int32_t frames;          // back-pointer rows the kernel holds in LDS at a time (set by launch_backtrace)
     int32_t *path;           // [B][N]
 };
+// Best path of a graph with probability-domain plans: the rows both directions have kept, [B][N][ld] floats (frames but the middle one).
+struct BestTraceParams {
+    const float *rows;
+    int64_t ld;              // a multiple of 4
+    const int32_t *lengths;
+    const int32_t *ptr[2];   // [K + 1] the arcs into every state, and out of every state: source (destination), weight in log2 units
+    const Arc *arcs[2];
+    const float *mid[2];     // [B][mid_ld] the vectors at the middle frame, without the shifts mid_off [B]
+    const double *mid_off[2];
+    int64_t mid_ld;
+    double *score;           // [B]
+    int32_t *path;           // [B][N]
+    int32_t B, N, K;
+};
+size_t best_trace_lds_bytes(int32_t K);
+int launch_best_linear(const RecParams &p, void *stream);
+int launch_best_trace(const BestTraceParams &p, void *stream);
 // The leaky-HMM form of the probability-domain kernel: its vector is kept 2^kLeakyBiasDrop lower, so that the sum over all
 // its entries and the share of it that a row gets are floats too (beyond that a run gives up as it does everywhere).
 constexpr int kLeakyBiasDrop = 22;

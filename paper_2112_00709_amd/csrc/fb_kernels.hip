@@ -694,7 +694,11 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)))
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
 // LOG: rows leave as logarithms.  FEW (kPFew, kPFewMost or 0): no wave has more than that many units, so all of them stay in
 // registers, nothing is re-read, and the registers that leaves take gathers further ahead.
-template <bool LEAKY, bool LOG, int FEW>
+// TROP: the best path (fb_viterbi).  The vector is scores in log2 units, the largest of the step before taken off at every step, the units
+// carry weights in log2 units, a row is the largest of its terms: two additions and one maximum of three a unit.  Which arc
+// attains it is not kept: rows leave as they are, and fb_best_trace_kernel finds it anew for the one row a frame that the
+// path takes.  A direction goes half way (path_middle); there is no range to leave.
+template <bool LEAKY, bool LOG, int FEW, bool TROP = false>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
     constexpr int NW = kNWShared, XF = kXsFixed, R = FEW ? FEW : kPResident;
@@ -707,6 +711,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const bool bwd = R_.backward != 0;
     const int K = P.Kcap, nC = S.Ccap;
     const int Tn = min(max(P.lengths[b], 0), P.N);
+    const int Ts = !TROP || Tn <= 0 ? Tn : bwd ? Tn - path_middle(Tn) : path_middle(Tn) + 1;   // frames this direction visits
+    constexpr float kNone = TROP ? -INFINITY : 0.0f;   // zero-bar
     const int nE = P.D;
     const int nX = K + nC + 1;                   // states, clone slots, dump slot
     // the two buffers of the vector in use lie kXbStride bytes apart, at least a buffer's length: a source or a target is
@@ -721,7 +727,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // either direction's rows as logarithms when that is the form they leave in; two buffers that follow each other,
     // present only when used
     constexpr bool log_rows = LOG;
-    const bool staged = bwd || log_rows;
+    const bool staged = !TROP && (bwd || log_rows);
     const int XL = LEAKY ? (nX + 3) & ~3 : XF;   // floats of a buffer behind the first (leaky: q needs the room)
     float *bh = xb + Xs + XL;
     float *red = staged ? bh + 2 * XL : bh;
@@ -888,7 +894,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             const CloneDesc cd = cdesc[j];
             if (out_lin) {
                 float t = srcv[cd.state];
-                for (int i = 0; i < cd.count; ++i) t += srcv[K + cd.first + i];
+                for (int i = 0; i < cd.count; ++i) t = TROP ? tmax(t, srcv[K + cd.first + i]) : t + srcv[K + cd.first + i];
                 orow[cd.state] = t;
             } else {   // logarithms (scaled by out_scale, which is positive): the (+)-sum of the clones
                 float m = srcv[cd.state];
@@ -909,7 +915,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
 
     // ---- first frame of this direction: the start weights and the frame's emissions, relative to their maximum
     if (tid < 3) {
-        *step_word(tid) = 0.0f;
+        *step_word(tid) = kNone;
         er[tid * Es + P.D] = -INFINITY;   // what the dump slot "emits" (staging never writes there): its entry stays zero
     }
     if (tid < 8) red[tid] = (tid == 7 || tid == 3) ? -INFINITY : 0.0f;
@@ -920,17 +926,17 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     __syncthreads();
     if (io_wave) {
         stage(frame(0), er);
-        if (Tn > 1) stage(frame(1), er + Es);
+        if (Ts > 1) stage(frame(1), er + Es);
         staged_wait();
-        const float e0 = emax_of(er);
-        const float e1 = Tn > 1 ? emax_of(er + Es) : 0.0f;
+        const float e0 = TROP ? 0.0f : emax_of(er);
+        const float e1 = !TROP && Ts > 1 ? emax_of(er + Es) : 0.0f;
         if (lane == 0) { emaxw[0] = e0; emaxw[1] = e1; }
-        if (Tn > 1 && lane == 0) er[Es + Es - 2] = e1;
-        if (Tn > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
+        if (Ts > 1 && lane == 0) er[Es + Es - 2] = e1;
+        if (Ts > 2) stage(frame(2), er + 2 * Es);   // lands while step 1 runs
     }
     __syncthreads();
     const float emx0 = emaxw[0];
-    {
+    if constexpr (!TROP) {
         float ymax = -INFINITY, smax = -INFINITY;
         for (int k = tid; k < K; k += NT) {
             const float s = R_.bound[k];
@@ -945,16 +951,23 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
     }
     lds_barrier();
-    const float M0 = red[7];
+    const float M0 = TROP ? 0.0f : red[7];
     // log2 of the first vector = log2 of its entries + base0 (+ the emission maximum).  The largest entry goes to
     // 2^bias; backward, the row that leaves is the start weights before the frame's emissions, which lie above the
     // vector by what the best state's emission lacks to the frame's largest: the scale is held back as far as that
     // row needs to stay a float (the vector's entries are then smaller, and below the range the run gives up as ever).
     float base0 = M0 > -INFINITY ? M0 - (float)kLinBias : 0.0f;
-    if (bwd && M0 > -INFINITY) base0 = tmax(base0, red[3] - 126.0f);
-    float wmax = 0.0f, wsum = 0.0f;
+    if (!TROP && bwd && M0 > -INFINITY) base0 = tmax(base0, red[3] - 126.0f);
+    float wmax = kNone, wsum = 0.0f;
     for (int k = tid; k < K; k += NT) {
         const float s = R_.bound[k];
+        if constexpr (TROP) {
+            // (the backward recursion ends before the emission of its last frame, which may be this one)
+            const float x = bwd && Ts == 1 ? s : fmaf(er[P.pdf[k]], (float)kLog2e, s);
+            xb[k] = x;
+            wmax = tmax(wmax, x);
+            continue;
+        }
         const float y = s + fmaf(er[P.pdf[k]], (float)kLog2e, -emx0) - base0;
         const float px = fexp2(y);
         xb[k] = px;
@@ -969,10 +982,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         if (lane == 0) slots[wave] = wsum;
     }
     for (int k = tid; k < nC; k += NT) {   // clones start empty: the state itself holds the start weight
-        xb[K + k] = 0.0f;
+        xb[K + k] = kNone;
         if (staged) bh[K + k] = log_rows ? -INFINITY : 0.0f;
     }
-    if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = 0.0f;   // the dump slot holds zero in both buffers, always
+    if (tid == 0) xb[nX - 1] = xb[Xs + nX - 1] = kNone;   // the dump slot holds zero(-bar) in both buffers, always
     wmax = wave_max_last(wmax);
     if (lane == kWave - 1) lds_raise(step_word(0), wmax);
     lds_barrier();
@@ -985,35 +998,35 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     bool ok = true;
     if (io_wave) {
         float c = base0 + (float)kLinBias + (bwd ? 0.0f : emx0);
-        csum = (double)c;
+        csum = TROP ? 0.0 : (double)c;
         if (lane == 0) {
             if (off_seq) off_seq[frame(0)] = csum * (double)R_.out_scale;
             if (R_.cum) R_.cum[(size_t)b * P.N + frame(0)] = (float)(csum - cum_shift);
         }
-        float e_prev = emx0, e_cur = Tn > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
+        float e_prev = emx0, e_cur = Ts > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
         float *row_a = er, *row_b = er + Es, *row_c = er + 2 * Es;   // rows of frame i - 1 (from step i on: i + 2), i, i + 1
-        for (int i = 1; i < Tn; ++i) {
+        for (int i = 1; i < Ts; ++i) {
             const int cur = (i - 1) & 1;
             const float mxv = row_a[Es - 1];
-            const bool more = i + 2 < Tn;
+            const bool more = i + 2 < Ts;
             // (the word of step i - 1 lies behind what is staged)
             if (more) stage(frame(i + 2), row_a);   // buffer of frame i-1: no longer read
             write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
             const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(mxv));
-            if (mx > 0x7f7fffffu) { ok = false; break; }
-            const float nls = mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
-            c = nls + (bwd ? e_prev : e_cur);
+            if (!TROP && mx > 0x7f7fffffu) { ok = false; break; }
+            const float nls = TROP ? (mxv > -INFINITY ? mxv : 0.0f) : mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
+            c = TROP ? nls : nls + (bwd ? e_prev : e_cur);
             csum += (double)c;
             if (lane == 0) {
                 if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
                 if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
             }
-            if (mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
+            if (!TROP && mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
             e_prev = e_cur;
-            if (i + 1 < Tn) {
+            if (i + 1 < Ts) {
                 staged_before(n_row_stores + (more ? n_requests : 0));   // frame i+1, requested a whole step ago, is in LDS
-                e_cur = emax_of(row_c);
-                if (lane < 2) row_c[Es - 2 + lane] = lane ? 0.0f : e_cur;   // and the word of step i + 1 starts empty
+                if constexpr (!TROP) e_cur = emax_of(row_c);
+                if (lane < 2) row_c[Es - 2 + lane] = lane ? kNone : e_cur;   // and the word of step i + 1 starts empty
             }
             if (LEAKY && lane == 0) slots[(i & 1) * NW + NC] = 0.0f;
             float *const t = row_a;
@@ -1131,11 +1144,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             uint32_t cw = cwv[0];
             float pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
             float sc = 1.0f;
-            wmax = 0.0f;
+            wmax = kNone;
+            const bool no_em = TROP && bwd && i == Ts - 1;   // (see the first frame)
             // the smallest entry this lane has written for a row whose sum is above zero, as its bit pattern (which keeps
             // the order of floats that are not negative)
             uint32_t wlow = 0x7f800000u;
-            float acc = 0.0f;
+            float acc = kNone;
             // leaky: the previous vector's sum (every wave adds the slots in the same order) and the next close's q
             float leaked = 0.0f, q_next = 0.0f, slot = 0.0f;
             if constexpr (LEAKY) {
@@ -1147,7 +1161,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             if (i == cur + 1)   // rows without arcs: zero from the second frame on, in both buffers
                 for (int z = tid; z < S.n_zero; z += NC * kWave) {
                     const int k = S.zero_rows[z];
-                    xn[k] = 0.0f;
+                    xn[k] = kNone;
                     if (staged) bn[k] = log_rows ? -INFINITY : 0.0f;
                 }
             // the two values a unit gathers; sources are byte offsets.  (In assembly so that the addresses are formed at every
@@ -1169,14 +1183,25 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (__builtin_expect(nclose < n_wide, 0)) {
                     const int lg = (int)((lg_lo >> (3 * nclose)) & 7u);
                     if constexpr (LEAKY) share = __uint_as_float((uint32_t)(127 - lg) << 23);
-                    for (int sft = 0; sft < lg; ++sft)   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
-                        acc += __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
+                    for (int sft = 0; sft < lg; ++sft) {   // the lanes of a row are neighbours: a butterfly over 2^lg lanes (few rows are that long)
+                        const float other = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ (1 << sft)) << 2, (int)__float_as_uint(acc)));
+                        acc = TROP ? tmax(acc, other) : acc + other;
+                    }
                 }
                 cw = cwv[++nclose];
                 const float q = q_next;
                 if constexpr (LEAKY) {
                     acc = bwd ? acc + ((int)__float_as_uint(q) >= 0 ? leaked : 0.0f) : fmaf(leaked, tmax(q, 0.0f), acc);
                     q_next = *(const float *)((const char *)qt + (cw & 0xffffu));
+                }
+                if constexpr (TROP) {
+                    const float xb_ = acc - sc;   // (sc: what is taken off, here)
+                    const float x = no_em ? xb_ : fmaf(pe, (float)kLog2e, xb_);
+                    pe = *(lds_cf *)(uintptr_t)(ern + (cw >> 16));
+                    *(lds_f *)(uintptr_t)(tgt + (uint32_t)(nxt * kXbStride)) = x;
+                    wmax = tmax(wmax, x);
+                    acc = kNone;
+                    return;
                 }
                 const float pb = acc * sc;
                 const float px = pb * fexp2(fmaf(pe, (float)kLog2e, -emx));
@@ -1210,8 +1235,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 gather(G[u], unit_at(std::integral_constant<int, u>{}));
             }, std::make_integer_sequence<int, GD>{});
             const uint32_t mx = __float_as_uint(mxv);
-            if (__builtin_expect((uint32_t)__builtin_amdgcn_readfirstlane((int)mx) > 0x7f7fffffu, 0)) return false;   // (the same word in every wave: all of them leave here)
-            sc = rescale(mx);
+            if (!TROP && __builtin_expect((uint32_t)__builtin_amdgcn_readfirstlane((int)mx) > 0x7f7fffffu, 0)) return false;   // (the same word in every wave: all of them leave here)
+            sc = TROP ? (mxv > -INFINITY ? mxv : 0.0f) : rescale(mx);
             if constexpr (LEAKY) leaked = P.leak * lane_value(row_sum_last(slot), 15);
             // Waves of equal priority are served oldest first, so with one fixed priority the younger waves of a SIMD
             // would do most of their step alone after the older ones have finished theirs.  A wave's priority therefore
@@ -1238,8 +1263,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             const Unit me = unit_at(std::integral_constant<int, u>{});
                             // (both values of the unit are taken at one point: one wait for the pair instead of one each)
                             asm volatile("" : "+v"(G[u % NGB].x), "+v"(G[u % NGB].y));
-                            acc = fmaf(G[u % NGB].x, me.w0, acc);
-                            acc = fmaf(G[u % NGB].y, me.w1, acc);
+                            if constexpr (TROP) {
+                                acc = tmax3(acc, G[u % NGB].x + me.w0, G[u % NGB].y + me.w1);
+                            } else {
+                                acc = fmaf(G[u % NGB].x, me.w0, acc);
+                                acc = fmaf(G[u % NGB].y, me.w1, acc);
+                            }
                             if constexpr (!FEW || (u & 1)) {   // (slices of pairs of units: PStreamHost::paired)
                                 if (__builtin_expect(((u < 32 ? m_lo : m_hi) >> (u & 31)) & 1u, 0)) close_slice();
                             }
@@ -1262,8 +1291,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                             request(ring[(mr + kPRing - 1) % kPRing], NP + t + kPRing - 1);
                             gather(G[(NP + tt + GD) % NGB], ring[(mr + GD) % kPRing]);
                             asm volatile("" : "+v"(G[(NP + tt) % NGB].x), "+v"(G[(NP + tt) % NGB].y));
-                            acc = fmaf(G[(NP + tt) % NGB].x, ring[mr % kPRing].w0, acc);
-                            acc = fmaf(G[(NP + tt) % NGB].y, ring[mr % kPRing].w1, acc);
+                            if (TROP) {
+                                acc = tmax3(acc, G[(NP + tt) % NGB].x + ring[mr % kPRing].w0, G[(NP + tt) % NGB].y + ring[mr % kPRing].w1);
+                            } else {
+                                acc = fmaf(G[(NP + tt) % NGB].x, ring[mr % kPRing].w0, acc);
+                                acc = fmaf(G[(NP + tt) % NGB].y, ring[mr % kPRing].w1, acc);
+                            }
                             const int at = NP + t;
                             const uint32_t word = at < 32 ? m_lo : at < 64 ? m_hi : at < 96 ? m1_lo : m1_hi;
                             if (__builtin_expect((word >> (at & 31)) & 1u, 0)) close_slice();
@@ -1277,7 +1310,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 request_at(ring[m], first);
             }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
             // an entry below the range: the run gives up (see above)
-            wmax = wave_max_last(wlow < __float_as_uint(kLinDimP) ? INFINITY : wmax);
+            wmax = wave_max_last(!TROP && wlow < __float_as_uint(kLinDimP) ? INFINITY : wmax);
             lds_raise_last(ern + to_word + 4u, wmax);
             if constexpr (LEAKY) {
                 wsum = wave_sum_last(wsum);
@@ -1286,10 +1319,27 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_barrier();
             return true;
         };
-        for (int i = 1; ok && i < Tn; ++i) {
+        for (int i = 1; ok && i < Ts; ++i) {
             ok = step(i, std::integral_constant<int, 0>{});
-            if (ok && ++i < Tn) ok = step(i, std::integral_constant<int, 1>{});
+            if (ok && ++i < Ts) ok = step(i, std::integral_constant<int, 1>{});
         }
+    }
+    if constexpr (TROP) {
+        // ---- the last vector, a cloned state's value the largest of its clones', for the kernel that joins the two halves: without its
+        // largest entry, or the other half's entries would be lost in it where this frame's emissions are some large mask
+        const float mxl = *step_word(Ts - 1), cl = mxl > -INFINITY ? mxl : 0.0f;
+        float *xl = xb + ((Ts - 1) & 1) * Xs;
+        for (int j = tid; j < S.n_clones; j += NT) {
+            const CloneDesc cd = cdesc[j];
+            float v = xl[cd.state];
+            for (int i = 0; i < cd.count; ++i) v = tmax(v, xl[K + cd.first + i]);
+            xl[cd.state] = v;
+        }
+        __syncthreads();
+        float *mrow = (float *)R_.mid + (size_t)b * R_.mid_ld;
+        for (int k = tid; k < K; k += NT) mrow[k] = xl[k] - cl;
+        if (io_wave && lane == 0) R_.mid_off[b] = csum + (double)cl;
+        return true;
     }
     // a state below the range in the last step: give up as well (every wave reads the same word)
     if (ok && !(*step_word(Tn - 1) < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
@@ -1355,6 +1405,19 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
         if (P.dir[which].fmt && threadIdx.x == 0) P.dir[which].fmt[b] = 0;   // this sequence's rows are in the log form
     }
     count_done(P);
+}
+
+// The best path's recursions, both of them half way.  Against the back-pointer form (fb_recursion_kernel, a comparison and two selects an arc, and
+// 2 bytes a state and frame instead of 4), 6000 states, 60 k arcs, 3000 pdfs, 128 sequences of 100 to 500 frames: the launch 1520 -> 870 us, the
+// trace behind it 144 -> 366, a call of fb_viterbi 1606 -> 1210.  What bounds it is what bounds the sums (LDS, issue).
+template <int FEW>
+__global__ __launch_bounds__(kNWShared * 64) void fb_best_linear_kernel(const RecParams P)
+{
+    __builtin_amdgcn_s_setprio(3);
+    extern __shared__ double lds_raw[];
+    int b, which;
+    resolve_sequence<kNWShared>(P, lds_raw, b, which);
+    linear_run<false, false, FEW, true>(P, b, which, lds_raw);
 }
 
 // The leaky-HMM's recursions (both directions, one launch); gave_up[which * B + b]: the run left its range (or the
@@ -2277,6 +2340,174 @@ __global__ __launch_bounds__(kBtThreads) void fb_backtrace_kernel(const Backtrac
     if (n_rows > 0) hand_over((n_rows - 1) / F * F, (n_rows - 1) / F & 1);
 }
 
+// Best path, rows kept whole (fb_best_linear_kernel): the two halves joined and followed.  The score and where it is attained as
+// in fb_backtrace_kernel; from there a path's state at the next frame is the source of the largest of its state's terms, formed
+// anew from that frame's row: the same additions as in the recursion, so the same largest (of equal ones the smallest source).
+// One workgroup per sequence and half.  A step is a chain: where the state's arcs begin (LDS), the arcs (L2), their sources' scores
+// (LDS: kTraceWalk waves walk), the largest over the workgroup; three waves bring the rows from memory straight into LDS, three frames ahead,
+// one keeps the path and stores 64 frames of it at a time: a walking wave has no memory operation on its way but the arcs it waits for.
+// Bound: the rows, read once (932 MB for 128 sequences of 100 to 500 frames over 6000 states: 366 us, 2.5 TB/s, while the
+// longest sequences are left; four walking waves instead of eight, or one arc a trip instead of four, take the same time).
+constexpr int kTraceWalk = 8, kTraceLoad = 3, kTraceRows = 4, kTraceThreads = (kTraceWalk + kTraceLoad + 1) * kWave;
+
+__global__ __launch_bounds__(kTraceThreads) void fb_best_trace_kernel(const BestTraceParams P)
+{
+    extern __shared__ float tr_rows[];   // [kTraceRows][ld], then ptr, candidates
+    const int b = blockIdx.x % P.B, half = blockIdx.x / P.B, tid = threadIdx.x;   // half 0: frames m .. 0, 1: m + 1 .. T - 1
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = min(max(P.lengths[b], 0), P.N), m = path_middle(T), K = P.K;
+    const int64_t ld = P.ld;
+    int32_t *prow = P.path + (size_t)b * P.N;
+    if (half == 0)
+        for (int n = T + tid; n < P.N; n += kTraceThreads) prow[n] = -1;
+    if (T == 0) {
+        if (half == 0 && tid == 0) P.score[b] = -INFINITY;
+        return;
+    }
+    int32_t *const ptr = (int32_t *)(tr_rows + kTraceRows * ld);
+    double *const red_v = (double *)(ptr + ((K + 2) & ~1));        // [waves]
+    int32_t *const red_a = (int32_t *)(red_v + kTraceThreads / kWave);
+    float *const cand_v = (float *)(red_a + kTraceThreads / kWave);   // [2][kTraceWalk]
+    int32_t *const cand_s = (int32_t *)(cand_v + 2 * kTraceWalk);
+    const int n_rows = half ? T - 1 - m : m;
+    auto frame_of = [&](int i) { return half ? m + 1 + i : m - 1 - i; };   // the i-th row: frame of the state it decides
+    // row i -> its place, by the loading waves
+    const int n16 = (int)(ld / 4), loader = wave - kTraceWalk;
+    const int mine = loader >= 0 && loader < kTraceLoad ? ((n16 + kWave - 1) / kWave - loader + kTraceLoad - 1) / kTraceLoad : 0;   // pieces of a row
+    auto issue = [&](int i) {
+        const float4 *row = (const float4 *)(P.rows + ((size_t)b * P.N + frame_of(i)) * ld);
+        float4 *dst = (float4 *)(tr_rows + (i % kTraceRows) * ld);
+        for (int p = loader; p * kWave < n16; p += kTraceLoad)
+            if (p * kWave + lane < n16)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + p * kWave + lane),
+                                                 (__attribute__((address_space(3))) void *)(dst + p * kWave), 16, 0, 0);
+    };
+    // all rows but the last `later` asked for have arrived
+    auto arrived = [&](int later) {
+        switch (later * mine) {   // (a wait for fewer than may be on their way is right as well)
+        case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+        case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+        case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+        case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+        case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
+        case 12: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+        case 14: asm volatile("s_waitcnt vmcnt(14)" ::: "memory"); break;
+        case 16: asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); break;
+        case 18: asm volatile("s_waitcnt vmcnt(18)" ::: "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+        }
+    };
+
+    // ---- the score and the path's state at frame m (both workgroups of a sequence find the same)
+    double best = -INFINITY;
+    int at = 0x7fffffff;
+    auto take = [&](double v, int a) {
+        if (v > best || (v == best && a < at)) { best = v; at = a; }
+    };
+    for (int k = tid; k < K; k += kTraceThreads) take((double)P.mid[0][(size_t)b * P.mid_ld + k] + (double)P.mid[1][(size_t)b * P.mid_ld + k], k);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double v = __shfl_xor(best, o, 64);
+        const int a = __shfl_xor(at, o, 64);
+        take(v, a);
+    }
+    if (lane == 0) { red_v[wave] = best; red_a[wave] = at; }
+    const int32_t *const gptr = P.ptr[half];
+    for (int k = tid; k <= K; k += kTraceThreads) ptr[k] = gptr[k];
+    __syncthreads();
+    best = red_v[0]; at = red_a[0];
+    for (int w = 1; w < kTraceThreads / kWave; ++w) take(red_v[w], red_a[w]);
+    const bool none = !(best > -INFINITY);
+    if (half == 0 && tid == 0) P.score[b] = none ? -INFINITY : (P.mid_off[0][b] + P.mid_off[1][b] + best) * kLn2;
+    if (none) {
+        for (int i = tid; i < (half ? n_rows : m + 1); i += kTraceThreads) prow[half ? m + 1 + i : i] = -1;
+        return;
+    }
+    if (half == 0 && tid == 0) prow[m] = at;
+
+    // ---- along the path
+    int s = __builtin_amdgcn_readfirstlane(at);
+    // what the waves have found in step i
+    auto chosen = [&](int i) {
+        const int c = (i & 1) * kTraceWalk;
+        float v = cand_v[c];
+        int a = cand_s[c];
+#pragma unroll
+        for (int w = 1; w < kTraceWalk; ++w) {
+            const float vw = cand_v[c + w];
+            const int aw = cand_s[c + w];
+            const bool better = vw > v || (vw == v && aw < a);
+            v = better ? vw : v;
+            a = better ? aw : a;
+        }
+        return __builtin_amdgcn_readfirstlane(a);
+    };
+    if (wave < kTraceWalk) {
+        const Arc *const arcs = P.arcs[half];
+        __syncthreads();                                    // row 0
+        for (int i = 0; i < n_rows; ++i) {
+            const float *row = tr_rows + (i % kTraceRows) * ld;
+            const int e0 = ptr[s], e1 = ptr[s + 1];
+            float v = -INFINITY;
+            int a = 0x7fffffff;
+            auto look = [&](const Arc &arc) {
+                const float x = row[arc.src] + arc.w;
+                const bool better = x > v || (x == v && arc.src < a);
+                v = better ? x : v;
+                a = better ? arc.src : a;
+            };
+            // (behind the row's end a lane looks at its last arc again: what is asked for at once then takes one trip to the L2)
+            constexpr int kStride = kTraceWalk * kWave, kAhead = 4;
+            const bool any = e0 + wave * kWave < e1;        // (uniform) this wave has an arc
+            if (any && e1 - e0 <= kStride) {
+                look(arcs[min(e0 + tid, e1 - 1)]);
+            } else if (any) {
+                for (int e = e0 + tid; e - lane < e1; e += kAhead * kStride) {
+                    Arc arc[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) arc[u] = arcs[min(e + u * kStride, e1 - 1)];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) look(arc[u]);
+                }
+            }
+            float top = -INFINITY;
+            int src = 0x7fffffff;
+            if (any) {
+                top = lane_value(wave_max_last(v), kWave - 1);
+                src = group_all(v == top ? a : 0x7fffffff, 6, lane, [](int x, int y) { return min(x, y); });
+            }
+            if (lane == 0) {
+                cand_v[(i & 1) * kTraceWalk + wave] = top;
+                cand_s[(i & 1) * kTraceWalk + wave] = src;
+            }
+            lds_barrier();
+            s = min(chosen(i), K - 1);                      // (the state's score is above zero-bar: a term of its row is)
+        }
+    } else if (loader < kTraceLoad) {
+        for (int i = 0; i < min(kTraceRows - 1, n_rows); ++i) issue(i);
+        arrived(n_rows >= kTraceRows - 1 ? kTraceRows - 2 : 0);
+        __syncthreads();
+        for (int i = 0; i < n_rows; ++i) {
+            const bool more = i + kTraceRows - 1 < n_rows;
+            if (more) issue(i + kTraceRows - 1);            // in the place of row i - 1
+            arrived(more ? kTraceRows - 2 : 0);             // row i + 1 is there
+            lds_barrier();
+        }
+    } else {
+        int kept = 0;
+        __syncthreads();
+        for (int i = 0; i < n_rows; ++i) {
+            lds_barrier();
+            const int a = min(chosen(i), K - 1);
+            kept = lane == (i & (kWave - 1)) ? a : kept;
+            if ((i & (kWave - 1)) == kWave - 1 || i == n_rows - 1) {
+                const int j = (i & ~(kWave - 1)) + lane;
+                if (j <= i) prow[frame_of(j)] = kept;
+            }
+        }
+    }
+}
+
 
 // ---------------------------------------------------------------------------
 // launchers
@@ -2311,7 +2542,8 @@ bool recursion_fixed_available()
                                  (const void *)fb_linear_kernel<false, kPFewMost>, (const void *)fb_linear_kernel<true, 0>,
                                  (const void *)fb_linear_kernel<true, kPFew>, (const void *)fb_linear_kernel<true, kPFewMost>,
                                  (const void *)fb_leaky_linear_kernel<0>, (const void *)fb_leaky_linear_kernel<kPFew>,
-                                 (const void *)fb_leaky_linear_kernel<kPFewMost>};
+                                 (const void *)fb_leaky_linear_kernel<kPFewMost>, (const void *)fb_best_linear_kernel<0>,
+                                 (const void *)fb_best_linear_kernel<kPFew>, (const void *)fb_best_linear_kernel<kPFewMost>};
         for (const void *k : kernels) {
             hipFuncAttributes attr{};
             if (hipFuncGetAttributes(&attr, k) != hipSuccess || attr.sharedSizeBytes != 0) return false;
@@ -2364,6 +2596,17 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
                    : launch_rec(fb_recursion_kernel<kNWShared, float, false, 0>, nw, p, lds_bytes, stream);
     return f64 ? launch_rec(fb_recursion_kernel<kNWSmall, double, false, 0>, nw, p, lds_bytes, stream)
                : launch_rec(fb_recursion_kernel<kNWSmall, float, false, 0>, nw, p, lds_bytes, stream);
+}
+
+int launch_best_linear(const RecParams &p, void *stream)
+{
+    for (int i = 0; i < p.n_dir; ++i)
+        if (!p.shared || !p.dir[i].prob.units || !p.dir[i].mid || !p.dir[i].out) return fail(FB_EHIP, "internal error: best-path launch without its plan");
+    const size_t lds = probability_lds_bytes(p.D, false);
+    if (lds > kLdsBytes || !recursion_fixed_available()) return fail(FB_EHIP, "internal error: best-path launch beyond the on-chip memory");
+    const int few = few_units(p);
+    auto kern = few == kPFew ? fb_best_linear_kernel<kPFew> : few ? fb_best_linear_kernel<kPFewMost> : fb_best_linear_kernel<0>;
+    return launch_rec(kern, kNWShared, p, lds, stream);
 }
 
 size_t leaky_linear_lds_bytes(int32_t K, int32_t Ccap, int32_t D, bool backward)
@@ -2419,6 +2662,22 @@ int launch_backtrace(const BacktraceParams &p, void *stream)
     }
     hipLaunchKernelGGL(fb_backtrace_kernel, dim3((unsigned)(2 * p.B)), dim3(kBtThreads), lds_bytes, (hipStream_t)stream, q);
     return check_launch("backtrace kernel launch");
+}
+
+size_t best_trace_lds_bytes(int32_t K)
+{
+    const size_t ld = ((size_t)K + 3) & ~(size_t)3;
+    return kTraceRows * ld * 4 + (((size_t)K + 2) & ~(size_t)1) * 4 + kTraceThreads / kWave * 12 + 2 * kTraceWalk * 8;
+}
+
+int launch_best_trace(const BestTraceParams &p, void *stream)
+{
+    const size_t lds = best_trace_lds_bytes(p.K);
+    if (lds > kLdsBytes || (p.ld & 3) != 0 || ((uintptr_t)p.rows & 15) != 0) return fail(FB_EHIP, "internal error: best-path trace launch");
+    const hipError_t e = hipFuncSetAttribute((const void *)fb_best_trace_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return fail(FB_EHIP, std::string("hipFuncSetAttribute(LDS size): ") + hipGetErrorString(e));
+    hipLaunchKernelGGL(fb_best_trace_kernel, dim3((unsigned)(2 * p.B)), dim3(kTraceThreads), lds, (hipStream_t)stream, p);
+    return check_launch("best-path trace kernel launch");
 }
 
 int launch_posteriors(const PostParams &p, size_t lds_bytes, void *stream)

@@ -652,6 +652,44 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
     return true;
 }
 
+// The plan's units with the best path's weights: the same arcs (rows [0, K), columns ascending, parallel ones merged by their largest), w in log2
+// units, -inf where the lane only pads.  False if an arc of the plan is not among them.
+bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units)
+{
+    units = S.units;
+    std::vector<int32_t> state_of((size_t)S.K + (size_t)S.Ccap + 1, -1);   // of a state, a clone; none for the dump slot
+    std::iota(state_of.begin(), state_of.begin() + S.K, 0);
+    for (const CloneDesc &cd : S.clones)
+        for (int32_t i = 0; i < cd.count; ++i) state_of[(size_t)S.K + (size_t)cd.first + (size_t)i] = cd.state;
+    for (const PWaveDesc &wd : S.waves) {
+        int c = 0, u0 = 0;
+        for (int u = 0; u < wd.n_units; ++u) {
+            if (!((wd.close_mask[u / 64] >> (u % 64)) & 1u)) continue;
+            const uint32_t *cw = S.close_words.data() + ((size_t)wd.cw_base + (size_t)c++) * kWave;
+            for (; u0 <= u; ++u0) {
+                uint32_t *unit = units.data() + ((size_t)wd.unit_base + (size_t)u0) * 3 * kWave;
+                for (int l = 0; l < kWave; ++l)
+                    for (int r = 0; r < 2; ++r) {
+                        float v;
+                        std::memcpy(&v, &unit[l * 3 + 1 + r], 4);
+                        if (v == 0.0f) {
+                            v = -INFINITY;
+                        } else {
+                            const int32_t row = state_of[(cw[l] & 0xffffu) / 4u];
+                            const int32_t src = state_of[(r ? unit[l * 3] >> 16 : unit[l * 3] & 0xffffu) / 4u];
+                            if (row < 0 || src < 0) return false;
+                            const int32_t *at = std::lower_bound(col + ptr[row], col + ptr[row + 1], src);
+                            if (at == col + ptr[row + 1] || *at != src) return false;
+                            v = w[at - col];
+                        }
+                        std::memcpy(&unit[l * 3 + 1 + r], &v, 4);
+                    }
+            }
+        }
+    }
+    return true;
+}
+
 // y = A x as the kernel forms it (lanes, groups of lanes, clones), in double; x and y hold one value per state
 // (ordinary numbers, not logs).  cycles (nullable): the gather cycles of a time step under the bank model above,
 // and the least any order could need (two per gather).

@@ -136,6 +136,30 @@ def test_viterbi_backtrace_block_edges(fb, K):
     check(fb, g, D, emis, lengths, f"block edges K={K}")
 
 
+@pytest.mark.parametrize("K,deg", [(1100, 2), (1300, 5), (3001, 12)])
+def test_viterbi_kept_rows(fb, K, deg):
+    """Graphs whose vectors are kept instead of back-pointers, in each of that kernel's forms (all units in registers, and not): halves of
+    fewer rows than are on their way at a time, and around the 64 frames of a path that are stored at once; equal scores."""
+    import torch
+    rng = np.random.default_rng(K)
+    D = 19
+    n = K * deg
+    src = np.concatenate([np.arange(K), rng.integers(0, K, n), rng.integers(0, K, 700)]).astype(np.int32)
+    dst = np.concatenate([(np.arange(K) + 1) % K, rng.integers(0, K, n), np.full(700, 5)]).astype(np.int32)
+    g = wl.Graph(K, src, dst, (-rng.exponential(size=src.size)).astype(np.float32), rng.integers(0, D, K).astype(np.int32),
+                 (-rng.exponential(size=K)).astype(np.float32), (-rng.exponential(size=K)).astype(np.float32))
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_linear_weights(h) == 2
+    h.destroy()
+    lengths = np.array([1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 127, 128, 129, 130, 131, 260], np.int32)
+    emis = (rng.standard_normal((lengths.size, int(lengths.max()), D)) * 2).astype(np.float32)
+    check(fb, g, D, emis, lengths, f"kept rows K={K}")
+    g.logw[:] = -1.0                                         # every path of a frame's count is worth the same
+    g.init[:] = 0
+    g.final[:] = 0
+    check(fb, g, D, np.zeros_like(emis), lengths, f"equal scores K={K}")
+
+
 @pytest.mark.parametrize("state", ["auto", "wide"])
 def test_viterbi_masked_meeting_frame(fb, state):
     """The frame where the halves meet masked with -1e20 in every pdf: what is behind it is the best path of that piece
