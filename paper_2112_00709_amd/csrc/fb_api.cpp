@@ -42,7 +42,7 @@ RecDir make_dir(const fb_graph *g, bool backward, void *out, bool out_carrier, d
     r.Ccap = backward ? g->h_bwd.Ccap : g->h_fwd.Ccap;
     r.backward = backward ? 1 : 0;
     r.fill_pad = fill_pad ? 1 : 0;
-    r.prob = backward ? g->pbwd : g->pfwd;
+    r.prob = backward ? g->pbwd : g->psum;
     r.small = backward ? g->sbwd : g->sfwd;
     return r;
 }
@@ -336,6 +336,7 @@ RecParams leaky_recursion_params(const fb_graph *g, const float *emis, const int
     p.Ecap = D;
     for (int i = 0; i < 2; ++i) {
         p.dir[i] = make_dir(g, i == 1, nullptr, true, nullptr, nullptr, 1.0f, false);
+        p.dir[i].prob = i == 1 ? g->pbwd : g->pfwd;   // (the leak reaches every state: none runs apart)
         p.dir[i].out_linear = 1;
     }
     return p;

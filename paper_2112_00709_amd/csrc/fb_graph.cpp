@@ -514,6 +514,14 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     rc = fail(FB_EHIP, "internal error: best-path weights of a probability-domain plan");
                     break;
                 }
+                if (dir == 0) {
+                    std::vector<int64_t> sptr;
+                    std::vector<int32_t> scol;
+                    std::vector<float> sw;
+                    merge_parallel(K, ptr, col, w, false, sptr, scol, sw);
+                    if (!pstream_apart(g->hp_fwd, D, sptr.data(), scol.data(), sw.data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain))
+                        g->apart_words.clear();
+                }
                 g->best_ptr[dir].assign(mptr.begin(), mptr.end());
                 g->best_arcs[dir].reserve(mcol.size());
                 for (size_t i = 0; i < mcol.size(); ++i) g->best_arcs[dir].push_back(Arc{mcol[i], mw[i]});
@@ -578,6 +586,11 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 if (g->linear_p) {
                     put_pstream(A, g->hp_fwd, g->pfwd);
                     put_pstream(A, g->hp_bwd, g->pbwd);
+                    if (!g->apart_words.empty()) {
+                        A.put(g->apart_units, &g->psum.units);
+                        A.put(g->apart_close, &g->psum.close_words);
+                        A.put(g->apart_words, &g->psum.apart);
+                    }
                     for (int dir = 0; dir < 2; ++dir) {
                         A.put(g->best_units[dir], &g->best[dir].units);
                         A.put(g->best_ptr[dir], &g->d_best_ptr[dir]);
@@ -586,6 +599,16 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 }
             }
             rc = A.finish(g);
+            if (g->linear_p) {
+                const PStreamDev apart = g->psum;
+                g->psum = g->pfwd;
+                if (apart.apart) {
+                    g->psum.units = apart.units;
+                    g->psum.close_words = apart.close_words;
+                    g->psum.apart = apart.apart;
+                    g->psum.apart_gain = g->apart_gain;
+                }
+            }
             if (g->linear_p)
                 for (int dir = 0; dir < 2; ++dir) {
                     const uint32_t *units = g->best[dir].units;

@@ -259,7 +259,13 @@ struct PStreamDev {
     int32_t max_units = 0;        // most units of a wave
     int32_t paired = 0;           // as PStreamHost::paired
     float dim = 0.0f;
+    // states that run apart (pstream_apart; nullptr: none): by lane of the data-moving wave the state (-1: none), the lanes of its
+    // row's sources (-1: none) and their weights, then the states outside that their arcs enter (-1: none)
+    const int32_t *apart = nullptr;
+    float apart_gain = 0.0f;      // log2 of the largest sum of weights from those states into one outside
 };
+constexpr int kApartArcs = 4, kApartTargets = 4;                      // per lane
+constexpr int kApartWords = (1 + 2 * kApartArcs + kApartTargets) * kWave;
 
 // rows [0, K) of a CSR-like matrix: entries ptr[r]..ptr[r+1], column col[], weight w[] (log2 units; -inf entries are
 // dropped); row_vidx[r] = emission index of row r, n_vidx = number of emission entries.  False, with the reason in
@@ -267,6 +273,10 @@ struct PStreamDev {
 bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const float *w, const int32_t *row_vidx, int32_t n_vidx,
                    PStreamHost &out, std::string &why);
 bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units);
+// The states of a forward plan that are better run apart (see there): its units and close words without them, and what the kernel
+// needs to run them.  False: none.
+bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
+                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain);
 bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why);
 bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why);
 
@@ -362,6 +372,10 @@ struct fb_graph {
     bool linear_p = false;            // the recursions run in the probability domain (linear_run): the plans below exist
     fb::PStreamHost hp_fwd, hp_bwd;   // its plans, host
     fb::PStreamDev pfwd, pbwd;        // and device
+    std::vector<uint32_t> apart_units, apart_close;   // the sums' forward plan of a graph with states that run apart
+    std::vector<int32_t> apart_words;
+    float apart_gain = 0.0f;
+    fb::PStreamDev psum;              // (device; pfwd where there are none)
     std::vector<uint32_t> best_units[2];      // the best path's: those plans with its weights, and the rows forward and backward
     std::vector<int32_t> best_ptr[2];
     std::vector<fb::Arc> best_arcs[2];

@@ -694,11 +694,16 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)))
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
 // LOG: rows leave as logarithms.  FEW (kPFew, kPFewMost or 0): no wave has more than that many units, so all of them stay in
 // registers, nothing is re-read, and the registers that leaves take gathers further ahead.
+// States that get nothing from the rest of the graph and so fall ever further behind it (PStreamDev::apart) are run by the
+// data-moving wave, a lane a state, in the log form: their entries of the vector are what a float holds of them, zero below its
+// range.  What that loses where such a state's arcs enter a state of the rest must be below rounding there, and once it has lost something the
+// rows keep less than all of them: from then on they may not matter any more - at every step their share of any state's sum below
+// 2^-24 of it, at the end of log Z - or the run gives up as below.
 // TROP: the best path (fb_viterbi).  The vector is scores in log2 units, the largest of the step before taken off at every step, the units
 // carry weights in log2 units, a row is the largest of its terms: two additions and one maximum of three a unit.  Which arc
 // attains it is not kept: rows leave as they are, and fb_best_trace_kernel finds it anew for the one row a frame that the
 // path takes.  A direction goes half way (path_middle); there is no range to leave.
-template <bool LEAKY, bool LOG, int FEW, bool TROP = false>
+template <bool LEAKY, bool LOG, int FEW, bool TROP = false, bool APART = false>
 __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, const int which, double *lds_raw)
 {
     constexpr int NW = kNWShared, XF = kXsFixed, R = FEW ? FEW : kPResident;
@@ -996,6 +1001,12 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // frame's own emission)
     double csum = 0.0;
     bool ok = true;
+    // (data-moving wave; the others only know whether there are such states)
+    const bool n_apart = APART && S.apart;   // (an instantiation of its own: the code beside the loop costs others 1 %)
+    int ap_state = -1;
+    double ap_value = 0.0;
+    float ap_floor = 0.0f, ap_top = 0.0f;   // what the next vector's entries may not lie below; the largest entry of those states
+    bool ap_lost = false;                   // some entry has left the range so far
     if (io_wave) {
         float c = base0 + (float)kLinBias + (bwd ? 0.0f : emx0);
         csum = TROP ? 0.0 : (double)c;
@@ -1003,6 +1014,61 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             if (off_seq) off_seq[frame(0)] = csum * (double)R_.out_scale;
             if (R_.cum) R_.cum[(size_t)b * P.N + frame(0)] = (float)(csum - cum_shift);
         }
+        // ---- the states that run apart: a lane's state, its sources' lanes and weights, its value (log2, true)
+        constexpr double kNoValue = -1.0e36;                // (below kNegBig: zero-bar)
+        int ap_pdf = 0;
+        int32_t ap_src[kApartArcs], ap_tgt[kApartTargets];
+        float ap_w[kApartArcs];
+        if (n_apart) {
+            const int32_t *ap = S.apart + lane;
+            ap_state = ap[0];
+#pragma unroll
+            for (int t = 0; t < kApartArcs; ++t) {
+                ap_src[t] = ap[(1 + t) * kWave];
+                ap_w[t] = __int_as_float(ap[(1 + kApartArcs + t) * kWave]);
+            }
+#pragma unroll
+            for (int t = 0; t < kApartTargets; ++t) ap_tgt[t] = ap[(1 + 2 * kApartArcs + t) * kWave];
+            ap_pdf = P.pdf[max(ap_state, 0)];
+            const double v = (double)R_.bound[max(ap_state, 0)] + (double)er[ap_pdf] * kLog2e;
+            ap_value = ap_state >= 0 && !(v < (double)kNegBig) ? v : kNoValue;
+        }
+        // the entries that arcs of theirs enter, in x, against what may have been lost on the way there
+        auto apart_check = [&](const float *x, float *word) {
+            float low = INFINITY;
+#pragma unroll
+            for (int t = 0; t < kApartTargets; ++t)
+                if (ap_tgt[t] >= 0) low = tmin(low, x[ap_tgt[t]]);
+            if (__any(low < ap_floor) && lane == kWave - 1) lds_raise(word, INFINITY);
+        };
+        auto apart_step = [&](int i, const float *row, float *word, float minus_log2_scale) {
+            const int nxt = i & 1;
+            if (ap_lost) apart_check(xb + (nxt ^ 1) * Xs, word);
+            // (for vector i: its sum takes the entries of vector i - 1, the lost ones below the range, times the step's scale)
+            ap_floor = !ap_lost ? 0.0f : fexp2(tmin(tmax(-minus_log2_scale + S.apart_gain + 24.0f + flog2(tmax(kLinDimP, ap_top)), -126.0f), 127.0f));
+            double v[kApartArcs], top = kNoValue;
+#pragma unroll
+            for (int t = 0; t < kApartArcs; ++t) {
+                v[t] = __shfl(ap_value, max(ap_src[t], 0), kWave) + (double)ap_w[t];
+                v[t] = ap_src[t] >= 0 ? v[t] : kNoValue;
+                top = fmax(top, v[t]);
+            }
+            float sum = 0.0f;
+#pragma unroll
+            for (int t = 0; t < kApartArcs; ++t) sum += fexp2((float)(v[t] - top));
+            const double now = top + (double)flog2(sum) + (double)row[ap_pdf] * kLog2e;
+            const bool live = ap_state >= 0 && !(now < (double)kNegBig);   // (a NaN is)
+            ap_value = live ? now : kNoValue;
+            const double at = ap_value - csum, e = __builtin_rint(at + (double)kLinBias);
+            const float x = live ? ldexpf(fexp2((float)(at + (double)kLinBias - e)), (int)fmin(fmax(e, -1000.0), 1000.0)) : 0.0f;
+            if (ap_state >= 0) {
+                xb[nxt * Xs + ap_state] = x;
+                if (staged) bh[nxt * XL + ap_state] = live ? (float)at * R_.out_scale : -INFINITY;
+            }
+            ap_lost = ap_lost || __any(live && x < kLinDimP);
+            ap_top = lane_value(wave_max_last(x), kWave - 1);
+            if (lane == kWave - 1) lds_raise(word, ap_top);
+        };
         float e_prev = emx0, e_cur = Ts > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
         float *row_a = er, *row_b = er + Es, *row_c = er + 2 * Es;   // rows of frame i - 1 (from step i on: i + 2), i, i + 1
         for (int i = 1; i < Ts; ++i) {
@@ -1021,6 +1087,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
                 if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
             }
+            if (n_apart) apart_step(i, row_b, row_b + Es - 1, nls);
             if (!TROP && mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
             e_prev = e_cur;
             if (i + 1 < Ts) {
@@ -1036,6 +1103,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
         if (lane == 0) emaxw[0] = e_prev;   // that of the last frame, for log Z
+        if (n_apart && ok && ap_lost) apart_check(xb + ((Ts - 1) & 1) * Xs, step_word(Ts - 1));
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
@@ -1341,15 +1409,19 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         if (io_wave && lane == 0) R_.mid_off[b] = csum + (double)cl;
         return true;
     }
+    if (n_apart && ok) lds_barrier();   // (the last vector has been looked at)
     // a state below the range in the last step: give up as well (every wave reads the same word)
     if (ok && !(*step_word(Tn - 1) < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
     __builtin_amdgcn_s_setprio(3);
-    if (!ok) {
+    auto give_up = [&]() {
         // every wave has left the time loop at the same step; nothing of this run may still be on its way to LDS or
         // to the output rows when the log form starts over
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
         if (!LEAKY && tid == 0) atomicAdd(&g_linear_restarts, 1u);
+    };
+    if (!ok) {
+        give_up();
         return false;
     }
 
@@ -1377,6 +1449,18 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // backward: the vector of the last step still lacks the scale of its frame's emissions
             R_.logz[b] = (csum + (bwd ? (double)em_last : 0.0) + (double)m + (double)flog2(s)) * kLn2;
         }
+        if (n_apart) {   // (64 states at most, each no more than the largest)
+            if (io_wave && ap_lost) {
+                const double share = ap_state >= 0 ? ap_value + (double)R_.obound[ap_state] : -1.0e36;
+                const double most = wave_max(share) + 6.0, all = lane_value(csum + (double)m + (double)flog2(s), 0);
+                if (lane == 0 && !(most < all - 24.0)) red[6] = 1.0f;
+            }
+            __syncthreads();
+            if (red[6] != 0.0f) {
+                give_up();
+                return false;
+            }
+        }
     }
     // ---- padded frames
     if (R_.fill_pad) {
@@ -1392,7 +1476,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     return true;
 }
 
-template <bool LOG, int FEW>
+template <bool LOG, int FEW, bool APART>
 __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecParams P)
 {
     __builtin_amdgcn_s_setprio(3);
@@ -1400,7 +1484,7 @@ __global__ __launch_bounds__(kNWShared * 64) void fb_linear_kernel(const RecPara
     int b, which;
     if (P.started && threadIdx.x == 0) atomicAdd(P.started, 1u);   // this workgroup has its compute unit
     resolve_sequence<kNWShared>(P, lds_raw, b, which);
-    if (!linear_run<false, LOG, FEW>(P, b, which, lds_raw)) {
+    if (!linear_run<false, LOG, FEW, false, APART>(P, b, which, lds_raw)) {
         recursion_run<kNWShared, float, false, kXsFixed, false>(P, b, which, lds_raw);
         if (P.dir[which].fmt && threadIdx.x == 0) P.dir[which].fmt[b] = 0;   // this sequence's rows are in the log form
     }
@@ -2531,6 +2615,20 @@ static int launch_rec(Kern kern, int nw, const RecParams &p, size_t lds_bytes, v
     return check_launch("recursion kernel launch");
 }
 
+typedef void (*rec_kernel_t)(const RecParams);
+
+static rec_kernel_t linear_kernel_of(bool logs, int few, bool apart)
+{
+    if (apart)
+        return few == kPFew ? (logs ? fb_linear_kernel<true, kPFew, true> : fb_linear_kernel<false, kPFew, true>)
+               : few        ? (logs ? fb_linear_kernel<true, kPFewMost, true> : fb_linear_kernel<false, kPFewMost, true>)
+                            : (logs ? fb_linear_kernel<true, 0, true> : fb_linear_kernel<false, 0, true>);
+    return few == kPFew ? (logs ? fb_linear_kernel<true, kPFew, false> : fb_linear_kernel<false, kPFew, false>)
+           : few        ? (logs ? fb_linear_kernel<true, kPFewMost, false> : fb_linear_kernel<false, kPFewMost, false>)
+                        : (logs ? fb_linear_kernel<true, 0, false> : fb_linear_kernel<false, 0, false>);
+}
+static const void *linear_kernel(bool logs, int few, bool apart) { return (const void *)linear_kernel_of(logs, few, apart); }
+
 bool recursion_fixed_available()
 {
     // the fixed-buffer instantiation addresses LDS from 0: usable only while the kernel has no static LDS in front
@@ -2538,9 +2636,10 @@ bool recursion_fixed_available()
     static const bool ok = [] {
         const void *kernels[] = {(const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed>,
                                  (const void *)fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>,
-                                 (const void *)fb_linear_kernel<false, 0>, (const void *)fb_linear_kernel<false, kPFew>,
-                                 (const void *)fb_linear_kernel<false, kPFewMost>, (const void *)fb_linear_kernel<true, 0>,
-                                 (const void *)fb_linear_kernel<true, kPFew>, (const void *)fb_linear_kernel<true, kPFewMost>,
+                                 linear_kernel(false, 0, false), linear_kernel(false, kPFew, false), linear_kernel(false, kPFewMost, false),
+                                 linear_kernel(true, 0, false), linear_kernel(true, kPFew, false), linear_kernel(true, kPFewMost, false),
+                                 linear_kernel(false, 0, true), linear_kernel(false, kPFew, true), linear_kernel(false, kPFewMost, true),
+                                 linear_kernel(true, 0, true), linear_kernel(true, kPFew, true), linear_kernel(true, kPFewMost, true),
                                  (const void *)fb_leaky_linear_kernel<0>, (const void *)fb_leaky_linear_kernel<kPFew>,
                                  (const void *)fb_leaky_linear_kernel<kPFewMost>, (const void *)fb_best_linear_kernel<0>,
                                  (const void *)fb_best_linear_kernel<kPFew>, (const void *)fb_best_linear_kernel<kPFewMost>};
@@ -2574,10 +2673,9 @@ int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t
                 lds_bytes = std::max(lds_bytes, probability_lds_bytes(p.D, p.dir[i].backward != 0 || logs));
             }
             if (lds_bytes > kLdsBytes) return fail(FB_EHIP, "internal error: probability-domain launch beyond the on-chip memory");
-            const int few = few_units(p);
-            auto kern = few == kPFew ? (logs ? fb_linear_kernel<true, kPFew> : fb_linear_kernel<false, kPFew>)
-                        : few        ? (logs ? fb_linear_kernel<true, kPFewMost> : fb_linear_kernel<false, kPFewMost>)
-                                     : (logs ? fb_linear_kernel<true, 0> : fb_linear_kernel<false, 0>);
+            bool apart = false;
+            for (int i = 0; i < p.n_dir; ++i) apart = apart || p.dir[i].prob.apart;
+            const rec_kernel_t kern = linear_kernel_of(logs, few_units(p), apart);
             return launch_rec(kern, nw, p, lds_bytes, stream);
         }
         if (p.linear_w) return launch_rec(fb_recursion_kernel<kNWShared, float, false, kXsFixed, true>, nw, p, lds_bytes, stream);

@@ -652,6 +652,106 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
     return true;
 }
 
+// States that get nothing from the rest of the graph - a cycle that no arc from outside enters, what only such cycles feed, and whatever
+// feeds those - lose some binary orders against the frame's largest entry at every frame (e^-9 with 3000 pdfs of standard deviation 3), leave a
+// float's range after some 40 frames, and used to send the whole run into the log form.  Graphs with skewed destinations often have
+// them: half of the drawn ones with 6000 states, 1 to 40 such states.  A set of states that contains all of its predecessors needs no
+// other state's value, so the wave that moves data runs it beside the others, a lane a state, in the log form (doubles); the plan's
+// rows of those states go (weights 0, the dump slot).  Taken while a lane holds a row (4 arcs) and there are lanes; the larger rest of the
+// graph is what the state with the most arcs in reaches.
+bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
+                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain)
+{
+    const int32_t K = S.K;
+    std::vector<std::vector<std::pair<int32_t, float>>> out((size_t)K);   // live arcs by source
+    std::vector<int32_t> n_in((size_t)K, 0), queue;
+    int32_t hub = 0;
+    for (int32_t r = 0; r < K; ++r) {
+        for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e)
+            if (w[e] > -INFINITY) { out[(size_t)col[e]].push_back({r, w[e]}); ++n_in[(size_t)r]; }
+        if (n_in[(size_t)r] > n_in[(size_t)hub]) hub = r;
+    }
+    auto reach = [&](std::vector<char> &seen) {             // ... of the states in queue
+        for (size_t h = 0; h < queue.size(); ++h)
+            for (const auto &a : out[(size_t)queue[h]])
+                if (!seen[(size_t)a.first]) { seen[(size_t)a.first] = 1; queue.push_back(a.first); }
+    };
+    std::vector<char> rest((size_t)K, 0);
+    rest[(size_t)hub] = 1;
+    queue = {hub};
+    reach(rest);
+    // what stays when states without an arc in from what stays go, one after the other, is reached from a cycle
+    std::vector<char> stays((size_t)K, 1);
+    queue.clear();
+    for (int32_t k = 0; k < K; ++k)
+        if (n_in[(size_t)k] == 0) { stays[(size_t)k] = 0; queue.push_back(k); }
+    for (size_t h = 0; h < queue.size(); ++h)
+        for (const auto &a : out[(size_t)queue[h]])
+            if (--n_in[(size_t)a.first] == 0) { stays[(size_t)a.first] = 0; queue.push_back(a.first); }
+    std::vector<int32_t> lane_of((size_t)K, -1), states;
+    auto add = [&](int32_t k) {
+        if (lane_of[(size_t)k] < 0) { lane_of[(size_t)k] = (int32_t)states.size(); states.push_back(k); }
+    };
+    for (int32_t k = 0; k < K && states.size() <= (size_t)kWave; ++k)
+        if (stays[(size_t)k] && !rest[(size_t)k]) add(k);
+    if (states.empty()) return false;
+    for (size_t h = 0; h < states.size(); ++h) {            // (with all that feeds them)
+        if (states.size() > (size_t)kWave || ptr[states[h] + 1] - ptr[states[h]] > kApartArcs) return false;
+        for (int64_t e = ptr[states[h]]; e < ptr[states[h] + 1]; ++e)
+            if (w[e] > -INFINITY) add(col[e]);
+    }
+    for (const CloneDesc &cd : S.clones)
+        if (lane_of[(size_t)cd.state] >= 0) return false;
+    words.assign((size_t)kApartWords, -1);
+    std::vector<double> into((size_t)K, 0.0);
+    std::vector<int32_t> targets;
+    for (size_t l = 0; l < states.size(); ++l) {
+        const int32_t k = states[l];
+        words[l] = k;
+        int t = 0;
+        for (int64_t e = ptr[k]; e < ptr[k + 1]; ++e) {
+            if (!(w[e] > -INFINITY)) continue;
+            words[(size_t)(1 + t) * kWave + l] = lane_of[(size_t)col[e]];
+            std::memcpy(&words[(size_t)(1 + kApartArcs + t) * kWave + l], &w[e], 4);
+            ++t;
+        }
+        for (const auto &a : out[(size_t)k])
+            if (lane_of[(size_t)a.first] < 0) {
+                if (into[(size_t)a.first] == 0.0) targets.push_back(a.first);
+                into[(size_t)a.first] += std::exp2((double)a.second);
+            }
+    }
+    if (targets.size() > (size_t)(kApartTargets * kWave)) return false;
+    double most = 0.0;
+    for (size_t i = 0; i < targets.size(); ++i) {
+        words[(size_t)(1 + 2 * kApartArcs) * kWave + i] = targets[i];
+        most = std::max(most, into[(size_t)targets[i]]);
+    }
+    gain = most > 0.0 ? (float)std::ceil(std::log2(most)) : 0.0f;
+    // the plan without their rows
+    units = S.units;
+    close_words = S.close_words;
+    const uint32_t dump = (uint32_t)(K + S.Ccap) * 4u | ((uint32_t)n_vidx * 4u) << 16;
+    for (const PWaveDesc &wd : S.waves) {
+        int c = 0, u0 = 0;
+        for (int u = 0; u < wd.n_units; ++u) {
+            if (!((wd.close_mask[u / 64] >> (u % 64)) & 1u)) continue;
+            uint32_t *cw = close_words.data() + ((size_t)wd.cw_base + (size_t)c++) * kWave;
+            for (int l = 0; l < kWave; ++l) {
+                const uint32_t row = (cw[l] & 0xffffu) / 4u;
+                if (row >= (uint32_t)K || lane_of[row] < 0) continue;
+                cw[l] = dump;
+                for (int v = u0; v <= u; ++v) {
+                    uint32_t *unit = units.data() + ((size_t)wd.unit_base + (size_t)v) * 3 * kWave + l * 3;
+                    unit[1] = unit[2] = 0u;                 // (weights of 0)
+                }
+            }
+            u0 = u + 1;
+        }
+    }
+    return true;
+}
+
 // The plan's units with the best path's weights: the same arcs (rows [0, K), columns ascending, parallel ones merged by their largest), w in log2
 // units, -inf where the lane only pads.  False if an arc of the plan is not among them.
 bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units)
