@@ -519,7 +519,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     std::vector<int32_t> scol;
                     std::vector<float> sw;
                     merge_parallel(K, ptr, col, w, false, sptr, scol, sw);
-                    if (!pstream_apart(g->hp_fwd, D, sptr.data(), scol.data(), sw.data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain))
+                    if (!pstream_apart(g->hp_fwd, D, sptr.data(), scol.data(), sw.data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain, g->apart_lasting))
                         g->apart_words.clear();
                 }
                 g->best_ptr[dir].assign(mptr.begin(), mptr.end());
@@ -607,6 +607,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     g->psum.close_words = apart.close_words;
                     g->psum.apart = apart.apart;
                     g->psum.apart_gain = g->apart_gain;
+                    g->psum.apart_lasting = g->apart_lasting;
                 }
             }
             if (g->linear_p)

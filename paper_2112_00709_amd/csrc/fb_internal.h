@@ -262,6 +262,7 @@ struct PStreamDev {
     // states that run apart (pstream_apart; nullptr: none): by lane of the data-moving wave the state (-1: none), the lanes of its
     // row's sources (-1: none) and their weights, then the states outside that their arcs enter (-1: none)
     const int32_t *apart = nullptr;
+    int32_t apart_lasting = 0;    // the first lanes: those alive for good, whose arcs those are
     float apart_gain = 0.0f;      // log2 of the largest sum of weights from those states into one outside
 };
 constexpr int kApartArcs = 4, kApartTargets = 4;                      // per lane
@@ -276,7 +277,7 @@ bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t 
 // The states of a forward plan that are better run apart (see there): its units and close words without them, and what the kernel
 // needs to run them.  False: none.
 bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
-                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain);
+                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain, int32_t &n_lasting);
 bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why);
 bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why);
 
@@ -375,6 +376,7 @@ struct fb_graph {
     std::vector<uint32_t> apart_units, apart_close;   // the sums' forward plan of a graph with states that run apart
     std::vector<int32_t> apart_words;
     float apart_gain = 0.0f;
+    int32_t apart_lasting = 0;
     fb::PStreamDev psum;              // (device; pfwd where there are none)
     std::vector<uint32_t> best_units[2];      // the best path's: those plans with its weights, and the rows forward and backward
     std::vector<int32_t> best_ptr[2];

@@ -696,9 +696,9 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)))
 // registers, nothing is re-read, and the registers that leaves take gathers further ahead.
 // States that get nothing from the rest of the graph and so fall ever further behind it (PStreamDev::apart) are run by the
 // data-moving wave, a lane a state, in the log form: their entries of the vector are what a float holds of them, zero below its
-// range.  What that loses where such a state's arcs enter a state of the rest must be below rounding there, and once it has lost something the
-// rows keep less than all of them: from then on they may not matter any more - at every step their share of any state's sum below
-// 2^-24 of it, at the end of log Z - or the run gives up as below.
+// range.  Such an entry is lost, and so is one of which more than 2^-24 came from lost ones: the rows that leave lack mass that it stands for.
+// A lost entry may not matter any more - its share in the sum of any state of the rest, and at the end in log Z, below 2^-24 - or the run
+// gives up as below.
 // TROP: the best path (fb_viterbi).  The vector is scores in log2 units, the largest of the step before taken off at every step, the units
 // carry weights in log2 units, a row is the largest of its terms: two additions and one maximum of three a unit.  Which arc
 // attains it is not kept: rows leave as they are, and fb_best_trace_kernel finds it anew for the one row a frame that the
@@ -1005,8 +1005,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     const bool n_apart = APART && S.apart;   // (an instantiation of its own: the code beside the loop costs others 1 %)
     int ap_state = -1;
     double ap_value = 0.0;
-    float ap_floor = 0.0f, ap_top = 0.0f;   // what the next vector's entries may not lie below; the largest entry of those states
-    bool ap_lost = false;                   // some entry has left the range so far
+    float ap_floor = 0.0f, ap_top = 0.0f;   // what the next vector's entries may not lie below; the largest lost entry
+    uint64_t ap_lost = 0;                   // the lanes whose entries are lost
     if (io_wave) {
         float c = base0 + (float)kLinBias + (bwd ? 0.0f : emx0);
         csum = TROP ? 0.0 : (double)c;
@@ -1043,8 +1043,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         };
         auto apart_step = [&](int i, const float *row, float *word, float minus_log2_scale) {
             const int nxt = i & 1;
-            if (ap_lost) apart_check(xb + (nxt ^ 1) * Xs, word);
-            // (for vector i: its sum takes the entries of vector i - 1, the lost ones below the range, times the step's scale)
+            if (ap_floor > 0.0f) apart_check(xb + (nxt ^ 1) * Xs, word);
+            // (for vector i: its sums take the lost entries of vector i - 1, times the step's scale)
             ap_floor = !ap_lost ? 0.0f : fexp2(tmin(tmax(-minus_log2_scale + S.apart_gain + 24.0f + flog2(tmax(kLinDimP, ap_top)), -126.0f), 127.0f));
             double v[kApartArcs], top = kNoValue;
 #pragma unroll
@@ -1056,7 +1056,10 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             float sum = 0.0f;
 #pragma unroll
             for (int t = 0; t < kApartArcs; ++t) sum += fexp2((float)(v[t] - top));
-            const double now = top + (double)flog2(sum) + (double)row[ap_pdf] * kLog2e;
+            const double all = top + (double)flog2(sum), now = all + (double)row[ap_pdf] * kLog2e;
+            bool lost = false;
+#pragma unroll
+            for (int t = 0; t < kApartArcs; ++t) lost = lost || (ap_src[t] >= 0 && ((ap_lost >> (ap_src[t] & 63)) & 1u) && !(v[t] < all - 24.0));
             const bool live = ap_state >= 0 && !(now < (double)kNegBig);   // (a NaN is)
             ap_value = live ? now : kNoValue;
             const double at = ap_value - csum, e = __builtin_rint(at + (double)kLinBias);
@@ -1065,9 +1068,13 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
                 xb[nxt * Xs + ap_state] = x;
                 if (staged) bh[nxt * XL + ap_state] = live ? (float)at * R_.out_scale : -INFINITY;
             }
-            ap_lost = ap_lost || __any(live && x < kLinDimP);
-            ap_top = lane_value(wave_max_last(x), kWave - 1);
-            if (lane == kWave - 1) lds_raise(word, ap_top);
+            lost = live && (lost || x < kLinDimP);
+            ap_lost = __ballot(lost);
+            ap_top = lane_value(wave_max_last(lost ? x : 0.0f), kWave - 1);
+            const float most = wave_max_last(x);
+            // (a lost entry of a state that is alive in the first frames only: what it enters is not looked at)
+            const bool odd = S.apart_lasting < kWave && (ap_lost >> S.apart_lasting) != 0;
+            if (lane == kWave - 1) lds_raise(word, odd ? INFINITY : most);
         };
         float e_prev = emx0, e_cur = Ts > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
         float *row_a = er, *row_b = er + Es, *row_c = er + 2 * Es;   // rows of frame i - 1 (from step i on: i + 2), i, i + 1
@@ -1103,7 +1110,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
         if (lane == 0) emaxw[0] = e_prev;   // that of the last frame, for log Z
-        if (n_apart && ok && ap_lost) apart_check(xb + ((Ts - 1) & 1) * Xs, step_word(Ts - 1));
+        if (n_apart && ok && ap_floor > 0.0f) apart_check(xb + ((Ts - 1) & 1) * Xs, step_word(Ts - 1));
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
@@ -1451,7 +1458,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }
         if (n_apart) {   // (64 states at most, each no more than the largest)
             if (io_wave && ap_lost) {
-                const double share = ap_state >= 0 ? ap_value + (double)R_.obound[ap_state] : -1.0e36;
+                const double share = (ap_lost >> lane) & 1u ? ap_value + (double)R_.obound[ap_state] : -1.0e36;
                 const double most = wave_max(share) + 6.0, all = lane_value(csum + (double)m + (double)flog2(s), 0);
                 if (lane == 0 && !(most < all - 24.0)) red[6] = 1.0f;
             }

@@ -660,7 +660,7 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
 // rows of those states go (weights 0, the dump slot).  Taken while a lane holds a row (4 arcs) and there are lanes; the larger rest of the
 // graph is what the state with the most arcs in reaches.
 bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
-                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain)
+                   std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain, int32_t &n_lasting)
 {
     const int32_t K = S.K;
     std::vector<std::vector<std::pair<int32_t, float>>> out((size_t)K);   // live arcs by source
@@ -695,6 +695,7 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
     for (int32_t k = 0; k < K && states.size() <= (size_t)kWave; ++k)
         if (stays[(size_t)k] && !rest[(size_t)k]) add(k);
     if (states.empty()) return false;
+    n_lasting = (int32_t)states.size();   // (what feeds them is alive in the first frames only, and so may be what it feeds beside them)
     for (size_t h = 0; h < states.size(); ++h) {            // (with all that feeds them)
         if (states.size() > (size_t)kWave || ptr[states[h] + 1] - ptr[states[h]] > kApartArcs) return false;
         for (int64_t e = ptr[states[h]]; e < ptr[states[h] + 1]; ++e)
@@ -716,7 +717,7 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
             ++t;
         }
         for (const auto &a : out[(size_t)k])
-            if (lane_of[(size_t)a.first] < 0) {
+            if (lane_of[(size_t)a.first] < 0 && l < (size_t)n_lasting) {
                 if (into[(size_t)a.first] == 0.0) targets.push_back(a.first);
                 into[(size_t)a.first] += std::exp2((double)a.second);
             }

@@ -19,16 +19,16 @@ def fb():
 
 def _graph(rng, K, D, deg, n_cycle, final_main=True):
     """A mixing graph of K states and, behind them, a cycle of n_cycle states that nothing enters, a state only it feeds, one
-    that feeds it and has no arc in, and a state with a self-loop; all of them have arcs into the rest.  Their pdf is D - 1, nobody else's."""
+    that feeds it and has no arc in (and feeds another that nothing else enters), and a state with a self-loop; all have arcs into the rest.  Their pdf is D - 1, nobody else's."""
     n = int(K * deg)
     src, dst = np.concatenate([np.arange(K), rng.integers(0, K, n)]), np.concatenate([(np.arange(K) + 1) % K, rng.integers(0, K, n)])
     cyc = K + np.arange(n_cycle)
-    fed, feeds, loop = K + n_cycle, K + n_cycle + 1, K + n_cycle + 2
-    extra = [(c, K + (c - K + 1) % n_cycle) for c in cyc] + [(cyc[0], fed), (cyc[-1], fed), (feeds, cyc[0]), (loop, loop), (feeds, 3)]
+    fed, feeds, loop, drain = K + n_cycle, K + n_cycle + 1, K + n_cycle + 2, K + n_cycle + 3
+    extra = [(c, K + (c - K + 1) % n_cycle) for c in cyc] + [(cyc[0], fed), (cyc[-1], fed), (feeds, cyc[0]), (loop, loop), (feeds, 3), (feeds, drain), (drain, 5)]
     extra += [(s, int(rng.integers(0, K))) for s in list(cyc) * 3 + [fed, fed, loop]]
     src = np.concatenate([src, [a for a, _ in extra]]).astype(np.int32)
     dst = np.concatenate([dst, [b for _, b in extra]]).astype(np.int32)
-    total = K + n_cycle + 3
+    total = K + n_cycle + 4
     pdf = rng.integers(0, D - 1, total).astype(np.int32)
     pdf[K:] = D - 1
     final = np.zeros(total, np.float32)
@@ -49,7 +49,7 @@ def _emissions(rng, D, T):
     return emis
 
 
-@pytest.mark.parametrize("K,D,deg,n_cycle", [(1100, 40, 2, 1), (1300, 101, 4, 2), (3001, 90, 13, 7), (1500, 64, 3, 61)])
+@pytest.mark.parametrize("K,D,deg,n_cycle", [(1100, 40, 2, 1), (1300, 101, 4, 2), (3001, 90, 13, 7), (1500, 64, 3, 60)])
 def test_alpha_beta_posteriors(fb, K, D, deg, n_cycle):
     import torch
     rng = np.random.default_rng(K)
