@@ -35,6 +35,8 @@
 // label-sequence graphs of 21-161 states, 209 frames, 194 -> 64 us, and 40 us from both ends (fb_viterbi).  What bounds it: the latency of that chain (310
 // clocks a step with one computing wave and two arcs a row); with 16 slices and more the issue of double arithmetic.
 //
+// Sums over shared graphs that mix run on probabilities instead (fb_small_linear.hip).
+//
 // Variants <NC, R, TM>: NC computing waves of R slices each, TM arcs per lane; the smallest that holds the batch's
 // largest sub-graph is launched.
 #include "fb_small_run.h"
