@@ -76,13 +76,13 @@ def test_log_z_of_lost_states(fb):
     import torch
     rng = np.random.default_rng(8)
     g = _graph(rng, 1300, 50, 4, 3, final_main=False)
-    emis = _emissions(rng, 50, 60)
+    emis = _emissions(rng, 50, 66)
     before = fb.fb_debug_linear_restarts()
     h = fb.graph_from(g, 50)
-    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(np.full(5, 60, np.int32)).cuda()
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(np.full(5, 66, np.int32)).cuda()
     z = fb.fb_alpha(h, e, l)[2].cpu().numpy()
     assert fb.fb_debug_linear_restarts() - before >= 2       # (the first and the last, which end with those states lost)
-    want = oracle.forward_backward(g, emis, np.full(5, 60, np.int32)).logz
+    want = oracle.forward_backward(g, emis, np.full(5, 66, np.int32)).logz
     assert np.all(np.abs(z - want) <= 1e-4 * np.abs(want))
     h.destroy()
 
