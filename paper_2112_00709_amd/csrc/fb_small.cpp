@@ -101,9 +101,9 @@ bool small_in_bounds(const SmallHost &S, std::string &why)
 // ordinary size, one cycle-bearing component, and every state on it or hanging off it within kDeep steps either way - an
 // entry then lies at most kDeep arcs and emissions behind the largest (twice 24 steps of 20 nats each are 1400 of the 1100
 // binary orders there are up to the largest: met by no emissions but masks, and a run that leaves the range is only slower).
-// Measured, a direction in the log form -> in the probability domain, us: 701 states, 3.5 k arcs, 97 pdfs, 23 x 211 frames 253 -> 139
-// (300 pdfs 259 -> 176); 1000 states, 4 k arcs, 16 x 200 242 -> 142; 300 states, 1.2 k arcs, 8 x 200 131 -> 64; 120 states 97 -> 67; 60
-// states 80 -> 46; 30 states 65 -> 37.
+// Measured, a direction in the log form -> in the probability domain, us: 701 states, 3.5 k arcs, 97 pdfs, 23 x 211 frames 253 -> 130
+// (300 pdfs 259 -> 156); 1000 states, 4 k arcs, 16 x 200 242 -> 135; 300 states, 1.2 k arcs, 8 x 200 131 -> 62; 120 states 97 -> 68; 60
+// states 80 -> 47; 30 states 65 -> 38.
 bool small_mixes(int32_t K, const std::vector<int64_t> &in_ptr, const std::vector<int32_t> &in_src, const std::vector<float> &in_w,
                  const std::vector<int64_t> &out_ptr, const std::vector<int32_t> &out_dst, const std::vector<float> &out_w,
                  const std::vector<float> &init2, const std::vector<float> &final2)

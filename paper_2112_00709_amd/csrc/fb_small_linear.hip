@@ -21,7 +21,11 @@
 // 2^(kTarget + 9 * 40) = 2^860.  A live entry is not below 2^-600 (kLowest), or a factor above zero below 2^-320 (kLowestFactor), without the run
 // being given up: a row's sum is then at least 2^-1020, an ordinary double, so nothing above zero is lost unseen.  A run that
 // is given up, and one that meets emissions larger than 65536 in size, is done over in the log form by the same workgroup
-// (small_again; 701 states over 211 frames, 23 sequences, a direction: 139 us, 466 when every run is given up, 253 in the log form at once).
+// (small_again; emissions of that size go straight to its plain form).  The waves that form the factors know of a mask some frames
+// ahead: what the first two frames hold ends the run before its first step, what a later one holds some steps behind it (`stop`).
+// 701 states over 211 frames, 23 sequences, a direction: 130 us; with a pdf masked by -1e4 in every frame 217 (467 when runs were given up
+// behind their last frame only, by functions whose memory accesses all counted as ones to LDS too), in the frame in the middle 285 (467), by
+// -1e20 in that frame 549 (913); in the log form at once 253, 253 and 706.  40 states, 100 frames: 28, 50 (70), 67 (70), 157 (195); 43, 43, 169.
 //
 // What bounds it: with one or two slices a wave the chain of a step (LDS read, three dependent double operations, the lanes of long rows,
 // LDS write, barrier: some 400 clocks at 60 states); with 24 slices the LDS (120 eight-byte gathers a step) and the issue of the three waves a
@@ -42,10 +46,18 @@ struct LinearShape {
     static constexpr int U = KS / kWave;                    // states (and pdfs) per lane of such a wave
     static constexpr int kRing = 16;                        // frames whose sums are kept
     // in LDS: two vectors, two before the emission (backward), two rows of factors, the pdfs' bytes in a row of emissions, sums by frame, first maxima, flags
+    // The word `stop` takes the first step in which some wave tells that the run leaves the range (as they count up: the least), 1 - kStop
+    // if that is known before the first one.
+    // Every wave goes by what it read at its last look; a look sees all that has been written in earlier steps (what is written in the
+    // same step it may see or not).  Computing waves look when kLook steps begin and decide about the kLook steps behind those: not
+    // having seen a word of step n, they go on to step n + 2 kLook - 1 at most.  The others look when a round begins and decide behind it about the
+    // next: to step n + 2 L - 1.  So all of them leave the loop in front of the same step, n + kStop.
+    static constexpr int kLook = NC <= 2 ? 16 : 8, kStop = 2 * kLook;   // (short steps: a look is 3 % of eight of them)
+    static_assert(L <= kLook && kStop >= 2 * kLook && kStop >= 2 * L, "nobody is past the step where all stop");
     static constexpr uint32_t kRow = XS * 8, kPre = 2 * kRow, kFac = 4 * kRow, kFacRow = KS * 8;
     static constexpr uint32_t kPdf = kFac + 2 * kFacRow, kCum = kPdf + KS * 4, kSum = kCum + kRing * 8, kFirst = kSum + kRing * 4, kFlag = kFirst + L * 4, kFin = kFlag + 64;
     static constexpr size_t kBytes = kFin + 8 * NC;
-    static_assert(L + 1 < kRing && L <= 16, "sums of the frames under way");
+    static_assert(L + 1 < kRing && L <= 8, "sums of the frames under way; flags, and the word `stop` behind them");
 };
 
 __device__ unsigned int g_small_restarts;   // diagnostic: runs given up since the library was loaded
@@ -88,15 +100,15 @@ __device__ __forceinline__ double row_total(double v, int lg, int lane)
     return v;
 }
 
-// the run done over in the log form
+// the run done over in the log form (plain: in that for large emissions, at once)
 template <int NC, int R, int L>
-__device__ __attribute__((noinline)) void small_again(__attribute__((address_space(3))) double *lds_raw, uint64_t args, int b_, int which_)
+__device__ __attribute__((noinline)) void small_again(__attribute__((address_space(3))) double *lds_raw, uint64_t args, int b_, int which_, int plain_)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     args = (uint64_t)(uint32_t)uniform((int)(uint32_t)args) | (uint64_t)(uint32_t)uniform((int)(uint32_t)(args >> 32)) << 32;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (rows of the first attempt arrive before these are stored)
     lds_barrier();
-    small_run<NC, R, 4, false, L>(*(const RecParams *)args, args, (double *)lds_raw, uniform(b_), uniform(which_));
+    small_run<NC, R, 4, false, L>(*(LaunchParams *)args, args, (double *)lds_raw, uniform(b_), uniform(which_), uniform(plain_) != 0);
 }
 
 }  // namespace
@@ -127,9 +139,12 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
     double *const cum_ring = (double *)(lds + S::kCum);     // true vector = vector * 2^cum_ring[frame]
     int *const sum_ring = (int *)(lds + S::kSum);           // the scales alone, summed up (scale_sum)
     float *const first_max = (float *)(lds + S::kFirst);
-    uint32_t *const flag = (uint32_t *)(lds + S::kFlag);    // [L] the run is to be done over
+    uint32_t *const flag = (uint32_t *)(lds + S::kFlag);    // [L] the run is to be done over (1), and in the plain form (3)
+    volatile __attribute__((address_space(3))) int *const stop = (__attribute__((address_space(3))) int *)(flag + 8);
     double *const fin = (double *)(lds + S::kFin);
-    bool again = false;
+    uint32_t again = 0;                                     // (uniform) the flags together
+    // the step the loop ends in front of, from what `stop` held
+    auto end_of = [&](int word) { return min(Tn, min(__builtin_amdgcn_readfirstlane(word), Tn) + S::kStop); };
 
     if (Tn > 0 && wave < NC) {
         // ---- computing waves
@@ -161,6 +176,7 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
             *(double *)(lds + tg[j]) = v * *(const double *)(lds + S::kFac + pl[j]);
             if (bwd) *(double *)(lds + S::kPre + tg[j]) = v;
         }
+        const int first_end = end_of(*stop);
         lds_barrier();
         __builtin_amdgcn_s_setprio(2);                      // (theirs is the chain)
         auto step = [&](auto cc, auto bwd_c) __attribute__((always_inline)) {
@@ -182,12 +198,17 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
             lds_barrier();
         };
         auto all_steps = [&](auto bwd_c) __attribute__((always_inline)) {
-            int i = 1;
-            for (; i + 1 < Tn; i += 2) {
-                step(std::integral_constant<uint32_t, 0>{}, bwd_c);
-                step(std::integral_constant<uint32_t, 1>{}, bwd_c);
+            int i = 1, end = first_end;
+            while (i + 1 < end) {
+                int word = *stop;                           // (arrives behind the gathers' backs)
+                for (const int last = min(i + S::kLook, end); i + 1 < last; i += 2) {
+                    step(std::integral_constant<uint32_t, 0>{}, bwd_c);
+                    step(std::integral_constant<uint32_t, 1>{}, bwd_c);
+                }
+                asm volatile("" : "+v"(word));
+                end = end_of(word);
             }
-            if (i < Tn) step(std::integral_constant<uint32_t, 0>{}, bwd_c);
+            if (i < end) step(std::integral_constant<uint32_t, 0>{}, bwd_c);
         };
         if (bwd) all_steps(std::true_type{});
         else all_steps(std::false_type{});
@@ -221,6 +242,7 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
         };
         uint32_t size = 0, lowest = ~0u;                    // large emissions; smallest high word above zero, less one
         int lowest_fac = 0;
+        auto too_low = [&]() { return (lowest < (uint32_t)((1023 + kLowest) << 20) - 1u) | (lowest_fac < kLowestFactor); };
         auto largest = [&](const float(&e)[PU]) __attribute__((always_inline)) {
             float mx = -INFINITY;
 #pragma unroll
@@ -252,6 +274,15 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
         load(q + L, ea);
         const float mx0 = largest(e0);
         if (lane == 0) first_max[q] = mx0;
+        if (q == 0 && lane == 0) *stop = Tn;
+        lds_barrier();
+        if (q < 2) factors(q, e0, in_log2(mx0), q == 0 ? kTarget : 0);
+        // in step n: what has been seen so far is told
+        auto tell = [&](int n) __attribute__((always_inline)) {
+            if (__builtin_expect(__any((size > kLargeBits) | too_low()), 0))   // (in assembly: few instructions where it is not so)
+                asm volatile("ds_min_i32 %0, %1" :: "v"((uint32_t)(uintptr_t)stop), "v"(n) : "memory");
+        };
+        tell(1 - S::kStop);                                 // (a label forbidden by a mask, say, is so in every frame: no step at all)
         lds_barrier();
         double cum = -(double)kTarget, cum_before = 0.0;    // of frame q and of the one before it
         for (int j = 0; j <= q; ++j) {
@@ -262,13 +293,12 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
             cum_ring[q] = cum;
             sum_ring[q] = kTarget;
         }
-        if (q < 2) factors(q, e0, in_log2(mx0), q == 0 ? kTarget : 0);
         // for rows before the emission everything is one frame back
         double row_cum = bwd ? cum_before : cum;
         int row_sum = bwd && q == 0 ? 0 : kTarget;
-        lds_barrier();
+        int end = end_of(*stop);
         lds_barrier();                                      // vector 0
-        auto bar = [&](int n) { if (n < Tn) lds_barrier(); };   // the end of step n
+        auto bar = [&](int n) { if (n < end) lds_barrier(); };   // the end of step n (kStop is more than L)
         for (int n = 1; n <= q; ++n) {
             if (n + 1 == q) factors(q, e0, in_log2(mx0), 0);
             bar(n);
@@ -308,7 +338,12 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
             // whole: all its L steps and frame i + L are there
             auto round = [&](int i, float(&en)[PU], auto whole) __attribute__((always_inline)) {
                 constexpr bool kWhole = decltype(whole)::value;
-                auto bar = [&](int m) __attribute__((always_inline)) { if (kWhole || m < Tn) lds_barrier(); };
+                // (arithmetic stays in its step: drawn together, two of them make one that the others wait for)
+                auto bar = [&](int m) __attribute__((always_inline)) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (kWhole || m < end) lds_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                };
                 float hi = 0.0f;                            // (high words of numbers that are not negative, compared as floats)
                 int s = 0, sum = 0, high = 0;
                 double next_cum = 0.0, mx2 = 0.0;
@@ -350,14 +385,21 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
                     }
                 };
                 auto prepare = [&]() __attribute__((always_inline)) {
-                    if constexpr (kWhole) {
-                        factors(i + L, en, mx2, s);
-                        load(i + (1 + kDepth) * L, en);
-                    }
+                    if constexpr (kWhole) factors(i + L, en, mx2, s);
+                };
+                auto request = [&]() __attribute__((always_inline)) {
+                    if constexpr (kWhole) load(i + (1 + kDepth) * L, en);
                 };
                 const char *row = lds + (bwd ? S::kPre : 0u) + (i & 1) * S::kRow;
 #pragma unroll
                 for (int u = 0; u < n; ++u) v[u] = *(const double *)(row + state[u] * 8);
+                int word = 0;
+                if (kWhole) {
+                    word = *stop;                           // (the look of this round: for the next one)
+                    // (in step i + 1, of the round before: behind the factors it would be in the longest of a round's steps, which all
+                    // waves wait for: 16 states 28 -> 36 us, 701 states 137 -> 152)
+                    tell(i + 1);
+                }
                 if constexpr (L == 4) {
                     look();
                     bar(i + 1);
@@ -368,6 +410,7 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
                     centre();
                     prepare();
                     bar(i + 3);
+                    request();
                     emit(i, P1{});
                     emit(i, P2{});
                     bar(i + 4);
@@ -387,21 +430,24 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
                     bar(i + 6);
                     prepare();
                     bar(i + 7);
+                    request();
                     bar(i + 8);
                 }
                 row_cum = next_cum;
                 row_sum = bwd ? sum : sum + s;
+                if (kWhole) end = end_of(word);
             };
             int i = q;
-            for (; i + kDepth * L < Tn; i += kDepth * L) {
+            // (two copies of a round, not a third for an odd last one: a short sequence meets each for the first time, and waits for the code)
+            for (; i + L < end; i += L) {
                 round(i, ea, std::true_type{});
-                if constexpr (kDepth == 2) round(i + L, eb, std::true_type{});
+                if constexpr (kDepth == 2) {
+                    i += L;
+                    if (i + L >= end) break;
+                    round(i, eb, std::true_type{});
+                }
             }
-            if (kDepth == 2 && i + L < Tn) {
-                round(i, ea, std::true_type{});
-                i += L;
-            }
-            if (i < Tn) round(i, ea, std::false_type{});   // (no emissions are asked of a last round)
+            if (i < end) round(i, ea, std::false_type{});   // (no emissions are asked of a last round)
         };
         auto sized = [&](auto rows_c) __attribute__((always_inline)) {
             if constexpr (U == 16) {
@@ -413,19 +459,17 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
         if (out_f) sized(std::integral_constant<int, 1>{});
         else if (out_t) sized(std::integral_constant<int, 2>{});
         else sized(std::integral_constant<int, 0>{});
-        const bool low = lowest < (uint32_t)((1023 + kLowest) << 20) - 1u || lowest_fac < kLowestFactor;
-        const bool any = __any(low || size > kLargeBits);
-        if (lane == 0) flag[q] = any ? 1u : 0u;
+        const uint32_t f = __any(size > kLargeBits) ? 3u : __any(too_low()) ? 1u : 0u;
+        if (lane == 0) flag[q] = f;
         lds_barrier();
     }
     if (Tn > 0) {
-        uint32_t f = 0;
-        for (int i = 0; i < L; ++i) f |= flag[i];
-        again = __builtin_amdgcn_readfirstlane((int)f) != 0;
+        for (int i = 0; i < L; ++i) again |= flag[i];
+        again = (uint32_t)__builtin_amdgcn_readfirstlane((int)again);
     }
-    if (__builtin_expect(again, 0)) {
+    if (__builtin_expect(again != 0, 0)) {
         if (threadIdx.x == 0) atomicAdd(&g_small_restarts, 1u);
-        small_again<NC, R, L>((__attribute__((address_space(3))) double *)lds_raw, (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), b, which);
+        small_again<NC, R, L>((__attribute__((address_space(3))) double *)lds_raw, (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), b, which, again >> 1);
     } else {
         if (Tn > 0) {
             // ---- log Z from the last vector and the end weights, by the computing waves
@@ -448,7 +492,7 @@ __global__ __launch_bounds__((LinearShape<NC, R>::NT)) void fb_small_linear_kern
         } else if (threadIdx.x == 0 && D.logz) {
             D.logz[b] = -INFINITY;
         }
-        small_pad<S::NT>(D, out_f, off_seq, out_ld, Tn, P.N, K);
+        small_pad<S::NT>(D.fill_pad != 0, out_f, off_seq, out_ld, Tn, P.N, K);
     }
     count_done(P);
 }

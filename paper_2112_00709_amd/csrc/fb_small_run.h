@@ -40,6 +40,16 @@ struct SmallShape {
     }
 };
 
+// The launch's parameters where the kernel finds them, and what they point to.  (Spelled out for functions that are not part of the
+// kernel, to which a pointer read from memory might point anywhere: an access through such a one counts as one to LDS too, so a barrier waits
+// for every load and store, and every store might change a parameter.)
+typedef const __attribute__((address_space(4))) RecParams LaunchParams;
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *in_global(T *p)
+{
+    return (__attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+
 // What a finite value is larger than kLarge in size by, as a number to take the maximum of: the size's bits, moved so that
 // infinities and NaN wrap round to small ones.
 constexpr uint32_t kLargeBits = (0x47800000u << 1) + 0x01000000u;   // ... that number of kLarge = 65536
@@ -232,10 +242,10 @@ __device__ __attribute__((noinline)) double small_plain(__attribute__((address_s
 }
 
 // The rows of the frames behind the sequence's end, by NT threads.
-template <int NT>
-__device__ __forceinline__ void small_pad(const RecDir &D, float *out_f, double *off_seq, size_t out_ld, int Tn, int N, int K)
+template <int NT, class F, class D64>
+__device__ __forceinline__ void small_pad(bool fill, F out_f, D64 off_seq, size_t out_ld, int Tn, int N, int K)
 {
-    if (!D.fill_pad) return;
+    if (!fill) return;
     const int tid = threadIdx.x;
     if (out_f)
         for (int f = Tn; f < N; ++f)
@@ -245,20 +255,20 @@ __device__ __forceinline__ void small_pad(const RecDir &D, float *out_f, double 
 }
 
 // A (sequence, direction) run by the whole workgroup of NC + NIO waves, its padded frames included; args: where the launch's parameters
-// are in memory (P is them).
-template <int NC, int R, int TM, bool TROP, int NIO>
-__device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, double *lds_raw, const int b, const int which)
+// are in memory (P is them); plain: in the plain form at once.
+template <int NC, int R, int TM, bool TROP, int NIO, class PARAMS>
+__device__ __forceinline__ void small_run(PARAMS &P, uint64_t args, double *lds_raw, const int b, const int which, const bool plain = false)
 {
     using S = SmallShape<NC, R, NIO>;
     constexpr int XS = S::XS, RPB = S::RPB, RB = S::RB, A = S::kAhead;
     constexpr double kNone = TROP ? -INFINITY : kZero;      // zero-bar
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const RecDir &D = P.dir[which];
+    const auto &D = P.dir[which];
     const bool bwd = D.backward != 0, pre = bwd && !TROP;   // pre: rows leave before the emission is applied
     const SmallSub sd = D.small.sub[P.shared ? 0 : b];
     const int K = sd.K, k0 = sd.k0;
-    const int Tn = min(max(P.lengths[b], 0), P.N);
+    const int Tn = min(max(in_global(P.lengths)[b], 0), P.N);
     const int mid = path_middle(Tn);
     const int Ts = Tn > 0 && TROP ? (bwd ? Tn - mid : mid + 1) : Tn;   // frames this direction visits
     auto frame = [&](int i) { return bwd ? Tn - 1 - i : i; };
@@ -272,9 +282,9 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
 
     const size_t out_ld = P.shared ? (size_t)(D.out_ld ? D.out_ld : K) : (size_t)P.Ktot;
     const size_t out_at = P.shared ? (size_t)b * P.N * out_ld : (size_t)k0;
-    float *out_f = (D.out && !D.out_carrier) ? (float *)D.out + out_at : nullptr;
-    double *out_t = (D.out && D.out_carrier) ? (double *)D.out + out_at : nullptr;
-    double *off_seq = D.off ? D.off + (size_t)b * P.N : nullptr;
+    const auto out_f = in_global((D.out && !D.out_carrier) ? (float *)D.out + out_at : nullptr);
+    const auto out_t = in_global((D.out && D.out_carrier) ? (double *)D.out + out_at : nullptr);
+    const auto off_seq = in_global(D.off ? D.off + (size_t)b * P.N : nullptr);
     const int n_bar = (Ts - 1 + RPB - 1) / RPB;             // blocks of rows behind the first one
     const bool shifted = !out_t && (out_f || off_seq);      // rows leave without their largest entry
     // (behind a barrier) whether a wave has told of large emissions
@@ -293,26 +303,28 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
             const int s = wave + j * NC;
             const bool have = s < sd.n_slice;               // (a slice that is not there: every lane adds up nothing)
             const size_t at = (size_t)(sd.slice0 + (have ? s : 0));
-            const uint32_t row = have ? D.small.rows[at * kWave + lane] : kSmallNoRow;
-            lg[j] = have ? __builtin_amdgcn_readfirstlane(D.small.lg[at]) : 0;
+            const uint32_t row = have ? in_global(D.small.rows)[at * kWave + lane] : kSmallNoRow;
+            lg[j] = have ? __builtin_amdgcn_readfirstlane(in_global(D.small.lg)[at]) : 0;
             tg[j] = row == kSmallNoRow ? (uint32_t)S::KS * 8u : row * 8u;
-            po[j] = (uint32_t)P.pdf[k0 + (row == kSmallNoRow ? 0 : (int)row)] * 4u;
+            po[j] = (uint32_t)in_global(P.pdf)[k0 + (row == kSmallNoRow ? 0 : (int)row)] * 4u;
 #pragma unroll
             for (int t = 0; t < TM; ++t) {
-                const Arc a = D.small.arcs[(at * TM + t) * kWave + lane];
-                so[j][t] = (uint32_t)a.src;
-                w[j][t] = have ? dmax((double)a.w, kNone) : kNone;
+                const auto a = in_global(D.small.arcs) + (at * TM + t) * kWave + lane;
+                so[j][t] = (uint32_t)a->src;
+                w[j][t] = have ? dmax((double)a->w, kNone) : kNone;
             }
         }
         // the row of emissions to ask for next (uniform): the frames in order of the steps, the last one again behind the end
         const ptrdiff_t em_step = bwd ? -(ptrdiff_t)P.D : (ptrdiff_t)P.D;
-        const float *em_row = P.emis + ((size_t)b * P.N + (size_t)frame(0)) * P.D;
+        auto em_row = in_global(P.emis + ((size_t)b * P.N + (size_t)frame(0)) * P.D);
         int em_left = Ts - 1;
         auto next_em = [&]() {
             em_row += em_left > 0 ? em_step : 0;
             --em_left;
         };
-        auto emission = [&](int j) { return *(const float *)((const char *)em_row + po[j]); };
+        typedef const __attribute__((address_space(1))) char gchar;
+        typedef const __attribute__((address_space(1))) float gfloat;
+        auto emission = [&](int j) { return *(gfloat *)((gchar *)em_row + po[j]); };
         auto ask = [&](float(&to)[R][A]) __attribute__((always_inline)) {   // the next A frames' emissions
 #pragma unroll
             for (int a = 0; a < A; ++a) {
@@ -321,7 +333,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
                 next_em();
             }
         };
-        uint32_t size = D.small.large;                      // the largest of size_bits() so far
+        uint32_t size = plain ? ~0u : D.small.large;        // the largest of size_bits() so far
         auto tell = [&](int at) {
             const bool any = __any(size > kLargeBits);
             if (lane == 0) large_w[at + wave] = any ? 1u : 0u;
@@ -336,7 +348,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const bool real = tg[j] != (uint32_t)S::KS * 8u;
-                const double s = real ? (double)D.bound[k0 + (int)(tg[j] >> 3)] : kNone;
+                const double s = real ? (double)in_global(D.bound)[k0 + (int)(tg[j] >> 3)] : kNone;
                 // (a best path's backward recursion ends before the emission of its last frame, which may be this one)
                 *(double *)(lds + tg[j]) = TROP ? dmax(s + (bwd && Ts == 1 ? 0.0 : (double)e0[j] * kLog2e), kNone) : dmax(s, kNone) + emitted(e0[j]);
                 if (pre) *(double *)((char *)pr + tg[j]) = s;
@@ -430,7 +442,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
             if constexpr (TROP) {
                 if (i > 0) {
                     const int row = bwd ? f + 1 : f;         // (path_middle)
-                    uint16_t *orow = D.bp + (P.shared ? ((size_t)b * P.N + row) * D.bp_ld : (size_t)row * D.bp_ld + k0);
+                    const auto orow = in_global(D.bp) + (P.shared ? ((size_t)b * P.N + row) * D.bp_ld : (size_t)row * D.bp_ld + k0);
 #pragma unroll
                     for (int u = u0; u < u1; ++u)
                         if (u * kWave < K) orow[at(u)] = r.p[u];
@@ -438,19 +450,19 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
             } else {
                 if (shifted) {
                     if (out_f) {
-                        float *orow = out_f + (size_t)f * out_ld;
+                        const auto orow = out_f + (size_t)f * out_ld;
 #pragma unroll
                         for (int u = u0; u < u1; ++u)
                             if (u * kWave < K) orow[at(u)] = is_zero(r.v[u]) ? -INFINITY : (float)(r.v[u] - r.c) * D.out_scale;
                     }
                     if (off_seq && u0 == 0 && lane == 0) off_seq[f] = r.c * scale;
                 } else if (out_t) {
-                    double *orow = out_t + (size_t)f * out_ld;
+                    const auto orow = out_t + (size_t)f * out_ld;
 #pragma unroll
                     for (int u = u0; u < u1; ++u)
                         if (u * kWave < K) orow[at(u)] = is_zero(r.v[u]) ? -INFINITY : r.v[u];
                 }
-                if (D.cum && u0 == 0 && lane == 0) D.cum[(size_t)b * P.N + f] = 0.0f;   // (carrier rows are not shifted)
+                if (D.cum && u0 == 0 && lane == 0) in_global(D.cum)[(size_t)b * P.N + f] = 0.0f;   // (carrier rows are not shifted)
             }
         };
         using N0 = std::integral_constant<int, 0>;
@@ -516,7 +528,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
         const double *xl = xr + (size_t)((Ts - 1) % RB) * XS;
         if constexpr (TROP) {
             // ---- the last vector, for the kernel that joins the two halves
-            double *mrow = (double *)D.mid + (size_t)b * D.mid_ld;
+            const auto mrow = in_global((double *)D.mid) + (size_t)b * D.mid_ld;
             double c = 0.0;
             if (__builtin_expect(again, 0)) {               // (without its largest entry: the other half's vector is added to it)
                 c = -INFINITY;
@@ -532,7 +544,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
             if (wave < NC) {
                 double m = (double)kNegBig;
                 float s = 0.0f;
-                for (int k = wave * kWave + lane; k < K; k += NC * kWave) lse_add(m, s, xl[k] + (double)D.obound[k0 + k]);
+                for (int k = wave * kWave + lane; k < K; k += NC * kWave) lse_add(m, s, xl[k] + (double)in_global(D.obound)[k0 + k]);
 #pragma unroll
                 for (int o = 32; o >= 1; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
                 if (lane == 0) { fin[wave] = m; fin[NC + wave] = (double)s; }
@@ -549,7 +561,7 @@ __device__ __forceinline__ void small_run(const RecParams &P, uint64_t args, dou
         D.logz[b] = -INFINITY;
     }
 
-    small_pad<(NC + NIO) * kWave>(D, out_f, off_seq, out_ld, Tn, P.N, K);
+    small_pad<(NC + NIO) * kWave>(D.fill_pad != 0, out_f, off_seq, out_ld, Tn, P.N, K);
 }
 
 }  // namespace

@@ -88,6 +88,88 @@ def test_runs_that_leave_the_range(K, deg, hub, D, frames):
     h.destroy()
 
 
+@pytest.mark.parametrize("K,deg,hub,D,frames", [SIZES[i] for i in (1, 4, 6, 8, 9, 11)])
+@pytest.mark.parametrize("mask", [-1.0e3, -7.0e4])
+def test_runs_that_end_early(K, deg, hub, D, frames, mask):
+    """One pdf masked in one frame, at every place of the rounds its waves go in: the waves leave the loop together, at once or a while behind
+    that frame, or at the end; so do two masks, found by different waves."""
+    import torch
+    rng = np.random.default_rng(K)
+    g = _graph(rng, K, deg, hub, D)
+    T = 41
+    at = list(range(T)) + [(3, 4), (5, 11), (17, 19), (7, 40)]
+    lengths = np.full(len(at) + 1, T, dtype=np.int32)
+    emis = (rng.standard_normal((lengths.size, T, D)) * 2).astype(np.float32)
+    for q, f in enumerate(at):
+        emis[q, f, int(g.pdf[1])] = mask
+    h = fb.graph_from(g, D)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    before = fb.fb_debug_linear_restarts()
+    a, ca, za = fb.fb_alpha(h, e, l)
+    b, cb, zb = fb.fb_beta(h, e, l)
+    gam, rho = fb.fb_posteriors(h, a, b, l, lengths.size, T)
+    given_up = fb.fb_debug_linear_restarts() - before
+    # (of frame 0 the forward form, of the last frame the backward form may keep a mask of 1000 nats: the first vector reaches further down)
+    assert 2 * len(at) - 4 <= given_up <= 2 * len(at)
+    a, b, ca, cb, za, zb, gam, rho = (t.cpu().numpy() for t in (a, b, ca, cb, za, zb, gam, rho))
+    ref = oracle.forward_backward(g, emis, lengths)
+    for z in (za, zb):
+        assert np.all(np.abs(z - ref.logz) <= 1e-6 * np.maximum(1.0, np.abs(ref.logz)))
+    for q in range(lengths.size):
+        # floats of the rows, as in test_runs_that_leave_the_range
+        tol = 1e-5 + 2.0 ** -24 * (np.abs(a[q]) + np.abs(b[q]))[ref.gamma[q] > 1e-7].max(initial=0.0)
+        assert np.abs(gam[q] - ref.gamma[q]).max() <= tol and np.abs(rho[q] - ref.rho[q]).max() <= tol
+        for x, c, want in ((a[q], ca[q], ref.alpha[q]), (b[q], cb[q], ref.beta[q])):
+            fin = np.isfinite(want)
+            assert np.array_equal(np.isfinite(x), fin)
+            assert np.all(np.abs((x + c[:, None])[fin] - want[fin]) <= 1e-7 * np.abs(x[fin]) + 2e-7 * T + 1e-6 + 3e-9 * np.abs(c).max())
+    h.destroy()
+
+
+def _time(f):
+    """us a call, the least of five rounds of ten"""
+    import torch
+    f()
+    best = np.inf
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 100.0)
+    return best
+
+
+@pytest.mark.parametrize("K,deg", [(40, 4), (200, 4), (701, 3)])
+def test_masks_cost_no_second_run(K, deg):
+    """A forbidden pdf, all along or in a late frame, costs about what it costs the log form, which the same graph with a state more that only
+    keeps its own mass runs in: what is done over in that form is given up as soon as it is known, not at the end."""
+    import torch
+    rng = np.random.default_rng(K)
+    D, T, B = 50, 200, 8
+    g = _graph(rng, K, deg, 0, D)
+    plus = wl.Graph(K + 1, np.append(g.src, K).astype(np.int32), np.append(g.dst, K).astype(np.int32), np.append(g.logw, -1.0).astype(np.float32),
+                    np.append(g.pdf, 0).astype(np.int32), np.append(g.init, 0.0).astype(np.float32), np.append(g.final, 0.0).astype(np.float32))
+    hs = [fb.graph_from(x, D) for x in (g, plus)]
+    assert [fb.fb_graph_small_linear(h) for h in hs] == [1, 0]
+    emis = (rng.standard_normal((B, T, D)) * 2).astype(np.float32)
+    l = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    p = int(g.pdf[1])
+    # (given up at the end as well, and slower there: 1.6 to 2.2 times; a mask of more than 65536 in the second half: 1.16 to 1.34)
+    for frames, mask, most in ((slice(0, T), -1.0e4, 1.25), (slice(T // 2, T // 2 + 1), -1.0e20, 1.05)):
+        x = emis.copy()
+        x[:, frames, p] = mask
+        e = torch.from_numpy(x).cuda()
+        for f in (fb.fb_alpha, fb.fb_beta):
+            t, t_log = (_time(lambda: f(h, e, l)) for h in hs)
+            print(f"[gpu-case] K={K} {f.__name__} mask {mask:g}: {t:.1f} us, log form {t_log:.1f} us", flush=True)
+            assert t <= most * t_log
+    for h in hs:
+        h.destroy()
+
+
 @pytest.mark.parametrize("K,arcs", [(9, 3), (20, 4), (23, 9)])
 def test_masked_frames_and_nan(K, arcs):
     """A frame of masks, one of zero-bar for all, one of zero-bar for some, a NaN: as the general kernel has them."""
