@@ -81,7 +81,8 @@ int run_recursion(const fb_graph *g, const float *emis, const int32_t *lengths, 
             if (tropical) p.dir[i].small = dirs[i].backward ? g->sbtrop : g->strop;
             slices = std::max(slices, (dirs[i].backward ? (own ? g->hs_btrop : g->hs_bwd) : own ? g->hs_trop : g->hs_fwd).max_slices);
         }
-        if (g->small_linear && !tropical) return launch_small_linear(p, slices, stream);
+        if (g->small_linear && !tropical && small_linear_pays(slices, (int64_t)(range.order ? range.count : B) * n_dir))
+            return launch_small_linear(p, slices, stream);
         return launch_small(p, g->hs_fwd.tm, slices, tropical, stream);
     }
     size_t lds = 0;

@@ -506,6 +506,7 @@ struct PostParams {
 // the small-graph kernel: tm, slices as the plans of the graph's directions have them (the most slices)
 int launch_small(const RecParams &p, int tm, int slices, bool tropical, void *stream);
 int launch_small_linear(const RecParams &p, int slices, void *stream);   // ... in the probability domain (four arcs a lane)
+bool small_linear_pays(int slices, int64_t workgroups);                  // ... which for a launch of so many workgroups is the faster form
 unsigned int small_linear_restarts();   // diagnostic: as linear_restarts, for that kernel
 int launch_recursion(int nw, bool f64, bool tropical, const RecParams &p, size_t lds_bytes, void *stream);
 bool recursion_fixed_available();   // the fixed-buffer instantiation (RecParams::xs_fixed) may be launched

@@ -525,6 +525,19 @@ unsigned int small_linear_restarts()
     return hipMemcpyFromSymbol(&n, HIP_SYMBOL(g_small_restarts), sizeof(n)) == hipSuccess ? n : 0u;
 }
 
+// A workgroup with one computing wave (up to two slices) has eight others here, and a wave up to 168 registers: one such workgroup fits a
+// compute unit, where four of the log form's three waves do.  More workgroups than compute units of so small a graph therefore run in that form.  A
+// direction, us, here / in the log form: 16 states, 50 frames, 256 sequences 15 / 21, 512 27 / 23, 1024 52 / 24; over 200 frames 38 / 65, 73 / 72, 143 / 75;
+// 60 states, 50 frames 19 / 26, 36 / 29, 69 / 32.  Of more computing waves the log form too fits once: 120 states, 1024 sequences, 50 frames 89 / 109.
+bool small_linear_pays(int slices, int64_t workgroups)
+{
+    static const int n_cu = [] {
+        int dev = 0, n = 0;
+        return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+    }();
+    return slices > 2 || workgroups <= n_cu;
+}
+
 int launch_small_linear(const RecParams &p, int slices, void *stream)
 {
     for (int i = 0; i < p.n_dir; ++i)

@@ -126,6 +126,36 @@ def test_runs_that_end_early(K, deg, hub, D, frames, mask):
     h.destroy()
 
 
+@pytest.mark.parametrize("K,deg,B,taken", [(16, 3, 256, True), (16, 3, 257, False), (60, 1.5, 300, False), (150, 3, 300, True)])
+def test_more_workgroups_than_compute_units(K, deg, B, taken):
+    """Graphs of one computing wave go to the log form when the chip is full: nothing is given up there."""
+    import torch
+    rng = np.random.default_rng(K)
+    D, T = 20, 6
+    g = _graph(rng, K, deg, 0, D)
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_small_linear(h) == 1 and torch.cuda.get_device_properties(0).multi_processor_count == 256
+    lengths = np.full(B, T, dtype=np.int32)
+    lengths[rng.permutation(B)[:40]] = rng.integers(0, T, 40)
+    emis = (rng.standard_normal((B, T, D)) * 2).astype(np.float32)
+    emis[:, :, int(g.pdf[1])] = -1.0e4
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    before = fb.fb_debug_linear_restarts()
+    a, _, za = fb.fb_alpha(h, e, l)
+    assert fb.fb_debug_linear_restarts() - before == (np.count_nonzero(lengths) if taken else 0)
+    b, _, zb = fb.fb_beta(h, e, l)
+    gam, _ = fb.fb_posteriors(h, a, b, l, B, T)
+    sel = np.flatnonzero(lengths)[::7]
+    ref = oracle.forward_backward(g, emis, lengths, sel=sel)
+    za, zb, gam = za.cpu().numpy(), zb.cpu().numpy(), gam.cpu().numpy()
+    for i, q in enumerate(sel):
+        for z in (za[q], zb[q]):
+            assert abs(z - ref.logz[i]) <= 1e-6 * max(1.0, abs(ref.logz[i]))
+        assert np.abs(gam[q][:lengths[q]] - ref.gamma[i][:lengths[q]]).max() <= 1e-5
+    assert np.all(np.isneginf(za[lengths == 0]))
+    h.destroy()
+
+
 def _time(f):
     """us a call, the least of five rounds of ten"""
     import torch
