@@ -110,12 +110,6 @@ int run_recursion(const fb_graph *g, const float *emis, const int32_t *lengths, 
     // graphs that run in the probability domain were found to fit the fixed buffers when they were created
     if (g->linear_p && !tropical) {
         if (!p.xs_fixed) return fail(FB_EHIP, "internal error: probability-domain kernel without fixed buffers");
-        // States apart (pstream_apart) cost the data-moving wave some 0.1 us a step of a large plan and 0.7 of one whose units all stay in
-        // registers, and save a run of the log form that starts over once they have left a float's range: 203 binary orders at 3 to
-        // 13 a frame.  6000 states, 60 k arcs, 64 sequences of 45 frames 323 -> 163 us a direction (158 on a graph without), of 30 frames that
-        // stay in range 108 -> 113; 1500 states, 7 k arcs, 64 x 60 170 -> 123, 64 x 30 that stay in range 46 -> 66.
-        for (int i = 0; i < n_dir; ++i)
-            if (p.dir[i].prob.apart && N < (p.dir[i].prob.paired ? 64 : 40)) p.dir[i].prob = g->pfwd;
         p.linear_p = 1;
     }
     // graphs whose streams carry weights as 2^w were found to fit the fixed buffers when they were created

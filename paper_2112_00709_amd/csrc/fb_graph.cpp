@@ -587,8 +587,8 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     put_pstream(A, g->hp_fwd, g->pfwd);
                     put_pstream(A, g->hp_bwd, g->pbwd);
                     if (!g->apart_words.empty()) {
-                        A.put(g->apart_units, &g->psum.units);
-                        A.put(g->apart_close, &g->psum.close_words);
+                        A.put(g->apart_units, &g->psum.apart_units);
+                        A.put(g->apart_close, &g->psum.apart_close);
                         A.put(g->apart_words, &g->psum.apart);
                     }
                     for (int dir = 0; dir < 2; ++dir) {
@@ -603,8 +603,8 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 const PStreamDev apart = g->psum;
                 g->psum = g->pfwd;
                 if (apart.apart) {
-                    g->psum.units = apart.units;
-                    g->psum.close_words = apart.close_words;
+                    g->psum.apart_units = apart.apart_units;
+                    g->psum.apart_close = apart.apart_close;
                     g->psum.apart = apart.apart;
                     g->psum.apart_gain = g->apart_gain;
                     g->psum.apart_lasting = g->apart_lasting;

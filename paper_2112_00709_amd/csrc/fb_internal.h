@@ -259,9 +259,10 @@ struct PStreamDev {
     int32_t max_units = 0;        // most units of a wave
     int32_t paired = 0;           // as PStreamHost::paired
     float dim = 0.0f;
-    // states that run apart (pstream_apart; nullptr: none): by lane of the data-moving wave the state (-1: none), the lanes of its
-    // row's sources (-1: none) and their weights, then the states outside that their arcs enter (-1: none)
+    // states that may run apart (pstream_apart; nullptr: none): by lane of the data-moving wave the state (-1: none), the lanes of its
+    // row's sources (-1: none) and their weights, then the states outside that their arcs enter (-1: none); the plan without their rows
     const int32_t *apart = nullptr;
+    const uint32_t *apart_units = nullptr, *apart_close = nullptr;
     int32_t apart_lasting = 0;    // the first lanes: those alive for good, whose arcs those are
     float apart_gain = 0.0f;      // log2 of the largest sum of weights from those states into one outside
 };

@@ -694,11 +694,11 @@ typedef uint32_t close_vector_t __attribute__((ext_vector_type(kPMaxClose + 1)))
 // says so).  A run that leaves the range gives up as below; its caller redoes that sequence with the plain kernel.
 // LOG: rows leave as logarithms.  FEW (kPFew, kPFewMost or 0): no wave has more than that many units, so all of them stay in
 // registers, nothing is re-read, and the registers that leaves take gathers further ahead.
-// States that get nothing from the rest of the graph and so fall ever further behind it (PStreamDev::apart) are run by the
-// data-moving wave, a lane a state, in the log form: their entries of the vector are what a float holds of them, zero below its
-// range.  Such an entry is lost, and so is one of which more than 2^-24 came from lost ones: the rows that leave lack mass that it stands for.
-// A lost entry may not matter any more - its share in the sum of any state of the rest, and at the end in log Z, below 2^-24 - or the run
-// gives up as below.
+// States that get nothing from the rest of the graph and so may fall ever further behind it (PStreamDev::apart) are run by the
+// data-moving wave, once an entry of the vector has come to lie below the range, a lane a state, in the log form: their entries are what a
+// float holds of them, zero below its range.  Such an entry is lost, and so is one of which more than 2^-24 came from lost ones: the rows that leave lack mass that it stands for.
+// A lost entry may not matter any more - its share in the sum of any state of the rest, in each frame, and at the end in log Z, below
+// 2^-24 - or the run gives up as below.  (Shares of several frames add up: of a posterior at most the number of frames times 2^-24 is missing.)
 // TROP: the best path (fb_viterbi).  The vector is scores in log2 units, the largest of the step before taken off at every step, the units
 // carry weights in log2 units, a row is the largest of its terms: two additions and one maximum of three a unit.  Which arc
 // attains it is not kept: rows leave as they are, and fb_best_trace_kernel finds it anew for the one row a frame that the
@@ -1001,8 +1001,19 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
     // frame's own emission)
     double csum = 0.0;
     bool ok = true;
-    // (data-moving wave; the others only know whether there are such states)
+    // States that may run apart: they begin in the plan like all others, which costs nothing, and are taken out of it where an entry first comes to lie
+    // below the range.  All waves see that at the start of step i, in the word of step i - 1; the vector of step i - 2 and its word
+    // are still there, and step i - 1 is done once more, the states apart, from those.  (A run that gives up for another reason gives up again there.)
+    // A direction of 64 x 100 frames, us, in the log form from the start where the range is left / apart from the first step on / so: 1500
+    // states, 5 k arcs, that stay in range 125 / 197 / 130, that leave it 253 / 208 / 183; 6000 states, 60 k arcs 640 / 340 / 341, over 30 frames
+    // 257 / - / 122.
     const bool n_apart = APART && S.apart;   // (an instantiation of its own: the code beside the loop costs others 1 %)
+    bool apart_on = false;                  // (uniform over the workgroup)
+    auto given_up = [&](const float *word) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(*word)) > 0x7f7fffffu; };
+    // whether step i - 1 is to be done once more (i: the step that found the word, or behind the last)
+    // (not for step 1: the rows without arcs of the first vector are gone when it is looked at)
+    auto to_apart = [&](int i, bool found) { return n_apart && !apart_on && i >= 3 && found; };
+    // (data-moving wave)
     int ap_state = -1;
     double ap_value = 0.0;
     float ap_floor = 0.0f, ap_top = 0.0f;   // what the next vector's entries may not lie below; the largest lost entry
@@ -1019,7 +1030,8 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         int ap_pdf = 0;
         int32_t ap_src[kApartArcs], ap_tgt[kApartTargets];
         float ap_w[kApartArcs];
-        if (n_apart) {
+        // from the vector x of a step on, whose shift is csum
+        auto apart_begin = [&](const float *x) {
             const int32_t *ap = S.apart + lane;
             ap_state = ap[0];
 #pragma unroll
@@ -1030,9 +1042,9 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
 #pragma unroll
             for (int t = 0; t < kApartTargets; ++t) ap_tgt[t] = ap[(1 + 2 * kApartArcs + t) * kWave];
             ap_pdf = P.pdf[max(ap_state, 0)];
-            const double v = (double)R_.bound[max(ap_state, 0)] + (double)er[ap_pdf] * kLog2e;
-            ap_value = ap_state >= 0 && !(v < (double)kNegBig) ? v : kNoValue;
-        }
+            const float v = x[max(ap_state, 0)];
+            ap_value = ap_state >= 0 && v > 0.0f ? csum + (double)log2_of(v) : kNoValue;
+        };
         // the entries that arcs of theirs enter, in x, against what may have been lost on the way there
         auto apart_check = [&](const float *x, float *word) {
             float low = INFINITY;
@@ -1078,39 +1090,71 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         };
         float e_prev = emx0, e_cur = Ts > 1 ? emaxw[1] : 0.0f;   // the largest emission of frame i - 1 and of frame i
         float *row_a = er, *row_b = er + Es, *row_c = er + 2 * Es;   // rows of frame i - 1 (from step i on: i + 2), i, i + 1
-        for (int i = 1; i < Ts; ++i) {
-            const int cur = (i - 1) & 1;
-            const float mxv = row_a[Es - 1];
-            const bool more = i + 2 < Ts;
-            // (the word of step i - 1 lies behind what is staged)
-            if (more) stage(frame(i + 2), row_a);   // buffer of frame i-1: no longer read
-            write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
-            const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(mxv));
-            if (!TROP && mx > 0x7f7fffffu) { ok = false; break; }
-            const float nls = TROP ? (mxv > -INFINITY ? mxv : 0.0f) : mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
-            c = TROP ? nls : nls + (bwd ? e_prev : e_cur);
-            csum += (double)c;
-            if (lane == 0) {
-                if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
-                if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
+        double csum_before = 0.0;   // the shift of the step before
+        // back to the start of step i - 1 from that of step i, the emissions of frame i + 2 asked for and row i - 1 stored or not
+        auto back = [&](int i) {
+            staged_wait();          // (a row that is stored again comes behind the one under way)
+            stage(frame(i - 1), row_a);
+            csum = csum_before;
+            e_cur = e_prev;
+            apart_begin(xb + (i & 1) * Xs);
+            __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0), as the compiler knows: the loop's waits count its own loads only
+            lds_barrier();          // every wave has read the word
+            if (lane == 0) row_a[Es - 1] = kNone;
+            lds_barrier();
+            float *const t = row_c;
+            row_c = row_b;
+            row_b = row_a;
+            row_a = t;
+            apart_on = true;
+        };
+        // The steps from step i on, to the first that finds a word that ends the run; returns it (Ts: none).  (A copy of the loop with
+        // the states apart and one without: registers that the former keeps cost the steps of the latter 10 % on small plans.)
+        auto steps = [&](int i, auto with_apart) __attribute__((always_inline)) -> int {
+            for (; i < Ts; ++i) {
+                const int cur = (i - 1) & 1;
+                const float mxv = row_a[Es - 1];
+                const bool more = i + 2 < Ts;
+                // (the word of step i - 1 lies behind what is staged)
+                if (more) stage(frame(i + 2), row_a);   // buffer of frame i-1: no longer read
+                write_row(frame(i - 1), staged ? bh + cur * XL : xb + cur * Xs);
+                const uint32_t mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(mxv));
+                if (!TROP && mx > 0x7f7fffffu) return i;
+                const float nls = TROP ? (mxv > -INFINITY ? mxv : 0.0f) : mx > 0u ? (float)((int)(mx >> 23) - 127 - kLinBias) : 0.0f;   // minus log2 of the step's scale
+                c = TROP ? nls : nls + (bwd ? e_prev : e_cur);
+                if constexpr (APART) csum_before = csum;
+                csum += (double)c;
+                if (lane == 0) {
+                    if (off_seq) off_seq[frame(i)] = csum * (double)R_.out_scale;
+                    if (R_.cum) R_.cum[(size_t)b * P.N + frame(i)] = (float)(csum - cum_shift);
+                }
+                if constexpr (decltype(with_apart)::value) apart_step(i, row_b, row_b + Es - 1, nls);
+                if (!TROP && mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
+                e_prev = e_cur;
+                if (i + 1 < Ts) {
+                    staged_before(n_row_stores + (more ? n_requests : 0));   // frame i+1, requested a whole step ago, is in LDS
+                    if constexpr (!TROP) e_cur = emax_of(row_c);
+                    if (lane < 2) row_c[Es - 2 + lane] = lane ? kNone : e_cur;   // and the word of step i + 1 starts empty
+                }
+                if (LEAKY && lane == 0) slots[(i & 1) * NW + NC] = 0.0f;
+                float *const t = row_a;
+                row_a = row_b;
+                row_b = row_c;
+                row_c = t;
+                lds_barrier();   // (the row's stores and the emissions asked for go on)
             }
-            if (n_apart) apart_step(i, row_b, row_b + Es - 1, nls);
-            if (!TROP && mx > 0u && mx < mx_floor && lane == kWave - 1) lds_raise(row_b + Es - 1, INFINITY);
-            e_prev = e_cur;
-            if (i + 1 < Ts) {
-                staged_before(n_row_stores + (more ? n_requests : 0));   // frame i+1, requested a whole step ago, is in LDS
-                if constexpr (!TROP) e_cur = emax_of(row_c);
-                if (lane < 2) row_c[Es - 2 + lane] = lane ? kNone : e_cur;   // and the word of step i + 1 starts empty
+            return i;
+        };
+        int reached = steps(1, std::false_type{});
+        if constexpr (APART) {
+            if (to_apart(reached, reached < Ts || given_up(row_a + Es - 1))) {
+                back(reached);
+                reached = steps(reached - 1, std::true_type{});
             }
-            if (LEAKY && lane == 0) slots[(i & 1) * NW + NC] = 0.0f;
-            float *const t = row_a;
-            row_a = row_b;
-            row_b = row_c;
-            row_c = t;
-            lds_barrier();   // (the row's stores and the emissions asked for go on)
         }
+        ok = reached >= Ts;
         if (lane == 0) emaxw[0] = e_prev;   // that of the last frame, for log Z
-        if (n_apart && ok && ap_floor > 0.0f) apart_check(xb + ((Ts - 1) & 1) * Xs, step_word(Ts - 1));
+        if (apart_on && ok && ap_floor > 0.0f) apart_check(xb + ((Ts - 1) & 1) * Xs, step_word(Ts - 1));
     } else {
         const PWaveDesc wd = S.waves[wave];
         const int n_units_w = __builtin_amdgcn_readfirstlane(wd.n_units);
@@ -1125,8 +1169,11 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         // Unit u of the wave: three words per lane, read through a buffer descriptor, whose scalar offset is the unit's: a
         // request takes no vector instruction (an address formed from a scalar base and a large constant takes four).
         constexpr int kUnitBytes = 3 * kWave * 4;
-        auto units = __builtin_amdgcn_make_buffer_rsrc((void *)(S.units + (size_t)uniform64((uint64_t)wd.unit_base) * (3 * kWave)), 0,
-                                                       max(n_units_w, FEW ? FEW : kPPatterned) * kUnitBytes, 0x00027000);
+        auto units_of = [&](const uint32_t *of) __attribute__((always_inline)) {
+            return __builtin_amdgcn_make_buffer_rsrc((void *)(of + (size_t)uniform64((uint64_t)wd.unit_base) * (3 * kWave)), 0,
+                                                     max(n_units_w, FEW ? FEW : kPPatterned) * kUnitBytes, 0x00027000);
+        };
+        auto units = units_of(S.units);
         const int lane12 = lane * 12;
         auto load_unit = [&](Unit &dst, int u) __attribute__((always_inline)) {
             typedef uint32_t u3 __attribute__((ext_vector_type(3)));
@@ -1153,18 +1200,21 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         }, std::make_integer_sequence<int, NP>{});
         if (n_units_w > NP) last_spos = n_units_w - 1;
         Unit res[R];   // (units behind the wave's last one are zero words or another wave's: never folded)
-        unrolled([&](auto qc) __attribute__((always_inline)) {
-            constexpr int q = decltype(qc)::value, pos = FEW ? q : p_resident_pos(q);
-            load_unit(res[q], pos);
-        }, std::make_integer_sequence<int, R>{});
         // The lane's close words, picked by the number of the close (uniform).  One vector of nine: picking from a vector of
         // eight is compiled into a chain of seven selects, from a longer one into one indexed register move.
         close_vector_t cwv;
+        auto load_plan = [&](const uint32_t *close_words) __attribute__((always_inline)) {
+            unrolled([&](auto qc) __attribute__((always_inline)) {
+                constexpr int q = decltype(qc)::value, pos = FEW ? q : p_resident_pos(q);
+                load_unit(res[q], pos);
+            }, std::make_integer_sequence<int, R>{});
 #pragma unroll
-        for (int c = 0; c < kPMaxClose; ++c) cwv[c] = S.close_words[((size_t)wd.cw_base + c) * kWave + lane];
-        cwv[kPMaxClose] = cwv[0];   // (what is asked for when the last slice has closed)
-        // (everything asked for so far has arrived: the waits inside the loop then count the loop's own loads only)
-        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+            for (int c = 0; c < kPMaxClose; ++c) cwv[c] = close_words[((size_t)wd.cw_base + c) * kWave + lane];
+            cwv[kPMaxClose] = cwv[0];   // (what is asked for when the last slice has closed)
+            // (everything asked for so far has arrived: the waits inside the loop then count the loop's own loads only)
+            __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        };
+        load_plan(S.close_words);
         Unit ring[kPRing];
         // streamed unit m -> its ring place (in the patterned part streamed unit m is position H + 3 m + 2; behind it, unit
         // NP + t is streamed unit NG + t)
@@ -1394,9 +1444,36 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             lds_barrier();
             return true;
         };
-        for (int i = 1; ok && i < Ts; ++i) {
-            ok = step(i, std::integral_constant<int, 0>{});
-            if (ok && ++i < Ts) ok = step(i, std::integral_constant<int, 1>{});
+        if constexpr (!APART) {
+            for (int i = 1; ok && i < Ts; ++i) {
+                ok = step(i, std::integral_constant<int, 0>{});
+                if (ok && ++i < Ts) ok = step(i, std::integral_constant<int, 1>{});
+            }
+        } else {
+            for (int i = 1;;) {
+                while (i < Ts) {
+                    if (i & 1) {   // (or the second step of two is the one done once more)
+                        ok = step(i, std::integral_constant<int, 0>{});
+                        if (!ok || ++i >= Ts) break;
+                    }
+                    ok = step(i, std::integral_constant<int, 1>{});
+                    if (!ok) break;
+                    ++i;
+                }
+                if (!to_apart(i, !ok || given_up(step_word(Ts - 1)))) break;
+                --i;
+                units = units_of(S.apart_units);
+                lds_barrier();
+                load_plan(S.apart_close);
+                unrolled([&](auto mc) __attribute__((always_inline)) {
+                    constexpr int m = decltype(mc)::value, first = p_streamed_pos(m);
+                    request_at(ring[m], first);
+                }, std::make_integer_sequence<int, FEW ? 0 : kPRing - 1>{});
+                row_cur = row_first + (uint32_t)((i - 1) % 3) * row_bytes;
+                lds_barrier();
+                ok = true;
+                apart_on = true;
+            }
         }
     }
     if constexpr (TROP) {
@@ -1416,7 +1493,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
         if (io_wave && lane == 0) R_.mid_off[b] = csum + (double)cl;
         return true;
     }
-    if (n_apart && ok) lds_barrier();   // (the last vector has been looked at)
+    if (apart_on && ok) lds_barrier();   // (the last vector has been looked at)
     // a state below the range in the last step: give up as well (every wave reads the same word)
     if (ok && !(*step_word(Tn - 1) < INFINITY)) ok = false;   // (the last vector is not rescaled: only a lane's give-up counts)
     __builtin_amdgcn_s_setprio(3);
@@ -1456,7 +1533,7 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             // backward: the vector of the last step still lacks the scale of its frame's emissions
             R_.logz[b] = (csum + (bwd ? (double)em_last : 0.0) + (double)m + (double)flog2(s)) * kLn2;
         }
-        if (n_apart) {   // (64 states at most, each no more than the largest)
+        if (apart_on) {   // (64 states at most, each no more than the largest)
             if (io_wave && ap_lost) {
                 const double share = (ap_lost >> lane) & 1u ? ap_value + (double)R_.obound[ap_state] : -1.0e36;
                 const double most = wave_max(share) + 6.0, all = lane_value(csum + (double)m + (double)flog2(s), 0);

@@ -656,8 +656,8 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
 // feeds those - lose some binary orders against the frame's largest entry at every frame (e^-9 with 3000 pdfs of standard deviation 3), leave a
 // float's range after some 40 frames, and used to send the whole run into the log form.  Graphs with skewed destinations often have
 // them: half of the drawn ones with 6000 states, 1 to 40 such states.  A set of states that contains all of its predecessors needs no
-// other state's value, so the wave that moves data runs it beside the others, a lane a state, in the log form (doubles); the plan's
-// rows of those states go (weights 0, the dump slot).  Taken while a lane holds a row (4 arcs) and there are lanes; the larger rest of the
+// other state's value, so the wave that moves data can run it beside the others, a lane a state, in the log form (doubles), with a plan
+// from which the rows of those states are gone (weights 0, the dump slot).  Taken while a lane holds a row (4 arcs) and there are lanes; the larger rest of the
 // graph is what the state with the most arcs in reaches.
 bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
                    std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain, int32_t &n_lasting)

@@ -71,6 +71,136 @@ def test_alpha_beta_posteriors(fb, K, D, deg, n_cycle):
     assert np.abs(out["gamma"][3] - ref.gamma[0]).max() <= tol and np.abs(out["rho"][3] - ref.rho[0]).max() <= tol
 
 
+def _check(fb, g, D, emis, lengths, rows=None):
+    """alpha, beta, posteriors against the oracle; the restarts of fb_alpha."""
+    import torch
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_linear_weights(h) == 2
+    before = fb.fb_debug_linear_restarts()
+    fb.fb_alpha(h, torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda())
+    given_up = fb.fb_debug_linear_restarts() - before
+    h.destroy()
+    compare_fb(fb, g, D, emis, lengths, sel=list(range(lengths.size)) if rows is None else rows, name="states apart")
+    return given_up
+
+
+@pytest.mark.parametrize("K,D,deg,T", [(1100, 40, 2, 37), (1300, 64, 5, 12), (3001, 90, 13, 23)])
+def test_every_step_may_be_the_one_that_takes_them_out(fb, K, D, deg, T):
+    """The states apart fall out of a float's range at one frame, another for every sequence, the last among them; no call is too
+    short.  (Of the first two frames the run is done over in the log form: the step before is not there to go back to.)"""
+    rng = np.random.default_rng(K)
+    g = _graph(rng, K, D, deg, 3)
+    emis = (rng.standard_normal((T + 1, T, D)) * 2).astype(np.float32)
+    for f in range(T):
+        emis[f, f, D - 1] = -300.0
+    lengths = np.full(T + 1, T, dtype=np.int32)
+    lengths[5] = 6                                           # (the last frame of a shorter sequence)
+    assert _check(fb, g, D, emis, lengths) == 2
+
+
+def test_states_that_stay_in_range_stay_in_the_plan(fb):
+    """As fast as they were before they could run apart: the same launch over a graph with such states and one without."""
+    import torch
+    rng = np.random.default_rng(7)
+    D, T, B = 60, 100, 64
+    graphs = [_graph(rng, 1500, D, 2.5, 2)]
+    graphs[0].logw[(graphs[0].src >= 1500) & (graphs[0].dst >= 1500)] = -1.0
+    graphs.append(wl.Graph(**{**graphs[0].__dict__}))
+    graphs[1].src, graphs[1].dst = np.append(graphs[1].src, np.full(6, 11, np.int32)), np.append(graphs[1].dst, np.arange(1500, 1506, dtype=np.int32))
+    graphs[1].logw = np.append(graphs[1].logw, np.full(6, -1.0, np.float32))   # (an arc from the rest into every one of them)
+    emis = torch.from_numpy((rng.standard_normal((B, T, D)) * 0.5).astype(np.float32)).cuda()
+    emis[:, :, D - 1] = 1.7                                  # (the rest gains ln(1.75) a frame, the cycle loses some 1)
+    l = torch.full((B,), T, dtype=torch.int32, device="cuda")
+    times = []
+    for g in graphs:
+        h = fb.graph_from(g, D)
+        best = np.inf
+        before = fb.fb_debug_linear_restarts()
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                fb.fb_alpha(h, emis, l)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100.0)
+        assert fb.fb_debug_linear_restarts() == before
+        times.append(best)
+        h.destroy()
+    print(f"[gpu-case] in range: {times[0]:.1f} us, no states apart: {times[1]:.1f} us", flush=True)
+    assert times[0] <= 1.2 * times[1]                        # (apart from the first step on: 1.5)
+
+
+@pytest.mark.parametrize("kind", ["-inf", "mask", "mask all", "-inf all"])
+def test_unusual_emissions(fb, kind):
+    """Of the states apart, or of all, in a frame while they are in the plan (frame 4) and one in which they run apart (frame 30)."""
+    rng = np.random.default_rng(len(kind))
+    D, T = 50, 44
+    g = _graph(rng, 1300, D, 4, 3)
+    emis = (rng.standard_normal((3, T, D)) * 2).astype(np.float32)
+    emis[:, 12, D - 1] = -200.0
+    value = -np.inf if "inf" in kind else -1.0e20
+    at = slice(None) if "all" in kind else D - 1
+    emis[0, 4, at] = value
+    emis[1, 30, at] = value
+    lengths = np.full(3, T, dtype=np.int32)
+    if "all" in kind:                                        # (log Z is the mask's, or there is no path: checked as such)
+        import torch
+        h = fb.graph_from(g, D)
+        e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+        a, _, za = fb.fb_alpha(h, e, l)
+        b, _, zb = fb.fb_beta(h, e, l)
+        gam, _ = fb.fb_posteriors(h, a, b, l, 3, T)
+        ref = oracle.forward_backward(g, emis, lengths)
+        for z in (za.cpu().numpy(), zb.cpu().numpy()):
+            assert np.all(np.isneginf(z) == np.isneginf(ref.logz))
+            fin = np.isfinite(ref.logz)
+            assert np.all(np.abs(z[fin] - ref.logz[fin]) <= 1e-4 * np.abs(ref.logz[fin]))
+        assert np.abs(gam[2].cpu().numpy() - ref.gamma[2]).max() <= 1e-5
+        h.destroy()
+    else:
+        assert _check(fb, g, D, emis, lengths) == 0
+
+
+def test_a_nan_stays_one(fb):
+    import torch
+    rng = np.random.default_rng(5)
+    D, T = 50, 40
+    g = _graph(rng, 1300, D, 4, 3)
+    emis = (rng.standard_normal((4, T, D)) * 2).astype(np.float32)
+    emis[2:, 12, D - 1] = -300.0
+    emis[0, 20, D - 1] = np.nan                              # of a state apart in the plan, of one of the rest, and either when they run apart
+    emis[1, 20, int(g.pdf[7])] = np.nan
+    emis[3, 20, int(g.pdf[7])] = np.nan
+    h = fb.graph_from(g, D)
+    a, _, z = fb.fb_alpha(h, torch.from_numpy(emis).cuda(), torch.full((4,), T, dtype=torch.int32, device="cuda"))
+    z = z.cpu().numpy()
+    assert np.isnan(z[[0, 1, 3]]).all() and np.isfinite(z[2])
+    assert np.isnan(a[0, T - 1].cpu().numpy()).any()
+    h.destroy()
+
+
+@pytest.mark.parametrize("what,taken", [("64 states", True), ("65 states", False), ("4 arcs", True), ("5 arcs", False), ("cloned target", True)])
+def test_what_may_run_apart(fb, what, taken):
+    """The limits, from both sides; a state of the rest whose row is spread over clones and takes arcs of theirs."""
+    rng = np.random.default_rng(len(what) + ord(what[0]))
+    D, T = 50, 30
+    K = 2300 if what == "cloned target" else 1300
+    g = _graph(rng, K, D, 2 if K > 2000 else 4, {"64 states": 61, "65 states": 62}.get(what, 6))   # (drain is not among them: it neither lasts nor feeds one that does)
+    if "arcs" in what:                                       # (the fed state gets an arc from the first and one from the last of the cycle)
+        n = int(what[0]) - 2
+        g.src, g.dst = np.append(g.src, K + np.arange(1, 1 + n)).astype(np.int32), np.append(g.dst, np.full(n, K + 6)).astype(np.int32)
+        g.logw = np.append(g.logw, np.full(n, -1.0)).astype(np.float32)
+        assert np.unique(g.src[g.dst == K + 6]).size == int(what[0])
+    if what == "cloned target":
+        every = np.arange(K, dtype=np.int32)
+        g.src, g.dst = np.concatenate([g.src, every, [K, K + 1]]).astype(np.int32), np.concatenate([g.dst, np.full(K + 2, 9)]).astype(np.int32)
+        g.logw = np.concatenate([g.logw, -rng.exponential(size=K + 2)]).astype(np.float32)
+    emis = (rng.standard_normal((2, T, D)) * 2).astype(np.float32)
+    emis[:, 9, D - 1] = -300.0
+    assert _check(fb, g, D, emis, np.full(2, T, dtype=np.int32)) == (0 if taken else 2)
+
+
 def test_log_z_of_lost_states(fb):
     """Only the states apart may end a sequence: log Z is theirs, which a float has lost."""
     import torch
