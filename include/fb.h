@@ -176,6 +176,9 @@ int fb_graph_layout(const fb_graph *g, int which, void *host_out, size_t bytes);
  *              kept by host-only handles of graphs that qualify), in ordinary arithmetic:
  *              y[j] = sum over arcs entering (leaving) j of e^logw x[src] - x and y are plain numbers here;
  *              FB_EUNSUPPORTED if the graph has no such plan
+ *   which = 7  the forward plan without the states that may run apart, and their rows as the kernel's own lanes hold them: same
+ *              results as 5 to rounding; FB_EUNSUPPORTED if there are none
+ *   which = 8, 9  those plans with the best path's weights (fb_viterbi): y[j] = max over arcs entering (leaving) j of (w + x[src]), log2 units
  *   which = 3, 4  the forward / backward plan in the form with weights as 2^w (see
  *              fb_graph_linear_weights), whatever form the device copy has: same results to
  *              rounding; FB_EUNSUPPORTED if a weight of the graph is out of that form's range;

@@ -506,12 +506,16 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             }
             if (g->host_only && prob_ok) g->linear_p = true;   // (host-only handles keep the plans for fb_graph_schedule_apply_host)
             // (graphs in the probability domain: the best path runs on their plans, with weights of its own)
-            const bool best = g->linear_p && !g->host_only;
+            const bool best = g->linear_p;
             for (int dir = 0; dir < 2 && rc == FB_OK && best; ++dir) {
                 rows_of(0, dir);
                 merge_parallel(K, ptr, col, w, true, mptr, mcol, mw);
                 if (!pstream_best_units(dir ? g->hp_bwd : g->hp_fwd, mptr.data(), mcol.data(), mw.data(), g->best_units[dir])) {
                     rc = fail(FB_EHIP, "internal error: best-path weights of a probability-domain plan");
+                    break;
+                }
+                if (!pstream_in_bounds(dir ? g->hp_bwd : g->hp_fwd, D, why, &g->best_units[dir], nullptr, true)) {
+                    rc = fail(FB_EHIP, "internal error: best-path plan out of bounds (" + why + ")");
                     break;
                 }
                 if (dir == 0) {
@@ -521,6 +525,9 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     merge_parallel(K, ptr, col, w, false, sptr, scol, sw);
                     if (!pstream_apart(g->hp_fwd, D, sptr.data(), scol.data(), sw.data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain, g->apart_lasting))
                         g->apart_words.clear();
+                    else if (!pstream_in_bounds(g->hp_fwd, D, why, &g->apart_units, &g->apart_close) ||
+                             !pstream_apart_in_bounds(g->hp_fwd, g->apart_words, g->apart_lasting, why))
+                        rc = fail(FB_EHIP, "internal error: plan without the states apart out of bounds (" + why + ")");
                 }
                 g->best_ptr[dir].assign(mptr.begin(), mptr.end());
                 g->best_arcs[dir].reserve(mcol.size());
@@ -679,13 +686,17 @@ static const void *layout_array(const fb_graph *g, int which, int64_t *n)
 int fb_graph_schedule_apply_host(const fb_graph *g, int which, int32_t sub, const double *x, double *y)
 {
     if (!g || !x || !y) return fail(FB_EINVAL, "fb_graph_schedule_apply_host: NULL argument");
-    if (which < 0 || which > 6 || sub < 0 || (size_t)sub >= g->h_pdf.sub.size())
+    if (which < 0 || which > 9 || sub < 0 || (size_t)sub >= g->h_pdf.sub.size())
         return fail(FB_EINVAL, "fb_graph_schedule_apply_host: unknown schedule or sub-graph");
     if (which >= 5) {   // the plans of the probability-domain kernel: ordinary arithmetic
         if (!g->linear_p) return fail(FB_EUNSUPPORTED, "fb_graph_schedule_apply_host: this graph has no probability-domain plan");
+        if (which == 7 && g->apart_words.empty()) return fail(FB_EUNSUPPORTED, "fb_graph_schedule_apply_host: this graph has no states that may run apart");
+        const PStreamHost &S = which == 6 || which == 9 ? g->hp_bwd : g->hp_fwd;
+        const std::vector<uint32_t> *units = which == 7 ? &g->apart_units : which >= 8 ? &g->best_units[which - 8] : nullptr;
         std::string why;
-        if (!pstream_apply_host(which == 5 ? g->hp_fwd : g->hp_bwd, x, y, nullptr, nullptr, why))
+        if (!pstream_apply_host(S, x, y, nullptr, nullptr, why, units, which == 7 ? &g->apart_close : nullptr, which >= 8))
             return fail(FB_EHIP, "internal error: probability-domain plan (" + why + ")");
+        if (which == 7) pstream_apart_apply_host(g->apart_words, x, y);
         return FB_OK;
     }
     if (g->small && which != 2) {   // the small-graph kernel's plans

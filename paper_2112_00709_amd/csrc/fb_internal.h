@@ -279,8 +279,13 @@ bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t 
 // needs to run them.  False: none.
 bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units,
                    std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain, int32_t &n_lasting);
-bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why);
-bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why);
+// units, close_words (nullptr: S's own): of a plan derived from S as above; scores: the units carry weights in log2 units
+bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why, const std::vector<uint32_t> *units = nullptr,
+                       const std::vector<uint32_t> *close_words = nullptr, bool scores = false);
+bool pstream_apart_in_bounds(const PStreamHost &S, const std::vector<int32_t> &words, int32_t n_lasting, std::string &why);
+bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why,
+                        const std::vector<uint32_t> *units = nullptr, const std::vector<uint32_t> *close_words = nullptr, bool scores = false);
+void pstream_apart_apply_host(const std::vector<int32_t> &words, const double *x, double *y);   // the rows of the states that run apart -> y
 
 // ---------------------------------------------------------------------------
 // Plan of the small-graph recursion kernel (fb_small.cpp, fb_small.hip): (sub-)graphs of at most kSmallStates states

@@ -612,8 +612,12 @@ bool pstream_build(int32_t K, const int64_t *ptr, const int32_t *col, const floa
 }
 
 // Everything the kernel will index while walking the plan stays in range.
-bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
+bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why, const std::vector<uint32_t> *units, const std::vector<uint32_t> *close_words,
+                       bool scores)
 {
+    const std::vector<uint32_t> &U = units ? *units : S.units, &C = close_words ? *close_words : S.close_words;
+    const float least = scores ? -INFINITY : 0.0f;
+    if (U.size() != S.units.size() || C.size() != S.close_words.size()) { why = "size of a derived plan"; return false; }
     const size_t n_units_total = S.units.size() / (3 * kWave), n_cw_total = S.close_words.size() / kWave;
     if (S.waves.size() != (size_t)(kNWShared - 1)) { why = "wave count"; return false; }
     if (S.K + S.Ccap + 1 > kXsFixed) { why = "index space"; return false; }
@@ -632,15 +636,15 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
         if (closes != wd.n_close) { why = "close mask and count disagree"; return false; }
         if (wd.n_units > 0 && !((wd.close_mask[(wd.n_units - 1) / 64] >> ((wd.n_units - 1) % 64)) & 1u)) { why = "last unit does not close"; return false; }
         for (size_t i = (size_t)wd.unit_base * 3 * kWave; i < ((size_t)wd.unit_base + (size_t)wd.n_units) * 3 * kWave; i += 3) {
-            const uint32_t s = S.units[i];
+            const uint32_t s = U[i];
             if ((s & 0xffffu) > top || (s >> 16) > top || (s & 3u) || ((s >> 16) & 3u)) { why = "arc source"; return false; }
             float w0, w1;
-            std::memcpy(&w0, &S.units[i + 1], 4);
-            std::memcpy(&w1, &S.units[i + 2], 4);
-            if (!(w0 >= 0.0f && w0 < INFINITY && w1 >= 0.0f && w1 < INFINITY)) { why = "arc weight"; return false; }
+            std::memcpy(&w0, &U[i + 1], 4);
+            std::memcpy(&w1, &U[i + 2], 4);
+            if (!(w0 >= least && w0 < INFINITY && w1 >= least && w1 < INFINITY)) { why = "arc weight"; return false; }
         }
         for (size_t i = (size_t)wd.cw_base * kWave; i < ((size_t)wd.cw_base + (size_t)wd.n_close) * kWave; ++i) {
-            const uint32_t cw = S.close_words[i];
+            const uint32_t cw = C[i];
             if ((cw & 0xffffu) > top || (cw & 3u) || (cw >> 16) > (uint32_t)n_vidx * 4u || ((cw >> 16) & 3u)) { why = "close word"; return false; }
             if ((cw & 0xffffu) == top && (cw >> 16) != (uint32_t)n_vidx * 4u) { why = "emission on the dump slot"; return false; }
         }
@@ -649,6 +653,32 @@ bool pstream_in_bounds(const PStreamHost &S, int32_t n_vidx, std::string &why)
         if (cd.state < 0 || cd.state >= S.K || cd.first < 0 || cd.count < 1 || cd.first + cd.count > S.Ccap) { why = "clone entry"; return false; }
     for (int32_t z : S.zero_rows)
         if (z < 0 || z >= S.K + S.Ccap) { why = "zero row"; return false; }
+    return true;
+}
+
+// The same for the states that run apart: each has one lane, takes from lanes that have a state, and enters states that have none.
+bool pstream_apart_in_bounds(const PStreamHost &S, const std::vector<int32_t> &words, int32_t n_lasting, std::string &why)
+{
+    if (words.size() != (size_t)kApartWords) { why = "states apart: size"; return false; }
+    std::vector<char> apart((size_t)S.K, 0);
+    int32_t n = 0;
+    while (n < kWave && words[(size_t)n] >= 0) ++n;
+    for (int32_t l = 0; l < kWave; ++l) {
+        const int32_t k = words[(size_t)l];
+        if ((l < n) != (k >= 0) || k < -1 || k >= S.K || (k >= 0 && apart[(size_t)k])) { why = "states apart: state"; return false; }
+        if (k >= 0) apart[(size_t)k] = 1;
+        for (int t = 0; t < kApartArcs; ++t) {
+            const int32_t src = words[(size_t)(1 + t) * kWave + l];
+            float w;
+            std::memcpy(&w, &words[(size_t)(1 + kApartArcs + t) * kWave + l], 4);
+            if (src < -1 || src >= n || (src >= 0 && (l >= n || !(w > -INFINITY && w < INFINITY)))) { why = "states apart: arc"; return false; }
+        }
+    }
+    for (int i = 0; i < kApartTargets * kWave; ++i) {
+        const int32_t k = words[(size_t)(1 + 2 * kApartArcs) * kWave + i];
+        if (k < -1 || k >= S.K || (k >= 0 && apart[(size_t)k])) { why = "states apart: target"; return false; }
+    }
+    if (n < 1 || n_lasting < 1 || n_lasting > n) { why = "states apart: count"; return false; }
     return true;
 }
 
@@ -792,18 +822,23 @@ bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t 
 }
 
 // y = A x as the kernel forms it (lanes, groups of lanes, clones), in double; x and y hold one value per state
-// (ordinary numbers, not logs).  cycles (nullable): the gather cycles of a time step under the bank model above,
+// (ordinary numbers, not logs; scores: in log2 units, y the largest sum).  cycles (nullable): the gather cycles of a time step under the bank model above,
 // and the least any order could need (two per gather).
-bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why)
+bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_t *cycles, int64_t *cycles_floor, std::string &why,
+                        const std::vector<uint32_t> *units, const std::vector<uint32_t> *close_words, bool scores)
 {
-    std::vector<double> xe((size_t)S.K + (size_t)S.Ccap + 1, 0.0), ye((size_t)S.K + (size_t)S.Ccap + 1, 0.0);
+    const std::vector<uint32_t> &U = units ? *units : S.units, &C = close_words ? *close_words : S.close_words;
+    const double none = scores ? -INFINITY : 0.0;
+    auto add = [&](double a, double v) { return scores ? std::max(a, v) : a + v; };
+    std::vector<double> xe((size_t)S.K + (size_t)S.Ccap + 1, none), ye((size_t)S.K + (size_t)S.Ccap + 1, none);
     for (int32_t k = 0; k < S.K; ++k) xe[k] = x[k];   // a cloned state's value sits in the state itself, its clones hold zero
     int64_t cyc = 0, floor_cyc = 0;
     for (const PWaveDesc &wd : S.waves) {
-        double acc[kWave] = {};
+        double acc[kWave];
+        std::fill(acc, acc + kWave, none);
         int c = 0;
         for (int u = 0; u < wd.n_units; ++u) {
-            const uint32_t *unit = S.units.data() + ((size_t)wd.unit_base + (size_t)u) * 3 * kWave;
+            const uint32_t *unit = U.data() + ((size_t)wd.unit_base + (size_t)u) * 3 * kWave;
             for (int r = 0; r < 2; ++r) {
                 int32_t addr[kWave];
                 for (int l = 0; l < kWave; ++l) {
@@ -811,23 +846,23 @@ bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_
                     addr[l] = (int32_t)((r ? s >> 16 : s & 0xffffu) / 4u);
                     float wt;
                     std::memcpy(&wt, &unit[l * 3 + 1 + r], 4);
-                    acc[l] += (double)wt * xe[(size_t)addr[l]];
+                    acc[l] = add(acc[l], scores ? (double)wt + xe[(size_t)addr[l]] : (double)wt * xe[(size_t)addr[l]]);
                 }
                 cyc += half_cycles(addr, kHalf) + half_cycles(addr + kHalf, kHalf);
                 floor_cyc += 2;
             }
             if ((wd.close_mask[u / 64] >> (u % 64)) & 1u) {
                 const int g = 1 << ((wd.lgs >> (3 * c)) & 7u);
-                const uint32_t *cw = S.close_words.data() + ((size_t)wd.cw_base + (size_t)c) * kWave;
+                const uint32_t *cw = C.data() + ((size_t)wd.cw_base + (size_t)c) * kWave;
                 for (int l = 0; l < kWave; l += g) {
-                    double tot = 0.0;
-                    for (int t = 0; t < g; ++t) tot += acc[l + t];
+                    double tot = none;
+                    for (int t = 0; t < g; ++t) tot = add(tot, acc[l + t]);
                     for (int t = 0; t < g; ++t) {
                         const uint32_t tgt = (cw[l + t] & 0xffffu) / 4u;
                         if (tgt != (cw[l] & 0xffffu) / 4u) { why = "lanes of a row disagree about its target"; return false; }
-                        if (tgt == (uint32_t)(S.K + S.Ccap) && tot != 0.0) { why = "a row's total goes to the dump slot"; return false; }
+                        if (tgt == (uint32_t)(S.K + S.Ccap) && tot != none) { why = "a row's total goes to the dump slot"; return false; }
                         ye[tgt] = tot;
-                        acc[l + t] = 0.0;
+                        acc[l + t] = none;
                     }
                 }
                 ++c;
@@ -835,11 +870,25 @@ bool pstream_apply_host(const PStreamHost &S, const double *x, double *y, int64_
         }
     }
     for (const CloneDesc &cd : S.clones)
-        for (int32_t i = 0; i < cd.count; ++i) ye[(size_t)cd.state] += ye[(size_t)S.K + (size_t)cd.first + i];
+        for (int32_t i = 0; i < cd.count; ++i) ye[(size_t)cd.state] = add(ye[(size_t)cd.state], ye[(size_t)S.K + (size_t)cd.first + i]);
     for (int32_t k = 0; k < S.K; ++k) y[k] = ye[(size_t)k];
     if (cycles) *cycles = cyc;
     if (cycles_floor) *cycles_floor = floor_cyc;
     return true;
+}
+
+void pstream_apart_apply_host(const std::vector<int32_t> &words, const double *x, double *y)
+{
+    for (int l = 0; l < kWave && words[(size_t)l] >= 0; ++l) {
+        double sum = 0.0;
+        for (int t = 0; t < kApartArcs; ++t) {
+            const int32_t src = words[(size_t)(1 + t) * kWave + l];
+            float w;
+            std::memcpy(&w, &words[(size_t)(1 + kApartArcs + t) * kWave + l], 4);
+            if (src >= 0) sum += std::exp2((double)w) * x[words[(size_t)src]];
+        }
+        y[words[(size_t)l]] = sum;
+    }
 }
 
 }  // namespace fb

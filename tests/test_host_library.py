@@ -345,3 +345,50 @@ def test_probability_domain_plans(seed):
     h = _host_graph(wl.Graph(g.K, g.src, g.dst, far, g.pdf, g.init, g.final), D)
     assert fb.fb_graph_linear_weights(h) != 2
     h.destroy()
+
+
+@pytest.mark.parametrize("extra", ["none", "cycle", "cycle, 64 states", "cycle, 65 states", "row of 4", "row of 5", "clones"])
+def test_plans_derived_from_the_probability_domain_plans(extra):
+    """The plan without the states that may run apart, with the rows the kernel's own lanes hold (which = 7), against the forward product; the
+    best path's weights on either plan (8, 9) against the largest sums, parallel arcs and zero-bar weights among them."""
+    rng = np.random.default_rng(len(extra))
+    K = 2300 if extra == "clones" else 1500
+    n = 3 * K
+    src, dst = np.concatenate([np.arange(K), rng.integers(0, K, n)]), np.concatenate([(np.arange(K) + 1) % K, rng.integers(0, K, n)])
+    if extra == "clones":                                    # a row of the rest spread over clones, which states apart enter too
+        src, dst = np.concatenate([src, np.arange(K)]), np.concatenate([dst, np.full(K, 9)])
+    total = K
+    if extra != "none":                                      # a cycle nothing enters, a state it feeds, one that feeds it; arcs into the rest
+        m = {"cycle, 64 states": 62, "cycle, 65 states": 63}.get(extra, 7)
+        cyc, fed, feeds = K + np.arange(m), K + m, K + m + 1
+        rows = {"row of 4": 4, "row of 5": 5}.get(extra, 2)
+        src = np.concatenate([src, cyc, cyc[:rows], [feeds], cyc, [fed, fed]])
+        dst = np.concatenate([dst, np.roll(cyc, -1), np.full(rows, fed), [cyc[0]], rng.integers(0, K, m), [9, 9]])
+        total = K + m + 2
+    again = rng.integers(0, src.size, 400)                   # parallel arcs
+    src, dst = np.concatenate([src, src[again]]).astype(np.int32), np.concatenate([dst, dst[again]]).astype(np.int32)
+    logw = (-rng.exponential(size=src.size)).astype(np.float32)
+    zero = rng.integers(0, K + n, 200)
+    logw[zero[dst[zero] != (src[zero] + 1) % K]] = -np.inf
+    D = 40
+    g = wl.Graph(total, src, dst, logw, rng.integers(0, D, total).astype(np.int32), np.zeros(total, np.float32), np.zeros(total, np.float32))
+    h = _host_graph(g, D)
+    assert fb.fb_graph_linear_weights(h) == 2
+    x = rng.random(total)
+    if extra in ("none", "cycle, 65 states", "row of 5"):
+        with pytest.raises(fb.FBError):
+            fb.fb_graph_schedule_apply_host(h, 7, 0, x, np.zeros(total))
+    else:
+        want = np.zeros(total)
+        np.add.at(want, g.dst, np.exp(logw.astype(np.float64)) * x[g.src])
+        y = fb.fb_graph_schedule_apply_host(h, 7, 0, x, np.full(total, np.nan))
+        np.testing.assert_allclose(y, want, rtol=2e-6, atol=0)
+    w2 = (logw.astype(np.float64) * 1.4426950408889634).astype(np.float32).astype(np.float64)
+    x = rng.standard_normal(total) * 5
+    x[rng.integers(0, total, 50)] = -np.inf
+    for which, rows, cols in ((8, g.dst, g.src), (9, g.src, g.dst)):
+        want = np.full(total, -np.inf)
+        np.maximum.at(want, rows, w2 + x[cols])
+        y = fb.fb_graph_schedule_apply_host(h, which, 0, x, np.full(total, np.nan))
+        np.testing.assert_allclose(y, want, rtol=0, atol=1e-5)   # (weights in log2 units as floats of at most some 20: 2e-6)
+    h.destroy()
