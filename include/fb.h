@@ -312,8 +312,11 @@ int lfmmi_loss_grad_static(const fb_graph *den, const fb_graph *num, const float
 /* Bytes of the scratch memory lfmmi_loss_grad_static works in. */
 size_t fb_static_scratch_bytes(void);
 
-/* Bytes of device workspace fb_viterbi needs for these sizes (0 on bad arguments). */
+/* Bytes of device workspace fb_viterbi works in at its fastest for these sizes, and the least it accepts (0 on bad arguments).  Where
+ * fb_graph_linear_weights(g) == 2 the former is a float per state and frame (states rounded up to a multiple of 4), about twice
+ * the latter; elsewhere they are the same.  With less than the former, but the latter, the call takes the form that keeps back-pointers. */
 size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N);
+size_t fb_viterbi_least_workspace_bytes(const fb_graph *g, int32_t B, int32_t N);
 
 /*
  * Best path (Conclusion section: the same forward recursion with the log semiring
@@ -325,9 +328,10 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N);
  * Several paths may attain the score; which one is returned is fixed for a given graph and
  * input (results do not depend on timing) but otherwise unspecified.
  *   score  out, device double [B];  path  out, device int32 [B][N]
- *   ws     device scratch of at least fb_viterbi_workspace_bytes(), 256-byte aligned
- *          (the back-pointers: 2 bytes per state and frame, a little more for graphs with very long rows; and per
- *          sequence two vectors, of 4 or 8 bytes per state of the largest (sub-)graph, and two numbers)
+ *   ws     device scratch of fb_viterbi_workspace_bytes(), at least fb_viterbi_least_workspace_bytes(), 256-byte aligned
+ *          (the back-pointers, 2 bytes per state and frame, a little more for graphs with very long rows, or the vectors
+ *          themselves, 4 bytes per state and frame; and per sequence two vectors, of 4 or 8 bytes per state of the
+ *          largest (sub-)graph, and two numbers)
  * Errors as fb_alpha.
  */
 int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D,

@@ -28,7 +28,7 @@ LAYOUT = {"in_ptr": 0, "in_src": 1, "in_w": 2, "in_perm": 3, "out_ptr": 4, "out_
 SYMBOLS = ["fb_graph_create", "fb_graph_destroy", "fb_graph_layout_size", "fb_graph_layout", "fb_check_lengths",
            "fb_alpha", "fb_beta", "fb_posteriors", "fb_lfmmi_workspace_bytes", "lfmmi_loss_grad", "lfmmi_loss_grad_ragged",
            "fb_limits_max_states", "fb_strerror", "fb_last_error", "fb_graph_schedule_apply_host",
-           "fb_profile_enable", "fb_profile_read", "fb_viterbi_workspace_bytes", "fb_viterbi", "fb_graph_linear_weights",
+           "fb_profile_enable", "fb_profile_read", "fb_viterbi_workspace_bytes", "fb_viterbi_least_workspace_bytes", "fb_viterbi", "fb_graph_linear_weights",
            "fb_debug_linear_restarts", "fb_graph_small_linear", "fb_graph_plan_cycles", "lfmmi_loss_grad_static", "fb_static_scratch_bytes",
            "fb_leaky_workspace_bytes", "fb_leaky_posteriors"]
 
@@ -93,6 +93,8 @@ def lib() -> ctypes.CDLL:
         L.fb_limits_max_states.restype = i32
         L.fb_viterbi_workspace_bytes.argtypes = [vp, i32, i32]
         L.fb_viterbi_workspace_bytes.restype = sz
+        L.fb_viterbi_least_workspace_bytes.argtypes = [vp, i32, i32]
+        L.fb_viterbi_least_workspace_bytes.restype = sz
         L.fb_viterbi.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, sz, vp]
         L.fb_viterbi.restype = ctypes.c_int
         L.fb_leaky_workspace_bytes.argtypes = [vp, i32, i32]
@@ -326,12 +328,15 @@ def fb_leaky_posteriors(g: Graph, emis, lengths, leak: float, ws=None):
 
 
 def fb_viterbi(g: Graph, emis, lengths, ws=None):
-    """-> (score [B] float64, path [B,N] int32), on the device."""
+    """-> (score [B] float64, path [B,N] int32), on the device.  ``ws``: a uint8 CUDA tensor of the library's
+    fb_viterbi_workspace_bytes, or with less speed on large graphs of its fb_viterbi_least_workspace_bytes."""
     torch = _torch()
     B, N, D = _dev_inputs(emis, lengths)
-    need = int(lib().fb_viterbi_workspace_bytes(g.handle, B, N))
     if ws is None:
-        ws = _new((need,), torch.uint8, emis.device)
+        try:
+            ws = _new((int(lib().fb_viterbi_workspace_bytes(g.handle, B, N)),), torch.uint8, emis.device)
+        except torch.cuda.OutOfMemoryError:                  # (half as much will do)
+            ws = _new((int(lib().fb_viterbi_least_workspace_bytes(g.handle, B, N)),), torch.uint8, emis.device)
     score = _new((B,), torch.float64, emis.device)
     path = _new((B, N), torch.int32, emis.device)
     _check(lib().fb_viterbi(g.handle, _dp(emis), _dp(lengths), B, N, D, _dp(score), _dp(path), _dp(ws), int(ws.numel()),

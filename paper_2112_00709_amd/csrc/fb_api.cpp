@@ -468,6 +468,12 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 {
     if (!g || B <= 0 || N <= 0) return 0;
     if (g->linear_p) return best_rows_bytes(g, B, N) + 2 * (align256((size_t)B * best_ld(g) * sizeof(float)) + align256((size_t)B * sizeof(double)));
+    return fb_viterbi_least_workspace_bytes(g, B, N);
+}
+
+size_t fb_viterbi_least_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
+{
+    if (!g || B <= 0 || N <= 0) return 0;
     const size_t rows = (g->n_seq == 0 ? (size_t)B * N : (size_t)N) * viterbi_bp_ld(g);
     // the back-pointers, then per direction the vector it ends with and that vector's shift
     return align256(rows * sizeof(uint16_t)) + 2 * (align256((size_t)B * viterbi_mid_ld(g) * (g->f64 ? 8 : 4)) + align256((size_t)B * sizeof(double)));
@@ -484,7 +490,8 @@ size_t fb_viterbi_workspace_bytes(const fb_graph *g, int32_t B, int32_t N)
 // Graphs that have probability-domain plans (fb_pstream.cpp) walk them with weights in log2 units and keep no back-pointers at
 // all: a row's largest term costs two additions and a maximum of three for every two arcs, where finding out which one it is as
 // well takes a comparison and two selects an arc.  The vectors leave as they are, and the trace forms the terms of the one row a
-// frame that the path takes anew.  (6000 states, 60 k arcs, 128 sequences of at most 500 frames: 1606 -> 1210 us a call, the workspace twice as large.)
+// frame that the path takes anew.  (6000 states, 60 k arcs, 128 sequences of at most 500 frames: 1606 -> 1210 us a call, the workspace twice as large:
+// a call with less takes the other form, so that whatever fitted a GPU before still does.)
 static int best_path(const fb_graph *g, const float *emis, const int32_t *lengths, int32_t B, int32_t N, int32_t D, double *score,
                      int32_t *path, void *ws, fb_stream stream)
 {
@@ -530,9 +537,10 @@ int fb_viterbi(const fb_graph *g, const float *emis, const int32_t *lengths, int
     int rc = check_common("fb_viterbi", g, emis, lengths, B, N, D);
     if (rc) return rc;
     if (!score || !path) return fail(FB_EINVAL, "fb_viterbi: score or path is NULL");
-    if (!ws || ws_bytes < fb_viterbi_workspace_bytes(g, B, N)) return fail(FB_EINVAL, "fb_viterbi: workspace missing or too small");
+    const bool keep_rows = g->linear_p && ws_bytes >= fb_viterbi_workspace_bytes(g, B, N);
+    if (!ws || (!keep_rows && ws_bytes < fb_viterbi_least_workspace_bytes(g, B, N))) return fail(FB_EINVAL, "fb_viterbi: workspace missing or too small");
     if (((uintptr_t)ws & 255) != 0) return fail(FB_EINVAL, "fb_viterbi: workspace must be 256-byte aligned");
-    if (g->linear_p) return best_path(g, emis, lengths, B, N, D, score, path, ws, stream);
+    if (keep_rows) return best_path(g, emis, lengths, B, N, D, score, path, ws, stream);
     const size_t rows = (g->n_seq == 0 ? (size_t)B * N : (size_t)N) * viterbi_bp_ld(g);
     const size_t mid_ld = viterbi_mid_ld(g), mid_bytes = align256((size_t)B * mid_ld * (g->f64 ? 8 : 4));
     BacktraceParams bt{};

@@ -533,7 +533,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 g->best_arcs[dir].reserve(mcol.size());
                 for (size_t i = 0; i < mcol.size(); ++i) g->best_arcs[dir].push_back(Arc{mcol[i], mw[i]});
             }
-            g->own_trop = !best && (any_parallel || g->linear_w);
+            g->own_trop = any_parallel || g->linear_w;   // (also beside those: the form with back-pointers takes half the workspace)
             for (int dir = 0; dir < 2 && rc == FB_OK && g->own_trop; ++dir) {
                 SellHost sell_trop;
                 sell_trop.nw = g->nw - 1;

@@ -22,14 +22,18 @@ def fb():
     return lib
 
 
-def check(fb, g, D, emis, lengths, name, sel=None, state="auto"):
+def check(fb, g, D, emis, lengths, name, sel=None, state="auto", least=False):
+    """least: in the least workspace that is accepted (the form with back-pointers, whatever the graph)"""
     import torch
     B, N, _ = emis.shape
     sel = list(range(B)) if sel is None else list(sel)
     print(f"[gpu-case] viterbi {name}: B={B} N={N} D={D} K={g.K} E={g.E} state={state}", flush=True)
     ref = oracle.viterbi(g, emis, lengths, sel=sel)
     G = fb.graph_from(g, D, state=state)
-    score, path = fb.fb_viterbi(G, torch.from_numpy(emis).cuda(), torch.from_numpy(lengths.astype(np.int32)).cuda())
+    ws = None
+    if least:
+        ws = torch.full((int(fb.lib().fb_viterbi_least_workspace_bytes(G.handle, B, N)),), 255, dtype=torch.uint8, device="cuda")
+    score, path = fb.fb_viterbi(G, torch.from_numpy(emis).cuda(), torch.from_numpy(lengths.astype(np.int32)).cuda(), ws=ws)
     torch.cuda.synchronize()
     score, path = score.cpu().numpy(), path.cpu().numpy()
     for i, b in enumerate(sel):
@@ -133,7 +137,76 @@ def test_viterbi_backtrace_block_edges(fb, K):
     lengths = np.array([2 * r + d for r in (F, 2 * F) for d in (-1, 0, 1, 2, 3)], np.int32)
     g = wl.random_graph(rng, K, D)
     emis = (rng.standard_normal((lengths.size, int(lengths.max()), D)) * 2).astype(np.float32)
-    check(fb, g, D, emis, lengths, f"block edges K={K}")
+    check(fb, g, D, emis, lengths, f"block edges K={K}")   # (K = 1300: a graph that keeps rows; in blocks they are with less workspace)
+    check(fb, g, D, emis, lengths, f"block edges K={K}, least workspace", least=True)
+
+
+@pytest.mark.parametrize("parallel", [False, True])
+def test_viterbi_workspaces(fb, parallel, monkeypatch):
+    """A large graph's call takes the form the workspace has room for: rows in the larger, back-pointers in what was enough before rows were
+    kept (2 bytes per state and frame), down to the last byte; with one byte less it is refused."""
+    import torch
+    rng = np.random.default_rng(2)
+    K, D, B, N = 1400, 23, 4, 31
+    src = np.concatenate([np.arange(K), rng.permutation(K), rng.permutation(K)]).astype(np.int32)
+    dst = np.concatenate([(np.arange(K) + 1) % K, rng.permutation(K), rng.permutation(K)]).astype(np.int32)
+    if parallel:
+        src, dst = np.concatenate([src, src[:700]]), np.concatenate([dst, dst[:700]])
+    else:
+        _, first = np.unique(src.astype(np.int64) * K + dst, return_index=True)
+        src, dst = src[first], dst[first]
+    g = wl.Graph(K, src, dst, (-rng.exponential(size=src.size)).astype(np.float32), rng.integers(0, D, K).astype(np.int32),
+                 (-rng.exponential(size=K)).astype(np.float32), (-rng.exponential(size=K)).astype(np.float32))
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_linear_weights(h) == 2
+    full, least = (int(f(h.handle, B, N)) for f in (fb.lib().fb_viterbi_workspace_bytes, fb.lib().fb_viterbi_least_workspace_bytes))
+    assert 4 * B * N * K <= full <= 4 * B * N * K + 16 * B * K and 2 * B * N * K <= least <= 2 * B * N * K + 16 * B * K and least < full
+    lengths = np.array([31, 1, 17, 30], np.int32)
+    emis = (rng.standard_normal((B, N, D)) * 2).astype(np.float32)
+    e, l = torch.from_numpy(emis).cuda(), torch.from_numpy(lengths).cuda()
+    ref = oracle.viterbi(g, emis, lengths, sel=list(range(B)))
+    for size in (full, full - 1, least):
+        score, path = fb.fb_viterbi(h, e, l, ws=torch.full((size,), 255, dtype=torch.uint8, device="cuda"))
+        score, path = score.cpu().numpy(), path.cpu().numpy()
+        assert np.all(np.abs(score - ref.score) <= TOL_REL * np.maximum(1.0, np.abs(ref.score)))
+        for b in range(B):
+            assert abs(oracle.path_score(g, emis[b], path[b, :lengths[b]]) - ref.score[b]) <= TOL_REL * max(1.0, abs(ref.score[b]))
+    with pytest.raises(fb.FBError):
+        fb.fb_viterbi(h, e, l, ws=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+    asked, new = [], fb._new                                 # no room for the larger: the binding takes the smaller
+    def no_room(shape, dtype, device):
+        asked.append(shape)
+        if shape == (full,):
+            raise torch.cuda.OutOfMemoryError("no room")
+        return new(shape, dtype, device)
+    monkeypatch.setattr(fb, "_new", no_room)
+    score = fb.fb_viterbi(h, e, l)[0].cpu().numpy()
+    assert asked[:2] == [(full,), (least,)] and np.all(np.abs(score - ref.score) <= TOL_REL * np.maximum(1.0, np.abs(ref.score)))
+    h.destroy()
+
+
+def test_viterbi_nan_inside_a_sequence(fb):
+    """Not a legal input, but what a diverged network hands over: a state whose score is NaN is never taken, whatever the form."""
+    import torch
+    rng = np.random.default_rng(4)
+    D, T = 29, 40
+    for K in (60, 1300):
+        g = wl.random_graph(rng, K, D)
+        emis = (rng.standard_normal((3, T, D)) * 2).astype(np.float32)
+        emis[0, 7, 3] = np.nan                               # in either half, and where they meet
+        emis[1, 30, 3] = np.nan
+        emis[2, (T - 1) // 2, 3] = np.nan
+        h = fb.graph_from(g, D)
+        e, l = torch.from_numpy(emis).cuda(), torch.full((3,), T, dtype=torch.int32, device="cuda")
+        ref = oracle.viterbi(g, np.nan_to_num(emis, nan=-np.inf), np.full(3, T, np.int32), sel=[0, 1, 2])
+        sizes = [int(fb.lib().fb_viterbi_workspace_bytes(h.handle, 3, T)), int(fb.lib().fb_viterbi_least_workspace_bytes(h.handle, 3, T))]
+        for size in sizes:
+            score, path = fb.fb_viterbi(h, e, l, ws=torch.full((size,), 255, dtype=torch.uint8, device="cuda"))
+            score, path = score.cpu().numpy(), path.cpu().numpy()
+            assert np.all(np.abs(score - ref.score) <= TOL_REL * np.maximum(1.0, np.abs(ref.score)))
+            for b in range(3):
+                assert abs(oracle.path_score(g, np.nan_to_num(emis[b], nan=-np.inf), path[b]) - ref.score[b]) <= TOL_REL * max(1.0, abs(ref.score[b]))
+        h.destroy()
 
 
 @pytest.mark.parametrize("K,deg", [(1100, 2), (1300, 5), (3001, 12)])
