@@ -350,6 +350,11 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
         // (the exported layout keeps them apart).  The two semirings add differently, so the best-path
         // plan is a plan of its own as soon as the graph has parallel arcs.
 
+        // (rows forward and backward of a shared graph, parallel arcs added, for what is made from them below)
+        std::vector<int64_t> sum_ptr[2];
+        std::vector<int32_t> sum_col[2];
+        std::vector<float> sum_w[2];
+
         // Small graphs with vectors in double: the small-graph kernel's plans, and no others, if every sub-graph fits it.
         g->small = g->f64 && g->nw == kNWSmall;
         int32_t longest = 0;   // most arcs of a row, parallel ones counted apart
@@ -367,16 +372,13 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 rows_of(s, dir);
                 any_parallel |= merge_parallel(Ks, ptr, col, w, false, mptr, mcol, mw);
                 g->small = small_append(dir ? g->hs_bwd : g->hs_fwd, k0, Ks, mptr.data(), mcol.data(), mw.data());
+                if (n_seq == 0) { sum_ptr[dir].swap(mptr); sum_col[dir].swap(mcol); sum_w[dir].swap(mw); }
             }
         }
         if (g->small && n_seq == 0 && g->hs_fwd.tm == 4) {   // the sums in the probability domain, if the graph mixes
-            std::vector<int64_t> iptr;
-            std::vector<int32_t> icol;
-            std::vector<float> iw, i2((size_t)K), f2((size_t)K);
-            rows_of(0, 0);   // (mptr .. hold the backward rows)
-            merge_parallel(K, ptr, col, w, false, iptr, icol, iw);
+            std::vector<float> i2((size_t)K), f2((size_t)K);
             for (int32_t k = 0; k < K; ++k) { i2[(size_t)k] = to_log2(init[k]); f2[(size_t)k] = to_log2(final_[k]); }
-            g->small_linear = small_mixes(K, iptr, icol, iw, mptr, mcol, mw, i2, f2);
+            g->small_linear = small_mixes(K, sum_ptr[0], sum_col[0], sum_w[0], sum_ptr[1], sum_col[1], sum_w[1], i2, f2);
             g->small_place.resize((size_t)K);
             for (int32_t d = 0; d < D && g->small_linear; ++d) {
                 if (L.pdf_ptr[(size_t)d] == L.pdf_ptr[(size_t)d + 1]) continue;
@@ -426,6 +428,7 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                     prob_ok = false;
                 }
                 any_parallel = any_parallel || dup;
+                if (prob_ok) { sum_ptr[dir].swap(mptr); sum_col[dir].swap(mcol); sum_w[dir].swap(mw); }
             }
             // states grouped by pdf: one row per pdf (every pdf for a shared graph, the pdfs the
             // sub-graph uses for packed graphs), states in ascending order inside a row
@@ -508,8 +511,19 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
             // (graphs in the probability domain: the best path runs on their plans, with weights of its own)
             const bool best = g->linear_p;
             for (int dir = 0; dir < 2 && rc == FB_OK && best; ++dir) {
-                rows_of(0, dir);
-                merge_parallel(K, ptr, col, w, true, mptr, mcol, mw);
+                if (dir == 0) {
+                    if (!pstream_apart(g->hp_fwd, D, sum_ptr[0].data(), sum_col[0].data(), sum_w[0].data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain, g->apart_lasting))
+                        g->apart_words.clear();
+                    else if (!pstream_in_bounds(g->hp_fwd, D, why, &g->apart_units, &g->apart_close) ||
+                             !pstream_apart_in_bounds(g->hp_fwd, g->apart_words, g->apart_lasting, why))
+                        rc = fail(FB_EHIP, "internal error: plan without the states apart out of bounds (" + why + ")");
+                }
+                if (any_parallel) {   // (they combine by max here)
+                    rows_of(0, dir);
+                    merge_parallel(K, ptr, col, w, true, mptr, mcol, mw);
+                } else {
+                    mptr.swap(sum_ptr[dir]); mcol.swap(sum_col[dir]); mw.swap(sum_w[dir]);
+                }
                 if (!pstream_best_units(dir ? g->hp_bwd : g->hp_fwd, mptr.data(), mcol.data(), mw.data(), g->best_units[dir])) {
                     rc = fail(FB_EHIP, "internal error: best-path weights of a probability-domain plan");
                     break;
@@ -517,17 +531,6 @@ int fb_graph_create(fb_graph **out, int32_t K, int64_t E, const int32_t *src, co
                 if (!pstream_in_bounds(dir ? g->hp_bwd : g->hp_fwd, D, why, &g->best_units[dir], nullptr, true)) {
                     rc = fail(FB_EHIP, "internal error: best-path plan out of bounds (" + why + ")");
                     break;
-                }
-                if (dir == 0) {
-                    std::vector<int64_t> sptr;
-                    std::vector<int32_t> scol;
-                    std::vector<float> sw;
-                    merge_parallel(K, ptr, col, w, false, sptr, scol, sw);
-                    if (!pstream_apart(g->hp_fwd, D, sptr.data(), scol.data(), sw.data(), g->apart_units, g->apart_close, g->apart_words, g->apart_gain, g->apart_lasting))
-                        g->apart_words.clear();
-                    else if (!pstream_in_bounds(g->hp_fwd, D, why, &g->apart_units, &g->apart_close) ||
-                             !pstream_apart_in_bounds(g->hp_fwd, g->apart_words, g->apart_lasting, why))
-                        rc = fail(FB_EHIP, "internal error: plan without the states apart out of bounds (" + why + ")");
                 }
                 g->best_ptr[dir].assign(mptr.begin(), mptr.end());
                 g->best_arcs[dir].reserve(mcol.size());

@@ -693,18 +693,28 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
                    std::vector<uint32_t> &close_words, std::vector<int32_t> &words, float &gain, int32_t &n_lasting)
 {
     const int32_t K = S.K;
-    std::vector<std::vector<std::pair<int32_t, float>>> out((size_t)K);   // live arcs by source
-    std::vector<int32_t> n_in((size_t)K, 0), queue;
+    std::vector<int32_t> n_in((size_t)K, 0), queue, out_ptr((size_t)K + 1, 0);
+    std::vector<std::pair<int32_t, float>> out;             // live arcs by source: out[out_ptr[k] .. out_ptr[k + 1]) leave state k
     int32_t hub = 0;
     for (int32_t r = 0; r < K; ++r) {
         for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e)
-            if (w[e] > -INFINITY) { out[(size_t)col[e]].push_back({r, w[e]}); ++n_in[(size_t)r]; }
+            if (w[e] > -INFINITY) { ++out_ptr[(size_t)col[e] + 1]; ++n_in[(size_t)r]; }
         if (n_in[(size_t)r] > n_in[(size_t)hub]) hub = r;
     }
+    for (int32_t k = 0; k < K; ++k) out_ptr[(size_t)k + 1] += out_ptr[(size_t)k];
+    out.resize((size_t)out_ptr[(size_t)K]);
+    std::vector<int32_t> at(out_ptr.begin(), out_ptr.end() - 1);
+    for (int32_t r = 0; r < K; ++r)
+        for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e)
+            if (w[e] > -INFINITY) out[(size_t)at[(size_t)col[e]]++] = {r, w[e]};
+    auto for_out = [&](int32_t k, auto body) {
+        for (int32_t i = out_ptr[(size_t)k]; i < out_ptr[(size_t)k + 1]; ++i) body(out[(size_t)i]);
+    };
     auto reach = [&](std::vector<char> &seen) {             // ... of the states in queue
         for (size_t h = 0; h < queue.size(); ++h)
-            for (const auto &a : out[(size_t)queue[h]])
+            for_out(queue[h], [&](const auto &a) {
                 if (!seen[(size_t)a.first]) { seen[(size_t)a.first] = 1; queue.push_back(a.first); }
+            });
     };
     std::vector<char> rest((size_t)K, 0);
     rest[(size_t)hub] = 1;
@@ -716,8 +726,9 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
     for (int32_t k = 0; k < K; ++k)
         if (n_in[(size_t)k] == 0) { stays[(size_t)k] = 0; queue.push_back(k); }
     for (size_t h = 0; h < queue.size(); ++h)
-        for (const auto &a : out[(size_t)queue[h]])
+        for_out(queue[h], [&](const auto &a) {
             if (--n_in[(size_t)a.first] == 0) { stays[(size_t)a.first] = 0; queue.push_back(a.first); }
+        });
     std::vector<int32_t> lane_of((size_t)K, -1), states;
     auto add = [&](int32_t k) {
         if (lane_of[(size_t)k] < 0) { lane_of[(size_t)k] = (int32_t)states.size(); states.push_back(k); }
@@ -746,11 +757,12 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
             std::memcpy(&words[(size_t)(1 + kApartArcs + t) * kWave + l], &w[e], 4);
             ++t;
         }
-        for (const auto &a : out[(size_t)k])
+        for_out(k, [&](const auto &a) {
             if (lane_of[(size_t)a.first] < 0 && l < (size_t)n_lasting) {
                 if (into[(size_t)a.first] == 0.0) targets.push_back(a.first);
                 into[(size_t)a.first] += std::exp2((double)a.second);
             }
+        });
     }
     if (targets.size() > (size_t)(kApartTargets * kWave)) return false;
     double most = 0.0;
@@ -783,7 +795,7 @@ bool pstream_apart(const PStreamHost &S, int32_t n_vidx, const int64_t *ptr, con
     return true;
 }
 
-// The plan's units with the best path's weights: the same arcs (rows [0, K), columns ascending, parallel ones merged by their largest), w in log2
+// The plan's units with the best path's weights: the same arcs (rows [0, K), parallel ones merged by their largest), w in log2
 // units, -inf where the lane only pads.  False if an arc of the plan is not among them.
 bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t *col, const float *w, std::vector<uint32_t> &units)
 {
@@ -792,30 +804,36 @@ bool pstream_best_units(const PStreamHost &S, const int64_t *ptr, const int32_t 
     std::iota(state_of.begin(), state_of.begin() + S.K, 0);
     for (const CloneDesc &cd : S.clones)
         for (int32_t i = 0; i < cd.count; ++i) state_of[(size_t)S.K + (size_t)cd.first + (size_t)i] = cd.state;
+    std::vector<int32_t> row_of((size_t)S.K, -1);           // by column: the row that is laid out, and its weight there
+    std::vector<float> w_of((size_t)S.K);
     for (const PWaveDesc &wd : S.waves) {
         int c = 0, u0 = 0;
         for (int u = 0; u < wd.n_units; ++u) {
             if (!((wd.close_mask[u / 64] >> (u % 64)) & 1u)) continue;
             const uint32_t *cw = S.close_words.data() + ((size_t)wd.cw_base + (size_t)c++) * kWave;
-            for (; u0 <= u; ++u0) {
-                uint32_t *unit = units.data() + ((size_t)wd.unit_base + (size_t)u0) * 3 * kWave;
-                for (int l = 0; l < kWave; ++l)
+            int32_t laid = -1;
+            for (int l = 0; l < kWave; ++l) {
+                const int32_t row = state_of[(cw[l] & 0xffffu) / 4u];
+                if (row >= 0 && row != laid)
+                    for (int64_t e = ptr[row]; e < ptr[row + 1]; ++e) { row_of[(size_t)col[e]] = row; w_of[(size_t)col[e]] = w[e]; }
+                laid = row;
+                for (int v = u0; v <= u; ++v) {
+                    uint32_t *unit = units.data() + ((size_t)wd.unit_base + (size_t)v) * 3 * kWave + l * 3;
                     for (int r = 0; r < 2; ++r) {
-                        float v;
-                        std::memcpy(&v, &unit[l * 3 + 1 + r], 4);
-                        if (v == 0.0f) {
-                            v = -INFINITY;
+                        float x;
+                        std::memcpy(&x, &unit[1 + r], 4);
+                        if (x == 0.0f) {
+                            x = -INFINITY;
                         } else {
-                            const int32_t row = state_of[(cw[l] & 0xffffu) / 4u];
-                            const int32_t src = state_of[(r ? unit[l * 3] >> 16 : unit[l * 3] & 0xffffu) / 4u];
-                            if (row < 0 || src < 0) return false;
-                            const int32_t *at = std::lower_bound(col + ptr[row], col + ptr[row + 1], src);
-                            if (at == col + ptr[row + 1] || *at != src) return false;
-                            v = w[at - col];
+                            const int32_t src = state_of[(r ? unit[0] >> 16 : unit[0] & 0xffffu) / 4u];
+                            if (row < 0 || src < 0 || row_of[(size_t)src] != row) return false;
+                            x = w_of[(size_t)src];
                         }
-                        std::memcpy(&unit[l * 3 + 1 + r], &v, 4);
+                        std::memcpy(&unit[1 + r], &x, 4);
                     }
+                }
             }
+            u0 = u + 1;
         }
     }
     return true;
