@@ -53,12 +53,60 @@ def test_parity(K, deg, hub, D, frames):
     assert fb.fb_debug_linear_restarts() == before
 
 
-@pytest.mark.parametrize("K,deg,hub,D,frames", [SIZES[i] for i in (1, 3, 5, 7, 9, 11, 14)])
+def _slices(g):
+    """Slices of the larger of the two plans: rows of up to four arcs take a lane, longer ones the least power of two that holds them; widest
+    rows first, a slice's lanes per row are its first row's."""
+    most = 0
+    for rows, cols in ((g.dst, g.src), (g.src, g.dst)):
+        pairs = np.unique(rows.astype(np.int64) * g.K + cols)
+        n = np.bincount(pairs // g.K, minlength=g.K)
+        lanes = np.sort([1 << max(0, int(np.ceil(np.log2(max(x, 1) / 4)))) for x in n])[::-1]
+        used, at, wide = 0, 64, 1
+        for w in lanes:
+            if at >= 64:
+                used, at, wide = used + 1, 0, int(w)
+            at += wide
+        most = max(most, used)
+    return most
+
+
+def _circulant(rng, K, arcs, D):
+    """Every row the same number of arcs, every pdf used where there are no more of them than states."""
+    src = np.tile(np.arange(K), arcs)
+    dst = (src + np.repeat(np.concatenate([[1], rng.permutation(np.arange(2, K))[:arcs - 1]]), K)) % K
+    return wl.Graph(K, src.astype(np.int32), dst.astype(np.int32), (-rng.exponential(size=src.size)).astype(np.float32),
+                    rng.permutation(np.arange(K) % D).astype(np.int32), (-rng.exponential(size=K)).astype(np.float32), (-rng.exponential(size=K)).astype(np.float32))
+
+
+# the instantiations that SIZES does not reach: (states, arcs a row, pdfs, slices): 25 to 32 slices with up to 128, 320 and more pdfs, 17 to 24 and 9 to 16
+# with as many, 5 to 8 with more than 128
+LARGEST = [(455, 9, 97, 29), (455, 9, 300, 29), (455, 9, 455, 29), (810, 5, 128, 26), (511, 8, 321, 16), (400, 5, 129, 13), (220, 4, 220, 4), (130, 9, 130, 9),
+           (125, 9, 129, 8), (200, 6, 200, 7)]
+
+
+@pytest.mark.parametrize("K,arcs,D,slices", LARGEST)
+def test_parity_of_the_largest_plans(K, arcs, D, slices):
+    rng = np.random.default_rng(K + D)
+    g = _circulant(rng, K, arcs, D)
+    assert _slices(g) == slices and np.unique(g.pdf).size == min(D, K)
+    lengths = np.array([0, 1, 2, 5, 9, 18, 33], dtype=np.int32)
+    emis = (rng.standard_normal((lengths.size, int(lengths.max()) + 1, D)) * 2).astype(np.float32)
+    for b in range(lengths.size):
+        emis[b, lengths[b]:] = np.nan
+    h = fb.graph_from(g, D)
+    assert fb.fb_graph_small_linear(h) == 1
+    h.destroy()
+    before = fb.fb_debug_linear_restarts()
+    _check(g, emis, lengths, D)
+    assert fb.fb_debug_linear_restarts() == before
+
+
+@pytest.mark.parametrize("K,deg,hub,D,frames", [SIZES[i] for i in (1, 3, 5, 7, 9, 11, 14)] + [(K, arcs, -1, D, None) for K, arcs, D, _ in (LARGEST[0], LARGEST[2], LARGEST[9])])
 def test_runs_that_leave_the_range(K, deg, hub, D, frames):
     """Emissions hundreds of nats apart: one sequence all along, one in a single frame, one a masked state, one not at all."""
     import torch
     rng = np.random.default_rng(K)
-    g = _graph(rng, K, deg, hub, D)
+    g = _graph(rng, K, deg, hub, D) if hub >= 0 else _circulant(rng, K, deg, D)
     T = 26
     lengths = np.array([T, T, T, T], dtype=np.int32)
     emis = (rng.standard_normal((4, T, D)) * 2).astype(np.float32)
