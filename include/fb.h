@@ -379,7 +379,8 @@ int32_t fb_limits_max_states(int32_t D, int shared);
 int fb_graph_linear_weights(const fb_graph *g);
 
 /* Diagnostic: 1 if g is a small shared graph (vectors in double, at most 1024 states) whose sums run on probabilities: every state lies
- * on or near the one strongly connected part, and the weights are of ordinary size; 0: any other graph; -1: g is NULL. */
+ * on or near the one strongly connected part, and the weights are of ordinary size (calls of more sequences than the GPU has compute units
+ * take the log form all the same where the graph has few states); 0: any other graph; -1: g is NULL. */
 int fb_graph_small_linear(const fb_graph *g);
 
 /* Diagnostic: how many (sequence, direction) runs the probability-domain recursion kernels have given up and

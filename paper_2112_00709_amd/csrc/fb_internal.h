@@ -379,7 +379,7 @@ struct fb_graph {
     bool linear_p = false;            // the recursions run in the probability domain (linear_run): the plans below exist
     fb::PStreamHost hp_fwd, hp_bwd;   // its plans, host
     fb::PStreamDev pfwd, pbwd;        // and device
-    std::vector<uint32_t> apart_units, apart_close;   // the sums' forward plan of a graph with states that run apart
+    std::vector<uint32_t> apart_units, apart_close;   // the sums' forward plan without the states that may run apart
     std::vector<int32_t> apart_words;
     float apart_gain = 0.0f;
     int32_t apart_lasting = 0;

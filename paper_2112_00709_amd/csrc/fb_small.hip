@@ -11,7 +11,8 @@
 //     at every step, so that the frames before and behind such a frame keep their resolution.  So is every sequence of a
 //     graph with weights of that size.  Calls with such emissions in every frame, against the general kernel and (in
 //     brackets) against ordinary emissions: fb_alpha, fb_beta and fb_posteriors of 16 states over 50 frames 121 -> 118 us
-//     (41), of 32 chains 283 -> 322 (70), of 701 states 878 -> 1063 (525); best path of 32 label sequences 252 -> 139 (53).
+//     (41), of 32 chains 283 -> 322 (70), of 701 states 878 -> 1063 (525; with the sums on probabilities
+//     first, fb_small_linear.hip, 1120 and 285); best path of 32 label sequences 252 -> 139 (53).
 //   * (A few scalars of the variants of 24 and 32 slices, and 13 vector registers of the best path's of 32, sit elsewhere.)
 //     The arcs, targets and pdf ids of a lane sit in registers for the whole time loop (fb_small.cpp); a lane asks for
 //     the emissions of its rows kAhead frames at a time, one such group ahead, straight into registers, so a step touches LDS for the gathers

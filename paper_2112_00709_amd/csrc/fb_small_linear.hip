@@ -28,8 +28,9 @@
 // -1e20 in that frame 549 (913); in the log form at once 253, 253 and 706.  40 states, 100 frames: 28, 50 (70), 67 (70), 157 (195); 43, 43, 169.
 //
 // What bounds it: with one or two slices a wave the chain of a step (LDS read, three dependent double operations, the lanes of long rows,
-// LDS write, barrier: some 400 clocks at 60 states); with 24 slices the LDS (120 eight-byte gathers a step) and the issue of the three waves a
-// SIMD has, 1380 clocks a step against 2700 in the log form.  Figures by size stand at small_mixes() in fb_small.cpp.
+// LDS write, barrier: some 400 clocks at 60 states); with 24 slices that chain still: of 1480 clocks a step (2700 in the log form) the LDS is busy for
+// 820, 430 of them bank conflicts of its 166 accesses, and a SIMD issues vector instructions in 505 (counted, start and end included).  Figures
+// by size stand at small_mixes() in fb_small.cpp.
 #include "fb_small_run.h"
 
 namespace fb {
