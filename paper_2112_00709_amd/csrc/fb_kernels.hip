@@ -1242,6 +1242,14 @@ __device__ __forceinline__ bool linear_run(const RecParams &P, const int b, cons
             __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
         };
         load_plan(S.close_words);
+        // The steps' code begins so many words behind a line of the 32 bytes that instructions are fetched by, whatever comes before it:
+        // where steps are mostly short blocks and jumps, the place alone makes up to a tenth.  At zero to seven words, us a call:
+        // LF-MMI of 1163 states, 17 k arcs, 2777 labels, 31 sequences  1065 1062 1059 1080 1084 1152 1063 1047 (1155 where it happened to fall),
+        // sums of 1444 states, 20 k arcs, 61 sequences                  878  876  876  879  880  904  908  950,
+        // sums of 4830 states, 27 k arcs, 23 sequences, states apart    372  382  364  365  362  363  363  370,
+        // LF-MMI of 6000 states, 60 k arcs, 128 sequences              2116 2111 2145 2129 2116 2128 2116 2125.
+        constexpr int kWords = FEW && !APART && !TROP ? 2 : 4;
+        asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" : : "n"(kWords));
         Unit ring[kPRing];
         // streamed unit m -> its ring place (in the patterned part streamed unit m is position H + 3 m + 2; behind it, unit
         // NP + t is streamed unit NG + t)
